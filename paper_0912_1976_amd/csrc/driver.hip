@@ -84,26 +84,35 @@ struct Arena {
 // out of the stored entries; the FP64 per-row term is `d` if given
 // (difference form: the deficit) else a_ii.  FP32 copy: a_ij / a_ii with
 // s32 = a_ii and dh32 = d / a_ii (square), or float(a_ij) (rectangular).
+// colour (square): each row's couplings to earlier colours come first, then
+// those to later ones, the two parts padded apart (Sell::smid).
 Sell pack_sell(Arena &ar, hipStream_t st, const Csr &A, bool square, const std::vector<double> *d,
                const std::vector<double> *diag, int64_t *stored = nullptr,
-               const std::vector<int32_t> *subset = nullptr) {
+               const std::vector<int32_t> *subset = nullptr, const std::vector<int32_t> *colour = nullptr) {
   // subset: pack only these rows of A, row i of the result being A's row
   // (*subset)[i] with its entries (columns unchanged) in the same order
   int64_t n = subset ? (int64_t)subset->size() : A.nrows, ns = (n + kWave - 1) / kWave;
   auto row_of = [&](int64_t i) -> int64_t { return subset ? (int64_t)(*subset)[i] : i; };
-  std::vector<int64_t> sptr(ns + 1, 0);
-  std::vector<int64_t> len(n);
-  for (int64_t i = 0; i < n; ++i) {
-    const int64_t r = row_of(i);
-    int64_t c = 0;
-    for (int64_t k = A.ptr[r]; k < A.ptr[r + 1]; ++k)
-      if (!(square && A.idx[k] == r)) ++c;
-    len[i] = c;
-  }
+  // part of entry e of row r: 0 (earlier colour, or no colours) or 1; -1: not stored
+  auto part_of = [&](int64_t r, int64_t e) {
+    const int64_t c = A.idx[e];
+    if (square && c == r) return -1;
+    return colour && (*colour)[c] > (*colour)[r] ? 1 : 0;
+  };
+  std::vector<int64_t> sptr(ns + 1, 0), smid(ns, 0);
   for (int64_t s = 0; s < ns; ++s) {
-    int64_t L = 0;
-    for (int64_t r = s * kWave; r < std::min(n, (s + 1) * kWave); ++r) L = std::max(L, len[r]);
-    sptr[s + 1] = sptr[s] + L * kWave;
+    int64_t L[2] = {0, 0};
+    for (int64_t i = s * kWave; i < std::min(n, (s + 1) * kWave); ++i) {
+      const int64_t r = row_of(i);
+      int64_t len[2] = {0, 0};
+      for (int64_t e = A.ptr[r]; e < A.ptr[r + 1]; ++e) {
+        const int p = part_of(r, e);
+        if (p >= 0) ++len[p];
+      }
+      for (int p = 0; p < 2; ++p) L[p] = std::max(L[p], len[p]);
+    }
+    smid[s] = sptr[s] + L[0] * kWave;
+    sptr[s + 1] = smid[s] + L[1] * kWave;
   }
   std::vector<int32_t> col(sptr[ns]);
   std::vector<double> val(sptr[ns], 0.0);
@@ -117,42 +126,40 @@ Sell pack_sell(Arena &ar, hipStream_t st, const Csr &A, bool square, const std::
     dv[i] = d ? (*d)[r] : ad[i];
   }
   for (int64_t s = 0; s < ns; ++s) {
-    int64_t L = (sptr[s + 1] - sptr[s]) / kWave;
     for (int t = 0; t < kWave; ++t) {
       const int64_t i = s * kWave + t, r = i < n ? row_of(i) : -1;
-      int64_t k = 0;
-      if (i < n) {
-        for (int64_t e = A.ptr[r]; e < A.ptr[r + 1]; ++e) {
-          if (square && A.idx[e] == r) continue;
-          int64_t pos = sptr[s] + k * kWave + t;
-          col[pos] = A.idx[e];
-          val[pos] = A.val[e];
-          val32[pos] = square ? (float)(A.val[e] / ad[i]) : (float)A.val[e];
-          ++k;
-        }
+      int64_t pos[2] = {sptr[s] + t, smid[s] + t};
+      for (int64_t e = i < n ? A.ptr[r] : 0; i < n && e < A.ptr[r + 1]; ++e) {
+        const int p = part_of(r, e);
+        if (p < 0) continue;
+        col[pos[p]] = A.idx[e];
+        val[pos[p]] = A.val[e];
+        val32[pos[p]] = square ? (float)(A.val[e] / ad[i]) : (float)A.val[e];
+        pos[p] += kWave;
       }
-      for (; k < L; ++k) {
-        int64_t pos = sptr[s] + k * kWave + t;
-        col[pos] = (square && i < n) ? (int32_t)r : 0;
-        val[pos] = 0.0;
-        val32[pos] = 0.0f;
-      }
+      const int64_t end[2] = {smid[s], sptr[s + 1]};
+      for (int p = 0; p < 2; ++p)
+        for (; pos[p] < end[p]; pos[p] += kWave) col[pos[p]] = (square && i < n) ? (int32_t)r : 0;
     }
   }
   if (stored) *stored = sptr[ns];
   Sell M;
   M.nrows = n;
   M.sptr = ar.upload(sptr, st);
+  if (colour) M.smid = ar.upload(smid, st);
   M.col = ar.upload(col, st);
   M.val64 = ar.upload(val, st);
   M.val32 = ar.upload(val32, st);
   if (square) {
+    std::vector<double> inv(n);
     std::vector<float> s32(n), dh32(n);
     for (int64_t r = 0; r < n; ++r) {
+      inv[r] = 1.0 / ad[r];
       s32[r] = (float)ad[r];
       dh32[r] = (float)(dv[r] / ad[r]);
     }
     M.d64 = ar.upload(dv, st);
+    M.i64 = ar.upload(inv, st);
     M.s32 = ar.upload(s32, st);
     M.dh32 = ar.upload(dh32, st);
   }
@@ -483,63 +490,43 @@ void vcycle(hipStream_t st, int K, std::vector<DLevel> &H, size_t l, const int *
   }
   const int nc = (int)(L.fine ? L.cstart.size() : L.pc_start.size()) - 1;
   // forward (zero start: x needs no fill, the colours not swept yet are not
-  // read) and backward sweeps of colour c (coarse levels: patch colour c)
+  // read) and backward sweeps of colour c (coarse levels: patch colour c);
+  // on A_bar's fine level (no top range) the top columns multiply the
+  // smoother vector's top part, which is zero
   auto gs = [&](int c, bool first) {
     if (L.fine) {
-      // A_bar's fine level (no top range) never reads the top columns: they
-      // multiply the smoother vector's top part, which is zero
-      ZeroStart zs;
-      zs.on = first;
-      zs.n_top = L.n_top;
-      zs.top_lim = L.cstart_top.empty() ? 0 : L.cstart_top[c];
-      zs.bar_lim = L.cstart[c];
       if (!L.cstart_top.empty()) {
         launch_gs<T>(st, K, L.As, L.cstart_top[c], L.cstart_top[c + 1], L.cstart[c], L.cstart[c + 1], g, x, done,
-                     zs);
+                     first);
       } else {
-        launch_gs<T>(st, K, L.As, L.cstart[c], L.cstart[c + 1], 0, 0, g, x, done, zs);
+        launch_gs<T>(st, K, L.As, L.cstart[c], L.cstart[c + 1], 0, 0, g, x, done, first);
       }
     } else {
       launch_patch_gs<T>(st, K, L.Ac, L.ps, L.pc_start[c], L.pc_start[c + 1] - L.pc_start[c], g, x, done,
                          first ? L.pc_row[c] : -1, !first);
     }
   };
-  // the rows of the last colour have a zero residual after the forward sweep
-  ZeroRows zr;
-  if (L.fine && nc > 0) {
-    if (!L.cstart_top.empty()) {
-      zr.a0 = L.cstart_top[nc - 1];
-      zr.a1 = L.cstart_top[nc];
-    }
-    zr.b0 = L.cstart[nc - 1];
-    zr.b1 = L.cstart[nc];
-  }
   if (reuse && L.fine && L.cstart_top.empty()) {
     // x and r hold the SOR cycle's values (x once its forward sweep is done,
     // r once its residual is); sweep and recompute only the rows where the
     // two differ, with the same arithmetic
     if (reuse->phase == 1) {
       for (int c = 0; c < nc; ++c) {
-        ZeroStart zs;
-        zs.on = true;
-        zs.n_top = L.n_top;
-        zs.top_lim = 0;
-        zs.bar_lim = L.cstart[c];
         const int64_t a = (*reuse->gs_start)[c], b = (*reuse->gs_start)[c + 1];
-        launch_gs_rows<T>(st, K, (*reuse->gs_sell)[c], reuse->gs + a, b - a, g, x, done, zs);
+        launch_gs_rows<T>(st, K, (*reuse->gs_sell)[c], reuse->gs + a, b - a, g, x, done);
       }
       return;
     }
     if (reuse->full_res)
-      launch_spmv<T>(st, K, L.As, 1, L.row0, L.row0 + L.n, x, g, r, nullptr, done, L.order, zr);
+      launch_spmv<T>(st, K, L.As, 1, L.row0, L.row0 + L.n, x, r, nullptr, done, L.order);
     else
-      launch_spmv_rows<T>(st, K, *reuse->res_sell, reuse->res, reuse->nres, x, g, r, done, zr);
+      launch_spmv_rows<T>(st, K, *reuse->res_sell, reuse->res, reuse->nres, x, r, done);
   } else {
     for (int c = 0; c < nc; ++c) gs(c, true);
   }
   if (L.fine) {
     if (!(reuse && L.cstart_top.empty()))
-      launch_spmv<T>(st, K, L.As, 1, L.row0, L.row0 + L.n, x, g, r, nullptr, done, L.order, zr);
+      launch_spmv<T>(st, K, L.As, 1, L.row0, L.row0 + L.n, x, r, nullptr, done, L.order);
   } else
     launch_csr_spmv<T>(st, K, L.Ac, 1, 0, L.n, x, g, r, done);
   DLevel &C = H[l + 1];
@@ -579,31 +566,12 @@ void sor_cycle(Handle *h, hipStream_t st, int K, const T *rr, T *zz, const int *
       b0 = P.bar_colour_start[c];
       b1 = P.bar_colour_start[c + 1];
     }
-    ZeroStart zs;
-    zs.on = first;
-    zs.n_top = m;
-    zs.top_lim = P.top_colour_start[std::min(c, nct)];
-    zs.bar_lim = P.bar_colour_start[std::min(c, ncb)];
-    launch_gs<T>(st, K, h->A, a0, a1, b0, b1, rr, zz, done, zs, first ? x2 : nullptr, m);
+    launch_gs<T>(st, K, h->A, a0, a1, b0, b1, rr, zz, done, first, first ? x2 : nullptr, m);
   };
   if (part == 0 || part == 1)
     for (int c = 0; c < nc; ++c) sweep(c, true);
   if (part == 0 || part == 3) {
-    if (m > 0) {
-      // the rows swept by the last launch have a zero residual
-      ZeroRows zr;
-      if (nc > 0) {
-        if (nc - 1 < nct) {
-          zr.a0 = P.top_colour_start[nc - 1];
-          zr.a1 = P.top_colour_start[nc];
-        }
-        if (nc - 1 < ncb) {
-          zr.b0 = P.bar_colour_start[nc - 1];
-          zr.b1 = P.bar_colour_start[nc];
-        }
-      }
-      launch_spmv<T>(st, K, h->A, 1, 0, n, zz, rr, v.res, nullptr, done, h->order_all, zr, r2, m);
-    }
+    if (m > 0) launch_spmv<T>(st, K, h->A, 1, 0, n, zz, v.res, nullptr, done, h->order_all, r2, m);
   }
   if (part == 1 || part == 3) return;
   if (m > 0) {
@@ -832,7 +800,7 @@ void pcg_segment(Handle *h, int K, int kind, int seg) {
   const bool mixed = kind == kGraphMixedPC;
   switch (seg) {
     case kSegPre:
-      launch_spmv<T>(st, K, h->A, 0, 0, n, v.p, (const T *)nullptr, v.q, h->part_pq, done, h->order_all);
+      launch_spmv<T>(st, K, h->A, 0, 0, n, v.p, v.q, h->part_pq, done, h->order_all);
       launch_pcg_alpha(st, K, h->scal, h->part_pq, sell_blocks(0, n));
       launch_pcg_xr<T>(st, K, h->scal, v.x, v.r, v.p, v.q, n, h->part_rr);
       launch_pcg_conv(st, K, h->scal, h->part_rr, vec_blocks(n));
@@ -906,7 +874,7 @@ void pcg_iteration(Handle *h, int K, int kind) {
     pcg_segment<T>(h, K, kind, kSegPost);
     return;
   }
-  launch_spmv<T>(st, K, h->A, 0, 0, n, v.p, (const T *)nullptr, v.q, h->part_pq, done, h->order_all);
+  launch_spmv<T>(st, K, h->A, 0, 0, n, v.p, v.q, h->part_pq, done, h->order_all);
   launch_pcg_alpha(st, K, h->scal, h->part_pq, sell_blocks(0, n));
   launch_pcg_xr<T>(st, K, h->scal, v.x, v.r, v.p, v.q, n, h->part_rr);
   launch_pcg_conv(st, K, h->scal, h->part_rr, vec_blocks(n));
@@ -1233,7 +1201,7 @@ void upload(Handle *h) {
   int64_t n = P.n, m = P.n_top;
   const bool count = h->ar.count_only;
   h->ar.release();
-  h->A = pack_sell(h->ar, st, P.Aoff, true, &P.d, &P.diag, &h->nnz_A);
+  h->A = pack_sell(h->ar, st, P.Aoff, true, &P.d, &P.diag, &h->nnz_A, nullptr, &P.colour);
   if (m > 0) {
     h->E = pack_sell(h->ar, st, P.E, false, nullptr, nullptr, &h->nnz_E);
     h->Et = pack_csrg(h->ar, st, P.Et, false, nullptr, &P.loc_rank, 0);
@@ -1288,14 +1256,12 @@ void upload(Handle *h) {
   // from zero on the same right-hand side; the smoother holds the top rows at
   // zero where the SOR cycle has swept them.  A non-top row of colour c gets
   // the same value in both, bit for bit, unless one of its neighbours of an
-  // earlier colour is a top row or such a row itself ("dirty"); its residual
-  // is the same unless the row, or a neighbour, is dirty or a neighbour is a
-  // top row, or the two zero it differently (the smoother zeroes its last
-  // colour, the SOR cycle the rows of its last launch).
+  // earlier colour is a top row or such a row itself ("dirty"); its residual,
+  // which takes only its neighbours of later colours, is the same unless one
+  // of them is a top row or dirty.
   {  // for every preconditioner: a handle may be switched to VL + additive smoother
     const Csr &O = P.Aoff;
-    const int ncb = (int)P.bar_colour_start.size() - 1, nct = (int)P.top_colour_start.size() - 1;
-    const bool same_last = std::max(nct, ncb) == ncb;
+    const int ncb = (int)P.bar_colour_start.size() - 1;
     std::vector<uint8_t> dirty(n, 0);
     std::vector<int32_t> rows, res;
     h->reuse_gs_start.assign(1, 0);
@@ -1314,11 +1280,12 @@ void upload(Handle *h) {
       }
       rows.insert(rows.end(), rc.begin(), rc.end());
       h->reuse_gs_start.push_back((int64_t)rows.size());
-      h->reuse_gs_sell.push_back(pack_sell(h->ar, st, P.Aoff, true, &P.d, &P.diag, nullptr, &rc));
+      h->reuse_gs_sell.push_back(pack_sell(h->ar, st, P.Aoff, true, &P.d, &P.diag, nullptr, &rc, &P.colour));
     }
     for (int64_t i = m; i < n; ++i) {
-      bool d = dirty[i] || (!same_last && ncb > 0 && P.colour[i] == ncb - 1);
-      for (int64_t k = O.ptr[i]; k < O.ptr[i + 1] && !d; ++k) d = O.idx[k] < m || dirty[O.idx[k]];
+      bool d = false;
+      for (int64_t k = O.ptr[i]; k < O.ptr[i + 1] && !d; ++k)
+        d = P.colour[O.idx[k]] > P.colour[i] && (O.idx[k] < m || dirty[O.idx[k]]);
       if (d) res.push_back((int32_t)i);
     }
     // without a top surface no row is dirty, but the SOR cycle computes no
@@ -1327,7 +1294,7 @@ void upload(Handle *h) {
     if (h->reuse_full_res) res.clear();
     h->reuse_gs = h->ar.upload(rows, st);
     h->reuse_res = h->ar.upload(res, st);
-    h->reuse_res_sell = pack_sell(h->ar, st, P.Aoff, true, &P.d, &P.diag, nullptr, &res);
+    h->reuse_res_sell = pack_sell(h->ar, st, P.Aoff, true, &P.d, &P.diag, nullptr, &res, &P.colour);
     h->share_min_rows = share_min_rows();
     h->n_reuse_res = (int64_t)res.size();
     h->reuse = true;
@@ -1425,7 +1392,7 @@ void apply_op(Handle *h, int op, const T *in, T *out) {
   Work<T> &v = work_of<T>(h);
   switch (op) {
     case VEMG_OP_A:
-      launch_spmv<T>(st, 1, h->A, 0, 0, n, in, (const T *)nullptr, out, nullptr, nullptr, h->order_all);
+      launch_spmv<T>(st, 1, h->A, 0, 0, n, in, out, nullptr, nullptr, h->order_all);
       break;
     case VEMG_OP_PRECOND: {
       launch_copy<T>(st, in, v.tmp, n, nullptr);
@@ -1454,7 +1421,6 @@ void apply_op(Handle *h, int op, const T *in, T *out) {
       break;
     }
     case VEMG_OP_GS_FWD: {
-      launch_fill<T>(st, out, n, T(0), nullptr);
       int nct = (int)P.top_colour_start.size() - 1, ncb = (int)P.bar_colour_start.size() - 1;
       for (int c = 0; c < std::max(nct, ncb); ++c) {
         int64_t a0 = 0, a1 = 0, b0 = 0, b1 = 0;
@@ -1466,7 +1432,7 @@ void apply_op(Handle *h, int op, const T *in, T *out) {
           b0 = P.bar_colour_start[c];
           b1 = P.bar_colour_start[c + 1];
         }
-        launch_gs<T>(st, 1, h->A, a0, a1, b0, b1, in, out, nullptr);
+        launch_gs<T>(st, 1, h->A, a0, a1, b0, b1, in, out, nullptr, true);
       }
       break;
     }
@@ -1506,7 +1472,7 @@ void time_once(Handle *h, int op, int K) {
   int64_t n = P.n;
   Work<T> &v = work_of<T>(h);
   if (op == VEMG_OP_A) {
-    launch_spmv<T>(st, K, h->A, 0, 0, n, v.p, (const T *)nullptr, v.q, h->part_pq, nullptr, h->order_all);
+    launch_spmv<T>(st, K, h->A, 0, 0, n, v.p, v.q, h->part_pq, nullptr, h->order_all);
     return;
   }
   if (op == VEMG_OP_ET) {
@@ -1540,7 +1506,7 @@ void time_once(Handle *h, int op, int K) {
       b0 = P.bar_colour_start[c];
       b1 = P.bar_colour_start[c + 1];
     }
-    launch_gs<T>(st, K, h->A, a0, a1, b0, b1, v.r, v.z, nullptr);
+    launch_gs<T>(st, K, h->A, a0, a1, b0, b1, v.r, v.z, nullptr, false);
   }
 }
 
@@ -2175,7 +2141,7 @@ vemg_status vemg_matvec(vemg_solver s, const double *x_dev, double *y_dev) {
     int64_t n = s->P.n;
     vemg::sync_in(s);
     vemg::launch_gather(st, 1, 0, x_dev, s->perm, s->v64.tmp, n);
-    vemg::launch_spmv<double>(st, 1, s->A, 0, 0, n, s->v64.tmp, nullptr, s->v64.res, nullptr, nullptr, s->order_all);
+    vemg::launch_spmv<double>(st, 1, s->A, 0, 0, n, s->v64.tmp, s->v64.res, nullptr, nullptr, s->order_all);
     vemg::launch_fill<double>(st, y_dev, s->P.n_nodes, 0.0, nullptr);
     vemg::launch_scatter(st, 1, 0, s->v64.res, s->perm, y_dev, n);
     HIPCHK(hipGetLastError());
@@ -2198,7 +2164,7 @@ vemg_status vemg_matvec_noalloc(vemg_solver s, const double *x_dev, double *y_de
     int64_t n = s->P.n;
     vemg::sync_in(s);
     vemg::launch_gather(st, 1, 0, x_dev, s->perm, buf, n);
-    vemg::launch_spmv<double>(st, 1, s->A, 0, 0, n, buf, nullptr, buf + n, nullptr, nullptr, s->order_all);
+    vemg::launch_spmv<double>(st, 1, s->A, 0, 0, n, buf, buf + n, nullptr, nullptr, s->order_all);
     vemg::launch_fill<double>(st, y_dev, s->P.n_nodes, 0.0, nullptr);
     vemg::launch_scatter(st, 1, 0, buf + n, s->perm, y_dev, n);
     HIPCHK(hipGetLastError());

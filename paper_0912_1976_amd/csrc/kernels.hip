@@ -106,45 +106,34 @@ constexpr int sell_unroll() {
 
 // Off-diagonal terms of one SELL row (position t of slice s) for the C
 // columns [q C, q C + C) of a K-column batch: acc = sum_j v_j (x_j - x_r)
-// (DIFF) or sum_j v_j x_j, and off = sum_j v_j.  Every column is summed over
-// the row's entries in storage order, whatever C is.
-template <class T, int K, int C, bool DIFF, bool ZS = false>
+// (DIFF) or sum_j v_j x_j, over all the row's entries or the fine matrix's L
+// or U entries alone.  Every column is summed in storage order, whatever C is.
+// The padding entries of L point at the row itself, which the sweep has not
+// written yet, so their gathered value is replaced by zero.
+enum Part { kAll, kLower, kUpper };
+
+template <class T, int K, int C, bool DIFF, int PART = kAll>
 __device__ __forceinline__ void sell_row(const Sell &A, int64_t s, int t, int q, const T *__restrict__ x,
-                                         const Row<T, C> &xr, T (&acc)[C], T &off,
-                                         const ZeroStart &z = ZeroStart()) {
-  const int64_t base = A.sptr[s];
-  const int len = (int)((A.sptr[s + 1] - base) >> 6);
+                                         const Row<T, C> &xr, T (&acc)[C], int32_t own = -1) {
+  const int64_t base = PART == kUpper ? A.smid[s] : A.sptr[s];
+  const int len = (int)(((PART == kLower ? A.smid[s] : A.sptr[s + 1]) - base) >> 6);
   const int32_t *__restrict__ cp = A.col + base + t;
   const T *__restrict__ vp = sell_vals<T>(A) + base + t;
   const T *__restrict__ xq = x + q * C;
 #pragma unroll
   for (int k = 0; k < C; ++k) acc[k] = T(0);
-  off = T(0);
   constexpr int U = sell_unroll<T, C>();
 #pragma unroll U
   for (int e = 0; e < len; ++e) {
     const int32_t c = cp[(int64_t)e * 64];
     const T v = vp[(int64_t)e * 64];
-    if constexpr (ZS && K > 2) {
-      // wide rows: the gathers of colours not swept yet are skipped
-      if (c < (c < z.n_top ? z.top_lim : z.bar_lim)) {
-        const Row<T, C> xc = *reinterpret_cast<const Row<T, C> *>(xq + (int64_t)c * K);
+    Row<T, C> xc = *reinterpret_cast<const Row<T, C> *>(xq + (int64_t)c * K);
+    if constexpr (PART == kLower) {
 #pragma unroll
-        for (int k = 0; k < C; ++k) acc[k] += DIFF ? v * (xc.v[k] - xr.v[k]) : v * xc.v[k];
-      }
-    } else {
-      // narrow rows: load every entry (the loads stay pipelined) and zero
-      // the ones not swept yet
-      Row<T, C> xc = *reinterpret_cast<const Row<T, C> *>(xq + (int64_t)c * K);
-      if constexpr (ZS) {
-        const bool live = c < (c < z.n_top ? z.top_lim : z.bar_lim);
-#pragma unroll
-        for (int k = 0; k < C; ++k) xc.v[k] = live ? xc.v[k] : T(0);
-      }
-#pragma unroll
-      for (int k = 0; k < C; ++k) acc[k] += DIFF ? v * (xc.v[k] - xr.v[k]) : v * xc.v[k];
+      for (int k = 0; k < C; ++k) xc.v[k] = c != own ? xc.v[k] : T(0);
     }
-    off += v;
+#pragma unroll
+    for (int k = 0; k < C; ++k) acc[k] += DIFF ? v * (xc.v[k] - xr.v[k]) : v * xc.v[k];
   }
 }
 
@@ -198,56 +187,51 @@ __device__ __forceinline__ void block_sum_rows(const double (&v)[K / LPR], doubl
 }
 
 // ------------------------------------------------------------- fine matrix
-// (A x)_r in difference form (MODE 0), or g_r - (A x)_r (MODE 1), columns
-// [q C, q C + C); the row's own operands are loaded before its entries
-// (mi: the row's index in A, r: its index in the vectors; equal unless A
-// holds a subset of the rows)
-template <class T, int K, int C, int MODE>
-__device__ __forceinline__ Row<T, C> fine_row(const Sell &A, int64_t s, int t, int q, int64_t mi, int64_t r,
-                                              const T *__restrict__ x, const Row<T, C> &xr,
-                                              const T *__restrict__ g) {
-  Row<T, C> gr;
-  if (MODE == 1) gr = ldp<T, K, C>(g, r, q);
+// (A x)_r in difference form, columns [q C, q C + C); the row's own operands
+// are loaded before its entries
+template <class T, int K, int C>
+__device__ __forceinline__ Row<T, C> fine_row(const Sell &A, int64_t s, int t, int q, int64_t r,
+                                              const T *__restrict__ x, const Row<T, C> &xr) {
   T d0, d1 = T(0);
   if constexpr (std::is_same<T, double>::value) {
-    d0 = A.d64[mi];
+    d0 = A.d64[r];
   } else {
-    d0 = A.s32[mi];
-    d1 = A.dh32[mi];
+    d0 = A.s32[r];
+    d1 = A.dh32[r];
   }
-  T acc[C], off;
-  sell_row<T, K, C, true>(A, s, t, q, x, xr, acc, off);
+  T acc[C];
+  sell_row<T, K, C, true>(A, s, t, q, x, xr, acc);
   Row<T, C> out;
-  if constexpr (std::is_same<T, double>::value) {
 #pragma unroll
-    for (int k = 0; k < C; ++k) out.v[k] = acc[k] + d0 * xr.v[k];
-  } else {
-#pragma unroll
-    for (int k = 0; k < C; ++k) out.v[k] = d0 * (acc[k] + d1 * xr.v[k]);
-  }
-  if (MODE == 1) {
-#pragma unroll
-    for (int k = 0; k < C; ++k) out.v[k] = gr.v[k] - out.v[k];
+  for (int k = 0; k < C; ++k) {
+    if constexpr (std::is_same<T, double>::value)
+      out.v[k] = acc[k] + d0 * xr.v[k];
+    else
+      out.v[k] = d0 * (acc[k] + d1 * xr.v[k]);
   }
   return out;
 }
 
-// y_r = g_r - (A x)_r by lane q of row r's lanes; the rows of zr are written
-// as zero without reading their entries (their residual is zero in exact
-// arithmetic); with y2, a row r >= y2_from is also stored there.
+// y_r = -(U x)_r, the residual after the forward sweep, by lane q of row r's
+// lanes; with y2, a row r >= y2_from is also stored there.
+// (mi: the row's index in A, r: its index in the vectors; equal unless A
+// holds a subset of the rows)
+// Bandwidth and gathers bound it, and U holds half of the row: with the
+// forward sweep reading L alone and this product U alone, FP64 solves of
+// 2,179,616 unknowns went from 314.2 to 293.1 ms (eight right-hand sides) and
+// from 123.8 to 115.6 ms (one).  On the same inputs one application of the
+// preconditioner moved by 2e-16 (relative), at aspect ratios 1e-2 to 1e-4.
 template <class T, int K>
 __device__ __forceinline__ void residual_row(const Sell &A, int64_t mi, int64_t r, int q, const T *__restrict__ x,
-                                             const T *__restrict__ g, T *y, const ZeroRows &zr, T *y2,
-                                             int64_t y2_from) {
+                                             T *y, T *y2, int64_t y2_from) {
   constexpr int LPR = row_lanes<T, K>(), C = K / LPR;
-  Row<T, C> out;
-  if ((r >= zr.a0 && r < zr.a1) || (r >= zr.b0 && r < zr.b1)) {
+  T s0 = T(1);
+  if constexpr (!std::is_same<T, double>::value) s0 = A.s32[mi];
+  Row<T, C> out{};
+  T acc[C];
+  sell_row<T, K, C, false, kUpper>(A, mi >> 6, (int)(mi & 63), q, x, out, acc);
 #pragma unroll
-    for (int k = 0; k < C; ++k) out.v[k] = T(0);
-  } else {
-    const Row<T, C> xr = ldp<T, K, C>(x, r, q);
-    out = fine_row<T, K, C, 1>(A, mi >> 6, (int)(mi & 63), q, mi, r, x, xr, g);
-  }
+  for (int k = 0; k < C; ++k) out.v[k] = -s0 * acc[k];
   stp<T, K, C>(y, r, q, out);
   if (y2 && r >= y2_from) stp<T, K, C>(y2, r, q, out);
 }
@@ -257,13 +241,13 @@ __device__ __forceinline__ void residual_row(const Sell &A, int64_t mi, int64_t 
 // order), so that its entries are read coalesced.
 template <class T, int K>
 __global__ __launch_bounds__(kBlock) void k_spmv_rows(Sell As, const int32_t *__restrict__ rows, int64_t nr,
-                                                     const T *__restrict__ x, const T *__restrict__ g,
-                                                     T *__restrict__ y, const int *__restrict__ done, ZeroRows zr) {
+                                                     const T *__restrict__ x, T *__restrict__ y,
+                                                     const int *__restrict__ done) {
   constexpr int LPR = row_lanes<T, K>();
   if (done && *done) return;
   const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / LPR;
   if (i >= nr) return;
-  residual_row<T, K>(As, i, rows[i], (int)(threadIdx.x % LPR), x, g, y, zr, (T *)nullptr, 0);
+  residual_row<T, K>(As, i, rows[i], (int)(threadIdx.x % LPR), x, y, (T *)nullptr, 0);
 }
 
 // Blocks of kBlock rows (four slices), row_lanes<T, K>() lanes per row.
@@ -273,8 +257,8 @@ __global__ __launch_bounds__(kBlock) void k_spmv_rows(Sell As, const int32_t *__
 template <class T, int K, int MODE, bool DOT>
 __global__ __launch_bounds__((kBlock * row_lanes<T, K>())) void k_spmv(
     Sell A, int64_t r0, int64_t r1, int64_t s_first, int64_t ns, int64_t nb, const int32_t *__restrict__ order,
-    const T *__restrict__ x, const T *__restrict__ g, T *__restrict__ y, double *__restrict__ partial,
-    const int *__restrict__ done, ZeroRows zr, T *__restrict__ y2, int64_t y2_from) {
+    const T *__restrict__ x, T *__restrict__ y, double *__restrict__ partial, const int *__restrict__ done,
+    T *__restrict__ y2, int64_t y2_from) {
   constexpr int LPR = row_lanes<T, K>(), C = K / LPR;
   static_assert(!(MODE == 1 && DOT), "the residual form has no block reduction");
   if (done && *done) return;
@@ -290,11 +274,11 @@ __global__ __launch_bounds__((kBlock * row_lanes<T, K>())) void k_spmv(
   if (i < ns && r >= r0 && r < r1) {
     if constexpr (MODE == 1) {
       // no block reduction in this form, so the lane may leave
-      residual_row<T, K>(A, r, r, q, x, g, y, zr, y2, y2_from);
+      residual_row<T, K>(A, r, r, q, x, y, y2, y2_from);
       return;
     }
     const Row<T, C> xr = ldp<T, K, C>(x, r, q);
-    const Row<T, C> out = fine_row<T, K, C, MODE>(A, s, t, q, r, r, x, xr, g);
+    const Row<T, C> out = fine_row<T, K, C>(A, s, t, q, r, x, xr);
     stp<T, K, C>(y, r, q, out);
     if (DOT) {
 #pragma unroll
@@ -315,51 +299,38 @@ struct GsDev {
   int64_t nbt;
 };
 
-// one Gauss-Seidel step of row r: x_r + (g_r - (A x)_r) / a_rr, with the
-// row's diagonal data d0, d1 loaded by the caller
-template <class T, int C>
-__device__ __forceinline__ Row<T, C> gs_apply(T d0, T d1, const Row<T, C> &xr, const Row<T, C> &gr,
-                                              const T (&acc)[C], T off) {
-  Row<T, C> out;
-  if constexpr (std::is_same<T, double>::value) {
-    const double dr = d0, diag = dr - off;
-#pragma unroll
-    for (int k = 0; k < C; ++k) out.v[k] = xr.v[k] + (gr.v[k] - (acc[k] + dr * xr.v[k])) / diag;
-  } else {
-    const float inv_s = 1.0f / d0, dh = d1, diag = dh - off;
-#pragma unroll
-    for (int k = 0; k < C; ++k) out.v[k] = xr.v[k] + (gr.v[k] * inv_s - (acc[k] + dh * xr.v[k])) / diag;
-  }
-  return out;
-}
-
 // One Gauss-Seidel step of row r by lane q of its row_lanes<T, K>() lanes
-// (columns [q C, q C + C)); with x2, a row r >= x2_from is also stored there.
+// (columns [q C, q C + C)): x_r + (g_r - (A x)_r) / a_rr, or with FIRST
+// (g_r - (L x)_r) / a_rr, the first sweep's step from zero, which reads L
+// alone; with x2, a row r >= x2_from is also stored there.
 // (mi: the row's index in A, r: its index in the vectors)
-template <class T, int K, bool ZS>
+template <class T, int K, bool FIRST>
 __device__ __forceinline__ void gs_row(const Sell &A, int64_t mi, int64_t r, int q, const T *__restrict__ g, T *x,
-                                       T *x2, int64_t x2_from, const ZeroStart &z) {
+                                       T *x2, int64_t x2_from) {
   constexpr int LPR = row_lanes<T, K>(), C = K / LPR;
   const int64_t s = mi >> 6;
   const int t = (int)(mi & 63);
-  Row<T, C> xr;
-  if constexpr (ZS) {
-#pragma unroll
-    for (int k = 0; k < C; ++k) xr.v[k] = T(0);
-  } else {
-    xr = ldp<T, K, C>(x, r, q);
-  }
+  Row<T, C> xr{};
+  if constexpr (!FIRST) xr = ldp<T, K, C>(x, r, q);
   const Row<T, C> gr = ldp<T, K, C>(g, r, q);
-  T d0, d1 = T(0);
+  T d = T(0), i0;
   if constexpr (std::is_same<T, double>::value) {
-    d0 = A.d64[mi];
+    i0 = A.i64[mi];
+    if (!FIRST) d = A.d64[mi];
   } else {
-    d0 = A.s32[mi];
-    d1 = A.dh32[mi];
+    i0 = 1.0f / A.s32[mi];  // the row-scaled operator has a unit diagonal
+    if (!FIRST) d = A.dh32[mi];
   }
-  T acc[C], off;
-  sell_row<T, K, C, true, ZS>(A, s, t, q, x, xr, acc, off, z);
-  const Row<T, C> out = gs_apply<T, C>(d0, d1, xr, gr, acc, off);
+  T acc[C];
+  sell_row<T, K, C, !FIRST, FIRST ? kLower : kAll>(A, s, t, q, x, xr, acc, (int32_t)r);
+  Row<T, C> out;
+#pragma unroll
+  for (int k = 0; k < C; ++k) {
+    if constexpr (std::is_same<T, double>::value)
+      out.v[k] = xr.v[k] + (gr.v[k] - (acc[k] + d * xr.v[k])) * i0;
+    else
+      out.v[k] = xr.v[k] + (gr.v[k] * i0 - (acc[k] + d * xr.v[k]));
+  }
   stp<T, K, C>(x, r, q, out);
   if (x2 && r >= x2_from) stp<T, K, C>(x2, r, q, out);
 }
@@ -367,10 +338,10 @@ __device__ __forceinline__ void gs_row(const Sell &A, int64_t mi, int64_t r, int
 // one slice per block (a colour holds few rows, so small blocks spread them
 // over every CU), row_lanes<T, K>() lanes per row; up to two row ranges (the
 // top and the non-top rows of one colour)
-template <class T, int K, bool ZS>
+template <class T, int K, bool FIRST>
 __global__ __launch_bounds__((kWave * row_lanes<T, K>())) void k_gs(Sell A, GsDev<T> J, const T *__restrict__ g,
-                                                                   const int *__restrict__ done, ZeroStart z) {
-  constexpr int LPR = row_lanes<T, K>(), C = K / LPR;
+                                                                   const int *__restrict__ done) {
+  constexpr int LPR = row_lanes<T, K>();
   if (done && *done) return;
   int64_t blk = xcd_block(blockIdx.x, J.nbt);
   int j = 0;
@@ -383,21 +354,20 @@ __global__ __launch_bounds__((kWave * row_lanes<T, K>())) void k_gs(Sell A, GsDe
   const int64_t s = J.sf[j] + blk;
   const int64_t r = s * 64 + t;
   if (r < r0 || r >= r1) return;
-  gs_row<T, K, ZS>(A, r, r, q, g, J.x, J.x2, J.x2_from, z);
+  gs_row<T, K, FIRST>(A, r, r, q, g, J.x, J.x2, J.x2_from);
 }
 
 // The listed rows rows[0 .. nr) (rows that share no entries), each by its
-// row_lanes<T, K>() lanes, with the arithmetic of k_gs; As holds those rows
+// row_lanes<T, K>() lanes, with the arithmetic of k_gs's first sweep; As holds those rows
 // (row i of As is row rows[i] of the matrix, its entries in the same order).
-template <class T, int K, bool ZS>
+template <class T, int K>
 __global__ __launch_bounds__(kBlock) void k_gs_rows(Sell As, const int32_t *__restrict__ rows, int64_t nr,
-                                                   const T *__restrict__ g, T *x, const int *__restrict__ done,
-                                                   ZeroStart z) {
+                                                   const T *__restrict__ g, T *x, const int *__restrict__ done) {
   constexpr int LPR = row_lanes<T, K>();
   if (done && *done) return;
   const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / LPR;
   if (i >= nr) return;
-  gs_row<T, K, ZS>(As, i, rows[i], (int)(threadIdx.x % LPR), g, x, (T *)nullptr, 0, z);
+  gs_row<T, K, true>(As, i, rows[i], (int)(threadIdx.x % LPR), g, x, (T *)nullptr, 0);
 }
 
 template <class T, int K, bool ACC>
@@ -412,8 +382,8 @@ __global__ __launch_bounds__(kBlock) void k_rect(Sell E, int64_t nb, const T *__
   Row<T, K> zero;
 #pragma unroll
   for (int k = 0; k < K; ++k) zero.v[k] = T(0);
-  T acc[K], off;
-  sell_row<T, K, K, false>(E, s, lane, 0, x, zero, acc, off);
+  T acc[K];
+  sell_row<T, K, K, false>(E, s, lane, 0, x, zero, acc);
   Row<T, K> out;
   if (ACC) out = ld<T, K>(y, r);
 #pragma unroll
@@ -438,8 +408,8 @@ __global__ __launch_bounds__(kBlock) void k_prolong_sum(Sell E, int64_t n_top, i
     Row<T, K> zero;
 #pragma unroll
     for (int k = 0; k < K; ++k) zero.v[k] = T(0);
-    T acc[K], off;
-    sell_row<T, K, K, false>(E, s, lane, 0, ys, zero, acc, off);
+    T acc[K];
+    sell_row<T, K, K, false>(E, s, lane, 0, ys, zero, acc);
     Row<T, K> out;
     if (r >= n_top) {
       const Row<T, K> wr = ld<T, K>(w, r);
@@ -1299,8 +1269,8 @@ void launch_slot_copy(hipStream_t stm, unsigned mask, const double *z, double *p
   }
 
 template <class T>
-void launch_spmv(hipStream_t stm, int K, const Sell &A, int mode, int64_t r0, int64_t r1, const T *x, const T *g,
-                 T *y, double *partial, const int *done, const int32_t *order, ZeroRows zr, T *y2, int64_t y2_from) {
+void launch_spmv(hipStream_t stm, int K, const Sell &A, int mode, int64_t r0, int64_t r1, const T *x, T *y,
+                 double *partial, const int *done, const int32_t *order, T *y2, int64_t y2_from) {
   int64_t nb = sell_blocks(r0, r1);
   if (!nb) return;
   int64_t sf = r0 / kWave, ns = (r1 + kWave - 1) / kWave - sf;
@@ -1308,14 +1278,14 @@ void launch_spmv(hipStream_t stm, int K, const Sell &A, int mode, int64_t r0, in
     const dim3 blk(kBlock * row_lanes<T, KK>());
     if (mode == 0) {
       if (partial)
-        hipLaunchKernelGGL((k_spmv<T, KK, 0, true>), grid(nb), blk, 0, stm, A, r0, r1, sf, ns, nb, order, x, g, y,
-                           partial, done, zr, y2, y2_from);
+        hipLaunchKernelGGL((k_spmv<T, KK, 0, true>), grid(nb), blk, 0, stm, A, r0, r1, sf, ns, nb, order, x, y,
+                           partial, done, y2, y2_from);
       else
-        hipLaunchKernelGGL((k_spmv<T, KK, 0, false>), grid(nb), blk, 0, stm, A, r0, r1, sf, ns, nb, order, x, g, y,
-                           partial, done, zr, y2, y2_from);
+        hipLaunchKernelGGL((k_spmv<T, KK, 0, false>), grid(nb), blk, 0, stm, A, r0, r1, sf, ns, nb, order, x, y,
+                           partial, done, y2, y2_from);
     } else {
-      hipLaunchKernelGGL((k_spmv<T, KK, 1, false>), grid(nb), blk, 0, stm, A, r0, r1, sf, ns, nb, order, x, g, y,
-                         partial, done, zr, y2, y2_from);
+      hipLaunchKernelGGL((k_spmv<T, KK, 1, false>), grid(nb), blk, 0, stm, A, r0, r1, sf, ns, nb, order, x, y,
+                         partial, done, y2, y2_from);
     }
   })
 }
@@ -1325,31 +1295,28 @@ static inline int64_t slices(int64_t r0, int64_t r1) {
 }
 
 template <class T>
-void launch_spmv_rows(hipStream_t stm, int K, const Sell &A, const int32_t *rows, int64_t nr, const T *x, const T *g,
-                      T *y, const int *done, ZeroRows zr) {
+void launch_spmv_rows(hipStream_t stm, int K, const Sell &A, const int32_t *rows, int64_t nr, const T *x, T *y,
+                      const int *done) {
   if (nr <= 0) return;
   VEMG_K_SWITCH(K, {
     const int64_t nb = (nr * row_lanes<T, KK>() + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL((k_spmv_rows<T, KK>), grid(nb), dim3(kBlock), 0, stm, A, rows, nr, x, g, y, done, zr);
+    hipLaunchKernelGGL((k_spmv_rows<T, KK>), grid(nb), dim3(kBlock), 0, stm, A, rows, nr, x, y, done);
   })
 }
 
 template <class T>
 void launch_gs_rows(hipStream_t stm, int K, const Sell &A, const int32_t *rows, int64_t nr, const T *g, T *x,
-                    const int *done, ZeroStart zs) {
+                    const int *done) {
   if (nr <= 0) return;
   VEMG_K_SWITCH(K, {
     const int64_t nb = (nr * row_lanes<T, KK>() + kBlock - 1) / kBlock;
-    if (zs.on)
-      hipLaunchKernelGGL((k_gs_rows<T, KK, true>), grid(nb), dim3(kBlock), 0, stm, A, rows, nr, g, x, done, zs);
-    else
-      hipLaunchKernelGGL((k_gs_rows<T, KK, false>), grid(nb), dim3(kBlock), 0, stm, A, rows, nr, g, x, done, zs);
+    hipLaunchKernelGGL((k_gs_rows<T, KK>), grid(nb), dim3(kBlock), 0, stm, A, rows, nr, g, x, done);
   })
 }
 
 template <class T>
 void launch_gs(hipStream_t stm, int K, const Sell &A, int64_t a0, int64_t a1, int64_t b0, int64_t b1, const T *g,
-               T *x, const int *done, ZeroStart zs, T *x2, int64_t x2_from) {
+               T *x, const int *done, bool first, T *x2, int64_t x2_from) {
   GsDev<T> J{};
   J.x = x;
   J.x2 = x2;
@@ -1368,10 +1335,10 @@ void launch_gs(hipStream_t stm, int K, const Sell &A, int64_t a0, int64_t a1, in
   if (!J.nbt) return;
   VEMG_K_SWITCH(K, {
     const dim3 blk(kWave * row_lanes<T, KK>());
-    if (zs.on)
-      hipLaunchKernelGGL((k_gs<T, KK, true>), grid(J.nbt), blk, 0, stm, A, J, g, done, zs);
+    if (first)
+      hipLaunchKernelGGL((k_gs<T, KK, true>), grid(J.nbt), blk, 0, stm, A, J, g, done);
     else
-      hipLaunchKernelGGL((k_gs<T, KK, false>), grid(J.nbt), blk, 0, stm, A, J, g, done, zs);
+      hipLaunchKernelGGL((k_gs<T, KK, false>), grid(J.nbt), blk, 0, stm, A, J, g, done);
   })
 }
 
@@ -1554,14 +1521,14 @@ void launch_pcg_resume(hipStream_t stm, int, Scal *s, unsigned keep) {
 }
 
 #define VEMG_INSTANTIATE(T)                                                                                          \
-  template void launch_spmv<T>(hipStream_t, int, const Sell &, int, int64_t, int64_t, const T *, const T *, T *,      \
-                               double *, const int *, const int32_t *, ZeroRows, T *, int64_t);                      \
-  template void launch_spmv_rows<T>(hipStream_t, int, const Sell &, const int32_t *, int64_t, const T *, const T *,   \
-                                    T *, const int *, ZeroRows);                                                     \
+  template void launch_spmv<T>(hipStream_t, int, const Sell &, int, int64_t, int64_t, const T *, T *, double *,       \
+                               const int *, const int32_t *, T *, int64_t);                                          \
+  template void launch_spmv_rows<T>(hipStream_t, int, const Sell &, const int32_t *, int64_t, const T *, T *,         \
+                                    const int *);                                                                    \
   template void launch_gs<T>(hipStream_t, int, const Sell &, int64_t, int64_t, int64_t, int64_t, const T *, T *,       \
-                             const int *, ZeroStart, T *, int64_t);                                                  \
+                             const int *, bool, T *, int64_t);                                                       \
   template void launch_gs_rows<T>(hipStream_t, int, const Sell &, const int32_t *, int64_t, const T *, T *,           \
-                                  const int *, ZeroStart);                                                           \
+                                  const int *);                                                                      \
   template void launch_rect<T>(hipStream_t, int, const Sell &, bool, const T *, T *, const int *);                    \
   template void launch_prolong_sum<T>(hipStream_t, int, const Sell &, int64_t, const T *, const T *, const T *, T *,   \
                                       double *, const int *);                                                        \

@@ -27,12 +27,18 @@ constexpr int kMaxBatch = 8;
 //   fine A (difference form): FP64 values a_ij with the deficit d64;
 //   FP32 copy: row-scaled values a_ij / a_ii with s32 = a_ii and
 //   dh32 = d_i / a_ii, so (A x)_i = s_i (sum_j w_ij (x_j - x_i) + dh_i x_i).
+// The fine A holds in every row first the couplings to earlier sweep colours
+// (the lower part L of its multicolour order), then those to later ones (U);
+// in slice s the L entries end at smid[s], each part padded to the slice's
+// longest.  The forward sweep from zero reads L alone and the residual after
+// it U alone (sell_row).
 struct Sell {
   const int64_t *sptr = nullptr;  // nslices + 1 entry offsets
+  const int64_t *smid = nullptr;  // fine A: where slice s's U entries begin
   const int32_t *col = nullptr;
   const double *val64 = nullptr;
   const float *val32 = nullptr;
-  const double *d64 = nullptr;
+  const double *d64 = nullptr, *i64 = nullptr;  // deficit d_i and 1 / a_ii
   const float *s32 = nullptr, *dh32 = nullptr;
   int64_t nrows = 0;
 };
@@ -83,50 +89,37 @@ inline int64_t sell_blocks(int64_t r0, int64_t r1) {
 inline int64_t vec_blocks(int64_t n) { return (n + kBlock - 1) / kBlock; }
 
 // ---- fine matrix (SELL, difference form) ---------------------------------
-// Rows [a0, a1) and [b0, b1) whose residual is zero in exact arithmetic: the
-// rows of the last colour of a forward multicolour Gauss-Seidel sweep with
-// relaxation 1, whose neighbours all lie in colours swept before them.
-struct ZeroRows {
-  int64_t a0 = 0, a1 = 0, b0 = 0, b1 = 0;
-};
-// y = A x (mode 0) or y = g - A x (mode 1) on rows [r0, r1).  With partial,
-// partial[block * K + k] = sum over the block's rows of x_ik y_ik.  order
-// (optional): the range's slices in visit order (offsets from slice r0 / 64),
-// so that the blocks of one XCD take one spatial region of every colour.  In
-// mode 1 the rows of zr get y = 0 without reading their entries.
-// Mode 1 only: with y2, the rows r >= y2_from are also stored to y2 (a copy
-// of the result for a second consumer).
+// y = A x (mode 0) on rows [r0, r1), or the residual y = g - A x right after a
+// forward multicolour Gauss-Seidel sweep from zero with relaxation 1 that gave
+// x (mode 1): (L + D) x = g, so g - A x = -U x and g is not read.  With
+// partial, partial[block * K + k] = sum over the block's rows of x_ik y_ik.
+// order (optional): the range's slices in visit order (offsets from slice
+// r0 / 64), so that the blocks of one XCD take one spatial region of every
+// colour.  Mode 1 only: with y2, the rows r >= y2_from are also stored to y2
+// (a copy of the result for a second consumer).
 template <class T>
-void launch_spmv(hipStream_t st, int K, const Sell &A, int mode, int64_t r0, int64_t r1, const T *x, const T *g,
-                 T *y, double *partial, const int *done, const int32_t *order = nullptr, ZeroRows zr = ZeroRows(),
-                 T *y2 = nullptr, int64_t y2_from = 0);
-// y = g - A x (mode 1 of launch_spmv, the same arithmetic row by row) on the
-// listed rows rows[0 .. nr) only, rows of zr written as zero.  A holds
-// exactly those rows: its row i is the matrix's row rows[i], with the same
-// entries in the same order.
+void launch_spmv(hipStream_t st, int K, const Sell &A, int mode, int64_t r0, int64_t r1, const T *x, T *y,
+                 double *partial, const int *done, const int32_t *order = nullptr, T *y2 = nullptr,
+                 int64_t y2_from = 0);
+// Mode 1 of launch_spmv (the same arithmetic row by row) on the listed rows
+// rows[0 .. nr) only.  A holds exactly those rows: its row i is the matrix's
+// row rows[i], with the same entries in the same order.
 template <class T>
-void launch_spmv_rows(hipStream_t st, int K, const Sell &A, const int32_t *rows, int64_t nr, const T *x, const T *g,
-                      T *y, const int *done, ZeroRows zr);
+void launch_spmv_rows(hipStream_t st, int K, const Sell &A, const int32_t *rows, int64_t nr, const T *x, T *y,
+                      const int *done);
 // One multicolour Gauss-Seidel step on the rows [a0,a1) and [b0,b1) (rows of
-// one colour): x_i += (g_i - (A x)_i) / a_ii.
-// Zero start (the first sweep from x = 0): of the top block (j < n_top) only
-// the columns j < top_lim are read, of the rest only j < bar_lim; every other
-// value (the colours not swept yet, and the row's own) is taken as zero
-// without being read, so x needs no fill beforehand.
-struct ZeroStart {
-  bool on = false;
-  int64_t n_top = 0, top_lim = 0, bar_lim = 0;
-};
+// one colour): x_i += (g_i - (A x)_i) / a_ii.  first: the first sweep from
+// x = 0, in ascending colours, x_i = (g_i - (L x)_i) / a_ii; x needs no fill.
 // With x2, the updated rows r >= x2_from are also stored to x2.
 template <class T>
 void launch_gs(hipStream_t st, int K, const Sell &A, int64_t a0, int64_t a1, int64_t b0, int64_t b1, const T *g,
-               T *x, const int *done, ZeroStart zs = ZeroStart(), T *x2 = nullptr, int64_t x2_from = 0);
-// The Gauss-Seidel step of launch_gs (the same arithmetic row by row) on the
+               T *x, const int *done, bool first, T *x2 = nullptr, int64_t x2_from = 0);
+// The first sweep's step of launch_gs (the same arithmetic row by row) on the
 // listed rows rows[0 .. nr) only; the rows must share no entries.  A holds
 // exactly those rows, as for launch_spmv_rows.
 template <class T>
 void launch_gs_rows(hipStream_t st, int K, const Sell &A, const int32_t *rows, int64_t nr, const T *g, T *x,
-                    const int *done, ZeroStart zs);
+                    const int *done);
 // y = E x (accumulate: y += E x) for a rectangular SELL matrix, rows [0, nrows).
 template <class T>
 void launch_rect(hipStream_t st, int K, const Sell &E, bool accumulate, const T *x, T *y, const int *done);
