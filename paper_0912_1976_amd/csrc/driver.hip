@@ -88,11 +88,8 @@ struct Arena {
 // those to later ones, the two parts padded apart (Sell::smid).
 Sell pack_sell(Arena &ar, hipStream_t st, const Csr &A, bool square, const std::vector<double> *d,
                const std::vector<double> *diag, int64_t *stored = nullptr,
-               const std::vector<int32_t> *subset = nullptr, const std::vector<int32_t> *colour = nullptr) {
-  // subset: pack only these rows of A, row i of the result being A's row
-  // (*subset)[i] with its entries (columns unchanged) in the same order
-  int64_t n = subset ? (int64_t)subset->size() : A.nrows, ns = (n + kWave - 1) / kWave;
-  auto row_of = [&](int64_t i) -> int64_t { return subset ? (int64_t)(*subset)[i] : i; };
+               const std::vector<int32_t> *colour = nullptr) {
+  int64_t n = A.nrows, ns = (n + kWave - 1) / kWave;
   // part of entry e of row r: 0 (earlier colour, or no colours) or 1; -1: not stored
   auto part_of = [&](int64_t r, int64_t e) {
     const int64_t c = A.idx[e];
@@ -102,8 +99,7 @@ Sell pack_sell(Arena &ar, hipStream_t st, const Csr &A, bool square, const std::
   std::vector<int64_t> sptr(ns + 1, 0), smid(ns, 0);
   for (int64_t s = 0; s < ns; ++s) {
     int64_t L[2] = {0, 0};
-    for (int64_t i = s * kWave; i < std::min(n, (s + 1) * kWave); ++i) {
-      const int64_t r = row_of(i);
+    for (int64_t r = s * kWave; r < std::min(n, (s + 1) * kWave); ++r) {
       int64_t len[2] = {0, 0};
       for (int64_t e = A.ptr[r]; e < A.ptr[r + 1]; ++e) {
         const int p = part_of(r, e);
@@ -118,28 +114,27 @@ Sell pack_sell(Arena &ar, hipStream_t st, const Csr &A, bool square, const std::
   std::vector<double> val(sptr[ns], 0.0);
   std::vector<float> val32(sptr[ns], 0.0f);
   std::vector<double> dv(square ? n : 0, 0.0), ad(square ? n : 0, 0.0);
-  for (int64_t i = 0; square && i < n; ++i) {
-    const int64_t r = row_of(i);
-    if (diag) ad[i] = (*diag)[r];
+  for (int64_t r = 0; square && r < n; ++r) {
+    if (diag) ad[r] = (*diag)[r];
     for (int64_t e = A.ptr[r]; e < A.ptr[r + 1]; ++e)
-      if (A.idx[e] == r) ad[i] = A.val[e];
-    dv[i] = d ? (*d)[r] : ad[i];
+      if (A.idx[e] == r) ad[r] = A.val[e];
+    dv[r] = d ? (*d)[r] : ad[r];
   }
   for (int64_t s = 0; s < ns; ++s) {
     for (int t = 0; t < kWave; ++t) {
-      const int64_t i = s * kWave + t, r = i < n ? row_of(i) : -1;
+      const int64_t r = s * kWave + t;
       int64_t pos[2] = {sptr[s] + t, smid[s] + t};
-      for (int64_t e = i < n ? A.ptr[r] : 0; i < n && e < A.ptr[r + 1]; ++e) {
+      for (int64_t e = r < n ? A.ptr[r] : 0; r < n && e < A.ptr[r + 1]; ++e) {
         const int p = part_of(r, e);
         if (p < 0) continue;
         col[pos[p]] = A.idx[e];
         val[pos[p]] = A.val[e];
-        val32[pos[p]] = square ? (float)(A.val[e] / ad[i]) : (float)A.val[e];
+        val32[pos[p]] = square ? (float)(A.val[e] / ad[r]) : (float)A.val[e];
         pos[p] += kWave;
       }
       const int64_t end[2] = {smid[s], sptr[s + 1]};
       for (int p = 0; p < 2; ++p)
-        for (; pos[p] < end[p]; pos[p] += kWave) col[pos[p]] = (square && i < n) ? (int32_t)r : 0;
+        for (; pos[p] < end[p]; pos[p] += kWave) col[pos[p]] = (square && r < n) ? (int32_t)r : 0;
     }
   }
   if (stored) *stored = sptr[ns];
@@ -166,6 +161,74 @@ Sell pack_sell(Arena &ar, hipStream_t st, const Csr &A, bool square, const std::
   return M;
 }
 
+// One entry of a row packed by pack_rows (col2: see Sell)
+struct RowEntry {
+  int32_t col, col2;
+  double v;
+  float v32;
+};
+
+// Row data of pack_rows (empty vectors: not stored): deficit and diagonal
+struct RowData {
+  std::vector<double> d, diag;
+};
+
+// Rows given one by one -> SELL-64 (device): row(i, out) appends row i's
+// entries, all of them in the lower part (smid at the slice's end); padding
+// entries have value 0 and column pad(i).
+template <class F, class G>
+Sell pack_rows(Arena &ar, hipStream_t st, int64_t n, bool pairs, F &&row, G &&pad, const RowData &data = RowData()) {
+  const int64_t ns = (n + kWave - 1) / kWave;
+  std::vector<int64_t> sptr(ns + 1, 0), ptr(n + 1, 0);
+  std::vector<RowEntry> all;
+  for (int64_t i = 0; i < n; ++i) {
+    row(i, all);
+    ptr[i + 1] = (int64_t)all.size();
+  }
+  for (int64_t s = 0; s < ns; ++s) {
+    int64_t L = 0;
+    for (int64_t i = s * kWave; i < std::min(n, (s + 1) * kWave); ++i) L = std::max(L, ptr[i + 1] - ptr[i]);
+    sptr[s + 1] = sptr[s] + L * kWave;
+  }
+  std::vector<int32_t> col(sptr[ns], 0), col2(pairs ? sptr[ns] : 0, -1);
+  std::vector<double> val(sptr[ns], 0.0);
+  std::vector<float> val32(sptr[ns], 0.0f);
+  for (int64_t s = 0; s < ns; ++s)
+    for (int t = 0; t < kWave && s * kWave + t < n; ++t) {
+      const int64_t i = s * kWave + t;
+      int64_t pos = sptr[s] + t;
+      for (int64_t e = ptr[i]; e < ptr[i + 1]; ++e, pos += kWave) {
+        col[pos] = all[e].col;
+        if (pairs) col2[pos] = all[e].col2;
+        val[pos] = all[e].v;
+        val32[pos] = all[e].v32;
+      }
+      for (; pos < sptr[s + 1]; pos += kWave) col[pos] = pad(i);
+    }
+  Sell M;
+  M.nrows = n;
+  M.sptr = ar.upload(sptr, st);
+  M.smid = M.sptr + 1;
+  M.col = ar.upload(col, st);
+  if (pairs) M.col2 = ar.upload(col2, st);
+  M.val64 = ar.upload(val, st);
+  M.val32 = ar.upload(val32, st);
+  if (!data.diag.empty()) {
+    std::vector<double> inv(n);
+    std::vector<float> s32(n), dh32(n);
+    for (int64_t i = 0; i < n; ++i) {
+      inv[i] = 1.0 / data.diag[i];
+      s32[i] = (float)data.diag[i];
+      dh32[i] = (float)(data.d[i] / data.diag[i]);
+    }
+    M.d64 = ar.upload(data.d, st);
+    M.i64 = ar.upload(inv, st);
+    M.s32 = ar.upload(s32, st);
+    M.dh32 = ar.upload(dh32, st);
+  }
+  return M;
+}
+
 // CSR (host) -> CsrG (device).  Square matrices keep only off-diagonals
 // (FP64 values with d64 = a_ii; FP32 values a_ij / a_ii with s32 = a_ii).
 // G = smallest power of two >= half the mean row length, clamped to [4, 64].
@@ -174,8 +237,10 @@ Sell pack_sell(Arena &ar, hipStream_t st, const Csr &A, bool square, const std::
 // the order of their smallest column rank and orow maps them back, so that
 // the rows one XCD works on gather from one region of the fine vector; each
 // row keeps its entries and their order.
+// colmap (optional): the stored column of column c is (*colmap)[c].
 CsrG pack_csrg(Arena &ar, hipStream_t st, const Csr &A, bool square, int64_t *stored = nullptr,
-               const std::vector<int64_t> *colkey = nullptr, int64_t coloff = 0) {
+               const std::vector<int64_t> *colkey = nullptr, int64_t coloff = 0,
+               const std::vector<int32_t> *colmap = nullptr) {
   std::vector<int32_t> ptr(A.nrows + 1, 0), col;
   std::vector<double> val, d(square ? A.nrows : 0, 0.0);
   std::vector<float> val32;
@@ -197,7 +262,7 @@ CsrG pack_csrg(Arena &ar, hipStream_t st, const Csr &A, bool square, int64_t *st
     const int64_t r = rows[i];
     for (int64_t k = A.ptr[r]; k < A.ptr[r + 1]; ++k) {
       if (square && A.idx[k] == r) continue;
-      col.push_back(A.idx[k]);
+      col.push_back(colmap ? (*colmap)[A.idx[k]] : A.idx[k]);
       val.push_back(A.val[k]);
       val32.push_back(square ? (float)(A.val[k] / d[r]) : (float)A.val[k]);
     }
@@ -274,11 +339,10 @@ struct DLevel {
 // the mixed-precision solve (the last iteration of every chunk)
 enum GraphKind { kGraphFP64 = 0, kGraphFP32 = 1, kGraphMixedPC = 2, kGraphFP32Reliable = 3 };
 
-// the captured graphs of one PCG iteration: a single graph, or four segments
-struct IterGraphs {
-  hipGraph_t graph[7] = {};
-  hipGraphExec_t exec[7] = {};
-  int parts = 0;
+// the captured graph of one PCG iteration
+struct IterGraph {
+  hipGraph_t graph = nullptr;
+  hipGraphExec_t exec = nullptr;
 };
 
 }  // namespace
@@ -287,11 +351,10 @@ struct IterGraphs {
 struct vemg_solver_s {
   vemg_options opt;
   int device = -1;
-  hipStream_t user = nullptr, work = nullptr, work2 = nullptr;  // work2: parallel preconditioner branch
-  bool own_streams = true;  // false: work and work2 belong to a server's stream pool
+  hipStream_t user = nullptr, work = nullptr;
+  bool own_stream = true;   // false: work belongs to a server's stream pool
   size_t footprint = 0;     // device bytes of the uploaded setup (counted before the upload)
-  // ev_res: the SOR cycle's residual is done (the shared forward sweep)
-  hipEvent_t ev = nullptr, ev_fork = nullptr, ev_join = nullptr, ev_res = nullptr;
+  hipEvent_t ev = nullptr;
   std::string err;
   bool ready = false;
   vemg::Problem P;
@@ -308,26 +371,20 @@ struct vemg_solver_s {
   // slice visit orders (spatial, across colours) of the products over all
   // rows and over the non-top rows
   int32_t *order_all = nullptr, *order_bar = nullptr;
-  // VL + additive smoother: the smoother's fine forward sweep and residual
-  // take the SOR cycle's for every non-top row they share; the rows that
-  // differ, per colour for the sweep (reuse_gs[reuse_gs_start[c] ..
-  // reuse_gs_start[c+1]), and for the residual (reuse_res, n_reuse_res)
-  bool reuse = false;
-  // the rows of reuse_gs of each colour, and those of reuse_res, packed as
-  // SELL matrices of their own (entries read coalesced)
-  std::vector<vemg::Sell> reuse_gs_sell;
-  vemg::Sell reuse_res_sell;
-  int64_t share_min_rows = 0;  // fine unknowns from which the forward sweep is shared
-  bool reuse_full_res = false;  // no top surface: the smoother's residual is computed in full
+  // VL + additive smoother: both cycles in one pair of fine sweeps (unless
+  // A_bar's hierarchy is a single dense level); D's rows of colour c are
+  // [dstart[c], dstart[c+1]), and merged_Pt restricts the smoother's residual
+  // from the extended vector
+  bool merged = false;
+  vemg::MergedRows M;
+  std::vector<int64_t> dstart;
+  vemg::CsrG merged_Pt;
   // the top block of the additive smoother's x (rows [0, n_top) of v64.w and
   // v32.w) is zero in the layout of every batch width up to w_clean
   int w_clean = vemg::kMaxBatch;
-  int32_t *reuse_gs = nullptr, *reuse_res = nullptr;
-  std::vector<int64_t> reuse_gs_start;
-  int64_t n_reuse_res = 0;
   vemg::Scal *scal = nullptr;
   int64_t nnz_A = 0, nnz_E = 0;
-  std::map<int, vemg::IterGraphs> graphs;  // key: kind * 16 + K
+  std::map<int, vemg::IterGraph> graphs;  // key: kind * 16 + K
   // false for server lanes once the scheduler runs: a capture on one thread
   // must not coincide with device-wide synchronisation on another
   bool allow_capture = true;
@@ -464,244 +521,276 @@ void build_levels(Handle *h, std::vector<Level> &H, std::vector<DLevel> &D, int 
   }
 }
 
-// The rows of a fine level whose forward sweep and residual differ from the
-// SOR cycle's, which has already stored its values for every other row (the
-// additive smoother beside the SOR cycle).
-struct Reuse {
-  const int32_t *gs = nullptr;           // dirty rows, colour by colour
-  const std::vector<int64_t> *gs_start = nullptr;
-  const std::vector<Sell> *gs_sell = nullptr;  // those rows of each colour, packed
-  const int32_t *res = nullptr;          // rows whose residual is recomputed
-  int64_t nres = 0;
-  const Sell *res_sell = nullptr;        // those rows, packed
-  bool full_res = false;                 // recompute every row's residual (no top surface)
-  int phase = 0;  // 1: the dirty rows' sweep only; 2: the residual rows and the rest of the cycle
+// The coarse part of one or two hierarchies, from levels l[i] (a coarse level,
+// or one that is the coarsest) down and up again; a null hierarchy is left
+// out.  The two are independent, so levels at the same height above their
+// coarsest share their launches, step by step.
+template <class T>
+struct Cycle {
+  std::vector<DLevel> *H = nullptr;
+  size_t l = 0;
+  int64_t left() const { return H ? (int64_t)(H->size() - l) : 0; }
+  DLevel &level() const { return (*H)[l]; }
 };
 
 template <class T>
-void vcycle(hipStream_t st, int K, std::vector<DLevel> &H, size_t l, const int *done,
-            const Reuse *reuse = nullptr) {
-  DLevel &L = H[l];
-  T *x = L.x<T>(), *g = L.g<T>(), *r = L.r<T>();
-  const int64_t o = L.row0 * K;
-  if (L.coarsest) {
-    launch_dense<T>(st, K, L.Cinv, L.n, g + o, x + o, L.dpart, done);
+void coarse_cycles(hipStream_t st, int K, Cycle<T> a, Cycle<T> b, const int *done) {
+  const int64_t ra = a.left(), rb = b.left();
+  if (ra == 0 && rb == 0) return;
+  DLevel *L[2];
+  int nl = 0;
+  if (ra >= rb) L[nl++] = &a.level();
+  if (rb >= ra) L[nl++] = &b.level();
+  if (L[0]->coarsest) {
+    DenseJob<T> J[2];
+    for (int i = 0; i < nl; ++i) {
+      const int64_t o = L[i]->row0 * K;
+      J[i].C = L[i]->Cinv;
+      J[i].m = L[i]->n;
+      J[i].g = L[i]->template g<T>() + o;
+      J[i].x = L[i]->template x<T>() + o;
+      J[i].part = L[i]->dpart;
+    }
+    launch_dense<T>(st, K, J, nl, done);
     return;
   }
-  const int nc = (int)(L.fine ? L.cstart.size() : L.pc_start.size()) - 1;
-  // forward (zero start: x needs no fill, the colours not swept yet are not
-  // read) and backward sweeps of colour c (coarse levels: patch colour c);
-  // on A_bar's fine level (no top range) the top columns multiply the
-  // smoother vector's top part, which is zero
-  auto gs = [&](int c, bool first) {
-    if (L.fine) {
-      if (!L.cstart_top.empty()) {
-        launch_gs<T>(st, K, L.As, L.cstart_top[c], L.cstart_top[c + 1], L.cstart[c], L.cstart[c + 1], g, x, done,
-                     first);
-      } else {
-        launch_gs<T>(st, K, L.As, L.cstart[c], L.cstart[c + 1], 0, 0, g, x, done, first);
-      }
-    } else {
-      launch_patch_gs<T>(st, K, L.Ac, L.ps, L.pc_start[c], L.pc_start[c + 1] - L.pc_start[c], g, x, done,
-                         first ? L.pc_row[c] : -1, !first);
+  int nc = 0;
+  for (int i = 0; i < nl; ++i) nc = std::max(nc, (int)L[i]->pc_start.size() - 1);
+  // the k-th launch of a sweep: each level's k-th patch colour in its order
+  auto sweep = [&](int k, bool first) {
+    PatchJob<T> J[2];
+    int nj = 0;
+    for (int i = 0; i < nl; ++i) {
+      const int own = (int)L[i]->pc_start.size() - 1;
+      if (k >= own) continue;
+      const int c = first ? k : own - 1 - k;
+      PatchJob<T> &j = J[nj++];
+      j.A = L[i]->Ac;
+      j.S = L[i]->ps;
+      j.p0 = L[i]->pc_start[c];
+      j.np = L[i]->pc_start[c + 1] - j.p0;
+      j.zlim = L[i]->pc_row[c];
+      j.g = L[i]->template g<T>();
+      j.x = L[i]->template x<T>();
     }
+    launch_patch_gs<T>(st, K, first ? kPatchFirst : kPatchBackward, J, nj, done);
   };
-  if (reuse && L.fine && L.cstart_top.empty()) {
-    // x and r hold the SOR cycle's values (x once its forward sweep is done,
-    // r once its residual is); sweep and recompute only the rows where the
-    // two differ, with the same arithmetic
-    if (reuse->phase == 1) {
-      for (int c = 0; c < nc; ++c) {
-        const int64_t a = (*reuse->gs_start)[c], b = (*reuse->gs_start)[c + 1];
-        launch_gs_rows<T>(st, K, (*reuse->gs_sell)[c], reuse->gs + a, b - a, g, x, done);
-      }
-      return;
-    }
-    if (reuse->full_res)
-      launch_spmv<T>(st, K, L.As, 1, L.row0, L.row0 + L.n, x, r, nullptr, done, L.order);
-    else
-      launch_spmv_rows<T>(st, K, *reuse->res_sell, reuse->res, reuse->nres, x, r, done);
-  } else {
-    for (int c = 0; c < nc; ++c) gs(c, true);
+  for (int k = 0; k < nc; ++k) sweep(k, true);
+  Cycle<T> na = a, nb = b;
+  if (ra >= rb) ++na.l;
+  if (rb >= ra) ++nb.l;
+  CsrJob<T> res[2], down[2], up[2];
+  for (int i = 0; i < nl; ++i) {
+    DLevel &C = i == 0 && ra >= rb ? na.level() : nb.level();
+    res[i].A = L[i]->Ac;
+    res[i].x = L[i]->template x<T>();
+    res[i].g = L[i]->template g<T>();
+    res[i].y = L[i]->template r<T>();
+    down[i].A = L[i]->Pt;
+    down[i].x = L[i]->template r<T>();
+    down[i].y = C.template g<T>();
+    up[i].A = L[i]->P;
+    up[i].x = C.template x<T>();
+    up[i].y = L[i]->template x<T>();
   }
-  if (L.fine) {
-    if (!(reuse && L.cstart_top.empty()))
-      launch_spmv<T>(st, K, L.As, 1, L.row0, L.row0 + L.n, x, r, nullptr, done, L.order);
-  } else
-    launch_csr_spmv<T>(st, K, L.Ac, 1, 0, L.n, x, g, r, done);
-  DLevel &C = H[l + 1];
-  launch_csr_rect<T>(st, K, L.Pt, false, r + o, C.g<T>(), done);
-  vcycle<T>(st, K, H, l + 1, done);
-  if (L.fine)
-    launch_rect<T>(st, K, L.Ps, true, C.x<T>(), x + o, done);
-  else
-    launch_csr_rect<T>(st, K, L.P, true, C.x<T>(), x + o, done);
-  for (int c = nc - 1; c >= 0; --c) gs(c, false);
+  launch_csr<T>(st, K, 1, res, nl, done);
+  launch_csr<T>(st, K, 2, down, nl, done);
+  coarse_cycles<T>(st, K, na, nb, done);
+  launch_csr<T>(st, K, 3, up, nl, done);
+  for (int k = 0; k < nc; ++k) sweep(k, false);
 }
 
-// One vertical-lumping multigrid cycle on stream st (Section 6, second
-// preconditioner): forward multicolour SOR on A from zero, E~ coarse
-// correction through one V-cycle on the surface operator, backward SOR.
-// part: 0 the whole cycle, 1 the forward sweep, 3 the residual, 2 the rest;
-// with share, the forward sweep's and the residual's non-top rows are also
-// stored to the additive smoother's fine vectors
 template <class T>
-void sor_cycle(Handle *h, hipStream_t st, int K, const T *rr, T *zz, const int *done, int part = 0,
-               bool share = false) {
+Cycle<T> cycle(std::vector<DLevel> &H, size_t l) {
+  Cycle<T> c;
+  c.H = &H;
+  c.l = l;
+  return c;
+}
+
+// Sweeps of a fine level on its own (A_bar's, whose top columns multiply the
+// smoother vector's top part, which is zero; or the baseline's whole A):
+// forward from zero with the residual, and backward.
+template <class T>
+void fine_forward(hipStream_t st, int K, DLevel &L, const int *done) {
+  T *x = L.x<T>(), *g = L.g<T>();
+  const bool top = !L.cstart_top.empty();
+  for (size_t c = 0; c + 1 < L.cstart.size(); ++c)
+    launch_gs<T>(st, K, L.As, top ? L.cstart_top[c] : 0, top ? L.cstart_top[c + 1] : 0, L.cstart[c], L.cstart[c + 1],
+                 g, x, done, true);
+  launch_spmv<T>(st, K, L.As, 1, L.row0, L.row0 + L.n, x, L.r<T>(), nullptr, done, L.order);
+}
+template <class T>
+void fine_backward(hipStream_t st, int K, DLevel &L, const int *done) {
+  const bool top = !L.cstart_top.empty();
+  for (size_t c = L.cstart.size() - 1; c-- > 0;)
+    launch_gs<T>(st, K, L.As, top ? L.cstart_top[c] : 0, top ? L.cstart_top[c + 1] : 0, L.cstart[c], L.cstart[c + 1],
+                 L.g<T>(), L.x<T>(), done, false);
+}
+
+// One V-cycle of a hierarchy with a fine level, and the coarse part of a
+// second, independent one beside it (its own down job, if given, beside the
+// fine level's restriction).
+template <class T>
+void fine_cycle(hipStream_t st, int K, std::vector<DLevel> &H, Cycle<T> other, const CsrJob<T> *other_down,
+                const int *done) {
+  DLevel &L = H[0];
+  CsrJob<T> down[2];
+  int nd = 0;
+  if (other_down) down[nd++] = *other_down;
+  if (L.coarsest) {
+    if (nd) launch_csr<T>(st, K, 2, down, nd, done);
+    coarse_cycles<T>(st, K, other, cycle<T>(H, 0), done);
+    return;
+  }
+  fine_forward<T>(st, K, L, done);
+  const int64_t o = L.row0 * K;
+  down[nd].A = L.Pt;
+  down[nd].x = L.r<T>() + o;
+  down[nd++].y = H[1].g<T>();
+  launch_csr<T>(st, K, 2, down, nd, done);
+  coarse_cycles<T>(st, K, other, cycle<T>(H, 1), done);
+  launch_rect<T>(st, K, L.Ps, true, H[1].x<T>(), L.x<T>() + o, done);
+  fine_backward<T>(st, K, L, done);
+}
+
+// The rows of sweep colour c: the top's and the non-top block's
+struct ColourRows {
+  int64_t a0 = 0, a1 = 0, b0 = 0, b1 = 0;
+};
+int fine_colours(const Problem &P) {
+  return std::max((int)P.top_colour_start.size(), (int)P.bar_colour_start.size()) - 1;
+}
+ColourRows colour_rows(const Problem &P, int c) {
+  ColourRows r;
+  if (c + 1 < (int)P.top_colour_start.size()) {
+    r.a0 = P.top_colour_start[c];
+    r.a1 = P.top_colour_start[c + 1];
+  }
+  if (c + 1 < (int)P.bar_colour_start.size()) {
+    r.b0 = P.bar_colour_start[c];
+    r.b1 = P.bar_colour_start[c + 1];
+  }
+  return r;
+}
+
+// The restriction of the SOR cycle's residual to the surface
+template <class T>
+CsrJob<T> surface_down(Handle *h, const T *r) {
+  CsrJob<T> J;
+  J.A = h->Et;
+  J.x = r;
+  J.y = h->S[0].g<T>();
+  return J;
+}
+
+// zz = one vertical-lumping multigrid cycle on rr (Section 6, second
+// preconditioner): forward multicolour SOR on A from zero, E~ coarse
+// correction through one V-cycle on the surface operator, backward SOR; with
+// dense, the additive smoother of a single dense level runs beside the surface
+// cycle.
+template <class T>
+void sor_cycle(Handle *h, int K, const T *rr, T *zz, const int *done, bool dense = false) {
+  hipStream_t st = h->work;
   const Problem &P = h->P;
-  int64_t n = P.n, m = P.n_top;
+  const int nc = fine_colours(P);
   Work<T> &v = work_of<T>(h);
-  int nct = (int)P.top_colour_start.size() - 1, ncb = (int)P.bar_colour_start.size() - 1;
-  int nc = std::max(nct, ncb);
-  T *x2 = share ? v.w : nullptr, *r2 = share ? v.resA : nullptr;
-  // the forward sweep starts from zero: zz needs no fill, and colour c reads
-  // only the colours before it (in each block)
+  // the forward sweep starts from zero: zz needs no fill
+  for (int c = 0; c < nc; ++c) {
+    const ColourRows q = colour_rows(P, c);
+    launch_gs<T>(st, K, h->A, q.a0, q.a1, q.b0, q.b1, rr, zz, done, true);
+  }
+  Cycle<T> S, B;
+  if (P.n_top > 0) {
+    launch_spmv<T>(st, K, h->A, 1, 0, P.n, zz, v.res, nullptr, done, h->order_all);
+    const CsrJob<T> J = surface_down<T>(h, v.res);
+    launch_csr<T>(st, K, 2, &J, 1, done);
+    S = cycle<T>(h->S, 0);
+  }
+  T *saved = h->Ab[0].g<T>();
+  if (dense) {
+    h->Ab[0].g<T>() = const_cast<T *>(rr);
+    B = cycle<T>(h->Ab, 0);
+  }
+  coarse_cycles<T>(st, K, S, B, done);
+  h->Ab[0].g<T>() = saved;
+  if (P.n_top > 0) launch_rect<T>(st, K, h->E, true, h->S[0].x<T>(), zz, done);
+  for (int c = nc - 1; c >= 0; --c) {
+    const ColourRows q = colour_rows(P, c);
+    launch_gs<T>(st, K, h->A, q.a0, q.a1, q.b0, q.b1, rr, zz, done, false);
+  }
+}
+
+// zz = VL_SOR(rr) + Z Vcyc_Abar(Z^T rr) with one pair of fine sweeps for both
+// cycles (MergedRows); zz has n + nx rows.
+template <class T>
+void merged_cycle(Handle *h, int K, const T *rr, T *zz, const int *done) {
+  hipStream_t st = h->work;
+  const Problem &P = h->P;
+  const int nc = fine_colours(P);
+  Work<T> &v = work_of<T>(h);
   auto sweep = [&](int c, bool first) {
-    int64_t a0 = 0, a1 = 0, b0 = 0, b1 = 0;
-    if (c < nct) {
-      a0 = P.top_colour_start[c];
-      a1 = P.top_colour_start[c + 1];
-    }
-    if (c < ncb) {
-      b0 = P.bar_colour_start[c];
-      b1 = P.bar_colour_start[c + 1];
-    }
-    launch_gs<T>(st, K, h->A, a0, a1, b0, b1, rr, zz, done, first, first ? x2 : nullptr, m);
+    const ColourRows q = colour_rows(P, c);
+    const bool d = c + 1 < (int)h->dstart.size();
+    launch_gs_merged<T>(st, K, h->A, h->M, q.a0, q.a1, q.b0, q.b1, d ? h->dstart[c] : 0, d ? h->dstart[c + 1] : 0,
+                        rr, zz, done, first);
   };
-  if (part == 0 || part == 1)
-    for (int c = 0; c < nc; ++c) sweep(c, true);
-  if (part == 0 || part == 3) {
-    if (m > 0) launch_spmv<T>(st, K, h->A, 1, 0, n, zz, v.res, nullptr, done, h->order_all, r2, m);
-  }
-  if (part == 1 || part == 3) return;
-  if (m > 0) {
-    launch_csr_rect<T>(st, K, h->Et, false, v.res, h->S[0].g<T>(), done);
-    vcycle<T>(st, K, h->S, 0, done);
-    launch_rect<T>(st, K, h->E, true, h->S[0].x<T>(), zz, done);
-  }
+  for (int c = 0; c < nc; ++c) sweep(c, true);
+  launch_res_merged<T>(st, K, h->A, h->M, zz, v.res, done, h->order_all);
+  CsrJob<T> down[2];
+  int nd = 0;
+  if (P.n_top > 0) down[nd++] = surface_down<T>(h, v.res);
+  down[nd].A = h->merged_Pt;
+  down[nd].x = v.res;
+  down[nd++].y = h->Ab[1].g<T>();
+  launch_csr<T>(st, K, 2, down, nd, done);
+  coarse_cycles<T>(st, K, P.n_top > 0 ? cycle<T>(h->S, 0) : Cycle<T>(), cycle<T>(h->Ab, 1), done);
+  const T *ya = h->Ab[1].x<T>();
+  launch_prolong_merged<T>(st, K, h->M, P.n_top > 0 ? h->S[0].x<T>() : ya, ya, zz, done);
   for (int c = nc - 1; c >= 0; --c) sweep(c, false);
 }
 
-// w = Z Vcyc_Abar(Z^T rr) on stream st (the additive smoother; rows of the top
-// block of w stay zero)
-// phase 0: the whole V-cycle; 1 and 2: its two parts beside the SOR cycle's
-// shared forward sweep (see Reuse)
+// w = Z Vcyc_Abar(Z^T rr) (the additive smoother; rows of the top block of w
+// stay zero), with the surface cycle of `other` beside it
 template <class T>
-void additive_smoother(Handle *h, hipStream_t st, int K, const T *rr, const int *done, int phase = 0) {
+void additive_smoother(Handle *h, int K, const T *rr, Cycle<T> other, const CsrJob<T> *other_down, const int *done) {
   T *saved = h->Ab[0].g<T>();
   h->Ab[0].g<T>() = const_cast<T *>(rr);
-  Reuse R;
-  R.gs = h->reuse_gs;
-  R.gs_start = &h->reuse_gs_start;
-  R.gs_sell = &h->reuse_gs_sell;
-  R.res = h->reuse_res;
-  R.nres = h->n_reuse_res;
-  R.res_sell = &h->reuse_res_sell;
-  R.full_res = h->reuse_full_res;
-  R.phase = phase;
-  vcycle<T>(st, K, h->Ab, 0, done, phase ? &R : nullptr);
+  fine_cycle<T>(h->work, K, h->Ab, other, other_down, done);
   h->Ab[0].g<T>() = saved;
 }
 
-// The two VL+additive forms have a second, independent branch: the additive
-// smoother beside the SOR cycle (VEMG_PC_VL_ADDITIVE), or the surface branch
-// beside the smoother (VEMG_PC_VL_ADDITIVE_ONLY with a non-empty surface).
-bool has_branch(const Handle *h) {
-  return h->opt.pc == VEMG_PC_VL_ADDITIVE || (h->opt.pc == VEMG_PC_VL_ADDITIVE_ONLY && h->P.n_top > 0);
-}
-
-// Whether the additive smoother takes the SOR cycle's forward sweep and
-// residual.  The smoother then starts only after that sweep, which costs
-// overlap; the sweeps it saves outweigh that only when they are long: on
-// meshes of a million fine unknowns and more (any batch width), not below.
-// The environment's VEMG_SHARE_MIN_ROWS, when set, replaces that bound (0:
-// always), so that small meshes can exercise the shared form.
-constexpr int64_t kShareMinRows = 1000000;
-int64_t share_min_rows() {
-  if (const char *e = std::getenv("VEMG_SHARE_MIN_ROWS")) {
-    char *end = nullptr;
-    const long long v = std::strtoll(e, &end, 10);
-    if (end != e && *end == '\0' && v >= 0) return (int64_t)v;
-  }
-  return kShareMinRows;
-}
-bool shares(const Handle *h, int) {
-  return h->reuse && h->opt.pc == VEMG_PC_VL_ADDITIVE && h->P.n >= h->share_min_rows;
-}
-
-// second branch, on stream st2.  When shares(h, K) it comes in two phases:
-// 1 after the SOR cycle's forward sweep, 2 after its residual.
-template <class T>
-void precond_branch(Handle *h, hipStream_t st2, int K, const T *rr, const int *done, int phase = 0) {
-  if (h->opt.pc == VEMG_PC_VL_ADDITIVE) {
-    additive_smoother<T>(h, st2, K, rr, done, shares(h, K) ? phase : 0);
-  } else {
-    launch_csr_rect<T>(st2, K, h->Et, false, rr, h->S[0].g<T>(), done);
-    vcycle<T>(st2, K, h->S, 0, done);
-  }
-}
-
-// first branch, on stream st.  When shares(h, K) it comes in three parts:
-// 1 the SOR cycle's forward sweep and 3 its residual (both shared with the
-// second branch), then 2 the rest.
-template <class T>
-void precond_main(Handle *h, hipStream_t st, int K, const T *rr, T *zz, const int *done, int part = 0) {
-  if (h->opt.pc == VEMG_PC_VL_ADDITIVE)
-    sor_cycle<T>(h, st, K, rr, zz, done, shares(h, K) ? part : 0,
-                 shares(h, K) && (part == 1 || part == 3));
-  else if (part == 0 || part == 2)
-    additive_smoother<T>(h, st, K, rr, done);
-}
-
-// after both branches: z = sum of the two, partials of rr . z (returns their count)
-template <class T>
-int64_t precond_join(Handle *h, hipStream_t st, int K, const T *rr, T *zz, double *part, const int *done) {
-  const int64_t n = h->P.n, m = h->P.n_top;
-  Work<T> &v = work_of<T>(h);
-  if (h->opt.pc == VEMG_PC_VL_ADDITIVE) {
-    launch_add_dot<T>(st, K, v.w, rr, zz, m, n, part, done);
-    return vec_blocks(n);
-  }
-  launch_prolong_sum<T>(st, K, h->E, m, h->S[0].x<T>(), v.w, rr, zz, part, done);
-  return sell_blocks(0, n);
-}
-
-// z = M^{-1} rr in precision T; partial sums of rr . z go to part (blocks in *np)
+// z = M^{-1} rr in precision T; partial sums of rr . z go to part (blocks in
+// *np).  zz: the handle's own z vector (the merged cycles extend it).
 template <class T>
 void precond(Handle *h, int K, const T *rr, T *zz, double *part, int64_t *np, const int *done) {
   hipStream_t st = h->work;
   const Problem &P = h->P;
   int64_t n = P.n;
   Work<T> &v = work_of<T>(h);
-  if (has_branch(h)) {
-    const bool sh = shares(h, K);
-    if (sh) precond_main<T>(h, st, K, rr, zz, done, 1);
-    HIPCHK(hipEventRecord(h->ev_fork, st));
-    HIPCHK(hipStreamWaitEvent(h->work2, h->ev_fork, 0));
-    precond_branch<T>(h, h->work2, K, rr, done, sh ? 1 : 0);
-    if (sh) {
-      precond_main<T>(h, st, K, rr, zz, done, 3);
-      HIPCHK(hipEventRecord(h->ev_res, st));
-      HIPCHK(hipStreamWaitEvent(h->work2, h->ev_res, 0));
-      precond_branch<T>(h, h->work2, K, rr, done, 2);
-    }
-    HIPCHK(hipEventRecord(h->ev_join, h->work2));
-    precond_main<T>(h, st, K, rr, zz, done, sh ? 2 : 0);
-    HIPCHK(hipStreamWaitEvent(st, h->ev_join, 0));
-    *np = precond_join<T>(h, st, K, rr, zz, part, done);
-    return;
-  }
+  *np = vec_blocks(n);
   switch (h->opt.pc) {
-    case VEMG_PC_VL_ADDITIVE_ONLY:  // empty surface: the additive smoother alone
-      additive_smoother<T>(h, st, K, rr, done);
+    case VEMG_PC_VL_ADDITIVE:
+      if (h->merged) {
+        merged_cycle<T>(h, K, rr, zz, done);
+        break;
+      }
+      sor_cycle<T>(h, K, rr, zz, done, true);
+      launch_add_dot<T>(st, K, v.w, rr, zz, P.n_top, n, part, done);
+      return;
+    case VEMG_PC_VL_ADDITIVE_ONLY:
+      if (P.n_top > 0) {
+        const CsrJob<T> J = surface_down<T>(h, rr);
+        additive_smoother<T>(h, K, rr, cycle<T>(h->S, 0), &J, done);
+        launch_prolong_sum<T>(st, K, h->E, P.n_top, h->S[0].x<T>(), v.w, rr, zz, part, done);
+        *np = sell_blocks(0, n);
+        return;
+      }
+      additive_smoother<T>(h, K, rr, Cycle<T>(), nullptr, done);  // empty surface: the smoother alone
       launch_copy<T>(st, v.w, zz, n * K, done);
-      launch_dot<T>(st, K, rr, zz, n, part, done);
-      *np = vec_blocks(n);
       break;
     case VEMG_PC_VL_SOR:
-      sor_cycle<T>(h, st, K, rr, zz, done);
-      launch_dot<T>(st, K, rr, zz, n, part, done);
-      *np = vec_blocks(n);
+      sor_cycle<T>(h, K, rr, zz, done);
       break;
     case VEMG_PC_SA: {
       // one V-cycle of the baseline hierarchy, its fine level on rr -> zz
@@ -709,24 +798,19 @@ void precond(Handle *h, int K, const T *rr, T *zz, double *part, int64_t *np, co
       T *sx = F.x<T>(), *sg = F.g<T>();
       F.x<T>() = zz;
       F.g<T>() = const_cast<T *>(rr);
-      vcycle<T>(st, K, h->SA, 0, done);
+      fine_cycle<T>(st, K, h->SA, Cycle<T>(), nullptr, done);
       F.x<T>() = sx;
       F.g<T>() = sg;
-      launch_dot<T>(st, K, rr, zz, n, part, done);
-      *np = vec_blocks(n);
       break;
     }
     case VEMG_PC_JACOBI:
       launch_jacobi<T>(st, K, rr, h->diag, zz, n, done);
-      launch_dot<T>(st, K, rr, zz, n, part, done);
-      *np = vec_blocks(n);
       break;
     default:
       launch_copy<T>(st, rr, zz, n * K, done);
-      launch_dot<T>(st, K, rr, zz, n, part, done);
-      *np = vec_blocks(n);
       break;
   }
+  launch_dot<T>(st, K, rr, zz, n, part, done);
 }
 
 // The additive smoother reads the top columns of its x and takes them as
@@ -754,26 +838,6 @@ int64_t precond_mixed(Handle *h, int K, const double *rr, double *zz, const int 
   return vec_blocks(n);
 }
 
-// One PCG iteration in precision T (kind FP64/FP32) or FP64 with an FP32
-// preconditioner (kind MixedPC), in four segments: the Krylov part up to the
-// convergence test (and the FP32 demotion), the preconditioner's second
-// branch (stream work2), its first branch, and the join plus the rest of the
-// Krylov update.  Eagerly they run back to back with an event fork and join;
-// as graphs each segment is captured on its own and launched on its stream,
-// so that the two branches overlap on the device.
-// (with the shared forward sweep also kSegMainFront, the SOR cycle's forward
-// sweep; kSegMainRes, its residual; kSegBranchRest, the second branch's part
-// after that residual)
-enum Segment {
-  kSegPre = 0,
-  kSegBranch = 1,
-  kSegMain = 2,
-  kSegPost = 3,
-  kSegMainFront = 4,
-  kSegMainRes = 5,
-  kSegBranchRest = 6
-};
-
 // Reliable update of the mixed-precision solve (FP32 PCG on A d = b / ||b||):
 // the FP32 correction accumulated since the last update is scaled by ||b||,
 // folded into the FP64 solution hi + lo without rounding error and cleared;
@@ -791,89 +855,14 @@ void reliable_update(Handle *h, int K) {
   launch_demote(st, K, h->v64.res, h->scale_in, h->v32.r, n, nullptr);
 }
 
-template <class T>
-void pcg_segment(Handle *h, int K, int kind, int seg) {
-  hipStream_t st = h->work;
-  int64_t n = h->P.n;
-  Work<T> &v = work_of<T>(h);
-  const int *done = &h->scal->all_done;
-  const bool mixed = kind == kGraphMixedPC;
-  switch (seg) {
-    case kSegPre:
-      launch_spmv<T>(st, K, h->A, 0, 0, n, v.p, v.q, h->part_pq, done, h->order_all);
-      launch_pcg_alpha(st, K, h->scal, h->part_pq, sell_blocks(0, n));
-      launch_pcg_xr<T>(st, K, h->scal, v.x, v.r, v.p, v.q, n, h->part_rr);
-      launch_pcg_conv(st, K, h->scal, h->part_rr, vec_blocks(n));
-      if constexpr (std::is_same<T, double>::value)
-        if (mixed) launch_demote(st, K, v.r, h->scale_in, h->v32.tmp, n, done);
-      if constexpr (std::is_same<T, float>::value)
-        if (kind == kGraphFP32Reliable) reliable_update(h, K);
-      break;
-    case kSegBranch:
-    case kSegBranchRest: {
-      const int phase = !shares(h, K) ? 0 : seg == kSegBranch ? 1 : 2;
-      if (mixed)
-        precond_branch<float>(h, h->work2, K, h->v32.tmp, done, phase);
-      else
-        precond_branch<T>(h, h->work2, K, v.r, done, phase);
-      break;
-    }
-    case kSegMainFront:
-    case kSegMainRes:
-    case kSegMain: {
-      const int part = !shares(h, K) ? 0 : seg == kSegMainFront ? 1 : seg == kSegMainRes ? 3 : 2;
-      if (mixed)
-        precond_main<float>(h, st, K, h->v32.tmp, h->v32.z, done, part);
-      else
-        precond_main<T>(h, st, K, v.r, v.z, done, part);
-      break;
-    }
-    case kSegPost: {
-      int64_t np;
-      if constexpr (std::is_same<T, double>::value) {
-        if (mixed) {
-          precond_join<float>(h, st, K, h->v32.tmp, h->v32.z, h->part_t, done);
-          launch_promote(st, K, h->v32.z, h->scale_out, v.z, n, false, done);
-          launch_dot<double>(st, K, v.r, v.z, n, h->part_rz, done);
-          np = vec_blocks(n);
-        } else {
-          np = precond_join<T>(h, st, K, v.r, v.z, h->part_rz, done);
-        }
-      } else {
-        np = precond_join<T>(h, st, K, v.r, v.z, h->part_rz, done);
-      }
-      launch_pcg_beta(st, K, h->scal, h->part_rz, np);
-      launch_pcg_p<T>(st, K, h->scal, v.p, v.z, n);
-      break;
-    }
-  }
-}
-
+// One PCG iteration in precision T (kind FP64/FP32) or FP64 with an FP32
+// preconditioner (kind MixedPC), on one stream.
 template <class T>
 void pcg_iteration(Handle *h, int K, int kind) {
   hipStream_t st = h->work;
   int64_t n = h->P.n;
   Work<T> &v = work_of<T>(h);
   const int *done = &h->scal->all_done;
-  if (has_branch(h)) {
-    const bool sh = shares(h, K);
-    pcg_segment<T>(h, K, kind, kSegPre);
-    if (sh) pcg_segment<T>(h, K, kind, kSegMainFront);
-    HIPCHK(hipEventRecord(h->ev_fork, st));
-    HIPCHK(hipStreamWaitEvent(h->work2, h->ev_fork, 0));
-    pcg_segment<T>(h, K, kind, kSegBranch);
-    if (sh) {
-      pcg_segment<T>(h, K, kind, kSegMainRes);
-      HIPCHK(hipEventRecord(h->ev_res, st));
-      HIPCHK(hipStreamWaitEvent(h->work2, h->ev_res, 0));
-      pcg_segment<T>(h, K, kind, kSegBranchRest);
-    }
-    HIPCHK(hipEventRecord(h->ev_join, h->work2));
-    pcg_segment<T>(h, K, kind, kSegMain);
-    HIPCHK(hipStreamWaitEvent(st, h->ev_join, 0));
-    pcg_segment<T>(h, K, kind, kSegPost);
-    return;
-  }
   launch_spmv<T>(st, K, h->A, 0, 0, n, v.p, v.q, h->part_pq, done, h->order_all);
   launch_pcg_alpha(st, K, h->scal, h->part_pq, sell_blocks(0, n));
   launch_pcg_xr<T>(st, K, h->scal, v.x, v.r, v.p, v.q, n, h->part_rr);
@@ -891,68 +880,35 @@ void pcg_iteration(Handle *h, int K, int kind) {
 }
 
 void destroy_graphs(Handle *h) {
-  for (auto &kv : h->graphs)
-    for (int i = 0; i < 7; ++i) {
-      if (kv.second.exec[i]) (void)hipGraphExecDestroy(kv.second.exec[i]);
-      if (kv.second.graph[i]) (void)hipGraphDestroy(kv.second.graph[i]);
-    }
+  for (auto &kv : h->graphs) {
+    if (kv.second.exec) (void)hipGraphExecDestroy(kv.second.exec);
+    if (kv.second.graph) (void)hipGraphDestroy(kv.second.graph);
+  }
   h->graphs.clear();
 }
 
-template <class F>
-void capture(hipStream_t st, hipGraph_t *g, hipGraphExec_t *ge, F &&record) {
-  HIPCHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-  record();
-  HIPCHK(hipStreamEndCapture(st, g));
-  HIPCHK(hipGraphInstantiate(ge, *g, nullptr, nullptr, 0));
-}
-
-// graphs of one iteration for (kind, K), captured on first use when allowed:
-// one graph, or the four segments when the preconditioner has two branches
+// graph of one iteration for (kind, K), captured on first use when allowed
 template <class T>
-const IterGraphs *iteration_graphs(Handle *h, int K, int kind) {
+const IterGraph *iteration_graph(Handle *h, int K, int kind) {
   int key = kind * 16 + K;
   auto it = h->graphs.find(key);
   if (it != h->graphs.end()) return &it->second;
   if (!h->allow_capture) return nullptr;
-  IterGraphs ig;
-  if (has_branch(h)) {
-    ig.parts = shares(h, K) ? 7 : 4;
-    for (int seg = 0; seg < ig.parts; ++seg)
-      capture(seg == kSegBranch || seg == kSegBranchRest ? h->work2 : h->work, &ig.graph[seg], &ig.exec[seg],
-              [&]() { pcg_segment<T>(h, K, kind, seg); });
-  } else {
-    ig.parts = 1;
-    capture(h->work, &ig.graph[0], &ig.exec[0], [&]() { pcg_iteration<T>(h, K, kind); });
-  }
+  IterGraph ig;
+  HIPCHK(hipStreamBeginCapture(h->work, hipStreamCaptureModeThreadLocal));
+  pcg_iteration<T>(h, K, kind);
+  HIPCHK(hipStreamEndCapture(h->work, &ig.graph));
+  HIPCHK(hipGraphInstantiate(&ig.exec, ig.graph, nullptr, nullptr, 0));
   return &h->graphs.emplace(key, ig).first->second;
 }
 
 template <class T>
 void run_iteration(Handle *h, int K, int kind) {
-  const IterGraphs *ig = h->opt.use_graphs ? iteration_graphs<T>(h, K, kind) : nullptr;
-  if (!ig) {
+  const IterGraph *ig = h->opt.use_graphs ? iteration_graph<T>(h, K, kind) : nullptr;
+  if (ig)
+    HIPCHK(hipGraphLaunch(ig->exec, h->work));
+  else
     pcg_iteration<T>(h, K, kind);
-  } else if (ig->parts == 1) {
-    HIPCHK(hipGraphLaunch(ig->exec[0], h->work));
-  } else {
-    const bool sh = ig->parts == 7;
-    HIPCHK(hipGraphLaunch(ig->exec[kSegPre], h->work));
-    if (sh) HIPCHK(hipGraphLaunch(ig->exec[kSegMainFront], h->work));
-    HIPCHK(hipEventRecord(h->ev_fork, h->work));
-    HIPCHK(hipStreamWaitEvent(h->work2, h->ev_fork, 0));
-    HIPCHK(hipGraphLaunch(ig->exec[kSegBranch], h->work2));
-    if (sh) {
-      HIPCHK(hipGraphLaunch(ig->exec[kSegMainRes], h->work));
-      HIPCHK(hipEventRecord(h->ev_res, h->work));
-      HIPCHK(hipStreamWaitEvent(h->work2, h->ev_res, 0));
-      HIPCHK(hipGraphLaunch(ig->exec[kSegBranchRest], h->work2));
-    }
-    HIPCHK(hipEventRecord(h->ev_join, h->work2));
-    HIPCHK(hipGraphLaunch(ig->exec[kSegMain], h->work));
-    HIPCHK(hipStreamWaitEvent(h->work, h->ev_join, 0));
-    HIPCHK(hipGraphLaunch(ig->exec[kSegPost], h->work));
-  }
 }
 
 Scal read_scal(Handle *h) {
@@ -1192,6 +1148,118 @@ void solve_ir(Handle *h, int K, double rtol, int max_iter, ColResult *res) {
   launch_round(st, h->v64.xs, h->v64.xl, h->v64.x, n * K);
 }
 
+// The rows of MergedRows (its comment defines D and R) and their packed forms;
+// returns the number of extended rows.
+int64_t merged_rows(Handle *h) {
+  const Problem &P = h->P;
+  const Csr &O = P.Aoff;
+  const int64_t n = P.n, m = P.n_top;
+  h->M = MergedRows();
+  h->dstart.clear();
+  h->merged = P.Abar.size() > 1;
+  if (!h->merged) return 0;
+  MergedRows &M = h->M;
+  auto on = [&](int64_t i, int64_t j) { return j < m ? 0 : P.colour[j] < P.colour[i] ? -1 : 1; };
+  std::vector<uint8_t> dirty(n, 0);
+  std::vector<int32_t> drow, rrow, xpos(n, -1), rpos;
+  const int ncb = (int)P.bar_colour_start.size() - 1;
+  h->dstart.assign(1, 0);
+  for (int c = 0; c < ncb; ++c) {
+    for (int64_t i = P.bar_colour_start[c]; i < P.bar_colour_start[c + 1]; ++i) {
+      for (int64_t k = O.ptr[i]; k < O.ptr[i + 1] && !dirty[i]; ++k) {
+        const int64_t j = O.idx[k];
+        if (P.colour[j] < c && (j < m || dirty[j])) dirty[i] = 1;
+      }
+      if (dirty[i]) {
+        xpos[i] = (int32_t)drow.size();
+        drow.push_back((int32_t)i);
+      }
+    }
+    h->dstart.push_back((int64_t)drow.size());
+  }
+  M.n = n;
+  M.n_top = m;
+  M.nd = M.nx = (int64_t)drow.size();
+  for (int64_t i = m; i < n; ++i) {
+    bool r = false;
+    for (int64_t k = O.ptr[i]; k < O.ptr[i + 1] && !r; ++k) {
+      const int64_t j = O.idx[k];
+      r = P.colour[j] > P.colour[i] && (j < m || dirty[j]);
+    }
+    if (!r) continue;
+    if (xpos[i] < 0) xpos[i] = (int32_t)M.nx++;
+    rrow.push_back((int32_t)i);
+    rpos.push_back(xpos[i]);
+  }
+  M.nr = (int64_t)rrow.size();
+  if (n + M.nx > INT32_MAX) throw DeviceError(VEMG_ERR_DEVICE, "too many unknowns for 32-bit columns");
+  Arena &ar = h->ar;
+  hipStream_t st = h->work;
+  // column of neighbour j where the smoother's value is meant
+  auto fwd_col = [&](int64_t j) { return (int32_t)(dirty[j] ? n + xpos[j] : j); };
+  auto ext_col = [&](int64_t j) {
+    if (xpos[j] < 0) throw DeviceError(VEMG_ERR_DEVICE, "merged sweeps: a row outside the extended set is read");
+    return (int32_t)(n + xpos[j]);
+  };
+  auto entry = [&](int64_t i, int64_t k, int32_t col, int32_t col2) {
+    return RowEntry{col, col2, O.val[k], (float)(O.val[k] / P.diag[i])};
+  };
+  RowData dd, dt;
+  dd.d.resize(M.nd);
+  dd.diag.resize(M.nd);
+  for (int64_t q = 0; q < M.nd; ++q) {
+    const int64_t i = drow[q];
+    double d = P.d[i];
+    for (int64_t k = O.ptr[i]; k < O.ptr[i + 1]; ++k)
+      if (O.idx[k] < m) d -= O.val[k];
+    dd.d[q] = d;
+    dd.diag[q] = P.diag[i];
+  }
+  auto dpad = [&](int64_t q) { return (int32_t)(n + q); };
+  M.fwd = pack_rows(ar, st, M.nd, false, [&](int64_t q, std::vector<RowEntry> &out) {
+    const int64_t i = drow[q];
+    for (int64_t k = O.ptr[i]; k < O.ptr[i + 1]; ++k)
+      if (on(i, O.idx[k]) < 0) out.push_back(entry(i, k, fwd_col(O.idx[k]), -1));
+  }, dpad, dd);
+  M.bwd = pack_rows(ar, st, M.nd, false, [&](int64_t q, std::vector<RowEntry> &out) {
+    const int64_t i = drow[q];
+    for (int64_t k = O.ptr[i]; k < O.ptr[i + 1]; ++k)
+      if (on(i, O.idx[k]) != 0) out.push_back(entry(i, k, ext_col(O.idx[k]), -1));
+  }, dpad, dd);
+  RowData dr;
+  dr.d.assign(M.nr, 0.0);
+  for (int64_t q = 0; q < M.nr; ++q) dr.diag.push_back(P.diag[rrow[q]]);
+  M.res = pack_rows(ar, st, M.nr, false, [&](int64_t q, std::vector<RowEntry> &out) {
+    const int64_t i = rrow[q];
+    for (int64_t k = O.ptr[i]; k < O.ptr[i + 1]; ++k)
+      if (on(i, O.idx[k]) > 0) out.push_back(entry(i, k, fwd_col(O.idx[k]), -1));
+  }, [&](int64_t q) { return rrow[q]; }, dr);
+  dt.d.assign(P.d.begin(), P.d.begin() + m);
+  dt.diag.assign(P.diag.begin(), P.diag.begin() + m);
+  M.top = pack_rows(ar, st, m, true, [&](int64_t i, std::vector<RowEntry> &out) {
+    for (int64_t k = O.ptr[i]; k < O.ptr[i + 1]; ++k)
+      out.push_back(entry(i, k, O.idx[k], O.idx[k] < m ? -1 : ext_col(O.idx[k])));
+  }, [&](int64_t i) { return (int32_t)i; }, dt);
+  const Csr &P0 = P.Abar[0].P;
+  M.prol = pack_rows(ar, st, n, false, [&](int64_t i, std::vector<RowEntry> &out) {
+    if (m > 0)
+      for (int64_t k = P.E.ptr[i]; k < P.E.ptr[i + 1]; ++k)
+        out.push_back({P.E.idx[k], -1, P.E.val[k], (float)P.E.val[k]});
+    if (i >= m)
+      for (int64_t k = P0.ptr[i - m]; k < P0.ptr[i - m + 1]; ++k)
+        out.push_back({(int32_t)(m + P0.idx[k]), -1, P0.val[k], (float)P0.val[k]});
+  }, [&](int64_t) { return (int32_t)m; });
+  // the smoother's residual: R's extended rows, else the matrix rows
+  std::vector<int32_t> map(n - m);
+  for (int64_t i = m; i < n; ++i) map[i - m] = (int32_t)i;
+  for (int64_t q = 0; q < M.nr; ++q) map[rrow[q] - m] = (int32_t)(n + rpos[q]);
+  h->merged_Pt = pack_csrg(ar, st, transpose(P0), false, nullptr, &P.loc_rank, m, &map);
+  M.drow = ar.upload(drow, st);
+  M.rpos = ar.upload(rpos, st);
+  M.xpos = ar.upload(xpos, st);
+  return M.nx;
+}
+
 // Packs the host setup into HBM.  With h->ar.count_only the same sequence
 // of allocations is only counted (no device call), which gives the footprint
 // of a handle before (or without) its upload.
@@ -1201,20 +1269,21 @@ void upload(Handle *h) {
   int64_t n = P.n, m = P.n_top;
   const bool count = h->ar.count_only;
   h->ar.release();
-  h->A = pack_sell(h->ar, st, P.Aoff, true, &P.d, &P.diag, &h->nnz_A, nullptr, &P.colour);
+  h->A = pack_sell(h->ar, st, P.Aoff, true, &P.d, &P.diag, &h->nnz_A, &P.colour);
   if (m > 0) {
     h->E = pack_sell(h->ar, st, P.E, false, nullptr, nullptr, &h->nnz_E);
     h->Et = pack_csrg(h->ar, st, P.Et, false, nullptr, &P.loc_rank, 0);
   }
   size_t cnt = (size_t)n * kMaxBatch;
+  const size_t ext = (size_t)(n + merged_rows(h)) * kMaxBatch;
   auto mk64 = [&](Work<double> &v) {
     v.x = h->ar.alloc<double>(cnt);
     v.r = h->ar.alloc<double>(cnt);
-    v.z = h->ar.alloc<double>(cnt);
+    v.z = h->ar.alloc<double>(ext);
     v.p = h->ar.alloc<double>(cnt);
     v.q = h->ar.alloc<double>(cnt);
     v.w = h->ar.alloc<double>(cnt);
-    v.res = h->ar.alloc<double>(cnt);
+    v.res = h->ar.alloc<double>(ext);
     v.resA = h->ar.alloc<double>(cnt);
     v.tmp = h->ar.alloc<double>(cnt);
     v.xs = h->ar.alloc<double>(cnt);
@@ -1223,11 +1292,11 @@ void upload(Handle *h) {
   auto mk32 = [&](Work<float> &v) {
     v.x = h->ar.alloc<float>(cnt);
     v.r = h->ar.alloc<float>(cnt);
-    v.z = h->ar.alloc<float>(cnt);
+    v.z = h->ar.alloc<float>(ext);
     v.p = h->ar.alloc<float>(cnt);
     v.q = h->ar.alloc<float>(cnt);
     v.w = h->ar.alloc<float>(cnt);
-    v.res = h->ar.alloc<float>(cnt);
+    v.res = h->ar.alloc<float>(ext);
     v.resA = h->ar.alloc<float>(cnt);
     v.tmp = h->ar.alloc<float>(cnt);
   };
@@ -1252,53 +1321,6 @@ void upload(Handle *h) {
   };
   h->order_all = slice_order(0, n);
   h->order_bar = slice_order(m, n);
-  // The SOR cycle and the additive smoother both start with a forward sweep
-  // from zero on the same right-hand side; the smoother holds the top rows at
-  // zero where the SOR cycle has swept them.  A non-top row of colour c gets
-  // the same value in both, bit for bit, unless one of its neighbours of an
-  // earlier colour is a top row or such a row itself ("dirty"); its residual,
-  // which takes only its neighbours of later colours, is the same unless one
-  // of them is a top row or dirty.
-  {  // for every preconditioner: a handle may be switched to VL + additive smoother
-    const Csr &O = P.Aoff;
-    const int ncb = (int)P.bar_colour_start.size() - 1;
-    std::vector<uint8_t> dirty(n, 0);
-    std::vector<int32_t> rows, res;
-    h->reuse_gs_start.assign(1, 0);
-    h->reuse_gs_sell.clear();
-    for (int c = 0; c < ncb; ++c) {
-      std::vector<int32_t> rc;
-      for (int64_t i = P.bar_colour_start[c]; i < P.bar_colour_start[c + 1]; ++i) {
-        for (int64_t k = O.ptr[i]; k < O.ptr[i + 1]; ++k) {
-          const int64_t j = O.idx[k];
-          if (P.colour[j] < c && (j < m || dirty[j])) {
-            dirty[i] = 1;
-            break;
-          }
-        }
-        if (dirty[i]) rc.push_back((int32_t)i);
-      }
-      rows.insert(rows.end(), rc.begin(), rc.end());
-      h->reuse_gs_start.push_back((int64_t)rows.size());
-      h->reuse_gs_sell.push_back(pack_sell(h->ar, st, P.Aoff, true, &P.d, &P.diag, nullptr, &rc, &P.colour));
-    }
-    for (int64_t i = m; i < n; ++i) {
-      bool d = false;
-      for (int64_t k = O.ptr[i]; k < O.ptr[i + 1] && !d; ++k)
-        d = P.colour[O.idx[k]] > P.colour[i] && (O.idx[k] < m || dirty[O.idx[k]]);
-      if (d) res.push_back((int32_t)i);
-    }
-    // without a top surface no row is dirty, but the SOR cycle computes no
-    // residual: the smoother computes all of its own
-    h->reuse_full_res = m == 0;
-    if (h->reuse_full_res) res.clear();
-    h->reuse_gs = h->ar.upload(rows, st);
-    h->reuse_res = h->ar.upload(res, st);
-    h->reuse_res_sell = pack_sell(h->ar, st, P.Aoff, true, &P.d, &P.diag, nullptr, &res, &P.colour);
-    h->share_min_rows = share_min_rows();
-    h->n_reuse_res = (int64_t)res.size();
-    h->reuse = true;
-  }
   int64_t npmax = (std::max(sell_blocks(0, n), vec_blocks(n)) + 8) * kMaxBatch;
   h->part_pq = h->ar.alloc<double>(npmax);
   h->part_rr = h->ar.alloc<double>(npmax);
@@ -1390,6 +1412,10 @@ void apply_op(Handle *h, int op, const T *in, T *out) {
   const Problem &P = h->P;
   int64_t n = P.n, m = P.n_top;
   Work<T> &v = work_of<T>(h);
+  CsrJob<T> et;
+  et.A = h->Et;
+  et.x = in;
+  et.y = out;
   switch (op) {
     case VEMG_OP_A:
       launch_spmv<T>(st, 1, h->A, 0, 0, n, in, out, nullptr, nullptr, h->order_all);
@@ -1397,42 +1423,31 @@ void apply_op(Handle *h, int op, const T *in, T *out) {
     case VEMG_OP_PRECOND: {
       launch_copy<T>(st, in, v.tmp, n, nullptr);
       int64_t np = 0;
-      precond<T>(h, 1, v.tmp, out, h->part_t, &np, nullptr);
+      precond<T>(h, 1, v.tmp, v.z, h->part_t, &np, nullptr);
+      launch_copy<T>(st, v.z, out, n, nullptr);
       break;
     }
     case VEMG_OP_ET:
-      launch_csr_rect<T>(st, 1, h->Et, false, in, out, nullptr);
+      launch_csr<T>(st, 1, 2, &et, 1, nullptr);
       break;
     case VEMG_OP_E:
       launch_rect<T>(st, 1, h->E, false, in, out, nullptr);
       break;
     case VEMG_OP_VCYCLE_S:
       launch_copy<T>(st, in, h->S[0].g<T>(), m, nullptr);
-      vcycle<T>(st, 1, h->S, 0, nullptr);
+      coarse_cycles<T>(st, 1, cycle<T>(h->S, 0), Cycle<T>(), nullptr);
       launch_copy<T>(st, h->S[0].x<T>(), out, m, nullptr);
       break;
     case VEMG_OP_VCYCLE_ABAR: {
       launch_copy<T>(st, in, v.tmp + m, n - m, nullptr);
-      T *saved = h->Ab[0].g<T>();
-      h->Ab[0].g<T>() = v.tmp;
-      vcycle<T>(st, 1, h->Ab, 0, nullptr);
-      h->Ab[0].g<T>() = saved;
+      additive_smoother<T>(h, 1, v.tmp, Cycle<T>(), nullptr, nullptr);
       launch_copy<T>(st, v.w + m, out, n - m, nullptr);
       break;
     }
     case VEMG_OP_GS_FWD: {
-      int nct = (int)P.top_colour_start.size() - 1, ncb = (int)P.bar_colour_start.size() - 1;
-      for (int c = 0; c < std::max(nct, ncb); ++c) {
-        int64_t a0 = 0, a1 = 0, b0 = 0, b1 = 0;
-        if (c < nct) {
-          a0 = P.top_colour_start[c];
-          a1 = P.top_colour_start[c + 1];
-        }
-        if (c < ncb) {
-          b0 = P.bar_colour_start[c];
-          b1 = P.bar_colour_start[c + 1];
-        }
-        launch_gs<T>(st, 1, h->A, a0, a1, b0, b1, in, out, nullptr, true);
+      for (int c = 0; c < fine_colours(P); ++c) {
+        const ColourRows q = colour_rows(P, c);
+        launch_gs<T>(st, 1, h->A, q.a0, q.a1, q.b0, q.b1, in, out, nullptr, true);
       }
       break;
     }
@@ -1476,7 +1491,8 @@ void time_once(Handle *h, int op, int K) {
     return;
   }
   if (op == VEMG_OP_ET) {
-    launch_csr_rect<T>(st, K, h->Et, false, v.r, h->S[0].g<T>(), nullptr);
+    const CsrJob<T> J = surface_down<T>(h, v.r);
+    launch_csr<T>(st, K, 2, &J, 1, nullptr);
     return;
   }
   if (op == VEMG_OP_E) {
@@ -1485,28 +1501,21 @@ void time_once(Handle *h, int op, int K) {
   }
   if (op == VEMG_OP_COARSEST) {
     DLevel &L = h->S.back();
-    launch_dense<T>(st, K, L.Cinv, L.n, L.g<T>(), L.x<T>(), L.dpart, nullptr);
+    const DenseJob<T> J{L.Cinv, L.n, L.g<T>(), L.x<T>(), L.dpart};
+    launch_dense<T>(st, K, &J, 1, nullptr);
     return;
   }
   if (op == VEMG_OP_GS_COARSE) {
     DLevel &L = h->Ab[1];
-    for (size_t c = 0; c + 1 < L.pc_start.size(); ++c)
-      launch_patch_gs<T>(st, K, L.Ac, L.ps, L.pc_start[c], L.pc_start[c + 1] - L.pc_start[c], L.g<T>(), L.x<T>(),
-                         nullptr, -1, false);
+    for (size_t c = 0; c + 1 < L.pc_start.size(); ++c) {
+      const PatchJob<T> J{L.Ac, L.ps, L.pc_start[c], L.pc_start[c + 1] - L.pc_start[c], 0, L.g<T>(), L.x<T>()};
+      launch_patch_gs<T>(st, K, kPatchForward, &J, 1, nullptr);
+    }
     return;
   }
-  int nct = (int)P.top_colour_start.size() - 1, ncb = (int)P.bar_colour_start.size() - 1;
-  for (int c = 0; c < std::max(nct, ncb); ++c) {
-    int64_t a0 = 0, a1 = 0, b0 = 0, b1 = 0;
-    if (c < nct) {
-      a0 = P.top_colour_start[c];
-      a1 = P.top_colour_start[c + 1];
-    }
-    if (c < ncb) {
-      b0 = P.bar_colour_start[c];
-      b1 = P.bar_colour_start[c + 1];
-    }
-    launch_gs<T>(st, K, h->A, a0, a1, b0, b1, v.r, v.z, nullptr, false);
+  for (int c = 0; c < fine_colours(P); ++c) {
+    const ColourRows q = colour_rows(P, c);
+    launch_gs<T>(st, K, h->A, q.a0, q.a1, q.b0, q.b1, v.r, v.z, nullptr, false);
   }
 }
 
@@ -1522,7 +1531,7 @@ int do_time(Handle *h, int op, int K, int reps, double *avg_ms, int *launches) {
   if ((op == VEMG_OP_ET || op == VEMG_OP_E) && (P.n_top == 0 || h->S.empty())) return VEMG_ERR_STATE;
   if (K != 1 && K != 2 && K != 4 && K != 8) return VEMG_ERR_INVALID_ARG;
   batch_layout(h, K);
-  int nc = std::max((int)P.top_colour_start.size() - 1, (int)P.bar_colour_start.size() - 1);
+  int nc = fine_colours(P);
   if (op == VEMG_OP_GS_COARSE) {
     nc = (int)h->Ab[1].pc_start.size() - 1;
     DLevel &L = h->Ab[1];
@@ -1639,9 +1648,8 @@ int do_export(Handle *h, const std::string &name, void *buf, size_t *bytes) {
 // ordering with the legacy null stream (so another thread's work cannot join
 // a graph being captured on it; ordering with the caller's stream is
 // explicit, see sync_in), and, being created with a CU mask (every CU, so
-// nothing is restricted), it does not share its queue, so the two
-// preconditioner branches cannot end up serialised behind each other or
-// behind another stream's work.
+// nothing is restricted), it does not share its queue, so a solve cannot end
+// up serialised behind another stream's work.
 hipError_t create_queue_stream(int device, hipStream_t *st) {
   hipDeviceProp_t prop;
   hipError_t e = hipGetDeviceProperties(&prop, device);
@@ -1759,11 +1767,10 @@ struct Lane {
   }
 };
 
-// At most kServerStreamPairs pairs of streams serve every lane (lane i uses
-// pair i mod kServerStreamPairs): a pair is the lane's Krylov stream and its
-// second preconditioner branch, each created with a (full) CU mask so that it
-// has a hardware queue of its own.
-constexpr int kServerStreamPairs = 2;
+// kServerStreams streams serve every lane (lane i uses stream i mod
+// kServerStreams), each created with a (full) CU mask so that it has a
+// hardware queue of its own (a process has four).
+constexpr int kServerStreams = 4;
 
 }  // namespace
 }  // namespace vemg
@@ -1772,7 +1779,7 @@ struct vemg_server_s {
   int device = 0;
   size_t budget = 0;
   vemg_options opt;
-  hipStream_t streams[2 * vemg::kServerStreamPairs] = {};
+  hipStream_t streams[vemg::kServerStreams] = {};
   std::vector<std::unique_ptr<vemg::Lane>> lanes;
   std::vector<std::unique_ptr<vemg::SReq>> reqs;  // owner; appended under mu
   std::map<uint64_t, vemg::SReq *> by_id;
@@ -2019,10 +2026,9 @@ bool valid_options(const vemg_options &opt) {
            opt.extrapolation < 0 || opt.extrapolation > 1);
 }
 
-// A handle on `device`.  pool == nullptr: the handle creates its own two work
-// streams; otherwise it runs on pool[0] (Krylov part, first branch) and
-// pool[1] (second branch), which stay the caller's.
-vemg_status create_handle(const vemg_options *o, int device, hipStream_t user, const hipStream_t *pool,
+// A handle on `device`.  pool == nullptr: the handle creates its own work
+// stream; otherwise it runs on pool, which stays the caller's.
+vemg_status create_handle(const vemg_options *o, int device, hipStream_t user, hipStream_t pool,
                           vemg_solver *out) {
   if (!out) return VEMG_ERR_INVALID_ARG;
   *out = nullptr;
@@ -2040,17 +2046,12 @@ vemg_status create_handle(const vemg_options *o, int device, hipStream_t user, c
   int st = guarded(h, [&]() -> int {
     if (device >= 0) {
       if (pool) {
-        h->own_streams = false;
-        h->work = pool[0];
-        h->work2 = pool[1];
+        h->own_stream = false;
+        h->work = pool;
       } else {
         HIPCHK(create_queue_stream(device, &h->work));
-        HIPCHK(create_queue_stream(device, &h->work2));
       }
       HIPCHK(hipEventCreateWithFlags(&h->ev, hipEventDisableTiming));
-      HIPCHK(hipEventCreateWithFlags(&h->ev_fork, hipEventDisableTiming));
-      HIPCHK(hipEventCreateWithFlags(&h->ev_join, hipEventDisableTiming));
-      HIPCHK(hipEventCreateWithFlags(&h->ev_res, hipEventDisableTiming));
     }
     return VEMG_OK;
   });
@@ -2199,10 +2200,7 @@ vemg_status vemg_set_preconditioner(vemg_solver s, int pc) {
     return VEMG_ERR_STATE;
   }
   return (vemg_status)guarded(s, [&]() -> int {
-    if (s->device >= 0) {
-      if (s->work) HIPCHK(hipStreamSynchronize(s->work));
-      if (s->work2) HIPCHK(hipStreamSynchronize(s->work2));
-    }
+    if (s->device >= 0 && s->work) HIPCHK(hipStreamSynchronize(s->work));
     vemg::destroy_graphs(s);
     s->opt.pc = pc;
     return VEMG_OK;
@@ -2262,15 +2260,10 @@ vemg_status vemg_destroy(vemg_solver s) {
   if (s->device >= 0) {
     (void)hipSetDevice(s->device);
     if (s->work) (void)hipStreamSynchronize(s->work);
-    if (s->work2) (void)hipStreamSynchronize(s->work2);
     vemg::destroy_graphs(s);
     s->ar.release();
     if (s->ev) (void)hipEventDestroy(s->ev);
-    if (s->ev_fork) (void)hipEventDestroy(s->ev_fork);
-    if (s->ev_join) (void)hipEventDestroy(s->ev_join);
-    if (s->ev_res) (void)hipEventDestroy(s->ev_res);
-    if (s->own_streams && s->work) (void)hipStreamDestroy(s->work);
-    if (s->own_streams && s->work2) (void)hipStreamDestroy(s->work2);
+    if (s->own_stream && s->work) (void)hipStreamDestroy(s->work);
   }
   delete s;
   return VEMG_OK;
@@ -2311,7 +2304,7 @@ vemg_status vemg_server_create(int device, size_t hbm_budget, const vemg_options
   sv->device = device;
   sv->budget = hbm_budget;
   hipError_t e = hipSetDevice(device);
-  for (int i = 0; e == hipSuccess && i < 2 * vemg::kServerStreamPairs; ++i)
+  for (int i = 0; e == hipSuccess && i < vemg::kServerStreams; ++i)
     e = vemg::create_queue_stream(device, &sv->streams[i]);
   if (e != hipSuccess) {
     (void)vemg_server_destroy(sv);
@@ -2330,9 +2323,8 @@ vemg_status vemg_server_add_mesh(vemg_server sv, int64_t n_nodes, const double *
     return VEMG_ERR_STATE;
   }
   const int lane = (int)sv->lanes.size();
-  const hipStream_t *pair = &sv->streams[2 * (lane % vemg::kServerStreamPairs)];
   vemg_solver h = nullptr;
-  vemg_status st = vemg::create_handle(&sv->opt, sv->device, nullptr, pair, &h);
+  vemg_status st = vemg::create_handle(&sv->opt, sv->device, nullptr, sv->streams[lane % vemg::kServerStreams], &h);
   if (st != VEMG_OK) return st;
   // a mesh that alone exceeds the budget is refused before its upload
   auto L = std::make_unique<vemg::Lane>();
@@ -2356,8 +2348,8 @@ vemg_status vemg_server_add_mesh(vemg_server sv, int64_t n_nodes, const double *
       throw vemg::DeviceError(VEMG_ERR_DEVICE, "device allocations differ from the counted footprint");
     // capture both iteration graphs now, while no other thread uses the device
     if (h->opt.use_graphs) {
-      vemg::iteration_graphs<double>(h, vemg::kMaxBatch, vemg::kGraphFP64);
-      vemg::iteration_graphs<double>(h, vemg::kMaxBatch, vemg::kGraphMixedPC);
+      vemg::iteration_graph<double>(h, vemg::kMaxBatch, vemg::kGraphFP64);
+      vemg::iteration_graph<double>(h, vemg::kMaxBatch, vemg::kGraphMixedPC);
       HIPCHK(hipStreamSynchronize(h->work));
     }
     L->resident = true;

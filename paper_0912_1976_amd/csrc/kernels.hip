@@ -212,42 +212,25 @@ __device__ __forceinline__ Row<T, C> fine_row(const Sell &A, int64_t s, int t, i
   return out;
 }
 
-// y_r = -(U x)_r, the residual after the forward sweep, by lane q of row r's
-// lanes; with y2, a row r >= y2_from is also stored there.
-// (mi: the row's index in A, r: its index in the vectors; equal unless A
-// holds a subset of the rows)
+// y_r = -(V x)_r by lane q of row r's lanes, V the part PART of row mi of A
+// (U: the residual after the forward sweep).
 // Bandwidth and gathers bound it, and U holds half of the row: with the
 // forward sweep reading L alone and this product U alone, FP64 solves of
 // 2,179,616 unknowns went from 314.2 to 293.1 ms (eight right-hand sides) and
 // from 123.8 to 115.6 ms (one).  On the same inputs one application of the
 // preconditioner moved by 2e-16 (relative), at aspect ratios 1e-2 to 1e-4.
-template <class T, int K>
+template <class T, int K, int PART>
 __device__ __forceinline__ void residual_row(const Sell &A, int64_t mi, int64_t r, int q, const T *__restrict__ x,
-                                             T *y, T *y2, int64_t y2_from) {
+                                             T *y) {
   constexpr int LPR = row_lanes<T, K>(), C = K / LPR;
   T s0 = T(1);
   if constexpr (!std::is_same<T, double>::value) s0 = A.s32[mi];
   Row<T, C> out{};
   T acc[C];
-  sell_row<T, K, C, false, kUpper>(A, mi >> 6, (int)(mi & 63), q, x, out, acc);
+  sell_row<T, K, C, false, PART>(A, mi >> 6, (int)(mi & 63), q, x, out, acc);
 #pragma unroll
   for (int k = 0; k < C; ++k) out.v[k] = -s0 * acc[k];
   stp<T, K, C>(y, r, q, out);
-  if (y2 && r >= y2_from) stp<T, K, C>(y2, r, q, out);
-}
-
-// The residual form on the listed rows rows[0 .. nr) only: As holds those
-// rows (row i of As is row rows[i] of the matrix, its entries in the same
-// order), so that its entries are read coalesced.
-template <class T, int K>
-__global__ __launch_bounds__(kBlock) void k_spmv_rows(Sell As, const int32_t *__restrict__ rows, int64_t nr,
-                                                     const T *__restrict__ x, T *__restrict__ y,
-                                                     const int *__restrict__ done) {
-  constexpr int LPR = row_lanes<T, K>();
-  if (done && *done) return;
-  const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / LPR;
-  if (i >= nr) return;
-  residual_row<T, K>(As, i, rows[i], (int)(threadIdx.x % LPR), x, y, (T *)nullptr, 0);
 }
 
 // Blocks of kBlock rows (four slices), row_lanes<T, K>() lanes per row.
@@ -257,8 +240,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_rows(Sell As, const int32_t *__
 template <class T, int K, int MODE, bool DOT>
 __global__ __launch_bounds__((kBlock * row_lanes<T, K>())) void k_spmv(
     Sell A, int64_t r0, int64_t r1, int64_t s_first, int64_t ns, int64_t nb, const int32_t *__restrict__ order,
-    const T *__restrict__ x, T *__restrict__ y, double *__restrict__ partial, const int *__restrict__ done,
-    T *__restrict__ y2, int64_t y2_from) {
+    const T *__restrict__ x, T *__restrict__ y, double *__restrict__ partial, const int *__restrict__ done) {
   constexpr int LPR = row_lanes<T, K>(), C = K / LPR;
   static_assert(!(MODE == 1 && DOT), "the residual form has no block reduction");
   if (done && *done) return;
@@ -274,7 +256,7 @@ __global__ __launch_bounds__((kBlock * row_lanes<T, K>())) void k_spmv(
   if (i < ns && r >= r0 && r < r1) {
     if constexpr (MODE == 1) {
       // no block reduction in this form, so the lane may leave
-      residual_row<T, K>(A, r, r, q, x, y, y2, y2_from);
+      residual_row<T, K, kUpper>(A, r, r, q, x, y);
       return;
     }
     const Row<T, C> xr = ldp<T, K, C>(x, r, q);
@@ -293,26 +275,24 @@ template <class T>
 struct GsDev {
   int64_t r0[2], r1[2], sf[2], nb[2];
   T *x;
-  T *x2;            // null, or a second output for the rows r >= x2_from
-  int64_t x2_from;
   int n;
   int64_t nbt;
 };
 
 // One Gauss-Seidel step of row r by lane q of its row_lanes<T, K>() lanes
-// (columns [q C, q C + C)): x_r + (g_r - (A x)_r) / a_rr, or with FIRST
-// (g_r - (L x)_r) / a_rr, the first sweep's step from zero, which reads L
-// alone; with x2, a row r >= x2_from is also stored there.
-// (mi: the row's index in A, r: its index in the vectors)
+// (columns [q C, q C + C)) with the right-hand side gs g_gi: x_r +
+// (gs g - (A x)_r) / a_rr, or with FIRST (g - (L x)_r) / a_rr, the first
+// sweep's step from zero, which reads L alone.
+// (mi: the row's index in A; r and gi: its index in x and in g)
 template <class T, int K, bool FIRST>
-__device__ __forceinline__ void gs_row(const Sell &A, int64_t mi, int64_t r, int q, const T *__restrict__ g, T *x,
-                                       T *x2, int64_t x2_from) {
+__device__ __forceinline__ void gs_row(const Sell &A, int64_t mi, int64_t r, int64_t gi, T gs, int q,
+                                       const T *__restrict__ g, T *x) {
   constexpr int LPR = row_lanes<T, K>(), C = K / LPR;
   const int64_t s = mi >> 6;
   const int t = (int)(mi & 63);
   Row<T, C> xr{};
   if constexpr (!FIRST) xr = ldp<T, K, C>(x, r, q);
-  const Row<T, C> gr = ldp<T, K, C>(g, r, q);
+  const Row<T, C> gr = ldp<T, K, C>(g, gi, q);
   T d = T(0), i0;
   if constexpr (std::is_same<T, double>::value) {
     i0 = A.i64[mi];
@@ -327,12 +307,63 @@ __device__ __forceinline__ void gs_row(const Sell &A, int64_t mi, int64_t r, int
 #pragma unroll
   for (int k = 0; k < C; ++k) {
     if constexpr (std::is_same<T, double>::value)
+      out.v[k] = xr.v[k] + (gs * gr.v[k] - (acc[k] + d * xr.v[k])) * i0;
+    else
+      out.v[k] = xr.v[k] + (gs * gr.v[k] * i0 - (acc[k] + d * xr.v[k]));
+  }
+  stp<T, K, C>(x, r, q, out);
+}
+
+// The backward step of top row r of the merged cycles: as gs_row, its non-top
+// neighbours' values taken as w - u (MergedRows).
+template <class T, int K>
+__device__ __forceinline__ void gs_top_row(const Sell &A, int64_t r, int q, const T *__restrict__ g, T *x) {
+  constexpr int LPR = row_lanes<T, K>(), C = K / LPR;
+  const int64_t s = r >> 6, base = A.sptr[s];
+  const int t = (int)(r & 63), len = (int)((A.sptr[s + 1] - base) >> 6);
+  const Row<T, C> xr = ldp<T, K, C>(x, r, q), gr = ldp<T, K, C>(g, r, q);
+  T d, i0;
+  if constexpr (std::is_same<T, double>::value) {
+    i0 = A.i64[r];
+    d = A.d64[r];
+  } else {
+    i0 = 1.0f / A.s32[r];
+    d = A.dh32[r];
+  }
+  T acc[C];
+#pragma unroll
+  for (int k = 0; k < C; ++k) acc[k] = T(0);
+#pragma unroll 2
+  for (int e = 0; e < len; ++e) {
+    const int64_t p = base + t + (int64_t)e * 64;
+    const int32_t c = A.col[p], cu = A.col2[p];
+    const T v = sell_vals<T>(A)[p];
+    const Row<T, C> xc = ldp<T, K, C>(x, c, q), uc = ldp<T, K, C>(x, cu < 0 ? c : cu, q);
+#pragma unroll
+    for (int k = 0; k < C; ++k) acc[k] += v * ((xc.v[k] - (cu < 0 ? T(0) : uc.v[k])) - xr.v[k]);
+  }
+  Row<T, C> out;
+#pragma unroll
+  for (int k = 0; k < C; ++k) {
+    if constexpr (std::is_same<T, double>::value)
       out.v[k] = xr.v[k] + (gr.v[k] - (acc[k] + d * xr.v[k])) * i0;
     else
       out.v[k] = xr.v[k] + (gr.v[k] * i0 - (acc[k] + d * xr.v[k]));
   }
   stp<T, K, C>(x, r, q, out);
-  if (x2 && r >= x2_from) stp<T, K, C>(x2, r, q, out);
+}
+
+// the row of block b (of J.nbt) and lane-in-slice t, or -1
+template <class T>
+__device__ __forceinline__ int64_t gs_block_row(const GsDev<T> &J, int64_t b, int t) {
+  int64_t blk = xcd_block(b, J.nbt);
+  int j = 0;
+  while (j + 1 < J.n && blk >= J.nb[j]) {
+    blk -= J.nb[j];
+    ++j;
+  }
+  const int64_t r = (J.sf[j] + blk) * 64 + t;
+  return r < J.r0[j] || r >= J.r1[j] ? -1 : r;
 }
 
 // one slice per block (a colour holds few rows, so small blocks spread them
@@ -343,31 +374,107 @@ __global__ __launch_bounds__((kWave * row_lanes<T, K>())) void k_gs(Sell A, GsDe
                                                                    const int *__restrict__ done) {
   constexpr int LPR = row_lanes<T, K>();
   if (done && *done) return;
-  int64_t blk = xcd_block(blockIdx.x, J.nbt);
-  int j = 0;
-  while (j + 1 < J.n && blk >= J.nb[j]) {
-    blk -= J.nb[j];
-    ++j;
-  }
-  const int64_t r0 = J.r0[j], r1 = J.r1[j];
-  const int t = threadIdx.x / LPR, q = threadIdx.x % LPR;
-  const int64_t s = J.sf[j] + blk;
-  const int64_t r = s * 64 + t;
-  if (r < r0 || r >= r1) return;
-  gs_row<T, K, FIRST>(A, r, r, q, g, J.x, J.x2, J.x2_from);
+  const int64_t r = gs_block_row(J, blockIdx.x, threadIdx.x / LPR);
+  if (r >= 0) gs_row<T, K, FIRST>(A, r, r, r, T(1), threadIdx.x % LPR, g, J.x);
 }
 
-// The listed rows rows[0 .. nr) (rows that share no entries), each by its
-// row_lanes<T, K>() lanes, with the arithmetic of k_gs's first sweep; As holds those rows
-// (row i of As is row rows[i] of the matrix, its entries in the same order).
-template <class T, int K>
-__global__ __launch_bounds__(kBlock) void k_gs_rows(Sell As, const int32_t *__restrict__ rows, int64_t nr,
-                                                   const T *__restrict__ g, T *x, const int *__restrict__ done) {
+// The merged cycles' colour: k_gs's blocks, then those of D's rows [d0, d1).
+template <class T, int K, bool FIRST>
+__global__ __launch_bounds__((kWave * row_lanes<T, K>())) void k_gs_merged(Sell A, MergedRows M, GsDev<T> J,
+                                                                          int64_t d0, int64_t d1,
+                                                                          const T *__restrict__ g,
+                                                                          const int *__restrict__ done) {
   constexpr int LPR = row_lanes<T, K>();
   if (done && *done) return;
-  const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / LPR;
-  if (i >= nr) return;
-  gs_row<T, K, true>(As, i, rows[i], (int)(threadIdx.x % LPR), g, x, (T *)nullptr, 0);
+  const int t = threadIdx.x / LPR, q = threadIdx.x % LPR;
+  if ((int64_t)blockIdx.x >= J.nbt) {
+    const int64_t k = (d0 / 64 + blockIdx.x - J.nbt) * 64 + t;
+    if (k >= d0 && k < d1) gs_row<T, K, FIRST>(FIRST ? M.fwd : M.bwd, k, M.n + k, M.drow[k], T(1), q, g, J.x);
+    return;
+  }
+  const int64_t r = gs_block_row(J, blockIdx.x, t);
+  if (r < 0) return;
+  if constexpr (!FIRST) {
+    if (r < M.n_top)
+      gs_top_row<T, K>(M.top, r, q, g, J.x);
+    else
+      gs_row<T, K, FIRST>(A, r, r, r, T(2), q, g, J.x);
+  } else {
+    gs_row<T, K, FIRST>(A, r, r, r, T(1), q, g, J.x);
+  }
+}
+
+// The merged cycles' residual: blocks [0, nb) as k_spmv's over all rows, the
+// others R's rows.
+template <class T, int K>
+__global__ __launch_bounds__((kBlock * row_lanes<T, K>())) void k_res_merged(Sell A, MergedRows M, int64_t nb,
+                                                                            const int32_t *__restrict__ order,
+                                                                            const T *__restrict__ x,
+                                                                            T *__restrict__ y,
+                                                                            const int *__restrict__ done) {
+  constexpr int LPR = row_lanes<T, K>();
+  if (done && *done) return;
+  const int rloc = threadIdx.x / LPR, q = threadIdx.x % LPR;
+  if ((int64_t)blockIdx.x >= nb) {
+    const int64_t k = (blockIdx.x - nb) * kBlock + rloc;
+    if (k < M.nr) residual_row<T, K, kAll>(M.res, k, M.n + M.rpos[k], q, x, y);
+    return;
+  }
+  const int64_t i = xcd_block(blockIdx.x, nb) * kSlicesPerBlock + (rloc >> 6);
+  if (i * 64 >= M.n) return;
+  const int64_t r = (int64_t)order[i] * 64 + (rloc & 63);
+  if (r < M.n) residual_row<T, K, kUpper>(A, r, r, q, x, y);
+}
+
+// Between the merged sweeps (MergedRows), row_lanes<T, K>() lanes per row: one
+// pass in place of the two prolongations and of the sum of the two cycles.
+template <class T, int K>
+__global__ __launch_bounds__((kBlock * row_lanes<T, K>())) void k_prolong_merged(MergedRows M, int64_t nb,
+                                                                                const T *__restrict__ ys,
+                                                                                const T *__restrict__ ya, T *x,
+                                                                                const int *__restrict__ done) {
+  constexpr int LPR = row_lanes<T, K>(), C = K / LPR;
+  if (done && *done) return;
+  const int rloc = threadIdx.x / LPR, q = threadIdx.x % LPR;
+  const int64_t r = xcd_block(blockIdx.x, nb) * kBlock + rloc;
+  if (r >= M.n) return;
+  const int64_t s = r >> 6, base = M.prol.sptr[s];
+  const int len = (int)((M.prol.sptr[s + 1] - base) >> 6);
+  const int32_t *__restrict__ cp = M.prol.col + base + (r & 63);
+  const T *__restrict__ vp = sell_vals<T>(M.prol) + base + (r & 63);
+  const int32_t pos = M.xpos[r];
+  const Row<T, C> xr = ldp<T, K, C>(x, r, q);
+  const int32_t nt = (int32_t)M.n_top;
+  T es[C], pa[C];
+#pragma unroll
+  for (int k = 0; k < C; ++k) es[k] = pa[k] = T(0);
+#pragma unroll 4
+  for (int e = 0; e < len; ++e) {
+    const int32_t c = cp[(int64_t)e * 64];
+    const T v = vp[(int64_t)e * 64];
+    const bool surf = c < nt;
+    const Row<T, C> yc = ldp<T, K, C>(surf ? ys : ya, surf ? c : c - nt, q);
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+      es[k] += (surf ? v : T(0)) * yc.v[k];
+      pa[k] += (surf ? T(0) : v) * yc.v[k];
+    }
+  }
+  Row<T, C> out;
+  if (r < nt) {
+#pragma unroll
+    for (int k = 0; k < C; ++k) out.v[k] = xr.v[k] + es[k];
+  } else {
+    Row<T, C> u = xr;
+    if (pos >= 0 && pos < M.nd) u = ldp<T, K, C>(x, M.n + pos, q);
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+      u.v[k] += pa[k];
+      out.v[k] = (xr.v[k] + es[k]) + u.v[k];
+    }
+    if (pos >= 0) stp<T, K, C>(x, M.n + pos, q, u);
+  }
+  stp<T, K, C>(x, r, q, out);
 }
 
 template <class T, int K, bool ACC>
@@ -428,10 +535,18 @@ __global__ __launch_bounds__(kBlock) void k_prolong_sum(Sell E, int64_t n_top, i
 }
 
 // ------------------------------------------------------------- CsrG
-// Off-diagonal sum of one row for K columns by its group of G lanes (the
-// result is valid in every lane of the group).
-template <class T, int K, int G>
-__device__ __forceinline__ void group_row(const CsrG &A, int64_t r, int gl, const T *__restrict__ x, T (&acc)[K]) {
+// Up to two jobs of one launch: blocks [0, nb0) are job 0's, the rest job 1's.
+template <class J>
+struct Jobs {
+  J j[2];
+  int64_t nb0, nb1;
+};
+
+// Off-diagonal sum of one row for K columns by its group of G lanes (a power
+// of two; the result is valid in every lane of the group).
+template <class T, int K>
+__device__ __forceinline__ void group_row(const CsrG &A, int G, int64_t r, int gl, const T *__restrict__ x,
+                                          T (&acc)[K]) {
   const int32_t b = A.ptr[r], e = A.ptr[r + 1];
   const T *__restrict__ vals = csr_vals<T>(A);
 #pragma unroll
@@ -443,10 +558,9 @@ __device__ __forceinline__ void group_row(const CsrG &A, int64_t r, int gl, cons
 #pragma unroll
     for (int k = 0; k < K; ++k) acc[k] += v * xc.v[k];
   }
-#pragma unroll
   for (int o = G / 2; o > 0; o >>= 1) {
 #pragma unroll
-    for (int k = 0; k < K; ++k) acc[k] += __shfl_xor(acc[k], o, G);
+    for (int k = 0; k < K; ++k) acc[k] += __shfl_xor(acc[k], o, kWave);
   }
 }
 
@@ -454,7 +568,7 @@ __device__ __forceinline__ void group_row(const CsrG &A, int64_t r, int gl, cons
 // writes).  The kernels below renumber their blocks like the fine ones, so
 // that each XCD works on a contiguous range of rows and the vector values
 // those rows gather stay in that XCD's L2.  MODE 0: y = A x, 1: y = g - A x (square); 2: y = P x, 3: y += P x.
-template <class T, int K, int G, int MODE>
+template <class T, int K, int MODE>
 __device__ __forceinline__ void csr_row_op(const CsrG &A, int64_t r, int gl, const T *x, const T *g, T *y) {
   // the row's own operands are loaded first, so that their latency overlaps
   // the row-pointer -> entries -> gathered values chain of group_row
@@ -475,7 +589,7 @@ __device__ __forceinline__ void csr_row_op(const CsrG &A, int64_t r, int gl, con
       dr = A.s32[r];
   }
   T acc[K];
-  group_row<T, K, G>(A, r, gl, x, acc);  // off-diagonal part only
+  group_row<T, K>(A, A.G, r, gl, x, acc);  // off-diagonal part only
   if (gl != 0) return;
   Row<T, K> out;
   if (MODE <= 1) {
@@ -501,15 +615,16 @@ __device__ __forceinline__ void csr_row_op(const CsrG &A, int64_t r, int gl, con
   st<T, K>(y, ro, out);
 }
 
-template <class T, int K, int G, int MODE>
-__global__ __launch_bounds__(kWave) void k_csr_spmv(CsrG A, int64_t r0, int64_t r1, const T *__restrict__ x,
-                                                     const T *__restrict__ g, T *__restrict__ y,
-                                                     const int *__restrict__ done) {
+template <class T, int K, int MODE>
+__global__ __launch_bounds__(kWave) void k_csr(Jobs<CsrJob<T>> P, const int *__restrict__ done) {
   if (done && *done) return;
-  const int gl = threadIdx.x & (G - 1);
-  const int64_t r = r0 + (xcd_block(blockIdx.x, gridDim.x) * kWave + threadIdx.x) / G;
-  if (r >= r1) return;
-  csr_row_op<T, K, G, MODE>(A, r, gl, x, g, y);
+  const bool second = (int64_t)blockIdx.x >= P.nb0;
+  const CsrJob<T> &J = second ? P.j[1] : P.j[0];
+  const int64_t blk = second ? xcd_block(blockIdx.x - P.nb0, P.nb1) : xcd_block(blockIdx.x, P.nb0);
+  const int G = J.A.G;
+  const int64_t r = (blk * kWave + threadIdx.x) / G;
+  if (r >= J.A.nrows) return;
+  csr_row_op<T, K, MODE>(J.A, r, threadIdx.x & (G - 1), J.x, J.g, J.y);
 }
 
 // Patch sweep: one block per patch, kPatchGroup lanes per unknown (a coarse
@@ -544,13 +659,18 @@ __device__ __forceinline__ void group_sum(T (&acc)[K]) {
 }
 
 template <class T, int K, bool ZS, bool BWD>
-__global__ __launch_bounds__(kPatchThreads) void k_patch_gs(CsrG A, PatchSweep S, int64_t p0, int64_t np,
-                                                            const T *__restrict__ g, T *__restrict__ x,
-                                                            const int *__restrict__ done, int64_t zlim) {
+__global__ __launch_bounds__(kPatchThreads) void k_patch_gs(Jobs<PatchJob<T>> P, const int *__restrict__ done) {
   constexpr int G = kPatchGroup;
   __shared__ Row<T, K> hs[kPatchLdsRows];
   if (done && *done) return;
-  const int64_t p = p0 + xcd_block(blockIdx.x, np);
+  const bool second = (int64_t)blockIdx.x >= P.nb0;
+  const PatchJob<T> &J = second ? P.j[1] : P.j[0];
+  const CsrG &A = J.A;
+  const PatchSweep &S = J.S;
+  const T *__restrict__ g = J.g;
+  T *__restrict__ x = J.x;
+  const int64_t zlim = J.zlim;
+  const int64_t p = J.p0 + (second ? xcd_block(blockIdx.x - P.nb0, P.nb1) : xcd_block(blockIdx.x, P.nb0));
   const int32_t ps = S.prow[p], pe = S.prow[p + 1];
   const int q = threadIdx.x / G, gl = threadIdx.x % G;
   const int32_t i = ps + q;
@@ -639,18 +759,20 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch_gs(CsrG A, PatchSweep S
 // k_dense_sum adds in chunk order (a single chunk is written directly).  No
 // summation order depends on K.
 template <class T, int K>
-__global__ __launch_bounds__(kBlock) void k_dense_part(const double *__restrict__ C, int64_t m,
-                                                       const T *__restrict__ g, double *__restrict__ part,
-                                                       T *__restrict__ x, const int *__restrict__ done) {
+__global__ __launch_bounds__(kBlock) void k_dense_part(Jobs<DenseJob<T>> P, const int *__restrict__ done) {
   if (done && *done) return;
+  const bool second = (int64_t)blockIdx.x >= P.nb0;
+  const DenseJob<T> &J = second ? P.j[1] : P.j[0];
+  const double *__restrict__ C = J.C;
+  const int64_t m = J.m, blk = blockIdx.x - (second ? P.nb0 : 0), tiles = (m + kWave - 1) / kWave;
   __shared__ double red[kSlicesPerBlock][K][kWave];
   __shared__ Row<T, K> gt[kDenseChunk];  // the chunk's g, read by every lane of a wavefront at once
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t i = (int64_t)blockIdx.x * kWave + lane;
-  const int64_t c = blockIdx.y;
+  const int64_t i = blk % tiles * kWave + lane;
+  const int64_t c = blk / tiles;
   const int64_t jc = c * kDenseChunk;
   const int nj = (int)(m - jc < kDenseChunk ? m - jc : kDenseChunk);
-  for (int j = threadIdx.x; j < nj; j += kBlock) gt[j] = ld<T, K>(g, jc + j);
+  for (int j = threadIdx.x; j < nj; j += kBlock) gt[j] = ld<T, K>(J.g, jc + j);
   __syncthreads();
   constexpr int Q = kDenseChunk / kSlicesPerBlock;
   const int j0 = w * Q;
@@ -680,25 +802,27 @@ __global__ __launch_bounds__(kBlock) void k_dense_part(const double *__restrict_
     for (int q = 1; q < kSlicesPerBlock; ++q) v += red[q][k][lane];
     s.v[k] = v;
   }
-  if (gridDim.y == 1) {
+  if (m <= kDenseChunk) {
     Row<T, K> out;
 #pragma unroll
     for (int k = 0; k < K; ++k) out.v[k] = (T)s.v[k];
-    st<T, K>(x, i, out);
+    st<T, K>(J.x, i, out);
   } else {
-    st<double, K>(part + c * m * K, i, s);
+    st<double, K>(J.part + c * m * K, i, s);
   }
 }
 
 template <class T, int K>
-__global__ __launch_bounds__(kBlock) void k_dense_sum(const double *__restrict__ part, int64_t m, int64_t nc,
-                                                      T *__restrict__ x, const int *__restrict__ done) {
+__global__ __launch_bounds__(kBlock) void k_dense_sum(Jobs<DenseJob<T>> P, const int *__restrict__ done) {
   if (done && *done) return;
-  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;  // output t = i K + k
+  const bool second = (int64_t)blockIdx.x >= P.nb0;
+  const DenseJob<T> &J = second ? P.j[1] : P.j[0];
+  const int64_t t = (blockIdx.x - (second ? P.nb0 : 0)) * kBlock + threadIdx.x;  // output t = i K + k
+  const int64_t m = J.m, nc = (m + kDenseChunk - 1) / kDenseChunk;
   if (t >= m * K) return;
-  double s = part[t];
-  for (int64_t c = 1; c < nc; ++c) s += part[c * m * K + t];
-  x[t] = (T)s;
+  double s = J.part[t];
+  for (int64_t c = 1; c < nc; ++c) s += J.part[c * m * K + t];
+  J.x[t] = (T)s;
 }
 
 // ------------------------------------------------------------- vectors
@@ -1244,33 +1368,9 @@ void launch_slot_copy(hipStream_t stm, unsigned mask, const double *z, double *p
     } break;                  \
   }
 
-#define VEMG_G_SWITCH(G, ...) \
-  switch (G) {                \
-    case 4: {                 \
-      constexpr int GG = 4;   \
-      __VA_ARGS__;            \
-    } break;                  \
-    case 8: {                 \
-      constexpr int GG = 8;   \
-      __VA_ARGS__;            \
-    } break;                  \
-    case 16: {                \
-      constexpr int GG = 16;  \
-      __VA_ARGS__;            \
-    } break;                  \
-    case 32: {                \
-      constexpr int GG = 32;  \
-      __VA_ARGS__;            \
-    } break;                  \
-    default: {                \
-      constexpr int GG = 64;  \
-      __VA_ARGS__;            \
-    } break;                  \
-  }
-
 template <class T>
 void launch_spmv(hipStream_t stm, int K, const Sell &A, int mode, int64_t r0, int64_t r1, const T *x, T *y,
-                 double *partial, const int *done, const int32_t *order, T *y2, int64_t y2_from) {
+                 double *partial, const int *done, const int32_t *order) {
   int64_t nb = sell_blocks(r0, r1);
   if (!nb) return;
   int64_t sf = r0 / kWave, ns = (r1 + kWave - 1) / kWave - sf;
@@ -1279,13 +1379,13 @@ void launch_spmv(hipStream_t stm, int K, const Sell &A, int mode, int64_t r0, in
     if (mode == 0) {
       if (partial)
         hipLaunchKernelGGL((k_spmv<T, KK, 0, true>), grid(nb), blk, 0, stm, A, r0, r1, sf, ns, nb, order, x, y,
-                           partial, done, y2, y2_from);
+                           partial, done);
       else
         hipLaunchKernelGGL((k_spmv<T, KK, 0, false>), grid(nb), blk, 0, stm, A, r0, r1, sf, ns, nb, order, x, y,
-                           partial, done, y2, y2_from);
+                           partial, done);
     } else {
       hipLaunchKernelGGL((k_spmv<T, KK, 1, false>), grid(nb), blk, 0, stm, A, r0, r1, sf, ns, nb, order, x, y,
-                         partial, done, y2, y2_from);
+                         partial, done);
     }
   })
 }
@@ -1295,32 +1395,9 @@ static inline int64_t slices(int64_t r0, int64_t r1) {
 }
 
 template <class T>
-void launch_spmv_rows(hipStream_t stm, int K, const Sell &A, const int32_t *rows, int64_t nr, const T *x, T *y,
-                      const int *done) {
-  if (nr <= 0) return;
-  VEMG_K_SWITCH(K, {
-    const int64_t nb = (nr * row_lanes<T, KK>() + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL((k_spmv_rows<T, KK>), grid(nb), dim3(kBlock), 0, stm, A, rows, nr, x, y, done);
-  })
-}
-
-template <class T>
-void launch_gs_rows(hipStream_t stm, int K, const Sell &A, const int32_t *rows, int64_t nr, const T *g, T *x,
-                    const int *done) {
-  if (nr <= 0) return;
-  VEMG_K_SWITCH(K, {
-    const int64_t nb = (nr * row_lanes<T, KK>() + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL((k_gs_rows<T, KK>), grid(nb), dim3(kBlock), 0, stm, A, rows, nr, g, x, done);
-  })
-}
-
-template <class T>
-void launch_gs(hipStream_t stm, int K, const Sell &A, int64_t a0, int64_t a1, int64_t b0, int64_t b1, const T *g,
-               T *x, const int *done, bool first, T *x2, int64_t x2_from) {
+static GsDev<T> gs_ranges(int64_t a0, int64_t a1, int64_t b0, int64_t b1, T *x) {
   GsDev<T> J{};
   J.x = x;
-  J.x2 = x2;
-  J.x2_from = x2_from;
   const int64_t ra[2] = {a0, b0}, rb[2] = {a1, b1};
   for (int i = 0; i < 2; ++i) {
     const int64_t nb = slices(ra[i], rb[i]);
@@ -1332,6 +1409,13 @@ void launch_gs(hipStream_t stm, int K, const Sell &A, int64_t a0, int64_t a1, in
     J.nbt += nb;
     ++J.n;
   }
+  return J;
+}
+
+template <class T>
+void launch_gs(hipStream_t stm, int K, const Sell &A, int64_t a0, int64_t a1, int64_t b0, int64_t b1, const T *g,
+               T *x, const int *done, bool first) {
+  const GsDev<T> J = gs_ranges(a0, a1, b0, b1, x);
   if (!J.nbt) return;
   VEMG_K_SWITCH(K, {
     const dim3 blk(kWave * row_lanes<T, KK>());
@@ -1340,6 +1424,39 @@ void launch_gs(hipStream_t stm, int K, const Sell &A, int64_t a0, int64_t a1, in
     else
       hipLaunchKernelGGL((k_gs<T, KK, false>), grid(J.nbt), blk, 0, stm, A, J, g, done);
   })
+}
+
+template <class T>
+void launch_gs_merged(hipStream_t stm, int K, const Sell &A, const MergedRows &M, int64_t a0, int64_t a1, int64_t b0,
+                      int64_t b1, int64_t d0, int64_t d1, const T *g, T *x, const int *done, bool first) {
+  const GsDev<T> J = gs_ranges(a0, a1, b0, b1, x);
+  const int64_t nb = J.nbt + slices(d0, d1);
+  if (!nb) return;
+  VEMG_K_SWITCH(K, {
+    const dim3 blk(kWave * row_lanes<T, KK>());
+    if (first)
+      hipLaunchKernelGGL((k_gs_merged<T, KK, true>), grid(nb), blk, 0, stm, A, M, J, d0, d1, g, done);
+    else
+      hipLaunchKernelGGL((k_gs_merged<T, KK, false>), grid(nb), blk, 0, stm, A, M, J, d0, d1, g, done);
+  })
+}
+
+template <class T>
+void launch_res_merged(hipStream_t stm, int K, const Sell &A, const MergedRows &M, const T *x, T *y, const int *done,
+                       const int32_t *order) {
+  const int64_t nb = sell_blocks(0, M.n), nbx = vec_blocks(M.nr);
+  if (!nb) return;
+  VEMG_K_SWITCH(K, hipLaunchKernelGGL((k_res_merged<T, KK>), grid(nb + nbx), dim3(kBlock * row_lanes<T, KK>()), 0,
+                                      stm, A, M, nb, order, x, y, done))
+}
+
+template <class T>
+void launch_prolong_merged(hipStream_t stm, int K, const MergedRows &M, const T *ys, const T *ya, T *x,
+                           const int *done) {
+  const int64_t nb = vec_blocks(M.n);
+  if (!nb) return;
+  VEMG_K_SWITCH(K, hipLaunchKernelGGL((k_prolong_merged<T, KK>), grid(nb), dim3(kBlock * row_lanes<T, KK>()), 0, stm,
+                                      M, nb, ys, ya, x, done))
 }
 
 template <class T>
@@ -1363,69 +1480,63 @@ void launch_prolong_sum(hipStream_t stm, int K, const Sell &E, int64_t n_top, co
                                       z, partial, done))
 }
 
-template <class T>
-static void csr_launch(hipStream_t stm, int K, int mode, const CsrG &A, int64_t r0, int64_t r1, const T *x,
-                       const T *g, T *y, const int *done) {
-  int64_t rows = r1 - r0;
-  if (rows <= 0) return;
-  int64_t nb = (rows * A.G + kWave - 1) / kWave;
-  VEMG_K_SWITCH(K, VEMG_G_SWITCH(A.G, {
-    switch (mode) {
-      case 0:
-        hipLaunchKernelGGL((k_csr_spmv<T, KK, GG, 0>), grid(nb), dim3(kWave), 0, stm, A, r0, r1, x, g, y, done);
-        break;
-      case 1:
-        hipLaunchKernelGGL((k_csr_spmv<T, KK, GG, 1>), grid(nb), dim3(kWave), 0, stm, A, r0, r1, x, g, y, done);
-        break;
-      case 2:
-        hipLaunchKernelGGL((k_csr_spmv<T, KK, GG, 2>), grid(nb), dim3(kWave), 0, stm, A, r0, r1, x, g, y, done);
-        break;
-      default:
-        hipLaunchKernelGGL((k_csr_spmv<T, KK, GG, 3>), grid(nb), dim3(kWave), 0, stm, A, r0, r1, x, g, y, done);
-        break;
-    }
-  }))
+// the one or two jobs of a launch, blocks(job) of them each
+template <class J, class F>
+static Jobs<J> two_jobs(const J *jobs, int nj, F &&blocks) {
+  Jobs<J> P{};
+  P.j[0] = jobs[0];
+  P.nb0 = blocks(jobs[0]);
+  if (nj > 1) {
+    P.j[1] = jobs[1];
+    P.nb1 = blocks(jobs[1]);
+  }
+  return P;
 }
 
 template <class T>
-void launch_csr_spmv(hipStream_t stm, int K, const CsrG &A, int mode, int64_t r0, int64_t r1, const T *x,
-                     const T *g, T *y, const int *done) {
-  csr_launch<T>(stm, K, mode == 0 ? 0 : 1, A, r0, r1, x, g, y, done);
-}
-
-template <class T>
-void launch_csr_rect(hipStream_t stm, int K, const CsrG &P, bool accumulate, const T *x, T *y, const int *done) {
-  csr_launch<T>(stm, K, accumulate ? 3 : 2, P, 0, P.nrows, x, nullptr, y, done);
-}
-
-template <class T>
-void launch_patch_gs(hipStream_t stm, int K, const CsrG &A, const PatchSweep &S, int64_t p0, int64_t np, const T *g,
-                     T *x, const int *done, int64_t zlim, bool backward) {
-  if (np <= 0) return;
+void launch_csr(hipStream_t stm, int K, int mode, const CsrJob<T> *jobs, int nj, const int *done) {
+  const auto P = two_jobs(jobs, nj, [](const CsrJob<T> &j) { return (j.A.nrows * j.A.G + kWave - 1) / kWave; });
+  const int64_t nb = P.nb0 + P.nb1;
+  if (!nb) return;
   VEMG_K_SWITCH(K, {
-    if (zlim >= 0)
-      hipLaunchKernelGGL((k_patch_gs<T, KK, true, false>), grid(np), dim3(kPatchThreads), 0, stm, A, S, p0, np, g, x,
-                         done, zlim);
-    else if (backward)
-      hipLaunchKernelGGL((k_patch_gs<T, KK, false, true>), grid(np), dim3(kPatchThreads), 0, stm, A, S, p0, np, g, x,
-                         done, int64_t(0));
-    else
-      hipLaunchKernelGGL((k_patch_gs<T, KK, false, false>), grid(np), dim3(kPatchThreads), 0, stm, A, S, p0, np, g, x,
-                         done, int64_t(0));
+    switch (mode) {
+      case 0: hipLaunchKernelGGL((k_csr<T, KK, 0>), grid(nb), dim3(kWave), 0, stm, P, done); break;
+      case 1: hipLaunchKernelGGL((k_csr<T, KK, 1>), grid(nb), dim3(kWave), 0, stm, P, done); break;
+      case 2: hipLaunchKernelGGL((k_csr<T, KK, 2>), grid(nb), dim3(kWave), 0, stm, P, done); break;
+      default: hipLaunchKernelGGL((k_csr<T, KK, 3>), grid(nb), dim3(kWave), 0, stm, P, done); break;
+    }
   })
 }
 
 template <class T>
-void launch_dense(hipStream_t stm, int K, const double *Cinv, int64_t m, const T *g, T *x, double *part,
-                  const int *done) {
-  if (m <= 0) return;
-  const int64_t nc = dense_chunks(m);
-  const dim3 gr((unsigned)((m + kWave - 1) / kWave), (unsigned)nc);
+void launch_patch_gs(hipStream_t stm, int K, PatchDir dir, const PatchJob<T> *jobs, int nj, const int *done) {
+  const auto P = two_jobs(jobs, nj, [](const PatchJob<T> &j) { return j.np; });
+  const int64_t nb = P.nb0 + P.nb1;
+  if (!nb) return;
   VEMG_K_SWITCH(K, {
-    hipLaunchKernelGGL((k_dense_part<T, KK>), gr, dim3(kBlock), 0, stm, Cinv, m, g, part, x, done);
-    if (nc > 1)
-      hipLaunchKernelGGL((k_dense_sum<T, KK>), grid((m * KK + kBlock - 1) / kBlock), dim3(kBlock), 0, stm, part, m,
-                         nc, x, done);
+    if (dir == kPatchFirst)
+      hipLaunchKernelGGL((k_patch_gs<T, KK, true, false>), grid(nb), dim3(kPatchThreads), 0, stm, P, done);
+    else if (dir == kPatchBackward)
+      hipLaunchKernelGGL((k_patch_gs<T, KK, false, true>), grid(nb), dim3(kPatchThreads), 0, stm, P, done);
+    else
+      hipLaunchKernelGGL((k_patch_gs<T, KK, false, false>), grid(nb), dim3(kPatchThreads), 0, stm, P, done);
+  })
+}
+
+template <class T>
+void launch_dense(hipStream_t stm, int K, const DenseJob<T> *jobs, int nj, const int *done) {
+  const auto P = two_jobs(jobs, nj, [](const DenseJob<T> &j) {
+    return (j.m + kWave - 1) / kWave * dense_chunks(j.m);
+  });
+  if (!(P.nb0 + P.nb1)) return;
+  VEMG_K_SWITCH(K, {
+    hipLaunchKernelGGL((k_dense_part<T, KK>), grid(P.nb0 + P.nb1), dim3(kBlock), 0, stm, P, done);
+    // a single chunk is complete already
+    const auto S = two_jobs(jobs, nj, [](const DenseJob<T> &j) {
+      return j.m > kDenseChunk ? (j.m * KK + kBlock - 1) / kBlock : int64_t(0);
+    });
+    if (S.nb0 + S.nb1)
+      hipLaunchKernelGGL((k_dense_sum<T, KK>), grid(S.nb0 + S.nb1), dim3(kBlock), 0, stm, S, done);
   })
 }
 
@@ -1522,22 +1633,21 @@ void launch_pcg_resume(hipStream_t stm, int, Scal *s, unsigned keep) {
 
 #define VEMG_INSTANTIATE(T)                                                                                          \
   template void launch_spmv<T>(hipStream_t, int, const Sell &, int, int64_t, int64_t, const T *, T *, double *,       \
-                               const int *, const int32_t *, T *, int64_t);                                          \
-  template void launch_spmv_rows<T>(hipStream_t, int, const Sell &, const int32_t *, int64_t, const T *, T *,         \
-                                    const int *);                                                                    \
+                               const int *, const int32_t *);                                                        \
   template void launch_gs<T>(hipStream_t, int, const Sell &, int64_t, int64_t, int64_t, int64_t, const T *, T *,       \
-                             const int *, bool, T *, int64_t);                                                       \
-  template void launch_gs_rows<T>(hipStream_t, int, const Sell &, const int32_t *, int64_t, const T *, T *,           \
-                                  const int *);                                                                      \
+                             const int *, bool);                                                                     \
+  template void launch_gs_merged<T>(hipStream_t, int, const Sell &, const MergedRows &, int64_t, int64_t, int64_t,     \
+                                    int64_t, int64_t, int64_t, const T *, T *, const int *, bool);                   \
+  template void launch_res_merged<T>(hipStream_t, int, const Sell &, const MergedRows &, const T *, T *, const int *,  \
+                                     const int32_t *);                                                               \
+  template void launch_prolong_merged<T>(hipStream_t, int, const MergedRows &, const T *, const T *, T *,             \
+                                         const int *);                                                               \
   template void launch_rect<T>(hipStream_t, int, const Sell &, bool, const T *, T *, const int *);                    \
   template void launch_prolong_sum<T>(hipStream_t, int, const Sell &, int64_t, const T *, const T *, const T *, T *,   \
                                       double *, const int *);                                                        \
-  template void launch_csr_spmv<T>(hipStream_t, int, const CsrG &, int, int64_t, int64_t, const T *, const T *, T *,   \
-                                   const int *);                                                                     \
-  template void launch_patch_gs<T>(hipStream_t, int, const CsrG &, const PatchSweep &, int64_t, int64_t, const T *,  \
-                                   T *, const int *, int64_t, bool);                                                 \
-  template void launch_csr_rect<T>(hipStream_t, int, const CsrG &, bool, const T *, T *, const int *);                \
-  template void launch_dense<T>(hipStream_t, int, const double *, int64_t, const T *, T *, double *, const int *);    \
+  template void launch_csr<T>(hipStream_t, int, int, const CsrJob<T> *, int, const int *);                            \
+  template void launch_patch_gs<T>(hipStream_t, int, PatchDir, const PatchJob<T> *, int, const int *);                \
+  template void launch_dense<T>(hipStream_t, int, const DenseJob<T> *, int, const int *);                             \
   template void launch_fill<T>(hipStream_t, T *, int64_t, T, const int *);                                           \
   template void launch_copy<T>(hipStream_t, const T *, T *, int64_t, const int *);                                   \
   template void launch_dot<T>(hipStream_t, int, const T *, const T *, int64_t, double *, const int *);                \

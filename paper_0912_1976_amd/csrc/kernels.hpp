@@ -36,6 +36,7 @@ struct Sell {
   const int64_t *sptr = nullptr;  // nslices + 1 entry offsets
   const int64_t *smid = nullptr;  // fine A: where slice s's U entries begin
   const int32_t *col = nullptr;
+  const int32_t *col2 = nullptr;  // rows over the difference of two vector rows (MergedRows::top): the second, or -1
   const double *val64 = nullptr;
   const float *val32 = nullptr;
   const double *d64 = nullptr, *i64 = nullptr;  // deficit d_i and 1 / a_ii
@@ -95,31 +96,57 @@ inline int64_t vec_blocks(int64_t n) { return (n + kBlock - 1) / kBlock; }
 // partial, partial[block * K + k] = sum over the block's rows of x_ik y_ik.
 // order (optional): the range's slices in visit order (offsets from slice
 // r0 / 64), so that the blocks of one XCD take one spatial region of every
-// colour.  Mode 1 only: with y2, the rows r >= y2_from are also stored to y2
-// (a copy of the result for a second consumer).
+// colour.
 template <class T>
 void launch_spmv(hipStream_t st, int K, const Sell &A, int mode, int64_t r0, int64_t r1, const T *x, T *y,
-                 double *partial, const int *done, const int32_t *order = nullptr, T *y2 = nullptr,
-                 int64_t y2_from = 0);
-// Mode 1 of launch_spmv (the same arithmetic row by row) on the listed rows
-// rows[0 .. nr) only.  A holds exactly those rows: its row i is the matrix's
-// row rows[i], with the same entries in the same order.
-template <class T>
-void launch_spmv_rows(hipStream_t st, int K, const Sell &A, const int32_t *rows, int64_t nr, const T *x, T *y,
-                      const int *done);
+                 double *partial, const int *done, const int32_t *order = nullptr);
 // One multicolour Gauss-Seidel step on the rows [a0,a1) and [b0,b1) (rows of
 // one colour): x_i += (g_i - (A x)_i) / a_ii.  first: the first sweep from
 // x = 0, in ascending colours, x_i = (g_i - (L x)_i) / a_ii; x needs no fill.
-// With x2, the updated rows r >= x2_from are also stored to x2.
 template <class T>
 void launch_gs(hipStream_t st, int K, const Sell &A, int64_t a0, int64_t a1, int64_t b0, int64_t b1, const T *g,
-               T *x, const int *done, bool first, T *x2 = nullptr, int64_t x2_from = 0);
-// The first sweep's step of launch_gs (the same arithmetic row by row) on the
-// listed rows rows[0 .. nr) only; the rows must share no entries.  A holds
-// exactly those rows, as for launch_spmv_rows.
+               T *x, const int *done, bool first);
+
+// VL + additive smoother in one pair of fine sweeps.  The preconditioner is
+// the sum of the SOR cycle (x) and the smoother's cycle on the non-top rows
+// (u, zero on the top), two cycles of one matrix and one right-hand side g:
+//   forward from zero: u = x except on the "dirty" rows D, the non-top rows
+//     with a top row or a dirty row among their neighbours of earlier colours;
+//   residual -U x: the smoother's differs only on the rows R with a top or a
+//     dirty row among their neighbours of later colours;
+//   backward: w = x + u (x on the top) obeys the sweep of the whole matrix
+//     with right-hand side 2 g on the non-top rows and g on the top; a top row
+//     needs its non-top neighbours' x = w - u, and the u of those
+//     neighbours, followed through the sweep, needs u on D, with old values
+//     on R: the same two sets.
+// So one sweep serves both cycles, and beside it only u on X = D + R is
+// carried, as nx more rows of the same vectors (row n + p for the p-th row of
+// X, those of D first and in colour order).
+struct MergedRows {
+  int64_t n = 0, n_top = 0, nd = 0, nr = 0, nx = 0;
+  const int32_t *drow = nullptr;  // D: matrix row of each
+  const int32_t *rpos = nullptr;  // R: position in X of each
+  const int32_t *xpos = nullptr;  // matrix row -> position in X, or -1
+  Sell fwd;   // D rows, couplings to non-top rows of earlier colours (columns of the extended vector)
+  Sell res;   // R rows, couplings to non-top rows of later colours
+  Sell bwd;   // D rows, couplings to all non-top rows; the deficit includes the top couplings
+  Sell top;   // top rows: column and, for non-top neighbours, their extended row (col2)
+  Sell prol;  // [E~ | P0]: columns < n_top of the surface vector, then those of A_bar's first coarse level
+};
+// One colour of the two cycles' forward (first) or backward sweep: the rows
+// [a0,a1) (top), [b0,b1) (non-top) and D's [d0,d1).
 template <class T>
-void launch_gs_rows(hipStream_t st, int K, const Sell &A, const int32_t *rows, int64_t nr, const T *g, T *x,
-                    const int *done);
+void launch_gs_merged(hipStream_t st, int K, const Sell &A, const MergedRows &M, int64_t a0, int64_t a1, int64_t b0,
+                      int64_t b1, int64_t d0, int64_t d1, const T *g, T *x, const int *done, bool first);
+// y = -U x on every row, and on R's extended rows.
+template <class T>
+void launch_res_merged(hipStream_t st, int K, const Sell &A, const MergedRows &M, const T *x, T *y, const int *done,
+                       const int32_t *order);
+// Between the sweeps: x = x + E~ ys on the top; below it w = (x + E~ ys) +
+// (u + P0 ya), with u + P0 ya stored on X's extended rows.
+template <class T>
+void launch_prolong_merged(hipStream_t st, int K, const MergedRows &M, const T *ys, const T *ya, T *x,
+                           const int *done);
 // y = E x (accumulate: y += E x) for a rectangular SELL matrix, rows [0, nrows).
 template <class T>
 void launch_rect(hipStream_t st, int K, const Sell &E, bool accumulate, const T *x, T *y, const int *done);
@@ -129,10 +156,18 @@ void launch_prolong_sum(hipStream_t st, int K, const Sell &E, int64_t n_top, con
                         T *z, double *partial, const int *done);
 
 // ---- coarse operators and transfers (CsrG) -------------------------------
-// mode 0: y = A x, 1: y = g - A x (square); rect: y = P x or y += P x.
+// The coarse operations take one or two jobs a launch: the surface and the
+// A_bar hierarchy are independent, their levels are too small to fill the
+// chip, and a launch costs as much for one as for both.
+// mode 0: y = A x, 1: y = g - A x (square); 2: y = P x, 3: y += P x
 template <class T>
-void launch_csr_spmv(hipStream_t st, int K, const CsrG &A, int mode, int64_t r0, int64_t r1, const T *x,
-                     const T *g, T *y, const int *done);
+struct CsrJob {
+  CsrG A;
+  const T *x = nullptr, *g = nullptr;
+  T *y = nullptr;
+};
+template <class T>
+void launch_csr(hipStream_t st, int K, int mode, const CsrJob<T> *jobs, int nj, const int *done);
 // Block multicolour (patch) order of a coarse level: its unknowns are stored
 // patch by patch (patch colour, patch, local colour), a patch holding at most
 // kPatchLdsRows unknowns.  Unknowns of patches of one colour are never
@@ -154,22 +189,34 @@ struct PatchSweep {
 };
 // One Gauss-Seidel sweep over the patches [p0, p0 + np) of one patch colour,
 // one block per patch (the patch colours launched in turn, ascending for a
-// forward sweep and descending for backward).  zlim >= 0: zero start
-// (forward from x = 0): of the other patches only the rows j < zlim (the
-// patch colours swept before) are read and the rest taken as zero, so x
-// needs no fill.
+// forward sweep and descending for backward).  first: the forward sweep from
+// x = 0: of the other patches only the rows j < zlim (the patch colours swept
+// before) are read and the rest taken as zero, so x needs no fill.
+enum PatchDir { kPatchFirst, kPatchForward, kPatchBackward };
 template <class T>
-void launch_patch_gs(hipStream_t st, int K, const CsrG &A, const PatchSweep &S, int64_t p0, int64_t np, const T *g,
-                     T *x, const int *done, int64_t zlim, bool backward);
+struct PatchJob {
+  CsrG A;
+  PatchSweep S;
+  int64_t p0 = 0, np = 0, zlim = 0;
+  const T *g = nullptr;
+  T *x = nullptr;
+};
 template <class T>
-void launch_csr_rect(hipStream_t st, int K, const CsrG &P, bool accumulate, const T *x, T *y, const int *done);
+void launch_patch_gs(hipStream_t st, int K, PatchDir dir, const PatchJob<T> *jobs, int nj, const int *done);
 // x = Cinv g (dense m x m FP64, symmetric, row-major), K columns; part:
 // dense_chunks(m) * m * K doubles of scratch for the column chunks' partial sums.
 constexpr int kDenseChunk = 512;
 inline int64_t dense_chunks(int64_t m) { return (m + kDenseChunk - 1) / kDenseChunk; }
 template <class T>
-void launch_dense(hipStream_t st, int K, const double *Cinv, int64_t m, const T *g, T *x, double *part,
-                  const int *done);
+struct DenseJob {
+  const double *C = nullptr;
+  int64_t m = 0;
+  const T *g = nullptr;
+  T *x = nullptr;
+  double *part = nullptr;
+};
+template <class T>
+void launch_dense(hipStream_t st, int K, const DenseJob<T> *jobs, int nj, const int *done);
 
 // ---- vectors ([n][K]) ----------------------------------------------------
 template <class T>
