@@ -339,7 +339,7 @@ struct DLevel {
 // the mixed-precision solve (the last iteration of every chunk)
 enum GraphKind { kGraphFP64 = 0, kGraphFP32 = 1, kGraphMixedPC = 2, kGraphFP32Reliable = 3 };
 
-// the captured graph of one PCG iteration
+// the captured graph of one or more PCG iterations
 struct IterGraph {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -384,7 +384,7 @@ struct vemg_solver_s {
   int w_clean = vemg::kMaxBatch;
   vemg::Scal *scal = nullptr;
   int64_t nnz_A = 0, nnz_E = 0;
-  std::map<int, vemg::IterGraph> graphs;  // key: kind * 16 + K
+  std::map<int, vemg::IterGraph> graphs;  // by kind, K and number of iterations
   // false for server lanes once the scheduler runs: a capture on one thread
   // must not coincide with device-wide synchronisation on another
   bool allow_capture = true;
@@ -887,28 +887,46 @@ void destroy_graphs(Handle *h) {
   h->graphs.clear();
 }
 
-// graph of one iteration for (kind, K), captured on first use when allowed
+// A chunk is poll_every iterations, after which the host reads the flags; the
+// FP32 form's last one ends in the reliable update.  Up to kGraphIterations
+// of them are one graph: in a chain of dependent kernels, those of a graph of
+// 40 nodes (one iteration) took 1.73 us each and of one of 400 nodes 1.55 us,
+// launched one by one 2.4 us and more, bound by the host.  A longer chunk
+// repeats the graph of one iteration.
+constexpr int kGraphIterations = 16;
+
 template <class T>
-const IterGraph *iteration_graph(Handle *h, int K, int kind) {
-  int key = kind * 16 + K;
+void chunk_iterations(Handle *h, int K, int kind, int count, bool last) {
+  for (int k = 0; k < count; ++k)
+    pcg_iteration<T>(h, K, kind == kGraphFP32 && last && k + 1 == count ? kGraphFP32Reliable : kind);
+}
+
+// graph of `count` iterations for (kind, K), captured on first use when allowed
+template <class T>
+const IterGraph *iteration_graph(Handle *h, int K, int kind, int count, bool last) {
+  const int key = ((last && kind == kGraphFP32 ? kGraphFP32Reliable : kind) * 16 + K) * 32 + count;
   auto it = h->graphs.find(key);
   if (it != h->graphs.end()) return &it->second;
   if (!h->allow_capture) return nullptr;
   IterGraph ig;
   HIPCHK(hipStreamBeginCapture(h->work, hipStreamCaptureModeThreadLocal));
-  pcg_iteration<T>(h, K, kind);
+  chunk_iterations<T>(h, K, kind, count, last);
   HIPCHK(hipStreamEndCapture(h->work, &ig.graph));
   HIPCHK(hipGraphInstantiate(&ig.exec, ig.graph, nullptr, nullptr, 0));
   return &h->graphs.emplace(key, ig).first->second;
 }
 
 template <class T>
-void run_iteration(Handle *h, int K, int kind) {
-  const IterGraph *ig = h->opt.use_graphs ? iteration_graph<T>(h, K, kind) : nullptr;
-  if (ig)
-    HIPCHK(hipGraphLaunch(ig->exec, h->work));
-  else
-    pcg_iteration<T>(h, K, kind);
+void run_chunk(Handle *h, int K, int kind) {
+  const int poll = std::max(1, h->opt.poll_every), unit = poll <= kGraphIterations ? poll : 1;
+  for (int done = 0; done < poll; done += unit) {
+    const bool last = done + unit == poll;
+    const IterGraph *ig = h->opt.use_graphs ? iteration_graph<T>(h, K, kind, unit, last) : nullptr;
+    if (ig)
+      HIPCHK(hipGraphLaunch(ig->exec, h->work));
+    else
+      chunk_iterations<T>(h, K, kind, unit, last);
+  }
 }
 
 Scal read_scal(Handle *h) {
@@ -921,9 +939,8 @@ Scal read_scal(Handle *h) {
 // iterate until every column is done
 template <class T>
 Scal iterate(Handle *h, int K, int kind) {
-  int poll = std::max(1, h->opt.poll_every);
   while (true) {
-    for (int k = 0; k < poll; ++k) run_iteration<T>(h, K, kind);
+    run_chunk<T>(h, K, kind);
     Scal hs = read_scal(h);
     if (hs.all_done) return hs;
   }
@@ -1047,18 +1064,6 @@ void solve_cg(Handle *h, int K, double rtol, int max_iter, ColResult *res) {
   launch_round(st, v.xs, v.xl, v.x, n * K);
 }
 
-// Iterates a mixed-precision solve until every column has stopped: chunks of
-// poll_every FP32 iterations, the last of each chunk with the reliable update.
-Scal iterate_reliable(Handle *h, int K) {
-  const int poll = std::max(1, h->opt.poll_every);
-  while (true) {
-    for (int k = 0; k + 1 < poll; ++k) run_iteration<float>(h, K, kGraphFP32);
-    run_iteration<float>(h, K, kGraphFP32Reliable);
-    Scal hs = read_scal(h);
-    if (hs.all_done) return hs;
-  }
-}
-
 // Mixed precision (VEMG_MIXED_IR): FP64 iterative refinement whose inner FP32
 // PCG keeps its Krylov space.  The inner PCG (SpMV, transfers, smoothers and
 // vectors in FP32 with per-row scaled operators, inner products accumulated
@@ -1105,7 +1110,7 @@ void solve_ir(Handle *h, int K, double rtol, int max_iter, ColResult *res) {
     precond<float>(h, K, v.r, v.z, h->part_rz, &np, nullptr);
     launch_pcg_set_rho(st, K, h->scal, h->part_rz, np);
     launch_copy<float>(st, v.z, v.p, n * K, nullptr);
-    Scal hs = iterate_reliable(h, K);
+    Scal hs = iterate<float>(h, K, kGraphFP32);
     // the last iteration folded every correction and left b - A (hi + lo) in v64.res
     launch_dot<double>(st, K, h->v64.res, h->v64.res, n, h->part_t, nullptr);
     launch_reduce(st, K, h->part_t, vec_blocks(n), h->dscal);
@@ -1979,7 +1984,7 @@ void server_loop(Server *sv) {
         for (auto &sl : L.slot) active += sl.req != nullptr;
         if (!active) continue;
         int kind = L.h->opt.precision != VEMG_FP64 ? kGraphMixedPC : kGraphFP64;
-        for (int it = 0; it < L.h->opt.poll_every; ++it) run_iteration<double>(L.h, kMaxBatch, kind);
+        run_chunk<double>(L.h, kMaxBatch, kind);
         HIPCHK(hipMemcpyAsync(L.scal_host, L.h->scal, sizeof(Scal), hipMemcpyDeviceToHost, L.h->work));
         HIPCHK(hipEventRecord(L.scal_ready, L.h->work));
         L.launched = true;
@@ -2346,10 +2351,11 @@ vemg_status vemg_server_add_mesh(vemg_server sv, int64_t n_nodes, const double *
     vemg::upload(h);
     if (h->ar.bytes != L->footprint)
       throw vemg::DeviceError(VEMG_ERR_DEVICE, "device allocations differ from the counted footprint");
-    // capture both iteration graphs now, while no other thread uses the device
+    // capture both precisions' graphs now, while no other thread uses the device
     if (h->opt.use_graphs) {
-      vemg::iteration_graph<double>(h, vemg::kMaxBatch, vemg::kGraphFP64);
-      vemg::iteration_graph<double>(h, vemg::kMaxBatch, vemg::kGraphMixedPC);
+      const int poll = h->opt.poll_every, unit = poll <= vemg::kGraphIterations ? poll : 1;
+      vemg::iteration_graph<double>(h, vemg::kMaxBatch, vemg::kGraphFP64, unit, true);
+      vemg::iteration_graph<double>(h, vemg::kMaxBatch, vemg::kGraphMixedPC, unit, true);
       HIPCHK(hipStreamSynchronize(h->work));
     }
     L->resident = true;
