@@ -753,28 +753,35 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch_gs(Jobs<PatchJob<T>> P,
 // consecutive outputs i and read 64 consecutive entries of row j of C
 // together, and g_j is the same for the whole wavefront; C is streamed once,
 // with several rows in flight per lane.  The columns j are cut into chunks of
-// kDenseChunk (dense_chunks of them); a block of four wavefronts takes 64
-// outputs over one chunk, each wavefront a quarter of it, sums the quarters
-// in LDS in wavefront order and writes the chunk's partial sums, which
+// kDenseChunk (dense_chunks of them); a block of kDenseWaves wavefronts takes
+// 64 outputs over one chunk, each wavefront an equal part of it, sums the
+// parts in LDS in wavefront order and writes the chunk's partial sums, which
 // k_dense_sum adds in chunk order (a single chunk is written directly).  No
 // summation order depends on K.
+// Bandwidth bounds it from about 5000 unknowns (494 MB in 98 us at 6218 and
+// 4820), below it the chain of loads of a wavefront, so 16 of them share a
+// chunk: against four, mixed batches of eight went from 17.6 to 15.4 ms (2172
+// and 2144 unknowns) and from 108.4 to 104.0 ms (2993 and 2296), with 6218 and
+// 4820 unknowns unchanged.  Chunks of 128 with four wavefronts: 16.4 and 106.3.
+constexpr int kDenseWaves = 16;
 template <class T, int K>
-__global__ __launch_bounds__(kBlock) void k_dense_part(Jobs<DenseJob<T>> P, const int *__restrict__ done) {
+__global__ __launch_bounds__(kWave *kDenseWaves) void k_dense_part(Jobs<DenseJob<T>> P,
+                                                                   const int *__restrict__ done) {
   if (done && *done) return;
   const bool second = (int64_t)blockIdx.x >= P.nb0;
   const DenseJob<T> &J = second ? P.j[1] : P.j[0];
   const double *__restrict__ C = J.C;
   const int64_t m = J.m, blk = blockIdx.x - (second ? P.nb0 : 0), tiles = (m + kWave - 1) / kWave;
-  __shared__ double red[kSlicesPerBlock][K][kWave];
+  __shared__ double red[kDenseWaves][K][kWave];
   __shared__ Row<T, K> gt[kDenseChunk];  // the chunk's g, read by every lane of a wavefront at once
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t i = blk % tiles * kWave + lane;
   const int64_t c = blk / tiles;
   const int64_t jc = c * kDenseChunk;
   const int nj = (int)(m - jc < kDenseChunk ? m - jc : kDenseChunk);
-  for (int j = threadIdx.x; j < nj; j += kBlock) gt[j] = ld<T, K>(J.g, jc + j);
+  for (int j = threadIdx.x; j < nj; j += kWave * kDenseWaves) gt[j] = ld<T, K>(J.g, jc + j);
   __syncthreads();
-  constexpr int Q = kDenseChunk / kSlicesPerBlock;
+  constexpr int Q = kDenseChunk / kDenseWaves;
   const int j0 = w * Q;
   const int j1 = j0 + Q < nj ? j0 + Q : nj;
   double t[K];
@@ -793,23 +800,15 @@ __global__ __launch_bounds__(kBlock) void k_dense_part(Jobs<DenseJob<T>> P, cons
 #pragma unroll
   for (int k = 0; k < K; ++k) red[w][k][lane] = t[k];
   __syncthreads();
-  if (w != 0 || i >= m) return;
-  Row<double, K> s;
+  // wavefront k sums column k (K <= kDenseWaves)
+  if (w >= K || i >= m) return;
+  double v = red[0][w][lane];
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-    double v = red[0][k][lane];
-#pragma unroll
-    for (int q = 1; q < kSlicesPerBlock; ++q) v += red[q][k][lane];
-    s.v[k] = v;
-  }
-  if (m <= kDenseChunk) {
-    Row<T, K> out;
-#pragma unroll
-    for (int k = 0; k < K; ++k) out.v[k] = (T)s.v[k];
-    st<T, K>(J.x, i, out);
-  } else {
-    st<double, K>(J.part + c * m * K, i, s);
-  }
+  for (int q = 1; q < kDenseWaves; ++q) v += red[q][w][lane];
+  if (m <= kDenseChunk)
+    J.x[i * K + w] = (T)v;
+  else
+    J.part[(c * m + i) * K + w] = v;
 }
 
 template <class T, int K>
@@ -821,6 +820,7 @@ __global__ __launch_bounds__(kBlock) void k_dense_sum(Jobs<DenseJob<T>> P, const
   const int64_t m = J.m, nc = (m + kDenseChunk - 1) / kDenseChunk;
   if (t >= m * K) return;
   double s = J.part[t];
+#pragma unroll 8
   for (int64_t c = 1; c < nc; ++c) s += J.part[c * m * K + t];
   J.x[t] = (T)s;
 }
@@ -1530,10 +1530,10 @@ void launch_dense(hipStream_t stm, int K, const DenseJob<T> *jobs, int nj, const
   });
   if (!(P.nb0 + P.nb1)) return;
   VEMG_K_SWITCH(K, {
-    hipLaunchKernelGGL((k_dense_part<T, KK>), grid(P.nb0 + P.nb1), dim3(kBlock), 0, stm, P, done);
+    hipLaunchKernelGGL((k_dense_part<T, KK>), grid(P.nb0 + P.nb1), dim3(kWave * kDenseWaves), 0, stm, P, done);
     // a single chunk is complete already
     const auto S = two_jobs(jobs, nj, [](const DenseJob<T> &j) {
-      return j.m > kDenseChunk ? (j.m * KK + kBlock - 1) / kBlock : int64_t(0);
+      return dense_chunks(j.m) > 1 ? (j.m * KK + kBlock - 1) / kBlock : int64_t(0);
     });
     if (S.nb0 + S.nb1)
       hipLaunchKernelGGL((k_dense_sum<T, KK>), grid(S.nb0 + S.nb1), dim3(kBlock), 0, stm, S, done);
