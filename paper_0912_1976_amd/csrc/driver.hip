@@ -231,7 +231,8 @@ Sell pack_rows(Arena &ar, hipStream_t st, int64_t n, bool pairs, F &&row, G &&pa
 
 // CSR (host) -> CsrG (device).  Square matrices keep only off-diagonals
 // (FP64 values with d64 = a_ii; FP32 values a_ij / a_ii with s32 = a_ii).
-// G = smallest power of two >= half the mean row length, clamped to [4, 64].
+// G = smallest power of two >= a sixth of the mean row length, clamped to
+// [2, 16]: a group of lanes keeps four to eight entries in flight.
 // With colkey (rectangular operators gathering from the fine level: the
 // spatial rank of column c is (*colkey)[c + coloff]) the rows are stored in
 // the order of their smallest column rank and orow maps them back, so that
@@ -241,7 +242,7 @@ Sell pack_rows(Arena &ar, hipStream_t st, int64_t n, bool pairs, F &&row, G &&pa
 CsrG pack_csrg(Arena &ar, hipStream_t st, const Csr &A, bool square, int64_t *stored = nullptr,
                const std::vector<int64_t> *colkey = nullptr, int64_t coloff = 0,
                const std::vector<int32_t> *colmap = nullptr) {
-  std::vector<int32_t> ptr(A.nrows + 1, 0), col;
+  std::vector<int32_t> ptr(A.nrows + 1, 0), upper(square ? A.nrows : 0), col;
   std::vector<double> val, d(square ? A.nrows : 0, 0.0);
   std::vector<float> val32;
   col.reserve(A.nnz());
@@ -262,15 +263,17 @@ CsrG pack_csrg(Arena &ar, hipStream_t st, const Csr &A, bool square, int64_t *st
     const int64_t r = rows[i];
     for (int64_t k = A.ptr[r]; k < A.ptr[r + 1]; ++k) {
       if (square && A.idx[k] == r) continue;
+      if (square && A.idx[k] < r) upper[i] = (int32_t)col.size() + 1;
       col.push_back(colmap ? (*colmap)[A.idx[k]] : A.idx[k]);
       val.push_back(A.val[k]);
       val32.push_back(square ? (float)(A.val[k] / d[r]) : (float)A.val[k]);
     }
     ptr[i + 1] = (int32_t)col.size();
+    if (square && upper[i] < ptr[i]) upper[i] = ptr[i];  // no earlier column
   }
   double mean = A.nrows ? (double)col.size() / (double)A.nrows : 0.0;
-  int G = 4;
-  while (G < 64 && G < mean / 2.0) G *= 2;
+  int G = 2;
+  while (G < 16 && G < mean / 6.0) G *= 2;
   if (stored) *stored = (int64_t)col.size();
   CsrG M;
   M.nrows = A.nrows;
@@ -288,6 +291,7 @@ CsrG pack_csrg(Arena &ar, hipStream_t st, const Csr &A, bool square, int64_t *st
     for (int64_t r = 0; r < A.nrows; ++r) s32[r] = (float)d[r];
     M.d64 = ar.upload(d, st);
     M.s32 = ar.upload(s32, st);
+    M.upper = ar.upload(upper, st);
   }
   return M;
 }
@@ -306,7 +310,7 @@ struct DLevel {
   Sell As;                      // fine A_bar level: rows [row0, row0 + n) of the fine SELL matrix
   CsrG Ac;                      // coarse levels: standard form, G lanes per row
   PatchSweep ps;                // coarse levels: the patches of the sweeps
-  std::vector<int64_t> pc_start, pc_row;  // patch colour c: stored patches [pc_start[c], pc_start[c+1]), first row
+  std::vector<int64_t> pc_start;  // patch colour c: stored patches [pc_start[c], pc_start[c+1])
   bool fine = false;
   int64_t n = 0, row0 = 0;
   int64_t n_top = 0;            // fine levels: rows of the top block in the fine matrix
@@ -400,35 +404,52 @@ Work<T> &work_of(Handle *h) {
   if constexpr (std::is_same<T, double>::value) return h->v64; else return h->v32;
 }
 
-// The patch arrays of a coarse level for its sweeps: row ranges of the stored
-// patches and, per patch, F = (D_p + L_p)^{-1} of its diagonal block in stored
-// order (forward substitution on the host in FP64) packed by rows, F^T packed
-// by rows for the backward sweep, and both times D_p rounded to FP32 for the
-// row-scaled FP32 operator.
+// The patch arrays of a coarse level for its sweeps (PatchSweep): row ranges
+// of the stored patches, every row's entry ranges (positions in the level's
+// CsrG, which drops the diagonals) and, per patch, F = (D_p + L_p)^{-1} of its
+// diagonal block in stored order (forward substitution on the host in FP64)
+// and F^T for the backward sweep, both also times D_p rounded to FP32 for the
+// row-scaled FP32 operator, in tiles.
 void pack_patches(Arena &ar, hipStream_t st, const Level &L, DLevel &dl) {
   static_assert(kPatchRows == kPatchLdsRows, "the patch size of the order and of the sweep kernel differ");
+  constexpr int64_t W = kPatchTile, S = kPatchLdsRows + 1;
   const int64_t n = L.n(), np = (int64_t)L.patch_list.size();
-  if (n > INT32_MAX) throw DeviceError(hipErrorInvalidValue, "coarse level above 2^31 rows");
-  std::vector<int32_t> prow(L.patch_row.begin(), L.patch_row.end());
-  std::vector<int64_t> toff(np + 1, 0);
+  if (n > INT32_MAX) throw DeviceError(VEMG_ERR_DEVICE, "coarse level above 2^31 rows");
+  std::vector<PatchDesc> desc(np);
+  std::vector<PatchRow> rows(np * S, PatchRow{0, 0, 0, 0});
+  int64_t tiles = 0;
   for (int64_t p = 0; p < np; ++p) {
-    const int64_t m = L.patch_row[p + 1] - L.patch_row[p];
-    if (m > kPatchLdsRows) throw DeviceError(hipErrorInvalidValue, "a patch exceeds the sweep kernel's rows");
-    toff[p + 1] = toff[p] + m * (m + 1) / 2;
+    const int64_t m = L.patch_row[p + 1] - L.patch_row[p], nt = (m + W - 1) / W;
+    if (m > kPatchLdsRows) throw DeviceError(VEMG_ERR_DEVICE, "a patch exceeds the sweep kernel's rows");
+    desc[p] = PatchDesc{(int32_t)L.patch_row[p], (int32_t)m, tiles * W * W};
+    tiles += nt * (nt + 1) / 2;
   }
-  std::vector<double> tf(toff[np]), tb(toff[np]);
-  std::vector<float> tf32(toff[np]), tb32(toff[np]);
+  std::vector<double> tf(tiles * W * W, 0.0), tb(tiles * W * W, 0.0);
+  std::vector<float> tf32(tiles * W * W, 0.0f), tb32(tiles * W * W, 0.0f);
   if (!ar.count_only) {
     std::vector<double> M, F;
+    int64_t diag = 0;  // diagonal entries passed so far: not stored in the CsrG
     for (int64_t p = 0; p < np; ++p) {
-      const int64_t ps = L.patch_row[p], m = L.patch_row[p + 1] - ps;
+      const int64_t ps = L.patch_row[p], m = L.patch_row[p + 1] - ps, pe = ps + m, nt = (m + W - 1) / W;
       M.assign(m * m, 0.0);
       F.assign(m * m, 0.0);
-      for (int64_t r = 0; r < m; ++r)
-        for (int64_t k = L.A.ptr[ps + r]; k < L.A.ptr[ps + r + 1]; ++k) {
+      for (int64_t r = 0; r < m; ++r) {
+        const int64_t i = ps + r;
+        int32_t at[4];  // entries with columns before the patch, before the row, up to the row, in the patch
+        const int64_t lim[4] = {ps, i, i + 1, pe};
+        for (int q = 0; q < 4; ++q)
+          at[q] = (int32_t)(std::lower_bound(L.A.idx.begin() + L.A.ptr[i], L.A.idx.begin() + L.A.ptr[i + 1],
+                                             (int32_t)lim[q]) - L.A.idx.begin());
+        const int32_t b = (int32_t)(L.A.ptr[i] - diag), e = (int32_t)(L.A.ptr[i + 1] - diag);
+        const int32_t own = (int32_t)(at[0] - diag), late = (int32_t)(at[1] - diag), has = at[2] - at[1];
+        rows[p * S + r] = PatchRow{b, own, late, (int32_t)(at[3] - diag - has)};
+        rows[p * S + r + 1].b = e - has;
+        diag += has;
+        for (int64_t k = L.A.ptr[i]; k < L.A.ptr[i + 1]; ++k) {
           const int64_t c = L.A.idx[k] - ps;
           if (c >= 0 && c <= r) M[r * m + c] = L.A.val[k];
         }
+      }
       // columns of F = (D + L)^{-1}: forward substitution on unit vectors
       for (int64_t c = 0; c < m; ++c) {
         F[c * m + c] = 1.0 / M[c * m + c];
@@ -438,29 +459,30 @@ void pack_patches(Arena &ar, hipStream_t st, const Level &L, DLevel &dl) {
           F[r * m + c] = -t / M[r * m + r];
         }
       }
-      double *fwd = tf.data() + toff[p], *bwd = tb.data() + toff[p];
-      float *fwd32 = tf32.data() + toff[p], *bwd32 = tb32.data() + toff[p];
-      for (int64_t r = 0, o = 0; r < m; ++r)
-        for (int64_t c = 0; c <= r; ++c, ++o) {
-          fwd[o] = F[r * m + c];
-          fwd32[o] = (float)(F[r * m + c] * M[c * m + c]);
+      // entry (r, c) of a tile row that starts at tile t0 with tile column j0
+      auto at = [&](int64_t t0, int64_t j0, int64_t r, int64_t c) {
+        return desc[p].toff + (t0 + c / W - j0) * W * W + c % W / 4 * 64 + c % 4 * W + r % W;
+      };
+      for (int64_t r = 0; r < m; ++r) {
+        const int64_t I = r / W, f0 = I * (I + 1) / 2, b0 = I * nt - I * (I - 1) / 2;
+        for (int64_t c = 0; c <= r; ++c) {
+          tf[at(f0, 0, r, c)] = F[r * m + c];
+          tf32[at(f0, 0, r, c)] = (float)(F[r * m + c] * M[c * m + c]);
         }
-      for (int64_t r = 0, o = 0; r < m; ++r)
-        for (int64_t c = r; c < m; ++c, ++o) {
-          bwd[o] = F[c * m + r];
-          bwd32[o] = (float)(F[c * m + r] * M[c * m + c]);
+        for (int64_t c = r; c < m; ++c) {
+          tb[at(b0, I, r, c)] = F[c * m + r];
+          tb32[at(b0, I, r, c)] = (float)(F[c * m + r] * M[c * m + c]);
         }
+      }
     }
   }
-  dl.ps.prow = ar.upload(prow, st);
-  dl.ps.toff = ar.upload(toff, st);
+  dl.ps.desc = ar.upload(desc, st);
+  dl.ps.rows = ar.upload(rows, st);
   dl.ps.tf64 = ar.upload(tf, st);
   dl.ps.tb64 = ar.upload(tb, st);
   dl.ps.tf32 = ar.upload(tf32, st);
   dl.ps.tb32 = ar.upload(tb32, st);
   dl.pc_start = L.pc_start;
-  dl.pc_row.resize(L.pc_start.size());
-  for (size_t c = 0; c < L.pc_start.size(); ++c) dl.pc_row[c] = L.patch_row[L.pc_start[c]];
 }
 
 enum LevelsOf { kLevelsS = 0, kLevelsAbar = 1, kLevelsSA = 2 };
@@ -569,7 +591,6 @@ void coarse_cycles(hipStream_t st, int K, Cycle<T> a, Cycle<T> b, const int *don
       j.S = L[i]->ps;
       j.p0 = L[i]->pc_start[c];
       j.np = L[i]->pc_start[c + 1] - j.p0;
-      j.zlim = L[i]->pc_row[c];
       j.g = L[i]->template g<T>();
       j.x = L[i]->template x<T>();
     }
@@ -584,7 +605,6 @@ void coarse_cycles(hipStream_t st, int K, Cycle<T> a, Cycle<T> b, const int *don
     DLevel &C = i == 0 && ra >= rb ? na.level() : nb.level();
     res[i].A = L[i]->Ac;
     res[i].x = L[i]->template x<T>();
-    res[i].g = L[i]->template g<T>();
     res[i].y = L[i]->template r<T>();
     down[i].A = L[i]->Pt;
     down[i].x = L[i]->template r<T>();
@@ -593,10 +613,10 @@ void coarse_cycles(hipStream_t st, int K, Cycle<T> a, Cycle<T> b, const int *don
     up[i].x = C.template x<T>();
     up[i].y = L[i]->template x<T>();
   }
-  launch_csr<T>(st, K, 1, res, nl, done);
-  launch_csr<T>(st, K, 2, down, nl, done);
+  launch_csr<T>(st, K, kCsrUpper, res, nl, done);
+  launch_csr<T>(st, K, kCsrMult, down, nl, done);
   coarse_cycles<T>(st, K, na, nb, done);
-  launch_csr<T>(st, K, 3, up, nl, done);
+  launch_csr<T>(st, K, kCsrAdd, up, nl, done);
   for (int k = 0; k < nc; ++k) sweep(k, false);
 }
 
@@ -639,7 +659,7 @@ void fine_cycle(hipStream_t st, int K, std::vector<DLevel> &H, Cycle<T> other, c
   int nd = 0;
   if (other_down) down[nd++] = *other_down;
   if (L.coarsest) {
-    if (nd) launch_csr<T>(st, K, 2, down, nd, done);
+    if (nd) launch_csr<T>(st, K, kCsrMult, down, nd, done);
     coarse_cycles<T>(st, K, other, cycle<T>(H, 0), done);
     return;
   }
@@ -648,7 +668,7 @@ void fine_cycle(hipStream_t st, int K, std::vector<DLevel> &H, Cycle<T> other, c
   down[nd].A = L.Pt;
   down[nd].x = L.r<T>() + o;
   down[nd++].y = H[1].g<T>();
-  launch_csr<T>(st, K, 2, down, nd, done);
+  launch_csr<T>(st, K, kCsrMult, down, nd, done);
   coarse_cycles<T>(st, K, other, cycle<T>(H, 1), done);
   launch_rect<T>(st, K, L.Ps, true, H[1].x<T>(), L.x<T>() + o, done);
   fine_backward<T>(st, K, L, done);
@@ -704,7 +724,7 @@ void sor_cycle(Handle *h, int K, const T *rr, T *zz, const int *done, bool dense
   if (P.n_top > 0) {
     launch_spmv<T>(st, K, h->A, 1, 0, P.n, zz, v.res, nullptr, done, h->order_all);
     const CsrJob<T> J = surface_down<T>(h, v.res);
-    launch_csr<T>(st, K, 2, &J, 1, done);
+    launch_csr<T>(st, K, kCsrMult, &J, 1, done);
     S = cycle<T>(h->S, 0);
   }
   T *saved = h->Ab[0].g<T>();
@@ -743,7 +763,7 @@ void merged_cycle(Handle *h, int K, const T *rr, T *zz, const int *done) {
   down[nd].A = h->merged_Pt;
   down[nd].x = v.res;
   down[nd++].y = h->Ab[1].g<T>();
-  launch_csr<T>(st, K, 2, down, nd, done);
+  launch_csr<T>(st, K, kCsrMult, down, nd, done);
   coarse_cycles<T>(st, K, P.n_top > 0 ? cycle<T>(h->S, 0) : Cycle<T>(), cycle<T>(h->Ab, 1), done);
   const T *ya = h->Ab[1].x<T>();
   launch_prolong_merged<T>(st, K, h->M, P.n_top > 0 ? h->S[0].x<T>() : ya, ya, zz, done);
@@ -1433,7 +1453,7 @@ void apply_op(Handle *h, int op, const T *in, T *out) {
       break;
     }
     case VEMG_OP_ET:
-      launch_csr<T>(st, 1, 2, &et, 1, nullptr);
+      launch_csr<T>(st, 1, kCsrMult, &et, 1, nullptr);
       break;
     case VEMG_OP_E:
       launch_rect<T>(st, 1, h->E, false, in, out, nullptr);
@@ -1497,7 +1517,7 @@ void time_once(Handle *h, int op, int K) {
   }
   if (op == VEMG_OP_ET) {
     const CsrJob<T> J = surface_down<T>(h, v.r);
-    launch_csr<T>(st, K, 2, &J, 1, nullptr);
+    launch_csr<T>(st, K, kCsrMult, &J, 1, nullptr);
     return;
   }
   if (op == VEMG_OP_E) {
@@ -1513,7 +1533,7 @@ void time_once(Handle *h, int op, int K) {
   if (op == VEMG_OP_GS_COARSE) {
     DLevel &L = h->Ab[1];
     for (size_t c = 0; c + 1 < L.pc_start.size(); ++c) {
-      const PatchJob<T> J{L.Ac, L.ps, L.pc_start[c], L.pc_start[c + 1] - L.pc_start[c], 0, L.g<T>(), L.x<T>()};
+      const PatchJob<T> J{L.Ac, L.ps, L.pc_start[c], L.pc_start[c + 1] - L.pc_start[c], L.g<T>(), L.x<T>()};
       launch_patch_gs<T>(st, K, kPatchForward, &J, 1, nullptr);
     }
     return;

@@ -542,101 +542,157 @@ struct Jobs {
   int64_t nb0, nb1;
 };
 
-// Off-diagonal sum of one row for K columns by its group of G lanes (a power
-// of two; the result is valid in every lane of the group).
-template <class T, int K>
-__device__ __forceinline__ void group_row(const CsrG &A, int G, int64_t r, int gl, const T *__restrict__ x,
-                                          T (&acc)[K]) {
-  const int32_t b = A.ptr[r], e = A.ptr[r + 1];
-  const T *__restrict__ vals = csr_vals<T>(A);
-#pragma unroll
-  for (int k = 0; k < K; ++k) acc[k] = T(0);
-#pragma unroll 2
-  for (int j = b + gl; j < e; j += G) {
-    const T v = vals[j];
-    const Row<T, K> xc = ld<T, K>(x, A.col[j]);
-#pragma unroll
-    for (int k = 0; k < K; ++k) acc[k] += v * xc.v[k];
-  }
-  for (int o = G / 2; o > 0; o >>= 1) {
-#pragma unroll
-    for (int k = 0; k < K; ++k) acc[k] += __shfl_xor(acc[k], o, kWave);
+// v + the value of lane (own lane xor D), D a power of two, in a few vector
+// instructions (a shuffle through LDS costs a pass of the LDS per word: at
+// K = 8 the reductions by shuffles took most of the restriction's time)
+template <int D>
+__device__ __forceinline__ int lane_xor(int v) {
+  static_assert(D == 1 || D == 2 || D == 4 || D == 8, "lane_xor");
+  if constexpr (D == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);   // quad_perm [1,0,3,2]
+  if constexpr (D == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);   // quad_perm [2,3,0,1]
+  if constexpr (D == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, true);  // row_ror 8
+  if constexpr (D == 4) {
+    const int t = __builtin_amdgcn_update_dpp(0, v, 0x104, 0xf, 0x5, false);  // row_shl 4 in the even banks
+    return __builtin_amdgcn_update_dpp(t, v, 0x114, 0xf, 0xa, false);         // row_shr 4 in the odd ones
   }
 }
-
-// Row r of a CsrG operation, by its group of G lanes (lane 0 of the group
-// writes).  The kernels below renumber their blocks like the fine ones, so
-// that each XCD works on a contiguous range of rows and the vector values
-// those rows gather stay in that XCD's L2.  MODE 0: y = A x, 1: y = g - A x (square); 2: y = P x, 3: y += P x.
-template <class T, int K, int MODE>
-__device__ __forceinline__ void csr_row_op(const CsrG &A, int64_t r, int gl, const T *x, const T *g, T *y) {
-  // the row's own operands are loaded first, so that their latency overlaps
-  // the row-pointer -> entries -> gathered values chain of group_row
-  Row<T, K> gr, xr, yr;
-  T dr = T(0);
-  // output row of a rectangular operator (its stored rows may be permuted)
-  int64_t ro = r;
-  if constexpr (MODE == 2 || MODE == 3) {
-    if (A.orow) ro = A.orow[r];
-  }
-  if (MODE == 1) gr = ld<T, K>(g, r);
-  if (MODE <= 1) xr = ld<T, K>(x, r);
-  if (MODE == 3) yr = ld<T, K>(y, ro);
-  if (MODE <= 1) {
-    if constexpr (std::is_same<T, double>::value)
-      dr = A.d64[r];
-    else
-      dr = A.s32[r];
-  }
-  T acc[K];
-  group_row<T, K>(A, A.G, r, gl, x, acc);  // off-diagonal part only
-  if (gl != 0) return;
-  Row<T, K> out;
-  if (MODE <= 1) {
-    if constexpr (std::is_same<T, double>::value) {
+template <class T, int N>
+struct Words {
+  int w[N];
+};
+template <int D, class T>
+__device__ __forceinline__ T add_xor(T v) {
+  constexpr int N = sizeof(T) / 4;
+  const auto a = __builtin_bit_cast(Words<T, N>, v);
+  Words<T, N> p, q = a;
 #pragma unroll
-      for (int k = 0; k < K; ++k) out.v[k] = acc[k] + dr * xr.v[k];
+  for (int i = 0; i < N; ++i) {
+    if constexpr (D == 16) {
+      const auto r = __builtin_amdgcn_permlane16_swap((unsigned)a.w[i], (unsigned)a.w[i], false, false);
+      q.w[i] = r[0];
+      p.w[i] = r[1];
+    } else if constexpr (D == 32) {
+      const auto r = __builtin_amdgcn_permlane32_swap((unsigned)a.w[i], (unsigned)a.w[i], false, false);
+      q.w[i] = r[0];
+      p.w[i] = r[1];
     } else {
-#pragma unroll
-      for (int k = 0; k < K; ++k) out.v[k] = dr * (acc[k] + xr.v[k]);
+      p.w[i] = lane_xor<D>(a.w[i]);
     }
-    if (MODE == 1) {
-#pragma unroll
-      for (int k = 0; k < K; ++k) out.v[k] = gr.v[k] - out.v[k];
-    }
-  } else if (MODE == 2) {
-#pragma unroll
-    for (int k = 0; k < K; ++k) out.v[k] = acc[k];
-  } else {
-    out = yr;
-#pragma unroll
-    for (int k = 0; k < K; ++k) out.v[k] += acc[k];
   }
-  st<T, K>(y, ro, out);
+  return __builtin_bit_cast(T, q) + __builtin_bit_cast(T, p);
 }
 
-template <class T, int K, int MODE>
-__global__ __launch_bounds__(kWave) void k_csr(Jobs<CsrJob<T>> P, const int *__restrict__ done) {
+// Sums over the G groups of LPR lanes each (lane = group * LPR + q): the
+// same tree over the groups whatever LPR is.
+template <class T, int C, int G, int LPR>
+__device__ __forceinline__ void groups_sum(T (&acc)[C]) {
+  if constexpr (G > 1) {
+#pragma unroll
+    for (int k = 0; k < C; ++k) acc[k] = add_xor<G / 2 * LPR>(acc[k]);
+    groups_sum<T, C, G / 2, LPR>(acc);
+  }
+}
+
+// Entries of a row taken by one group of lanes: those t = ge, ge + G, ... of
+// the n entries from b, skipping the gap [gap, gap + skip) of their storage;
+// acc += v x for the C columns of lane q.  U entries are in flight at once:
+// the loads past the row's end repeat its last entry and count as zero.
+template <class T, int K, int C, int G>
+__device__ __forceinline__ void group_entries(const int32_t *__restrict__ col, const T *__restrict__ val, int32_t b,
+                                              int32_t n, int32_t gap, int32_t skip, int ge, int q,
+                                              const T *__restrict__ x, T (&acc)[C]) {
+  constexpr int U = sizeof(T) * C > 8 ? 4 : 8;
+  for (int32_t t0 = ge; t0 < n; t0 += G * U) {
+    int32_t c[U];
+    T v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int32_t t = t0 + G * u < n ? t0 + G * u : n - 1;
+      const int32_t j = b + t + (t >= gap ? skip : 0);
+      c[u] = col[j];
+      v[u] = val[j];
+    }
+    Row<T, C> xc[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) xc[u] = ldp<T, K, C>(x, c[u], q);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool in = t0 + G * u < n;
+#pragma unroll
+      for (int k = 0; k < C; ++k) acc[k] += v[u] * (in ? xc[u].v[k] : T(0));
+    }
+  }
+}
+
+// A CsrG operation on row r by lane l of its G * row_lanes<T, K>() lanes.
+// Bound by the chain row pointer -> entries -> gathered values at K = 1 and by
+// the gathers at K = 8, where a lane of 16 bytes each makes a wavefront's load
+// touch a quarter of the lines that a lane of a whole row does.
+template <class T, int K, int G, CsrMode MODE>
+__device__ __forceinline__ void csr_row(const CsrG &A, int64_t r, int l, const T *__restrict__ x, T *y) {
+  constexpr int LPR = row_lanes<T, K>(), C = K / LPR;
+  const int ge = l / LPR, q = l % LPR;
+  const int32_t b = MODE == kCsrUpper ? A.upper[r] : A.ptr[r], e = A.ptr[r + 1];
+  // output row of a rectangular operator (its stored rows may be permuted)
+  const int64_t ro = MODE != kCsrUpper && A.orow ? (int64_t)A.orow[r] : r;
+  T s = T(1);
+  if constexpr (MODE == kCsrUpper && !std::is_same<T, double>::value) s = A.s32[r];
+  Row<T, C> out{};
+  if constexpr (MODE == kCsrAdd) out = ldp<T, K, C>(y, ro, q);
+  T acc[C];
+#pragma unroll
+  for (int k = 0; k < C; ++k) acc[k] = T(0);
+  group_entries<T, K, C, G>(A.col, csr_vals<T>(A), b, e - b, e - b, 0, ge, q, x, acc);
+  groups_sum<T, C, G, LPR>(acc);
+  if (ge != 0) return;
+#pragma unroll
+  for (int k = 0; k < C; ++k) {
+    if constexpr (MODE == kCsrUpper)
+      out.v[k] = -s * acc[k];
+    else
+      out.v[k] += acc[k];
+  }
+  stp<T, K, C>(y, ro, q, out);
+}
+
+template <class T, int K, int G, CsrMode MODE>
+__device__ __forceinline__ void csr_block(const CsrJob<T> &J, int64_t blk) {
+  constexpr int L = G * row_lanes<T, K>();
+  const int64_t r = (blk * kBlock + threadIdx.x) / L;
+  if (r < J.A.nrows) csr_row<T, K, G, MODE>(J.A, r, threadIdx.x % L, J.x, J.y);
+}
+
+// The blocks of each job are renumbered like the fine kernels', so that each
+// XCD works on a contiguous range of rows and the vector values those rows
+// gather stay in that XCD's L2.
+template <class T, int K, CsrMode MODE>
+__global__ __launch_bounds__(kBlock) void k_csr(Jobs<CsrJob<T>> P, const int *__restrict__ done) {
   if (done && *done) return;
   const bool second = (int64_t)blockIdx.x >= P.nb0;
   const CsrJob<T> &J = second ? P.j[1] : P.j[0];
   const int64_t blk = second ? xcd_block(blockIdx.x - P.nb0, P.nb1) : xcd_block(blockIdx.x, P.nb0);
-  const int G = J.A.G;
-  const int64_t r = (blk * kWave + threadIdx.x) / G;
-  if (r >= J.A.nrows) return;
-  csr_row_op<T, K, MODE>(J.A, r, threadIdx.x & (G - 1), J.x, J.g, J.y);
+  switch (J.A.G) {
+    case 2: csr_block<T, K, 2, MODE>(J, blk); break;
+    case 4: csr_block<T, K, 4, MODE>(J, blk); break;
+    case 8: csr_block<T, K, 8, MODE>(J, blk); break;
+    default: csr_block<T, K, 16, MODE>(J, blk); break;
+  }
 }
 
-// Patch sweep: one block per patch, kPatchGroup lanes per unknown (a coarse
-// row's few dozen couplings take a handful of loads per lane).  First every
-// unknown of the patch sums the couplings whose values the sweep takes as
-// they stand -- other patches (with a zero start only the patch colours swept
-// before) and, without a zero start, its own patch's later unknowns (earlier
-// ones backward) -- into h = g - sum (FP32: g / a_ii - sum over row-scaled
-// values); then every unknown takes its row of the patch's triangular factor
-// times h.  One block barrier; no sequential stages inside the patch.
-constexpr int kPatchGroup = 8;
-constexpr int kPatchThreads = kPatchGroup * kPatchLdsRows;
+// Patch sweep: one block of sixteen wavefronts per patch.  First every unknown
+// of the patch sums the couplings whose values the sweep takes as they stand
+// (PatchRow) -- other patches (from zero only those swept before) and, with a
+// start, its own patch's later unknowns (earlier ones backward) -- into
+// h = g - sum (FP32: g / a_ii - sum over row-scaled values), eight groups of
+// lanes an unknown.  Then the patch's factor times h, on the matrix cores:
+// two wavefronts per 16 rows, each taking every second tile of the tile row,
+// whose operands come straight from memory (each is used once) before the
+// sums are there.  No sequential stages inside the patch.
+// A launch holds about as many patches as the chip has CUs, so the chain of
+// one block sets its time: two dependent loads ahead of the gathers (the
+// descriptors by block and row, then entries, operands and factor together).
+constexpr int kPatchGroups = 8;
+constexpr int kPatchThreads = 1024;
 
 template <class T>
 __device__ __forceinline__ const T *patch_factor(const PatchSweep &S, bool bwd);
@@ -648,103 +704,105 @@ template <>
 __device__ __forceinline__ const float *patch_factor<float>(const PatchSweep &S, bool bwd) {
   return bwd ? S.tb32 : S.tf32;
 }
-
-template <class T, int K>
-__device__ __forceinline__ void group_sum(T (&acc)[K]) {
-#pragma unroll
-  for (int o = kPatchGroup / 2; o > 0; o >>= 1) {
-#pragma unroll
-    for (int k = 0; k < K; ++k) acc[k] += __shfl_xor(acc[k], o, kPatchGroup);
-  }
+typedef double Tile64 __attribute__((ext_vector_type(4)));
+typedef float Tile32 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ Tile64 tile_mac(double a, double b, Tile64 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ Tile32 tile_mac(float a, float b, Tile32 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+// row of result register r in lane l
+template <class T>
+__device__ __forceinline__ int tile_row(int l, int r) {
+  return sizeof(T) == 8 ? l / 16 + 4 * r : 4 * (l / 16) + r;
 }
 
-template <class T, int K, bool ZS, bool BWD>
-__global__ __launch_bounds__(kPatchThreads) void k_patch_gs(Jobs<PatchJob<T>> P, const int *__restrict__ done) {
-  constexpr int G = kPatchGroup;
+// whether the factor is loaded ahead of the sums (its registers beside theirs)
+template <class T, int K>
+constexpr bool patch_ahead() {
+  return row_lanes<T, K>() == 1;
+}
+template <class T, int K, PatchDir DIR>
+__global__ __launch_bounds__(kPatchThreads, (patch_ahead<T, K>() && sizeof(T) == 8 ? 4 : 8)) void k_patch_gs(
+    Jobs<PatchJob<T>> P, const int *__restrict__ done) {
+  constexpr int LPR = row_lanes<T, K>(), C = K / LPR, G = kPatchGroups, W = kPatchTile;
+  constexpr int RP = kPatchThreads / (G * LPR);  // unknowns summed at once
+  constexpr bool BWD = DIR == kPatchBackward;
+  using Tile = typename std::conditional<sizeof(T) == 8, Tile64, Tile32>::type;
   __shared__ Row<T, K> hs[kPatchLdsRows];
-  if (done && *done) return;
+  __shared__ T half[kPatchLdsRows][K];
   const bool second = (int64_t)blockIdx.x >= P.nb0;
   const PatchJob<T> &J = second ? P.j[1] : P.j[0];
   const CsrG &A = J.A;
-  const PatchSweep &S = J.S;
+  const int64_t p = J.p0 + (second ? xcd_block(blockIdx.x - P.nb0, P.nb1) : xcd_block(blockIdx.x, P.nb0));
+  const PatchDesc D = J.S.desc[p];
+  if (done && *done) return;
   const T *__restrict__ g = J.g;
   T *__restrict__ x = J.x;
-  const int64_t zlim = J.zlim;
-  const int64_t p = J.p0 + (second ? xcd_block(blockIdx.x - P.nb0, P.nb1) : xcd_block(blockIdx.x, P.nb0));
-  const int32_t ps = S.prow[p], pe = S.prow[p + 1];
-  const int q = threadIdx.x / G, gl = threadIdx.x % G;
-  const int32_t i = ps + q;
-  const bool own = i < pe;
-  const T *__restrict__ vals = csr_vals<T>(A);
-  // the row's part of the patch factor does not depend on the sums: load it
-  // first, beside the row's own operands (kPatchLdsRows / G entries a lane at most)
-  constexpr int FR = kPatchLdsRows / G;
-  const int m = pe - ps;
-  T fr[FR];
-  {
-    const T *__restrict__ f = patch_factor<T>(S, BWD) + S.toff[p];
-    // forward row q: columns 0..q packed from q (q + 1) / 2; backward: columns q..m-1 from q m - q (q - 1) / 2
-    const T *__restrict__ row = BWD ? f + q * m - q * (q - 1) / 2 - q : f + q * (q + 1) / 2;
+  const int l = threadIdx.x % (G * LPR), ge = l / LPR, q = l % LPR;
+  const int m = D.m, nt = (m + W - 1) / W;
+  // this wavefront's tiles: tile row I, tiles J0, J0 + 2, ...
+  const int lane = threadIdx.x & 63, I = threadIdx.x >> 7, odd = (threadIdx.x >> 6) & 1;
+  const int J0 = (BWD ? I : 0) + odd, J1 = I >= nt ? 0 : BWD ? nt : I + 1;
+  const T *__restrict__ f = patch_factor<T>(J.S, BWD) + D.toff + lane +
+                            (int64_t)((BWD ? I * nt - I * (I - 1) / 2 - I : I * (I + 1) / 2) + J0) * (W * W);
+  constexpr int NT = kPatchLdsRows / W / 2;
+  T a[NT][4];
+  auto load_factor = [&]() {
 #pragma unroll
-    for (int t = 0; t < FR; ++t) {
-      const int j = gl + t * G;
-      fr[t] = (own && (BWD ? (j >= q && j < m) : j <= q)) ? row[j] : T(0);
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) a[t][s] = J0 + 2 * t < J1 ? f[t * 2 * W * W + s * 64] : T(0);
+  };
+  if constexpr (patch_ahead<T, K>()) load_factor();
+#pragma unroll 1
+  for (int q0 = 0; q0 < kPatchLdsRows; q0 += RP) {
+    const int row = q0 + threadIdx.x / (G * LPR);
+    Row<T, C> h{};
+    if (row < m) {
+      const PatchRow R = J.S.rows[p * (kPatchLdsRows + 1) + row];
+      const int32_t end = J.S.rows[p * (kPatchLdsRows + 1) + row + 1].b;
+      const int64_t i = D.row0 + row;
+      const Row<T, C> gr = ldp<T, K, C>(g, i, q);
+      T inv = T(1);
+      if constexpr (sizeof(T) == 4) inv = 1.0f / A.s32[i];
+      T acc[C];
+#pragma unroll
+      for (int k = 0; k < C; ++k) acc[k] = T(0);
+      // what is taken: earlier patches; those and later ones beside the own patch's old values
+      const int32_t cut = DIR == kPatchBackward ? R.late : R.own, from = DIR == kPatchBackward ? R.next : R.late;
+      const int32_t n = DIR == kPatchFirst ? R.own - R.b : cut - R.b + end - from;
+      group_entries<T, K, C, G>(A.col, csr_vals<T>(A), R.b, n, cut - R.b, from - cut, ge, q, x, acc);
+      groups_sum<T, C, G, LPR>(acc);
+#pragma unroll
+      for (int k = 0; k < C; ++k) h.v[k] = gr.v[k] * inv - acc[k];
+    }
+    if (ge == 0) *reinterpret_cast<Row<T, C> *>(&hs[row].v[q * C]) = h;  // zero beyond the patch
+  }
+  if constexpr (!patch_ahead<T, K>()) load_factor();
+  __syncthreads();
+  const int col = lane % W;
+  Tile acc = {0, 0, 0, 0};
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    if (J0 + 2 * t >= J1) continue;  // uniform over the wavefront
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const T b = col < K ? hs[(J0 + 2 * t) * W + 4 * s + lane / W].v[col < K ? col : 0] : T(0);
+      acc = tile_mac(a[t][s], b, acc);
     }
   }
-  if (own) {
-    const Row<T, K> gr = ld<T, K>(g, i);
-    T dr = T(1);
-    if constexpr (!std::is_same<T, double>::value) dr = A.s32[i];
-    const int32_t b = A.ptr[i], e = A.ptr[i + 1];
-    T acc[K];
+  if (odd && col < K) {
 #pragma unroll
-    for (int k = 0; k < K; ++k) acc[k] = T(0);
-#pragma unroll 4
-    for (int32_t j = b + gl; j < e; j += G) {
-      const int32_t c = A.col[j];
-      const T v = vals[j];
-      const bool inside = c >= ps && c < pe;
-      const bool take = inside ? (!ZS && (BWD ? c < i : c > i)) : (!ZS || c < zlim);
-      if (take) {
-        const Row<T, K> xc = ld<T, K>(x, c);
-#pragma unroll
-        for (int k = 0; k < K; ++k) acc[k] += v * xc.v[k];
-      }
-    }
-    group_sum<T, K>(acc);
-    if (gl == 0) {
-      Row<T, K> h;
-      if constexpr (std::is_same<T, double>::value) {
-#pragma unroll
-        for (int k = 0; k < K; ++k) h.v[k] = gr.v[k] - acc[k];
-      } else {
-        const float inv_s = 1.0f / dr;
-#pragma unroll
-        for (int k = 0; k < K; ++k) h.v[k] = gr.v[k] * inv_s - acc[k];
-      }
-      hs[q] = h;
-    }
+    for (int r = 0; r < 4; ++r) half[I * W + tile_row<T>(lane, r)][col] = acc[r];
   }
   __syncthreads();
-  if (!own) return;
-  T acc[K];
+  if (odd || col >= K) return;
 #pragma unroll
-  for (int k = 0; k < K; ++k) acc[k] = T(0);
-#pragma unroll
-  for (int t = 0; t < FR; ++t) {
-    const int j = gl + t * G;
-    if (BWD ? (j >= q && j < m) : j <= q) {
-      const Row<T, K> hj = hs[j];
-#pragma unroll
-      for (int k = 0; k < K; ++k) acc[k] += fr[t] * hj.v[k];
-    }
-  }
-  group_sum<T, K>(acc);
-  if (gl == 0) {
-    Row<T, K> out;
-#pragma unroll
-    for (int k = 0; k < K; ++k) out.v[k] = acc[k];
-    st<T, K>(x, i, out);
+  for (int r = 0; r < 4; ++r) {
+    const int row = I * W + tile_row<T>(lane, r);
+    if (row < m) x[(int64_t)(D.row0 + row) * K + col] = acc[r] + half[row][col];
   }
 }
 
@@ -1494,17 +1552,19 @@ static Jobs<J> two_jobs(const J *jobs, int nj, F &&blocks) {
 }
 
 template <class T>
-void launch_csr(hipStream_t stm, int K, int mode, const CsrJob<T> *jobs, int nj, const int *done) {
-  const auto P = two_jobs(jobs, nj, [](const CsrJob<T> &j) { return (j.A.nrows * j.A.G + kWave - 1) / kWave; });
-  const int64_t nb = P.nb0 + P.nb1;
-  if (!nb) return;
+void launch_csr(hipStream_t stm, int K, CsrMode mode, const CsrJob<T> *jobs, int nj, const int *done) {
   VEMG_K_SWITCH(K, {
-    switch (mode) {
-      case 0: hipLaunchKernelGGL((k_csr<T, KK, 0>), grid(nb), dim3(kWave), 0, stm, P, done); break;
-      case 1: hipLaunchKernelGGL((k_csr<T, KK, 1>), grid(nb), dim3(kWave), 0, stm, P, done); break;
-      case 2: hipLaunchKernelGGL((k_csr<T, KK, 2>), grid(nb), dim3(kWave), 0, stm, P, done); break;
-      default: hipLaunchKernelGGL((k_csr<T, KK, 3>), grid(nb), dim3(kWave), 0, stm, P, done); break;
-    }
+    const auto P = two_jobs(jobs, nj, [](const CsrJob<T> &j) {
+      return (j.A.nrows * j.A.G * row_lanes<T, KK>() + kBlock - 1) / kBlock;
+    });
+    const int64_t nb = P.nb0 + P.nb1;
+    if (!nb) return;
+    if (mode == kCsrUpper)
+      hipLaunchKernelGGL((k_csr<T, KK, kCsrUpper>), grid(nb), dim3(kBlock), 0, stm, P, done);
+    else if (mode == kCsrMult)
+      hipLaunchKernelGGL((k_csr<T, KK, kCsrMult>), grid(nb), dim3(kBlock), 0, stm, P, done);
+    else
+      hipLaunchKernelGGL((k_csr<T, KK, kCsrAdd>), grid(nb), dim3(kBlock), 0, stm, P, done);
   })
 }
 
@@ -1515,11 +1575,11 @@ void launch_patch_gs(hipStream_t stm, int K, PatchDir dir, const PatchJob<T> *jo
   if (!nb) return;
   VEMG_K_SWITCH(K, {
     if (dir == kPatchFirst)
-      hipLaunchKernelGGL((k_patch_gs<T, KK, true, false>), grid(nb), dim3(kPatchThreads), 0, stm, P, done);
+      hipLaunchKernelGGL((k_patch_gs<T, KK, kPatchFirst>), grid(nb), dim3(kPatchThreads), 0, stm, P, done);
     else if (dir == kPatchBackward)
-      hipLaunchKernelGGL((k_patch_gs<T, KK, false, true>), grid(nb), dim3(kPatchThreads), 0, stm, P, done);
+      hipLaunchKernelGGL((k_patch_gs<T, KK, kPatchBackward>), grid(nb), dim3(kPatchThreads), 0, stm, P, done);
     else
-      hipLaunchKernelGGL((k_patch_gs<T, KK, false, false>), grid(nb), dim3(kPatchThreads), 0, stm, P, done);
+      hipLaunchKernelGGL((k_patch_gs<T, KK, kPatchForward>), grid(nb), dim3(kPatchThreads), 0, stm, P, done);
   })
 }
 
@@ -1645,7 +1705,7 @@ void launch_pcg_resume(hipStream_t stm, int, Scal *s, unsigned keep) {
   template void launch_rect<T>(hipStream_t, int, const Sell &, bool, const T *, T *, const int *);                    \
   template void launch_prolong_sum<T>(hipStream_t, int, const Sell &, int64_t, const T *, const T *, const T *, T *,   \
                                       double *, const int *);                                                        \
-  template void launch_csr<T>(hipStream_t, int, int, const CsrJob<T> *, int, const int *);                            \
+  template void launch_csr<T>(hipStream_t, int, CsrMode, const CsrJob<T> *, int, const int *);                            \
   template void launch_patch_gs<T>(hipStream_t, int, PatchDir, const PatchJob<T> *, int, const int *);                \
   template void launch_dense<T>(hipStream_t, int, const DenseJob<T> *, int, const int *);                             \
   template void launch_fill<T>(hipStream_t, T *, int64_t, T, const int *);                                           \

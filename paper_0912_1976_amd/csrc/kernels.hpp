@@ -44,14 +44,16 @@ struct Sell {
   int64_t nrows = 0;
 };
 
-// CSR matrix processed by groups of G lanes per row (G = 4..64, a power of
-// two chosen from the mean row length): the group reads consecutive entries
-// of its row (coalesced) and reduces with cross-lane shuffles, so long rows
-// (coarse multigrid operators, restrictions) cost a few memory round trips
-// instead of one per entry.  Square operators store off-diagonals only:
-// FP64 values with d64 = a_ii; FP32 values a_ij / a_ii with s32 = a_ii.
+// CSR matrix (coarse multigrid operators, restrictions, coarse prolongators):
+// a row's entries are dealt in turn to G groups of lanes (a power of two
+// chosen from the mean row length), each group holding the row's K columns 16
+// bytes a lane, and the groups' sums are added across lanes.  Square
+// operators store off-diagonals only: FP64 values with d64 = a_ii; FP32
+// values a_ij / a_ii with s32 = a_ii; row i's entries with columns > i (later
+// in the sweep order) begin at upper[i].
 struct CsrG {
   const int32_t *ptr = nullptr;  // nrows + 1
+  const int32_t *upper = nullptr;
   const int32_t *col = nullptr;
   const double *val64 = nullptr;
   const float *val32 = nullptr;
@@ -159,15 +161,17 @@ void launch_prolong_sum(hipStream_t st, int K, const Sell &E, int64_t n_top, con
 // The coarse operations take one or two jobs a launch: the surface and the
 // A_bar hierarchy are independent, their levels are too small to fill the
 // chip, and a launch costs as much for one as for both.
-// mode 0: y = A x, 1: y = g - A x (square); 2: y = P x, 3: y += P x
+// kCsrUpper: y = -U x, the residual g - A x right after a forward sweep from
+// zero that gave x (square); kCsrMult: y = P x; kCsrAdd: y += P x
+enum CsrMode { kCsrUpper, kCsrMult, kCsrAdd };
 template <class T>
 struct CsrJob {
   CsrG A;
-  const T *x = nullptr, *g = nullptr;
+  const T *x = nullptr;
   T *y = nullptr;
 };
 template <class T>
-void launch_csr(hipStream_t st, int K, int mode, const CsrJob<T> *jobs, int nj, const int *done);
+void launch_csr(hipStream_t st, int K, CsrMode mode, const CsrJob<T> *jobs, int nj, const int *done);
 // Block multicolour (patch) order of a coarse level: its unknowns are stored
 // patch by patch (patch colour, patch, local colour), a patch holding at most
 // kPatchLdsRows unknowns.  Unknowns of patches of one colour are never
@@ -178,26 +182,42 @@ void launch_csr(hipStream_t st, int K, int mode, const CsrJob<T> *jobs, int nj, 
 // lower part of the patch's block in stored order -- the sequential SOR
 // sweep in that order.  Backward: (D_p + U_p)^{-1} = ((D_p + L_p)^{-1})^T.
 constexpr int kPatchLdsRows = 128;
+constexpr int kPatchTile = 16;
+// stored patch: its first row, its number of rows m, and where its factor
+// tiles begin
+struct PatchDesc {
+  int32_t row0, m;
+  int64_t toff;
+};
+// A row's entries (columns ascending, so in sweep order) by what a sweep of
+// its patch takes: [b, own) earlier patches, [own, late) its own patch before
+// the row, [late, next) its own patch after it, and from next on later patches
+struct PatchRow {
+  int32_t b, own, late, next;
+};
 struct PatchSweep {
-  const int32_t *prow = nullptr;  // stored patch i: rows [prow[i], prow[i+1])
-  const int64_t *toff = nullptr;  // its factors start at toff[i] (m (m + 1) / 2 entries each)
-  // FP64: F = (D_p + L_p)^{-1} packed by rows (row r: columns 0..r) and F^T
-  // packed by rows (row r: columns r..m-1); FP32 (row-scaled operator):
-  // F D_p and F^T D_p, rounded
+  const PatchDesc *desc = nullptr;
+  const PatchRow *rows = nullptr;  // [patch][kPatchLdsRows + 1]; row m holds the end of row m - 1's entries
+  // FP64: F = (D_p + L_p)^{-1}; FP32 (row-scaled operator): F D_p, rounded;
+  // tb: the same of F^T.  Tiles of 16 x 16, zero beyond m, tile row I (of
+  // t = ceil(m / 16)) holding its tiles J <= I (tb: J >= I) in order from tile
+  // I (I + 1) / 2 (tb: I t - I (I - 1) / 2); a tile stores for s = 0..3 and
+  // lane l entry (l % 16, 4 s + l / 16), the operand order of the 16x16x4
+  // matrix instructions.
   const double *tf64 = nullptr, *tb64 = nullptr;
   const float *tf32 = nullptr, *tb32 = nullptr;
 };
 // One Gauss-Seidel sweep over the patches [p0, p0 + np) of one patch colour,
 // one block per patch (the patch colours launched in turn, ascending for a
-// forward sweep and descending for backward).  first: the forward sweep from
-// x = 0: of the other patches only the rows j < zlim (the patch colours swept
-// before) are read and the rest taken as zero, so x needs no fill.
+// forward sweep and descending for backward).  kPatchFirst: the forward sweep
+// from x = 0, which reads of the other patches only those swept before, so x
+// needs no fill.
 enum PatchDir { kPatchFirst, kPatchForward, kPatchBackward };
 template <class T>
 struct PatchJob {
   CsrG A;
   PatchSweep S;
-  int64_t p0 = 0, np = 0, zlim = 0;
+  int64_t p0 = 0, np = 0;
   const T *g = nullptr;
   T *x = nullptr;
 };
