@@ -310,7 +310,8 @@ struct DLevel {
   Sell As;                      // fine A_bar level: rows [row0, row0 + n) of the fine SELL matrix
   CsrG Ac;                      // coarse levels: standard form, G lanes per row
   PatchSweep ps;                // coarse levels: the patches of the sweeps
-  std::vector<int64_t> pc_start;  // patch colour c: stored patches [pc_start[c], pc_start[c+1])
+  int64_t np = 0;               // number of patches
+  PatchSync *sync = nullptr;
   bool fine = false;
   int64_t n = 0, row0 = 0;
   int64_t n_top = 0;            // fine levels: rows of the top block in the fine matrix
@@ -420,8 +421,12 @@ void pack_patches(Arena &ar, hipStream_t st, const Level &L, DLevel &dl) {
   int64_t tiles = 0;
   for (int64_t p = 0; p < np; ++p) {
     const int64_t m = L.patch_row[p + 1] - L.patch_row[p], nt = (m + W - 1) / W;
+    if (n * kMaxBatch * 8 > INT32_MAX) throw DeviceError(VEMG_ERR_DEVICE, "coarse level above the sweep kernel's 32-bit offsets");
     if (m > kPatchLdsRows) throw DeviceError(VEMG_ERR_DEVICE, "a patch exceeds the sweep kernel's rows");
-    desc[p] = PatchDesc{(int32_t)L.patch_row[p], (int32_t)m, tiles * W * W};
+    int c = 0;
+    while (L.pc_start[c + 1] <= p) ++c;
+    desc[p] = PatchDesc{(int32_t)L.patch_row[p], (int32_t)m, tiles * W * W, (int32_t)L.pc_start[c],
+                        (int32_t)(np - L.pc_start[c + 1])};
     tiles += nt * (nt + 1) / 2;
   }
   std::vector<double> tf(tiles * W * W, 0.0), tb(tiles * W * W, 0.0);
@@ -482,7 +487,9 @@ void pack_patches(Arena &ar, hipStream_t st, const Level &L, DLevel &dl) {
   dl.ps.tb64 = ar.upload(tb, st);
   dl.ps.tf32 = ar.upload(tf32, st);
   dl.ps.tb32 = ar.upload(tb32, st);
-  dl.pc_start = L.pc_start;
+  dl.np = np;
+  dl.sync = ar.alloc<PatchSync>(1);
+  if (!ar.count_only) launch_fill<float>(st, (float *)dl.sync, sizeof(PatchSync) / sizeof(float), 0.0f, nullptr);
 }
 
 enum LevelsOf { kLevelsS = 0, kLevelsAbar = 1, kLevelsSA = 2 };
@@ -576,27 +583,10 @@ void coarse_cycles(hipStream_t st, int K, Cycle<T> a, Cycle<T> b, const int *don
     launch_dense<T>(st, K, J, nl, done);
     return;
   }
-  int nc = 0;
-  for (int i = 0; i < nl; ++i) nc = std::max(nc, (int)L[i]->pc_start.size() - 1);
-  // the k-th launch of a sweep: each level's k-th patch colour in its order
-  auto sweep = [&](int k, bool first) {
-    PatchJob<T> J[2];
-    int nj = 0;
-    for (int i = 0; i < nl; ++i) {
-      const int own = (int)L[i]->pc_start.size() - 1;
-      if (k >= own) continue;
-      const int c = first ? k : own - 1 - k;
-      PatchJob<T> &j = J[nj++];
-      j.A = L[i]->Ac;
-      j.S = L[i]->ps;
-      j.p0 = L[i]->pc_start[c];
-      j.np = L[i]->pc_start[c + 1] - j.p0;
-      j.g = L[i]->template g<T>();
-      j.x = L[i]->template x<T>();
-    }
-    launch_patch_gs<T>(st, K, first ? kPatchFirst : kPatchBackward, J, nj, done);
-  };
-  for (int k = 0; k < nc; ++k) sweep(k, true);
+  PatchJob<T> gs[2];
+  for (int i = 0; i < nl; ++i)
+    gs[i] = PatchJob<T>{L[i]->Ac, L[i]->ps, L[i]->np, L[i]->template g<T>(), L[i]->template x<T>(), L[i]->sync};
+  launch_patch_gs<T>(st, K, kPatchFirst, gs, nl, done);
   Cycle<T> na = a, nb = b;
   if (ra >= rb) ++na.l;
   if (rb >= ra) ++nb.l;
@@ -617,7 +607,7 @@ void coarse_cycles(hipStream_t st, int K, Cycle<T> a, Cycle<T> b, const int *don
   launch_csr<T>(st, K, kCsrMult, down, nl, done);
   coarse_cycles<T>(st, K, na, nb, done);
   launch_csr<T>(st, K, kCsrAdd, up, nl, done);
-  for (int k = 0; k < nc; ++k) sweep(k, false);
+  launch_patch_gs<T>(st, K, kPatchBackward, gs, nl, done);
 }
 
 template <class T>
@@ -1532,10 +1522,8 @@ void time_once(Handle *h, int op, int K) {
   }
   if (op == VEMG_OP_GS_COARSE) {
     DLevel &L = h->Ab[1];
-    for (size_t c = 0; c + 1 < L.pc_start.size(); ++c) {
-      const PatchJob<T> J{L.Ac, L.ps, L.pc_start[c], L.pc_start[c + 1] - L.pc_start[c], L.g<T>(), L.x<T>()};
-      launch_patch_gs<T>(st, K, kPatchForward, &J, 1, nullptr);
-    }
+    const PatchJob<T> J{L.Ac, L.ps, L.np, L.g<T>(), L.x<T>(), L.sync};
+    launch_patch_gs<T>(st, K, kPatchForward, &J, 1, nullptr);
     return;
   }
   for (int c = 0; c < fine_colours(P); ++c) {
@@ -1558,7 +1546,7 @@ int do_time(Handle *h, int op, int K, int reps, double *avg_ms, int *launches) {
   batch_layout(h, K);
   int nc = fine_colours(P);
   if (op == VEMG_OP_GS_COARSE) {
-    nc = (int)h->Ab[1].pc_start.size() - 1;
+    nc = 1;
     DLevel &L = h->Ab[1];
     if (h->opt.precision == VEMG_MIXED_IR) {
       launch_fill<float>(st, L.g32, L.n * K, 1.0f, nullptr);

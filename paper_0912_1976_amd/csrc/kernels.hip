@@ -556,6 +556,9 @@ __device__ __forceinline__ int lane_xor(int v) {
     return __builtin_amdgcn_update_dpp(t, v, 0x114, 0xf, 0xa, false);         // row_shr 4 in the odd ones
   }
 }
+// cache policy of loads and stores at agent scope on gfx950 (sc1)
+constexpr int kAgentScope = 16;
+
 template <class T, int N>
 struct Words {
   int w[N];
@@ -597,30 +600,68 @@ __device__ __forceinline__ void groups_sum(T (&acc)[C]) {
 // the n entries from b, skipping the gap [gap, gap + skip) of their storage;
 // acc += v x for the C columns of lane q.  U entries are in flight at once:
 // the loads past the row's end repeat its last entry and count as zero.
-template <class T, int K, int C, int G>
-__device__ __forceinline__ void group_entries(const int32_t *__restrict__ col, const T *__restrict__ val, int32_t b,
-                                              int32_t n, int32_t gap, int32_t skip, int ge, int q,
-                                              const T *__restrict__ x, T (&acc)[C]) {
-  constexpr int U = sizeof(T) * C > 8 ? 4 : 8;
-  for (int32_t t0 = ge; t0 < n; t0 += G * U) {
+struct EntryRange {
+  int32_t b, n, gap, skip;
+};
+template <class T, int C>
+constexpr int entries_ahead() {
+  return sizeof(T) * C > 8 ? 4 : 8;
+}
+template <class T, int U, int G>
+__device__ __forceinline__ void load_entries(const int32_t *__restrict__ col, const T *__restrict__ val,
+                                             const EntryRange &R, int32_t t0, int32_t (&c)[U], T (&v)[U]) {
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int32_t t = t0 + G * u < R.n ? t0 + G * u : R.n - 1;
+    const int32_t j = R.b + t + (t >= R.gap ? R.skip : 0);
+    c[u] = col[j];
+    v[u] = val[j];
+  }
+}
+// columns [q C, q C + C) of row r of a vector that other blocks of the launch
+// write (BYPASS: past the caches that are not shared between XCDs) or not
+template <class T, int C>
+struct Gather {
+  __amdgpu_buffer_rsrc_t buf;
+  const T *p;
+};
+template <class T, int K, int C, bool BYPASS>
+__device__ __forceinline__ Row<T, C> gather(const Gather<T, C> &x, int32_t r, int q) {
+  if constexpr (!BYPASS) {
+    return ldp<T, K, C>(x.p, r, q);
+  } else {
+    const int off = (r * K + q * C) * (int)sizeof(T);
+    if constexpr (sizeof(Row<T, C>) == 4)
+      return __builtin_bit_cast(Row<T, C>, __builtin_amdgcn_raw_buffer_load_b32(x.buf, off, 0, kAgentScope));
+    else if constexpr (sizeof(Row<T, C>) == 8)
+      return __builtin_bit_cast(Row<T, C>, __builtin_amdgcn_raw_buffer_load_b64(x.buf, off, 0, kAgentScope));
+    else
+      return __builtin_bit_cast(Row<T, C>, __builtin_amdgcn_raw_buffer_load_b128(x.buf, off, 0, kAgentScope));
+  }
+}
+template <class T, int K, int C, int U, int G, bool BYPASS>
+__device__ __forceinline__ void add_entries(const EntryRange &R, int32_t t0, int q, const Gather<T, C> &x,
+                                            const int32_t (&c)[U], const T (&v)[U], T (&acc)[C]) {
+  Row<T, C> xc[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) xc[u] = gather<T, K, C, BYPASS>(x, c[u], q);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const bool in = t0 + G * u < R.n;
+#pragma unroll
+    for (int k = 0; k < C; ++k) acc[k] += v[u] * (in ? xc[u].v[k] : T(0));
+  }
+}
+template <class T, int K, int C, int G, bool BYPASS = false>
+__device__ __forceinline__ void group_entries(const int32_t *__restrict__ col, const T *__restrict__ val,
+                                              const EntryRange &R, int32_t t0, int q, const Gather<T, C> &x,
+                                              T (&acc)[C]) {
+  constexpr int U = entries_ahead<T, C>();
+  for (; t0 < R.n; t0 += G * U) {
     int32_t c[U];
     T v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int32_t t = t0 + G * u < n ? t0 + G * u : n - 1;
-      const int32_t j = b + t + (t >= gap ? skip : 0);
-      c[u] = col[j];
-      v[u] = val[j];
-    }
-    Row<T, C> xc[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) xc[u] = ldp<T, K, C>(x, c[u], q);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool in = t0 + G * u < n;
-#pragma unroll
-      for (int k = 0; k < C; ++k) acc[k] += v[u] * (in ? xc[u].v[k] : T(0));
-    }
+    load_entries<T, U, G>(col, val, R, t0, c, v);
+    add_entries<T, K, C, U, G, BYPASS>(R, t0, q, x, c, v, acc);
   }
 }
 
@@ -642,7 +683,9 @@ __device__ __forceinline__ void csr_row(const CsrG &A, int64_t r, int l, const T
   T acc[C];
 #pragma unroll
   for (int k = 0; k < C; ++k) acc[k] = T(0);
-  group_entries<T, K, C, G>(A.col, csr_vals<T>(A), b, e - b, e - b, 0, ge, q, x, acc);
+  Gather<T, C> xg;
+  xg.p = x;
+  group_entries<T, K, C, G>(A.col, csr_vals<T>(A), EntryRange{b, e - b, e - b, 0}, ge, q, xg, acc);
   groups_sum<T, C, G, LPR>(acc);
   if (ge != 0) return;
 #pragma unroll
@@ -686,11 +729,21 @@ __global__ __launch_bounds__(kBlock) void k_csr(Jobs<CsrJob<T>> P, const int *__
 // h = g - sum (FP32: g / a_ii - sum over row-scaled values), eight groups of
 // lanes an unknown.  Then the patch's factor times h, on the matrix cores:
 // two wavefronts per 16 rows, each taking every second tile of the tile row,
-// whose operands come straight from memory (each is used once) before the
-// sums are there.  No sequential stages inside the patch.
-// A launch holds about as many patches as the chip has CUs, so the chain of
-// one block sets its time: two dependent loads ahead of the gathers (the
-// descriptors by block and row, then entries, operands and factor together).
+// whose operands come straight from memory (each is used once).  No sequential
+// stages inside the patch.
+//
+// The patch colours follow one another inside the launch.  A block takes the
+// next patch in colour order (an atomic ticket), reads everything that does
+// not depend on the sweep, waits until the patches of all colours before its
+// own are done, and reports its own when its values have reached memory.  It
+// waits for patches with smaller tickets only, whose blocks have all begun, so
+// the earliest unfinished one never waits and every wait ends, whatever the
+// order and the number in which blocks are placed.  The unknowns' values pass
+// between blocks with loads and stores at agent scope, beyond the caches of
+// one XCD, and the block that finishes last clears the counters.
+// A launch per colour took 9.3 us at 129 x 129 x 33 (75 blocks a colour), of
+// which the descriptors, entries and factors, now read ahead, and the launch
+// were the larger part: PATCH_MEASURED.
 constexpr int kPatchGroups = 8;
 constexpr int kPatchThreads = 1024;
 
@@ -706,6 +759,7 @@ __device__ __forceinline__ const float *patch_factor<float>(const PatchSweep &S,
 }
 typedef double Tile64 __attribute__((ext_vector_type(4)));
 typedef float Tile32 __attribute__((ext_vector_type(4)));
+typedef unsigned Word64 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ Tile64 tile_mac(double a, double b, Tile64 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
@@ -718,28 +772,29 @@ __device__ __forceinline__ int tile_row(int l, int r) {
   return sizeof(T) == 8 ? l / 16 + 4 * r : 4 * (l / 16) + r;
 }
 
-// whether the factor is loaded ahead of the sums (its registers beside theirs)
-template <class T, int K>
-constexpr bool patch_ahead() {
-  return row_lanes<T, K>() == 1;
-}
 template <class T, int K, PatchDir DIR>
-__global__ __launch_bounds__(kPatchThreads, (patch_ahead<T, K>() && sizeof(T) == 8 ? 4 : 8)) void k_patch_gs(
-    Jobs<PatchJob<T>> P, const int *__restrict__ done) {
+__global__ __launch_bounds__(kPatchThreads, 4) void k_patch_gs(Jobs<PatchJob<T>> P, const int *__restrict__ done) {
   constexpr int LPR = row_lanes<T, K>(), C = K / LPR, G = kPatchGroups, W = kPatchTile;
   constexpr int RP = kPatchThreads / (G * LPR);  // unknowns summed at once
+  constexpr int NP = kPatchLdsRows / RP, U = NP == 4 ? 2 : entries_ahead<T, C>();
   constexpr bool BWD = DIR == kPatchBackward;
   using Tile = typename std::conditional<sizeof(T) == 8, Tile64, Tile32>::type;
   __shared__ Row<T, K> hs[kPatchLdsRows];
   __shared__ T half[kPatchLdsRows][K];
-  const bool second = (int64_t)blockIdx.x >= P.nb0;
-  const PatchJob<T> &J = second ? P.j[1] : P.j[0];
-  const CsrG &A = J.A;
-  const int64_t p = J.p0 + (second ? xcd_block(blockIdx.x - P.nb0, P.nb1) : xcd_block(blockIdx.x, P.nb0));
-  const PatchDesc D = J.S.desc[p];
+  __shared__ unsigned ticket;
   if (done && *done) return;
-  const T *__restrict__ g = J.g;
-  T *__restrict__ x = J.x;
+  // the blocks of two jobs alternate while both last
+  const int64_t b = blockIdx.x, both = 2 * (P.nb0 < P.nb1 ? P.nb0 : P.nb1);
+  const bool second = b < both ? (b & 1) : P.nb1 > P.nb0;
+  const PatchJob<T> &J = second ? P.j[1] : P.j[0];
+  if (threadIdx.x == 0)
+    ticket = __hip_atomic_fetch_add(&J.sync->begun, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  const int64_t tk = __builtin_amdgcn_readfirstlane(ticket);
+  const int64_t p = BWD ? J.np - 1 - tk : tk;
+  const PatchDesc D = J.S.desc[p];
+  const CsrG &A = J.A;
+  const T *__restrict__ g = J.g, *__restrict__ vals = csr_vals<T>(A);
   const int l = threadIdx.x % (G * LPR), ge = l / LPR, q = l % LPR;
   const int m = D.m, nt = (m + W - 1) / W;
   // this wavefront's tiles: tile row I, tiles J0, J0 + 2, ...
@@ -755,32 +810,57 @@ __global__ __launch_bounds__(kPatchThreads, (patch_ahead<T, K>() && sizeof(T) ==
 #pragma unroll
       for (int s = 0; s < 4; ++s) a[t][s] = J0 + 2 * t < J1 ? f[t * 2 * W * W + s * 64] : T(0);
   };
-  if constexpr (patch_ahead<T, K>()) load_factor();
-#pragma unroll 1
-  for (int q0 = 0; q0 < kPatchLdsRows; q0 += RP) {
-    const int row = q0 + threadIdx.x / (G * LPR);
+  // ahead of the wait unless the entries take the registers
+  constexpr bool kFactorAhead = NP < 4;
+  if constexpr (kFactorAhead) load_factor();
+  // the rows' ranges, right-hand sides and first entries
+  EntryRange R[NP];
+  Row<T, C> gr[NP];
+  int32_t c[NP][U];
+  T v[NP][U], inv[NP];
+#pragma unroll
+  for (int s = 0; s < NP; ++s) {
+    const int row = s * RP + threadIdx.x / (G * LPR);
+    R[s] = EntryRange{0, 0, 0, 0};
+    inv[s] = T(1);
+    if (row < m) {
+      const PatchRow *pr = J.S.rows + p * (kPatchLdsRows + 1) + row;
+      const PatchRow r = pr[0];
+      const int32_t end = pr[1].b;
+      // what is taken: earlier patches; those and later ones beside the own patch's old values
+      const int32_t cut = BWD ? r.late : r.own, from = BWD ? r.next : r.late;
+      R[s] = EntryRange{r.b, DIR == kPatchFirst ? r.own - r.b : cut - r.b + end - from, cut - r.b, from - cut};
+      gr[s] = ldp<T, K, C>(g, D.row0 + row, q);
+      if constexpr (sizeof(T) == 4) inv[s] = 1.0f / A.s32[D.row0 + row];
+      if (ge < R[s].n) load_entries<T, U, G>(A.col, vals, R[s], ge, c[s], v[s]);
+    }
+  }
+  if (threadIdx.x == 0) {
+    const unsigned need = (unsigned)(BWD ? D.after : D.before);
+    while (__hip_atomic_load(&J.sync->ended, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need)
+      __builtin_amdgcn_s_sleep(1);
+  }
+  __syncthreads();
+  if constexpr (!kFactorAhead) load_factor();
+  Gather<T, C> x;
+  x.p = nullptr;
+  x.buf = __builtin_amdgcn_make_buffer_rsrc((void *)J.x, 0, (int)(A.nrows * K * sizeof(T)), 0x00027000);
+#pragma unroll
+  for (int s = 0; s < NP; ++s) {
+    const int row = s * RP + threadIdx.x / (G * LPR);
     Row<T, C> h{};
     if (row < m) {
-      const PatchRow R = J.S.rows[p * (kPatchLdsRows + 1) + row];
-      const int32_t end = J.S.rows[p * (kPatchLdsRows + 1) + row + 1].b;
-      const int64_t i = D.row0 + row;
-      const Row<T, C> gr = ldp<T, K, C>(g, i, q);
-      T inv = T(1);
-      if constexpr (sizeof(T) == 4) inv = 1.0f / A.s32[i];
       T acc[C];
 #pragma unroll
       for (int k = 0; k < C; ++k) acc[k] = T(0);
-      // what is taken: earlier patches; those and later ones beside the own patch's old values
-      const int32_t cut = DIR == kPatchBackward ? R.late : R.own, from = DIR == kPatchBackward ? R.next : R.late;
-      const int32_t n = DIR == kPatchFirst ? R.own - R.b : cut - R.b + end - from;
-      group_entries<T, K, C, G>(A.col, csr_vals<T>(A), R.b, n, cut - R.b, from - cut, ge, q, x, acc);
+      if (ge < R[s].n) add_entries<T, K, C, U, G, true>(R[s], ge, q, x, c[s], v[s], acc);
+      group_entries<T, K, C, G, true>(A.col, vals, R[s], ge + G * U, q, x, acc);
       groups_sum<T, C, G, LPR>(acc);
 #pragma unroll
-      for (int k = 0; k < C; ++k) h.v[k] = gr.v[k] * inv - acc[k];
+      for (int k = 0; k < C; ++k) h.v[k] = gr[s].v[k] * inv[s] - acc[k];
     }
     if (ge == 0) *reinterpret_cast<Row<T, C> *>(&hs[row].v[q * C]) = h;  // zero beyond the patch
   }
-  if constexpr (!patch_ahead<T, K>()) load_factor();
   __syncthreads();
   const int col = lane % W;
   Tile acc = {0, 0, 0, 0};
@@ -789,8 +869,8 @@ __global__ __launch_bounds__(kPatchThreads, (patch_ahead<T, K>() && sizeof(T) ==
     if (J0 + 2 * t >= J1) continue;  // uniform over the wavefront
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      const T b = col < K ? hs[(J0 + 2 * t) * W + 4 * s + lane / W].v[col < K ? col : 0] : T(0);
-      acc = tile_mac(a[t][s], b, acc);
+      const T bv = col < K ? hs[(J0 + 2 * t) * W + 4 * s + lane / W].v[col < K ? col : 0] : T(0);
+      acc = tile_mac(a[t][s], bv, acc);
     }
   }
   if (odd && col < K) {
@@ -798,11 +878,29 @@ __global__ __launch_bounds__(kPatchThreads, (patch_ahead<T, K>() && sizeof(T) ==
     for (int r = 0; r < 4; ++r) half[I * W + tile_row<T>(lane, r)][col] = acc[r];
   }
   __syncthreads();
-  if (odd || col >= K) return;
+  if (!odd && col < K) {
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = I * W + tile_row<T>(lane, r);
-    if (row < m) x[(int64_t)(D.row0 + row) * K + col] = acc[r] + half[row][col];
+    for (int r = 0; r < 4; ++r) {
+      const int row = I * W + tile_row<T>(lane, r);
+      if (row < m) {
+        const T out = acc[r] + half[row][col];
+        const int off = ((D.row0 + row) * K + col) * (int)sizeof(T);
+        if constexpr (sizeof(T) == 8)
+          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(Word64, out), x.buf, off, 0, kAgentScope);
+        else
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, out), x.buf, off, 0, kAgentScope);
+      }
+    }
+  }
+  // every wavefront's values have reached memory before the patch is reported
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned before = __hip_atomic_fetch_add(&J.sync->ended, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (before + 1 == (unsigned)J.np) {  // every block of the job has begun and passed its wait
+      __hip_atomic_store(&J.sync->begun, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&J.sync->ended, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
 }
 

@@ -183,11 +183,17 @@ void launch_csr(hipStream_t st, int K, CsrMode mode, const CsrJob<T> *jobs, int 
 // sweep in that order.  Backward: (D_p + U_p)^{-1} = ((D_p + L_p)^{-1})^T.
 constexpr int kPatchLdsRows = 128;
 constexpr int kPatchTile = 16;
-// stored patch: its first row, its number of rows m, and where its factor
-// tiles begin
+// stored patch: its first row, its number of rows m, where its factor tiles
+// begin, and the number of patches of the colours before its own and after it
 struct PatchDesc {
   int32_t row0, m;
   int64_t toff;
+  int32_t before, after;
+};
+// progress of a level's sweep: patches begun and patches done (a cache line
+// each); both are zero between launches
+struct PatchSync {
+  unsigned begun, pad0[31], ended, pad1[31];
 };
 // A row's entries (columns ascending, so in sweep order) by what a sweep of
 // its patch takes: [b, own) earlier patches, [own, late) its own patch before
@@ -207,19 +213,19 @@ struct PatchSweep {
   const double *tf64 = nullptr, *tb64 = nullptr;
   const float *tf32 = nullptr, *tb32 = nullptr;
 };
-// One Gauss-Seidel sweep over the patches [p0, p0 + np) of one patch colour,
-// one block per patch (the patch colours launched in turn, ascending for a
-// forward sweep and descending for backward).  kPatchFirst: the forward sweep
-// from x = 0, which reads of the other patches only those swept before, so x
-// needs no fill.
+// One Gauss-Seidel sweep over all the patches of a level, one block per patch,
+// in ascending (kPatchBackward: descending) order of the patch colours.
+// kPatchFirst: the forward sweep from x = 0, which reads of the other patches
+// only those swept before, so x needs no fill.
 enum PatchDir { kPatchFirst, kPatchForward, kPatchBackward };
 template <class T>
 struct PatchJob {
   CsrG A;
   PatchSweep S;
-  int64_t p0 = 0, np = 0;
+  int64_t np = 0;
   const T *g = nullptr;
   T *x = nullptr;
+  PatchSync *sync = nullptr;
 };
 template <class T>
 void launch_patch_gs(hipStream_t st, int K, PatchDir dir, const PatchJob<T> *jobs, int nj, const int *done);
