@@ -311,7 +311,7 @@ struct DLevel {
   CsrG Ac;                      // coarse levels: standard form, G lanes per row
   PatchSweep ps;                // coarse levels: the patches of the sweeps
   int64_t np = 0;               // number of patches
-  PatchSync *sync = nullptr;
+  PatchCount *count = nullptr;
   bool fine = false;
   int64_t n = 0, row0 = 0;
   int64_t n_top = 0;            // fine levels: rows of the top block in the fine matrix
@@ -418,15 +418,40 @@ void pack_patches(Arena &ar, hipStream_t st, const Level &L, DLevel &dl) {
   if (n > INT32_MAX) throw DeviceError(VEMG_ERR_DEVICE, "coarse level above 2^31 rows");
   std::vector<PatchDesc> desc(np);
   std::vector<PatchRow> rows(np * S, PatchRow{0, 0, 0, 0});
+  std::vector<int32_t> halo, lcol;
   int64_t tiles = 0;
+  for (size_t c = 0; c + 1 < L.pc_start.size(); ++c)  // each colour waits for the one before alone
+    if (L.pc_start[c + 1] <= L.pc_start[c]) throw DeviceError(VEMG_ERR_DEVICE, "empty patch colour");
   for (int64_t p = 0; p < np; ++p) {
     const int64_t m = L.patch_row[p + 1] - L.patch_row[p], nt = (m + W - 1) / W;
     if (n * kMaxBatch * 8 > INT32_MAX) throw DeviceError(VEMG_ERR_DEVICE, "coarse level above the sweep kernel's 32-bit offsets");
     if (m > kPatchLdsRows) throw DeviceError(VEMG_ERR_DEVICE, "a patch exceeds the sweep kernel's rows");
     int c = 0;
     while (L.pc_start[c + 1] <= p) ++c;
-    desc[p] = PatchDesc{(int32_t)L.patch_row[p], (int32_t)m, tiles * W * W, (int32_t)L.pc_start[c],
-                        (int32_t)(np - L.pc_start[c + 1])};
+    auto size = [&](int k) {
+      return k < 0 || k + 1 >= (int)L.pc_start.size() ? 0 : (int32_t)(L.pc_start[k + 1] - L.pc_start[k]);
+    };
+    desc[p] = PatchDesc{(int32_t)L.patch_row[p], (int32_t)m, tiles * W * W, (int32_t)halo.size(), 0, 0, c,
+                        size(c - 1), size(c), size(c + 1)};
+    // the halo: the listed part of the other patches' rows, ascending
+    const int64_t ps = L.patch_row[p], pe = ps + m;
+    std::vector<int32_t> out;
+    for (int64_t k = L.A.ptr[ps]; k < L.A.ptr[pe]; ++k)
+      if (L.A.idx[k] < ps || L.A.idx[k] >= pe) out.push_back(L.A.idx[k]);
+    std::sort(out.begin(), out.end());
+    out.erase(std::unique(out.begin(), out.end()), out.end());
+    if ((int64_t)out.size() > kPatchHalo) out.resize(kPatchHalo);
+    desc[p].nhalo = (int32_t)out.size();
+    for (int32_t j : out) desc[p].nearly += j < ps;
+    for (int64_t i = ps; i < pe; ++i)
+      for (int64_t k = L.A.ptr[i]; k < L.A.ptr[i + 1]; ++k) {
+        const int32_t j = L.A.idx[k];
+        if (j == i) continue;
+        const auto at = std::lower_bound(out.begin(), out.end(), j);
+        lcol.push_back(j >= ps && j < pe ? (int32_t)(j - ps)
+                       : at != out.end() && *at == j ? (int32_t)(kPatchLdsRows + (at - out.begin())) : ~j);
+      }
+    halo.insert(halo.end(), out.begin(), out.end());
     tiles += nt * (nt + 1) / 2;
   }
   std::vector<double> tf(tiles * W * W, 0.0), tb(tiles * W * W, 0.0);
@@ -487,9 +512,14 @@ void pack_patches(Arena &ar, hipStream_t st, const Level &L, DLevel &dl) {
   dl.ps.tb64 = ar.upload(tb, st);
   dl.ps.tf32 = ar.upload(tf32, st);
   dl.ps.tb32 = ar.upload(tb32, st);
+  dl.ps.halo = ar.upload(halo, st);
+  dl.ps.lcol = ar.upload(lcol, st);
+  dl.ps.ncolours = (int)L.pc_start.size() - 1;
   dl.np = np;
-  dl.sync = ar.alloc<PatchSync>(1);
-  if (!ar.count_only) launch_fill<float>(st, (float *)dl.sync, sizeof(PatchSync) / sizeof(float), 0.0f, nullptr);
+  const size_t nc = L.pc_start.size();
+  dl.count = ar.alloc<PatchCount>(nc);
+  if (!ar.count_only)
+    launch_fill<float>(st, (float *)dl.count, (int64_t)(nc * sizeof(PatchCount) / sizeof(float)), 0.0f, nullptr);
 }
 
 enum LevelsOf { kLevelsS = 0, kLevelsAbar = 1, kLevelsSA = 2 };
@@ -585,7 +615,7 @@ void coarse_cycles(hipStream_t st, int K, Cycle<T> a, Cycle<T> b, const int *don
   }
   PatchJob<T> gs[2];
   for (int i = 0; i < nl; ++i)
-    gs[i] = PatchJob<T>{L[i]->Ac, L[i]->ps, L[i]->np, L[i]->template g<T>(), L[i]->template x<T>(), L[i]->sync};
+    gs[i] = PatchJob<T>{L[i]->Ac, L[i]->ps, L[i]->np, L[i]->template g<T>(), L[i]->template x<T>(), L[i]->count};
   launch_patch_gs<T>(st, K, kPatchFirst, gs, nl, done);
   Cycle<T> na = a, nb = b;
   if (ra >= rb) ++na.l;
@@ -1522,7 +1552,7 @@ void time_once(Handle *h, int op, int K) {
   }
   if (op == VEMG_OP_GS_COARSE) {
     DLevel &L = h->Ab[1];
-    const PatchJob<T> J{L.Ac, L.ps, L.np, L.g<T>(), L.x<T>(), L.sync};
+    const PatchJob<T> J{L.Ac, L.ps, L.np, L.g<T>(), L.x<T>(), L.count};
     launch_patch_gs<T>(st, K, kPatchForward, &J, 1, nullptr);
     return;
   }

@@ -618,33 +618,13 @@ __device__ __forceinline__ void load_entries(const int32_t *__restrict__ col, co
     v[u] = val[j];
   }
 }
-// columns [q C, q C + C) of row r of a vector that other blocks of the launch
-// write (BYPASS: past the caches that are not shared between XCDs) or not
-template <class T, int C>
-struct Gather {
-  __amdgpu_buffer_rsrc_t buf;
-  const T *p;
-};
-template <class T, int K, int C, bool BYPASS>
-__device__ __forceinline__ Row<T, C> gather(const Gather<T, C> &x, int32_t r, int q) {
-  if constexpr (!BYPASS) {
-    return ldp<T, K, C>(x.p, r, q);
-  } else {
-    const int off = (r * K + q * C) * (int)sizeof(T);
-    if constexpr (sizeof(Row<T, C>) == 4)
-      return __builtin_bit_cast(Row<T, C>, __builtin_amdgcn_raw_buffer_load_b32(x.buf, off, 0, kAgentScope));
-    else if constexpr (sizeof(Row<T, C>) == 8)
-      return __builtin_bit_cast(Row<T, C>, __builtin_amdgcn_raw_buffer_load_b64(x.buf, off, 0, kAgentScope));
-    else
-      return __builtin_bit_cast(Row<T, C>, __builtin_amdgcn_raw_buffer_load_b128(x.buf, off, 0, kAgentScope));
-  }
-}
-template <class T, int K, int C, int U, int G, bool BYPASS>
-__device__ __forceinline__ void add_entries(const EntryRange &R, int32_t t0, int q, const Gather<T, C> &x,
-                                            const int32_t (&c)[U], const T (&v)[U], T (&acc)[C]) {
+// x(c): the row of column c
+template <class T, int C, int U, int G, class X>
+__device__ __forceinline__ void add_entries(const EntryRange &R, int32_t t0, X &&x, const int32_t (&c)[U],
+                                            const T (&v)[U], T (&acc)[C]) {
   Row<T, C> xc[U];
 #pragma unroll
-  for (int u = 0; u < U; ++u) xc[u] = gather<T, K, C, BYPASS>(x, c[u], q);
+  for (int u = 0; u < U; ++u) xc[u] = x(c[u]);
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const bool in = t0 + G * u < R.n;
@@ -652,16 +632,15 @@ __device__ __forceinline__ void add_entries(const EntryRange &R, int32_t t0, int
     for (int k = 0; k < C; ++k) acc[k] += v[u] * (in ? xc[u].v[k] : T(0));
   }
 }
-template <class T, int K, int C, int G, bool BYPASS = false>
+template <class T, int C, int G, class X>
 __device__ __forceinline__ void group_entries(const int32_t *__restrict__ col, const T *__restrict__ val,
-                                              const EntryRange &R, int32_t t0, int q, const Gather<T, C> &x,
-                                              T (&acc)[C]) {
+                                              const EntryRange &R, int32_t t0, X &&x, T (&acc)[C]) {
   constexpr int U = entries_ahead<T, C>();
   for (; t0 < R.n; t0 += G * U) {
     int32_t c[U];
     T v[U];
     load_entries<T, U, G>(col, val, R, t0, c, v);
-    add_entries<T, K, C, U, G, BYPASS>(R, t0, q, x, c, v, acc);
+    add_entries<T, C, U, G>(R, t0, x, c, v, acc);
   }
 }
 
@@ -683,9 +662,8 @@ __device__ __forceinline__ void csr_row(const CsrG &A, int64_t r, int l, const T
   T acc[C];
 #pragma unroll
   for (int k = 0; k < C; ++k) acc[k] = T(0);
-  Gather<T, C> xg;
-  xg.p = x;
-  group_entries<T, K, C, G>(A.col, csr_vals<T>(A), EntryRange{b, e - b, e - b, 0}, ge, q, xg, acc);
+  group_entries<T, C, G>(A.col, csr_vals<T>(A), EntryRange{b, e - b, e - b, 0}, ge,
+                         [&](int32_t c) { return ldp<T, K, C>(x, c, q); }, acc);
   groups_sum<T, C, G, LPR>(acc);
   if (ge != 0) return;
 #pragma unroll
@@ -740,10 +718,15 @@ __global__ __launch_bounds__(kBlock) void k_csr(Jobs<CsrJob<T>> P, const int *__
 // the earliest unfinished one never waits and every wait ends, whatever the
 // order and the number in which blocks are placed.  The unknowns' values pass
 // between blocks with loads and stores at agent scope, beyond the caches of
-// one XCD, and the block that finishes last clears the counters.
+// one XCD; so each row of the halo is read once, into LDS.  The block that
+// finishes the last colour clears the counters.
 // A launch per colour took 9.3 us at 129 x 129 x 33 (75 blocks a colour), of
 // which the descriptors, entries and factors, now read ahead, and the launch
-// were the larger part: PATCH_MEASURED.
+// were the larger part: a sweep of seven colours took 65 us in seven launches,
+// 44 in one with every entry gathered at agent scope, and takes 39 with the
+// halo in LDS (2,179,616 unknowns: 92, 82 and 79 us).  One block a CU: two, with
+// the factor and the entries read after the wait to fit their registers, took
+// 173 us there.
 constexpr int kPatchGroups = 8;
 constexpr int kPatchThreads = 1024;
 
@@ -772,6 +755,19 @@ __device__ __forceinline__ int tile_row(int l, int r) {
   return sizeof(T) == 8 ? l / 16 + 4 * r : 4 * (l / 16) + r;
 }
 
+// columns [q C, q C + C) of row r of a vector that other blocks of the launch
+// write
+template <class T, int K, int C>
+__device__ __forceinline__ Row<T, C> agent_row(__amdgpu_buffer_rsrc_t x, int32_t r, int q) {
+  const int off = (r * K + q * C) * (int)sizeof(T);
+  if constexpr (sizeof(Row<T, C>) == 4)
+    return __builtin_bit_cast(Row<T, C>, __builtin_amdgcn_raw_buffer_load_b32(x, off, 0, kAgentScope));
+  else if constexpr (sizeof(Row<T, C>) == 8)
+    return __builtin_bit_cast(Row<T, C>, __builtin_amdgcn_raw_buffer_load_b64(x, off, 0, kAgentScope));
+  else
+    return __builtin_bit_cast(Row<T, C>, __builtin_amdgcn_raw_buffer_load_b128(x, off, 0, kAgentScope));
+}
+
 template <class T, int K, PatchDir DIR>
 __global__ __launch_bounds__(kPatchThreads, 4) void k_patch_gs(Jobs<PatchJob<T>> P, const int *__restrict__ done) {
   constexpr int LPR = row_lanes<T, K>(), C = K / LPR, G = kPatchGroups, W = kPatchTile;
@@ -779,6 +775,7 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch_gs(Jobs<PatchJob<T>>
   constexpr int NP = kPatchLdsRows / RP, U = NP == 4 ? 2 : entries_ahead<T, C>();
   constexpr bool BWD = DIR == kPatchBackward;
   using Tile = typename std::conditional<sizeof(T) == 8, Tile64, Tile32>::type;
+  __shared__ Row<T, K> xs[kPatchLdsRows + kPatchHalo];  // the patch's own old values, and its halo's
   __shared__ Row<T, K> hs[kPatchLdsRows];
   __shared__ T half[kPatchLdsRows][K];
   __shared__ unsigned ticket;
@@ -788,7 +785,7 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch_gs(Jobs<PatchJob<T>>
   const bool second = b < both ? (b & 1) : P.nb1 > P.nb0;
   const PatchJob<T> &J = second ? P.j[1] : P.j[0];
   if (threadIdx.x == 0)
-    ticket = __hip_atomic_fetch_add(&J.sync->begun, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    ticket = __hip_atomic_fetch_add(&J.count[0].n, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   const int64_t tk = __builtin_amdgcn_readfirstlane(ticket);
   const int64_t p = BWD ? J.np - 1 - tk : tk;
@@ -813,6 +810,18 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch_gs(Jobs<PatchJob<T>>
   // ahead of the wait unless the entries take the registers
   constexpr bool kFactorAhead = NP < 4;
   if constexpr (kFactorAhead) load_factor();
+  // the staged rows: with a start the patch's own, then the halo (from zero its
+  // earlier patches)
+  constexpr int own = DIR == kPatchFirst ? 0 : kPatchLdsRows;
+  const int nh = DIR == kPatchFirst ? D.nearly : D.nhalo;
+  const int st = threadIdx.x / LPR, sq = threadIdx.x % LPR;
+  constexpr int SP = kPatchThreads / LPR;  // rows staged at once
+  auto staged = [&](int i) {  // global row of staged row i, -1: none
+    return i < own ? (i < m ? D.row0 + i : -1) : i - own < nh ? J.S.halo[D.halo + i - own] : -1;
+  };
+  int32_t first[2];  // most patches need no more
+#pragma unroll
+  for (int s = 0; s < 2; ++s) first[s] = staged(st + s * SP);
   // the rows' ranges, right-hand sides and first entries
   EntryRange R[NP];
   Row<T, C> gr[NP];
@@ -832,19 +841,31 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch_gs(Jobs<PatchJob<T>>
       R[s] = EntryRange{r.b, DIR == kPatchFirst ? r.own - r.b : cut - r.b + end - from, cut - r.b, from - cut};
       gr[s] = ldp<T, K, C>(g, D.row0 + row, q);
       if constexpr (sizeof(T) == 4) inv[s] = 1.0f / A.s32[D.row0 + row];
-      if (ge < R[s].n) load_entries<T, U, G>(A.col, vals, R[s], ge, c[s], v[s]);
+      if (ge < R[s].n) load_entries<T, U, G>(J.S.lcol, vals, R[s], ge, c[s], v[s]);
     }
   }
-  if (threadIdx.x == 0) {
-    const unsigned need = (unsigned)(BWD ? D.after : D.before);
-    while (__hip_atomic_load(&J.sync->ended, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need)
+  // the patches of the colour before this one's are done (and so all earlier ones)
+  const unsigned need = (unsigned)(BWD ? D.n_after : D.n_before);
+  if (threadIdx.x == 0 && need) {
+    PatchCount *pc = J.count + 1 + (BWD ? D.colour + 1 : D.colour - 1);
+    while (__hip_atomic_load(&pc->n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need)
       __builtin_amdgcn_s_sleep(1);
   }
   __syncthreads();
+  const __amdgpu_buffer_rsrc_t x =
+      __builtin_amdgcn_make_buffer_rsrc((void *)J.x, 0, (int)(A.nrows * K * sizeof(T)), 0x00027000);
+  auto stage = [&](int i, int32_t r) {
+    if (r >= 0)
+      *reinterpret_cast<Row<T, C> *>(&xs[i < own ? i : i - own + kPatchLdsRows].v[sq * C]) = agent_row<T, K, C>(x, r, sq);
+  };
+#pragma unroll
+  for (int s = 0; s < 2; ++s) stage(st + s * SP, first[s]);
+  for (int i = st + 2 * SP; i < own + nh; i += SP) stage(i, staged(i));
   if constexpr (!kFactorAhead) load_factor();
-  Gather<T, C> x;
-  x.p = nullptr;
-  x.buf = __builtin_amdgcn_make_buffer_rsrc((void *)J.x, 0, (int)(A.nrows * K * sizeof(T)), 0x00027000);
+  __syncthreads();
+  auto value = [&](int32_t j) {
+    return j >= 0 ? *reinterpret_cast<const Row<T, C> *>(&xs[j].v[q * C]) : agent_row<T, K, C>(x, ~j, q);
+  };
 #pragma unroll
   for (int s = 0; s < NP; ++s) {
     const int row = s * RP + threadIdx.x / (G * LPR);
@@ -853,8 +874,8 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch_gs(Jobs<PatchJob<T>>
       T acc[C];
 #pragma unroll
       for (int k = 0; k < C; ++k) acc[k] = T(0);
-      if (ge < R[s].n) add_entries<T, K, C, U, G, true>(R[s], ge, q, x, c[s], v[s], acc);
-      group_entries<T, K, C, G, true>(A.col, vals, R[s], ge + G * U, q, x, acc);
+      if (ge < R[s].n) add_entries<T, C, U, G>(R[s], ge, value, c[s], v[s], acc);
+      group_entries<T, C, G>(J.S.lcol, vals, R[s], ge + G * U, value, acc);
       groups_sum<T, C, G, LPR>(acc);
 #pragma unroll
       for (int k = 0; k < C; ++k) h.v[k] = gr[s].v[k] * inv[s] - acc[k];
@@ -886,9 +907,9 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch_gs(Jobs<PatchJob<T>>
         const T out = acc[r] + half[row][col];
         const int off = ((D.row0 + row) * K + col) * (int)sizeof(T);
         if constexpr (sizeof(T) == 8)
-          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(Word64, out), x.buf, off, 0, kAgentScope);
+          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(Word64, out), x, off, 0, kAgentScope);
         else
-          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, out), x.buf, off, 0, kAgentScope);
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, out), x, off, 0, kAgentScope);
       }
     }
   }
@@ -896,11 +917,12 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch_gs(Jobs<PatchJob<T>>
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0) {
-    const unsigned before = __hip_atomic_fetch_add(&J.sync->ended, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (before + 1 == (unsigned)J.np) {  // every block of the job has begun and passed its wait
-      __hip_atomic_store(&J.sync->begun, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(&J.sync->ended, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    const unsigned n =
+        1 + __hip_atomic_fetch_add(&J.count[1 + D.colour].n, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the last patch of the last colour: every block of the job has passed its wait
+    if (n == (unsigned)D.n_own && (BWD ? D.n_before : D.n_after) == 0)
+      for (int i = 0; i <= J.S.ncolours; ++i)
+        __hip_atomic_store(&J.count[i].n, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 

@@ -183,17 +183,20 @@ void launch_csr(hipStream_t st, int K, CsrMode mode, const CsrJob<T> *jobs, int 
 // sweep in that order.  Backward: (D_p + U_p)^{-1} = ((D_p + L_p)^{-1})^T.
 constexpr int kPatchLdsRows = 128;
 constexpr int kPatchTile = 16;
+constexpr int kPatchHalo = 1024;
 // stored patch: its first row, its number of rows m, where its factor tiles
-// begin, and the number of patches of the colours before its own and after it
+// begin; its halo, the rows of other patches it is coupled to, ascending
+// (those of earlier patches first), at most kPatchHalo of them listed; its
+// colour, and the number of patches of the colours before, of and after it
 struct PatchDesc {
   int32_t row0, m;
   int64_t toff;
-  int32_t before, after;
+  int32_t halo, nearly, nhalo;
+  int32_t colour, n_before, n_own, n_after;
 };
-// progress of a level's sweep: patches begun and patches done (a cache line
-// each); both are zero between launches
-struct PatchSync {
-  unsigned begun, pad0[31], ended, pad1[31];
+// a cache line of its own for each progress counter
+struct PatchCount {
+  unsigned n, pad[31];
 };
 // A row's entries (columns ascending, so in sweep order) by what a sweep of
 // its patch takes: [b, own) earlier patches, [own, late) its own patch before
@@ -204,6 +207,11 @@ struct PatchRow {
 struct PatchSweep {
   const PatchDesc *desc = nullptr;
   const PatchRow *rows = nullptr;  // [patch][kPatchLdsRows + 1]; row m holds the end of row m - 1's entries
+  const int32_t *halo = nullptr;
+  // column of each entry of the level's CsrG: the row in its own patch, or
+  // kPatchLdsRows + its place in the halo, or ~column beyond the halo's list
+  const int32_t *lcol = nullptr;
+  int ncolours = 0;
   // FP64: F = (D_p + L_p)^{-1}; FP32 (row-scaled operator): F D_p, rounded;
   // tb: the same of F^T.  Tiles of 16 x 16, zero beyond m, tile row I (of
   // t = ceil(m / 16)) holding its tiles J <= I (tb: J >= I) in order from tile
@@ -225,7 +233,8 @@ struct PatchJob {
   int64_t np = 0;
   const T *g = nullptr;
   T *x = nullptr;
-  PatchSync *sync = nullptr;
+  // patches begun, then patches done of each colour; zero between launches
+  PatchCount *count = nullptr;
 };
 template <class T>
 void launch_patch_gs(hipStream_t st, int K, PatchDir dir, const PatchJob<T> *jobs, int nj, const int *done);
