@@ -80,6 +80,11 @@ struct Arena {
   }
 };
 
+// host copy of a Sell's sptr and smid
+struct SellSpans {
+  std::vector<int64_t> sptr, smid;
+};
+
 // CSR (host) -> SELL-64 (device).  Square: the diagonal entries are taken
 // out of the stored entries; the FP64 per-row term is `d` if given
 // (difference form: the deficit) else a_ii.  FP32 copy: a_ij / a_ii with
@@ -88,7 +93,7 @@ struct Arena {
 // those to later ones, the two parts padded apart (Sell::smid).
 Sell pack_sell(Arena &ar, hipStream_t st, const Csr &A, bool square, const std::vector<double> *d,
                const std::vector<double> *diag, int64_t *stored = nullptr,
-               const std::vector<int32_t> *colour = nullptr) {
+               const std::vector<int32_t> *colour = nullptr, SellSpans *spans = nullptr) {
   int64_t n = A.nrows, ns = (n + kWave - 1) / kWave;
   // part of entry e of row r: 0 (earlier colour, or no colours) or 1; -1: not stored
   auto part_of = [&](int64_t r, int64_t e) {
@@ -138,6 +143,7 @@ Sell pack_sell(Arena &ar, hipStream_t st, const Csr &A, bool square, const std::
     }
   }
   if (stored) *stored = sptr[ns];
+  if (spans) *spans = SellSpans{sptr, smid};
   Sell M;
   M.nrows = n;
   M.sptr = ar.upload(sptr, st);
@@ -317,7 +323,7 @@ struct DLevel {
   int64_t n_top = 0;            // fine levels: rows of the top block in the fine matrix
   std::vector<int64_t> cstart;  // colour ranges, global row indices
   std::vector<int64_t> cstart_top;  // fine level of the whole A_UU: top-block range of each colour
-  const int32_t *order = nullptr;   // fine levels: slice visit order of the residual product
+  const SliceRef *order = nullptr;  // fine levels: slice visit order of the residual product
   CsrG P, Pt;                   // prolongation (n x n_next) and restriction
   Sell Ps;                      // fine levels: the prolongation in SELL-64 (a few entries a row)
   double *Cinv = nullptr;       // coarsest level only: its explicit inverse
@@ -375,7 +381,7 @@ struct vemg_solver_s {
   int64_t *perm = nullptr;
   // slice visit orders (spatial, across colours) of the products over all
   // rows and over the non-top rows
-  int32_t *order_all = nullptr, *order_bar = nullptr;
+  vemg::SliceRef *order_all = nullptr, *order_bar = nullptr;
   // VL + additive smoother: both cycles in one pair of fine sweeps (unless
   // A_bar's hierarchy is a single dense level); D's rows of colour c are
   // [dstart[c], dstart[c+1]), and merged_Pt restricts the smoother's residual
@@ -1314,7 +1320,8 @@ void upload(Handle *h) {
   int64_t n = P.n, m = P.n_top;
   const bool count = h->ar.count_only;
   h->ar.release();
-  h->A = pack_sell(h->ar, st, P.Aoff, true, &P.d, &P.diag, &h->nnz_A, &P.colour);
+  SellSpans spans;
+  h->A = pack_sell(h->ar, st, P.Aoff, true, &P.d, &P.diag, &h->nnz_A, &P.colour, &spans);
   if (m > 0) {
     h->E = pack_sell(h->ar, st, P.E, false, nullptr, nullptr, &h->nnz_E);
     h->Et = pack_csrg(h->ar, st, P.Et, false, nullptr, &P.loc_rank, 0);
@@ -1362,7 +1369,12 @@ void upload(Handle *h) {
     std::stable_sort(ord.begin(), ord.end(), [&](int32_t a, int32_t b) {
       return P.loc_rank[std::max((s0 + a) * kWave, r0)] < P.loc_rank[std::max((s0 + b) * kWave, r0)];
     });
-    return h->ar.upload(ord, st);
+    std::vector<SliceRef> ref(ord.size());
+    for (size_t i = 0; i < ord.size(); ++i) {
+      const int64_t s = s0 + ord[i];
+      ref[i] = SliceRef{s, spans.sptr[s], spans.smid[s], spans.sptr[s + 1]};
+    }
+    return h->ar.upload(ref, st);
   };
   h->order_all = slice_order(0, n);
   h->order_bar = slice_order(m, n);

@@ -23,6 +23,18 @@ __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nb) {
   return (x < rem) ? x * (q + 1) + i : rem * (q + 1) + (x - rem) * q + i;
 }
 
+// Every kernel of an iteration leaves at once when all columns are done.  The
+// flag is read beside the kernel's first loads, which `keep` holds in front of
+// the branch on it: read on its own it puts a trip to memory ahead of them.
+__device__ const int kNeverDone = 0;
+__device__ __forceinline__ int stop_flag(const int *done) { return *(done ? done : &kNeverDone); }
+__device__ __forceinline__ void keep() {}
+template <class V, class... W>
+__device__ __forceinline__ void keep(const V &v, const W &...w) {
+  asm volatile("" ::"v"(v));
+  keep(w...);
+}
+
 template <class T, int K>
 struct alignas(sizeof(T) * K) Row {
   T v[K];
@@ -104,36 +116,106 @@ constexpr int sell_unroll() {
   return sizeof(T) * C >= 64 ? 1 : sizeof(T) * C >= 32 ? 2 : 4;
 }
 
-// Off-diagonal terms of one SELL row (position t of slice s) for the C
-// columns [q C, q C + C) of a K-column batch: acc = sum_j v_j (x_j - x_r)
-// (DIFF) or sum_j v_j x_j, over all the row's entries or the fine matrix's L
-// or U entries alone.  Every column is summed in storage order, whatever C is.
-// The padding entries of L point at the row itself, which the sweep has not
-// written yet, so their gathered value is replaced by zero.
-enum Part { kAll, kLower, kUpper };
+// value of lane O of every group of LPR consecutive lanes (2 or 4) in all of them
+template <int LPR, int O>
+__device__ __forceinline__ int group_bcast(int v) {
+  constexpr int ctrl = LPR == 4 ? O * 0x55 : O | O << 2 | (2 + O) << 4 | (2 + O) << 6;  // quad_perm
+  return __builtin_amdgcn_update_dpp(0, v, ctrl, 0xf, 0xf, true);
+}
+template <int LPR, int O>
+__device__ __forceinline__ float group_bcast(float v) {
+  return __builtin_bit_cast(float, group_bcast<LPR, O>(__builtin_bit_cast(int, v)));
+}
+template <int LPR, int O>
+__device__ __forceinline__ double group_bcast(double v) {
+  const int2 w = __builtin_bit_cast(int2, v);
+  return __builtin_bit_cast(double, make_int2(group_bcast<LPR, O>(w.x), group_bcast<LPR, O>(w.y)));
+}
 
-template <class T, int K, int C, bool DIFF, int PART = kAll>
-__device__ __forceinline__ void sell_row(const Sell &A, int64_t s, int t, int q, const T *__restrict__ x,
-                                         const Row<T, C> &xr, T (&acc)[C], int32_t own = -1) {
-  const int64_t base = PART == kUpper ? A.smid[s] : A.sptr[s];
-  const int len = (int)(((PART == kLower ? A.smid[s] : A.sptr[s + 1]) - base) >> 6);
-  const int32_t *__restrict__ cp = A.col + base + t;
-  const T *__restrict__ vp = sell_vals<T>(A) + base + t;
+// entry u of a step is lane u % LPR's u / LPR-th
+template <int LPR, class T, int N>
+__device__ __forceinline__ void spread(const int32_t (&c)[N], const T (&v)[N], int32_t (&cu)[N * LPR],
+                                       T (&vu)[N * LPR]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    cu[i * LPR] = group_bcast<LPR, 0>(c[i]);
+    vu[i * LPR] = group_bcast<LPR, 0>(v[i]);
+    cu[i * LPR + 1] = group_bcast<LPR, 1>(c[i]);
+    vu[i * LPR + 1] = group_bcast<LPR, 1>(v[i]);
+    if constexpr (LPR == 4) {
+      cu[i * LPR + 2] = group_bcast<LPR, 2>(c[i]);
+      vu[i * LPR + 2] = group_bcast<LPR, 2>(v[i]);
+      cu[i * LPR + 3] = group_bcast<LPR, 3>(c[i]);
+      vu[i * LPR + 3] = group_bcast<LPR, 3>(v[i]);
+    }
+  }
+}
+
+// Off-diagonal terms of one SELL row, entries [begin, end) of its slice at
+// position t, for the C columns [q C, q C + C) of a K-column batch:
+// acc = sum_j v_j (x_j - x_r) (DIFF) or sum_j v_j x_j.  Every column is summed
+// in storage order, whatever C is.  With OWN the entries pointing at row `own`
+// itself (the padding of the L part, whose value the sweep has not written
+// yet) count a zero.
+// With several lanes a row, each lane loads every LPR-th entry's column and
+// value for the others too, and those of the next four entries before the
+// current ones' gathers; loaded by every lane they were two of the three
+// loads an entry.  At K = 8 and 2,179,616 unknowns the prolongation between the
+// sweeps went from 221 to 143 us, the forward sweep from 218 to 195, the
+// residual from 174 to 153 and the product from 268 to 254.
+template <class T, int K, int C, bool DIFF, bool OWN = false>
+__device__ __forceinline__ void sell_span(const Sell &A, int64_t begin, int64_t end, int t, int q,
+                                          const T *__restrict__ x, const Row<T, C> &xr, T (&acc)[C],
+                                          int32_t own = -1) {
+  constexpr int LPR = K / C;
+  const int len = (int)((end - begin) >> 6);
+  const int32_t *__restrict__ cp = A.col + begin + t;
+  const T *__restrict__ vp = sell_vals<T>(A) + begin + t;
   const T *__restrict__ xq = x + q * C;
 #pragma unroll
   for (int k = 0; k < C; ++k) acc[k] = T(0);
-  constexpr int U = sell_unroll<T, C>();
-#pragma unroll U
-  for (int e = 0; e < len; ++e) {
-    const int32_t c = cp[(int64_t)e * 64];
-    const T v = vp[(int64_t)e * 64];
+  auto row = [&](int32_t c) {
     Row<T, C> xc = *reinterpret_cast<const Row<T, C> *>(xq + (int64_t)c * K);
-    if constexpr (PART == kLower) {
+    if constexpr (OWN) {
 #pragma unroll
       for (int k = 0; k < C; ++k) xc.v[k] = c != own ? xc.v[k] : T(0);
     }
+    return xc;
+  };
+  auto add = [&](T v, const Row<T, C> &xc) {
 #pragma unroll
     for (int k = 0; k < C; ++k) acc[k] += DIFF ? v * (xc.v[k] - xr.v[k]) : v * xc.v[k];
+  };
+  if constexpr (LPR == 1) {
+    constexpr int U = sell_unroll<T, C>();
+#pragma unroll U
+    for (int e = 0; e < len; ++e) add(vp[(int64_t)e * 64], row(cp[(int64_t)e * 64]));
+  } else {
+    constexpr int U = 4, N = U / LPR;  // entries a step, and of those this lane's
+    int32_t c[N];
+    T v[N];
+    auto load = [&](int e0) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const int e = e0 + i * LPR + q;
+        c[i] = e < len ? cp[(int64_t)e * 64] : 0;
+        v[i] = e < len ? vp[(int64_t)e * 64] : T(0);
+      }
+    };
+    load(0);
+    for (int e0 = 0; e0 < len; e0 += U) {
+      int32_t cu[U];
+      T vu[U];
+      spread<LPR>(c, v, cu, vu);
+      load(e0 + U);
+      Row<T, C> xc[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (e0 + u < len) xc[u] = row(cu[u]);  // uniform over the slice
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (e0 + u < len) add(vu[u], xc[u]);
+    }
   }
 }
 
@@ -190,7 +272,7 @@ __device__ __forceinline__ void block_sum_rows(const double (&v)[K / LPR], doubl
 // (A x)_r in difference form, columns [q C, q C + C); the row's own operands
 // are loaded before its entries
 template <class T, int K, int C>
-__device__ __forceinline__ Row<T, C> fine_row(const Sell &A, int64_t s, int t, int q, int64_t r,
+__device__ __forceinline__ Row<T, C> fine_row(const Sell &A, const SliceRef &S, int t, int q, int64_t r,
                                               const T *__restrict__ x, const Row<T, C> &xr) {
   T d0, d1 = T(0);
   if constexpr (std::is_same<T, double>::value) {
@@ -200,7 +282,7 @@ __device__ __forceinline__ Row<T, C> fine_row(const Sell &A, int64_t s, int t, i
     d1 = A.dh32[r];
   }
   T acc[C];
-  sell_row<T, K, C, true>(A, s, t, q, x, xr, acc);
+  sell_span<T, K, C, true>(A, S.begin, S.end, t, q, x, xr, acc);
   Row<T, C> out;
 #pragma unroll
   for (int k = 0; k < C; ++k) {
@@ -212,55 +294,57 @@ __device__ __forceinline__ Row<T, C> fine_row(const Sell &A, int64_t s, int t, i
   return out;
 }
 
-// y_r = -(V x)_r by lane q of row r's lanes, V the part PART of row mi of A
-// (U: the residual after the forward sweep).
+// y_r = -(V x)_r by lane q of row r's lanes, V the entries [begin, end) of row
+// mi's slice (U: the residual after the forward sweep).
 // Bandwidth and gathers bound it, and U holds half of the row: with the
 // forward sweep reading L alone and this product U alone, FP64 solves of
 // 2,179,616 unknowns went from 314.2 to 293.1 ms (eight right-hand sides) and
 // from 123.8 to 115.6 ms (one).  On the same inputs one application of the
 // preconditioner moved by 2e-16 (relative), at aspect ratios 1e-2 to 1e-4.
-template <class T, int K, int PART>
-__device__ __forceinline__ void residual_row(const Sell &A, int64_t mi, int64_t r, int q, const T *__restrict__ x,
-                                             T *y) {
+template <class T, int K>
+__device__ __forceinline__ void residual_row(const Sell &A, int64_t begin, int64_t end, int64_t mi, int64_t r, int q,
+                                             const T *__restrict__ x, T *y) {
   constexpr int LPR = row_lanes<T, K>(), C = K / LPR;
   T s0 = T(1);
   if constexpr (!std::is_same<T, double>::value) s0 = A.s32[mi];
   Row<T, C> out{};
   T acc[C];
-  sell_row<T, K, C, false, PART>(A, mi >> 6, (int)(mi & 63), q, x, out, acc);
+  sell_span<T, K, C, false>(A, begin, end, (int)(mi & 63), q, x, out, acc);
 #pragma unroll
   for (int k = 0; k < C; ++k) out.v[k] = -s0 * acc[k];
   stp<T, K, C>(y, r, q, out);
 }
 
 // Blocks of kBlock rows (four slices), row_lanes<T, K>() lanes per row.
-// order (may be null): the i-th slice of the range visited is s_first +
-// order[i], a permutation of the range's slices; the blocks of one XCD take a
+// order: the range's slices in visit order; the blocks of one XCD take a
 // contiguous part of it.
 template <class T, int K, int MODE, bool DOT>
 __global__ __launch_bounds__((kBlock * row_lanes<T, K>())) void k_spmv(
-    Sell A, int64_t r0, int64_t r1, int64_t s_first, int64_t ns, int64_t nb, const int32_t *__restrict__ order,
+    Sell A, int64_t r0, int64_t r1, int64_t ns, int64_t nb, const SliceRef *__restrict__ order,
     const T *__restrict__ x, T *__restrict__ y, double *__restrict__ partial, const int *__restrict__ done) {
   constexpr int LPR = row_lanes<T, K>(), C = K / LPR;
   static_assert(!(MODE == 1 && DOT), "the residual form has no block reduction");
-  if (done && *done) return;
+  const int stop = stop_flag(done);
   const int64_t blk = xcd_block(blockIdx.x, nb);
   const int rloc = threadIdx.x / LPR, q = threadIdx.x % LPR;
   const int t = rloc & 63;
-  const int64_t i = blk * kSlicesPerBlock + (rloc >> 6);
-  const int64_t s = s_first + (order && i < ns ? (int64_t)order[i] : i);
-  const int64_t r = s * 64 + t;
+  const int64_t i = blk * kSlicesPerBlock + __builtin_amdgcn_readfirstlane(rloc >> 6);
+  SliceRef S{0, 0, 0, 0};
+  if (i < ns) S = order[i];
+  keep(S.end);
+  if (stop) return;
+  const int64_t r = S.slice * 64 + t;
   double prod[C];
 #pragma unroll
   for (int k = 0; k < C; ++k) prod[k] = 0.0;
   if (i < ns && r >= r0 && r < r1) {
     if constexpr (MODE == 1) {
       // no block reduction in this form, so the lane may leave
-      residual_row<T, K, kUpper>(A, r, r, q, x, y);
+      residual_row<T, K>(A, S.mid, S.end, r, r, q, x, y);
       return;
     }
     const Row<T, C> xr = ldp<T, K, C>(x, r, q);
-    const Row<T, C> out = fine_row<T, K, C>(A, s, t, q, r, x, xr);
+    const Row<T, C> out = fine_row<T, K, C>(A, S, t, q, r, x, xr);
     stp<T, K, C>(y, r, q, out);
     if (DOT) {
 #pragma unroll
@@ -282,13 +366,12 @@ struct GsDev {
 // One Gauss-Seidel step of row r by lane q of its row_lanes<T, K>() lanes
 // (columns [q C, q C + C)) with the right-hand side gs g_gi: x_r +
 // (gs g - (A x)_r) / a_rr, or with FIRST (g - (L x)_r) / a_rr, the first
-// sweep's step from zero, which reads L alone.
+// sweep's step from zero, which reads L alone.  [begin, end): the entries of the row's slice (its L entries).
 // (mi: the row's index in A; r and gi: its index in x and in g)
 template <class T, int K, bool FIRST>
-__device__ __forceinline__ void gs_row(const Sell &A, int64_t mi, int64_t r, int64_t gi, T gs, int q,
-                                       const T *__restrict__ g, T *x) {
+__device__ __forceinline__ void gs_row(const Sell &A, int64_t begin, int64_t end, int64_t mi, int64_t r, int64_t gi,
+                                       T gs, int q, const T *__restrict__ g, T *x) {
   constexpr int LPR = row_lanes<T, K>(), C = K / LPR;
-  const int64_t s = mi >> 6;
   const int t = (int)(mi & 63);
   Row<T, C> xr{};
   if constexpr (!FIRST) xr = ldp<T, K, C>(x, r, q);
@@ -302,7 +385,7 @@ __device__ __forceinline__ void gs_row(const Sell &A, int64_t mi, int64_t r, int
     if (!FIRST) d = A.dh32[mi];
   }
   T acc[C];
-  sell_row<T, K, C, !FIRST, FIRST ? kLower : kAll>(A, s, t, q, x, xr, acc, (int32_t)r);
+  sell_span<T, K, C, !FIRST, FIRST>(A, begin, end, t, q, x, xr, acc, (int32_t)r);
   Row<T, C> out;
 #pragma unroll
   for (int k = 0; k < C; ++k) {
@@ -353,17 +436,16 @@ __device__ __forceinline__ void gs_top_row(const Sell &A, int64_t r, int q, cons
   stp<T, K, C>(x, r, q, out);
 }
 
-// the row of block b (of J.nbt) and lane-in-slice t, or -1
+// the slice of block b (of J.nbt) and its rows of the range
+struct GsSlice {
+  int64_t s, r0, r1;
+};
 template <class T>
-__device__ __forceinline__ int64_t gs_block_row(const GsDev<T> &J, int64_t b, int t) {
+__device__ __forceinline__ GsSlice gs_slice(const GsDev<T> &J, int64_t b) {
   int64_t blk = xcd_block(b, J.nbt);
-  int j = 0;
-  while (j + 1 < J.n && blk >= J.nb[j]) {
-    blk -= J.nb[j];
-    ++j;
-  }
-  const int64_t r = (J.sf[j] + blk) * 64 + t;
-  return r < J.r0[j] || r >= J.r1[j] ? -1 : r;
+  const bool second = J.n > 1 && blk >= J.nb[0];
+  if (second) blk -= J.nb[0];
+  return second ? GsSlice{J.sf[1] + blk, J.r0[1], J.r1[1]} : GsSlice{J.sf[0] + blk, J.r0[0], J.r1[0]};
 }
 
 // one slice per block (a colour holds few rows, so small blocks spread them
@@ -373,9 +455,13 @@ template <class T, int K, bool FIRST>
 __global__ __launch_bounds__((kWave * row_lanes<T, K>())) void k_gs(Sell A, GsDev<T> J, const T *__restrict__ g,
                                                                    const int *__restrict__ done) {
   constexpr int LPR = row_lanes<T, K>();
-  if (done && *done) return;
-  const int64_t r = gs_block_row(J, blockIdx.x, threadIdx.x / LPR);
-  if (r >= 0) gs_row<T, K, FIRST>(A, r, r, r, T(1), threadIdx.x % LPR, g, J.x);
+  const int stop = stop_flag(done);
+  const GsSlice S = gs_slice(J, blockIdx.x);
+  const int64_t begin = A.sptr[S.s], end = FIRST ? A.smid[S.s] : A.sptr[S.s + 1];
+  keep(begin, end);
+  if (stop) return;
+  const int64_t r = S.s * 64 + threadIdx.x / LPR;
+  if (r >= S.r0 && r < S.r1) gs_row<T, K, FIRST>(A, begin, end, r, r, r, T(1), threadIdx.x % LPR, g, J.x);
 }
 
 // The merged cycles' colour: k_gs's blocks, then those of D's rows [d0, d1).
@@ -385,22 +471,29 @@ __global__ __launch_bounds__((kWave * row_lanes<T, K>())) void k_gs_merged(Sell 
                                                                           const T *__restrict__ g,
                                                                           const int *__restrict__ done) {
   constexpr int LPR = row_lanes<T, K>();
-  if (done && *done) return;
+  const int stop = stop_flag(done);
   const int t = threadIdx.x / LPR, q = threadIdx.x % LPR;
   if ((int64_t)blockIdx.x >= J.nbt) {
-    const int64_t k = (d0 / 64 + blockIdx.x - J.nbt) * 64 + t;
-    if (k >= d0 && k < d1) gs_row<T, K, FIRST>(FIRST ? M.fwd : M.bwd, k, M.n + k, M.drow[k], T(1), q, g, J.x);
+    const Sell &X = FIRST ? M.fwd : M.bwd;
+    const int64_t s = d0 / 64 + blockIdx.x - J.nbt, begin = X.sptr[s], end = X.sptr[s + 1], k = s * 64 + t;
+    keep(begin, end);
+    if (!stop && k >= d0 && k < d1)
+      gs_row<T, K, FIRST>(X, begin, end, k, M.n + k, M.drow[k], T(1), q, g, J.x);
     return;
   }
-  const int64_t r = gs_block_row(J, blockIdx.x, t);
-  if (r < 0) return;
+  const GsSlice S = gs_slice(J, blockIdx.x);
+  const int64_t begin = A.sptr[S.s], end = FIRST ? A.smid[S.s] : A.sptr[S.s + 1];
+  keep(begin, end);
+  if (stop) return;
+  const int64_t r = S.s * 64 + t;
+  if (r < S.r0 || r >= S.r1) return;
   if constexpr (!FIRST) {
     if (r < M.n_top)
       gs_top_row<T, K>(M.top, r, q, g, J.x);
     else
-      gs_row<T, K, FIRST>(A, r, r, r, T(2), q, g, J.x);
+      gs_row<T, K, FIRST>(A, begin, end, r, r, r, T(2), q, g, J.x);
   } else {
-    gs_row<T, K, FIRST>(A, r, r, r, T(1), q, g, J.x);
+    gs_row<T, K, FIRST>(A, begin, end, r, r, r, T(1), q, g, J.x);
   }
 }
 
@@ -408,22 +501,28 @@ __global__ __launch_bounds__((kWave * row_lanes<T, K>())) void k_gs_merged(Sell 
 // others R's rows.
 template <class T, int K>
 __global__ __launch_bounds__((kBlock * row_lanes<T, K>())) void k_res_merged(Sell A, MergedRows M, int64_t nb,
-                                                                            const int32_t *__restrict__ order,
+                                                                            const SliceRef *__restrict__ order,
                                                                             const T *__restrict__ x,
                                                                             T *__restrict__ y,
                                                                             const int *__restrict__ done) {
   constexpr int LPR = row_lanes<T, K>();
-  if (done && *done) return;
-  const int rloc = threadIdx.x / LPR, q = threadIdx.x % LPR;
+  const int stop = stop_flag(done);
+  const int rloc = threadIdx.x / LPR, q = threadIdx.x % LPR, w = __builtin_amdgcn_readfirstlane(rloc >> 6);
   if ((int64_t)blockIdx.x >= nb) {
-    const int64_t k = (blockIdx.x - nb) * kBlock + rloc;
-    if (k < M.nr) residual_row<T, K, kAll>(M.res, k, M.n + M.rpos[k], q, x, y);
+    const int64_t s = (blockIdx.x - nb) * kSlicesPerBlock + w, k = s * 64 + (rloc & 63);
+    if (s * 64 >= M.nr) return;
+    const int64_t begin = M.res.sptr[s], end = M.res.sptr[s + 1];
+    keep(begin, end);
+    if (!stop && k < M.nr) residual_row<T, K>(M.res, begin, end, k, M.n + M.rpos[k], q, x, y);
     return;
   }
-  const int64_t i = xcd_block(blockIdx.x, nb) * kSlicesPerBlock + (rloc >> 6);
+  const int64_t i = xcd_block(blockIdx.x, nb) * kSlicesPerBlock + w;
   if (i * 64 >= M.n) return;
-  const int64_t r = (int64_t)order[i] * 64 + (rloc & 63);
-  if (r < M.n) residual_row<T, K, kUpper>(A, r, r, q, x, y);
+  const SliceRef S = order[i];
+  keep(S.end);
+  if (stop) return;
+  const int64_t r = S.slice * 64 + (rloc & 63);
+  if (r < M.n) residual_row<T, K>(A, S.mid, S.end, r, r, q, x, y);
 }
 
 // Between the merged sweeps (MergedRows), row_lanes<T, K>() lanes per row: one
@@ -434,12 +533,15 @@ __global__ __launch_bounds__((kBlock * row_lanes<T, K>())) void k_prolong_merged
                                                                                 const T *__restrict__ ya, T *x,
                                                                                 const int *__restrict__ done) {
   constexpr int LPR = row_lanes<T, K>(), C = K / LPR;
-  if (done && *done) return;
+  const int stop = stop_flag(done);
   const int rloc = threadIdx.x / LPR, q = threadIdx.x % LPR;
-  const int64_t r = xcd_block(blockIdx.x, nb) * kBlock + rloc;
-  if (r >= M.n) return;
-  const int64_t s = r >> 6, base = M.prol.sptr[s];
-  const int len = (int)((M.prol.sptr[s + 1] - base) >> 6);
+  const int64_t s = xcd_block(blockIdx.x, nb) * kSlicesPerBlock + __builtin_amdgcn_readfirstlane(rloc >> 6);
+  const int64_t r = s * 64 + (rloc & 63);
+  if (s * 64 >= M.n) return;
+  const int64_t base = M.prol.sptr[s], end = M.prol.sptr[s + 1];
+  keep(base, end);
+  if (stop || r >= M.n) return;
+  const int len = (int)((end - base) >> 6);
   const int32_t *__restrict__ cp = M.prol.col + base + (r & 63);
   const T *__restrict__ vp = sell_vals<T>(M.prol) + base + (r & 63);
   const int32_t pos = M.xpos[r];
@@ -448,16 +550,45 @@ __global__ __launch_bounds__((kBlock * row_lanes<T, K>())) void k_prolong_merged
   T es[C], pa[C];
 #pragma unroll
   for (int k = 0; k < C; ++k) es[k] = pa[k] = T(0);
-#pragma unroll 4
-  for (int e = 0; e < len; ++e) {
-    const int32_t c = cp[(int64_t)e * 64];
-    const T v = vp[(int64_t)e * 64];
-    const bool surf = c < nt;
-    const Row<T, C> yc = ldp<T, K, C>(surf ? ys : ya, surf ? c : c - nt, q);
+  auto row = [&](int32_t c) { return ldp<T, K, C>(c < nt ? ys : ya, c < nt ? c : c - nt, q); };
+  auto add = [&](int32_t c, T v, const Row<T, C> &yc) {
 #pragma unroll
     for (int k = 0; k < C; ++k) {
-      es[k] += (surf ? v : T(0)) * yc.v[k];
-      pa[k] += (surf ? T(0) : v) * yc.v[k];
+      es[k] += (c < nt ? v : T(0)) * yc.v[k];
+      pa[k] += (c < nt ? T(0) : v) * yc.v[k];
+    }
+  };
+  if constexpr (LPR == 1) {
+#pragma unroll 4
+    for (int e = 0; e < len; ++e) {
+      const int32_t c = cp[(int64_t)e * 64];
+      add(c, vp[(int64_t)e * 64], row(c));
+    }
+  } else {  // as sell_span
+    constexpr int U = 4, N = U / LPR;
+    int32_t c[N];
+    T v[N];
+    auto load = [&](int e0) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const int e = e0 + i * LPR + q;
+        c[i] = e < len ? cp[(int64_t)e * 64] : 0;
+        v[i] = e < len ? vp[(int64_t)e * 64] : T(0);
+      }
+    };
+    load(0);
+    for (int e0 = 0; e0 < len; e0 += U) {
+      int32_t cu[U];
+      T vu[U];
+      spread<LPR>(c, v, cu, vu);
+      load(e0 + U);
+      Row<T, C> yc[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (e0 + u < len) yc[u] = row(cu[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (e0 + u < len) add(cu[u], vu[u], yc[u]);
     }
   }
   Row<T, C> out;
@@ -490,7 +621,7 @@ __global__ __launch_bounds__(kBlock) void k_rect(Sell E, int64_t nb, const T *__
 #pragma unroll
   for (int k = 0; k < K; ++k) zero.v[k] = T(0);
   T acc[K];
-  sell_row<T, K, K, false>(E, s, lane, 0, x, zero, acc);
+  sell_span<T, K, K, false>(E, E.sptr[s], E.sptr[s + 1], lane, 0, x, zero, acc);
   Row<T, K> out;
   if (ACC) out = ld<T, K>(y, r);
 #pragma unroll
@@ -516,7 +647,7 @@ __global__ __launch_bounds__(kBlock) void k_prolong_sum(Sell E, int64_t n_top, i
 #pragma unroll
     for (int k = 0; k < K; ++k) zero.v[k] = T(0);
     T acc[K];
-    sell_row<T, K, K, false>(E, s, lane, 0, ys, zero, acc);
+    sell_span<T, K, K, false>(E, E.sptr[s], E.sptr[s + 1], lane, 0, ys, zero, acc);
     Row<T, K> out;
     if (r >= n_top) {
       const Row<T, K> wr = ld<T, K>(w, r);
@@ -644,15 +775,15 @@ __device__ __forceinline__ void group_entries(const int32_t *__restrict__ col, c
   }
 }
 
-// A CsrG operation on row r by lane l of its G * row_lanes<T, K>() lanes.
+// A CsrG operation on row r, entries [b, e), by its G * row_lanes<T, K>() lanes.
 // Bound by the chain row pointer -> entries -> gathered values at K = 1 and by
 // the gathers at K = 8, where a lane of 16 bytes each makes a wavefront's load
 // touch a quarter of the lines that a lane of a whole row does.
 template <class T, int K, int G, CsrMode MODE>
-__device__ __forceinline__ void csr_row(const CsrG &A, int64_t r, int l, const T *__restrict__ x, T *y) {
+__device__ __forceinline__ void csr_row(const CsrG &A, int64_t r, int32_t b, int32_t e, const T *__restrict__ x,
+                                        T *y) {
   constexpr int LPR = row_lanes<T, K>(), C = K / LPR;
-  const int ge = l / LPR, q = l % LPR;
-  const int32_t b = MODE == kCsrUpper ? A.upper[r] : A.ptr[r], e = A.ptr[r + 1];
+  const int l = threadIdx.x % (G * LPR), ge = l / LPR, q = l % LPR;
   // output row of a rectangular operator (its stored rows may be permuted)
   const int64_t ro = MODE != kCsrUpper && A.orow ? (int64_t)A.orow[r] : r;
   T s = T(1);
@@ -676,27 +807,25 @@ __device__ __forceinline__ void csr_row(const CsrG &A, int64_t r, int l, const T
   stp<T, K, C>(y, ro, q, out);
 }
 
-template <class T, int K, int G, CsrMode MODE>
-__device__ __forceinline__ void csr_block(const CsrJob<T> &J, int64_t blk) {
-  constexpr int L = G * row_lanes<T, K>();
-  const int64_t r = (blk * kBlock + threadIdx.x) / L;
-  if (r < J.A.nrows) csr_row<T, K, G, MODE>(J.A, r, threadIdx.x % L, J.x, J.y);
-}
-
 // The blocks of each job are renumbered like the fine kernels', so that each
 // XCD works on a contiguous range of rows and the vector values those rows
 // gather stay in that XCD's L2.
 template <class T, int K, CsrMode MODE>
 __global__ __launch_bounds__(kBlock) void k_csr(Jobs<CsrJob<T>> P, const int *__restrict__ done) {
-  if (done && *done) return;
+  const int stop = stop_flag(done);
   const bool second = (int64_t)blockIdx.x >= P.nb0;
   const CsrJob<T> &J = second ? P.j[1] : P.j[0];
   const int64_t blk = second ? xcd_block(blockIdx.x - P.nb0, P.nb1) : xcd_block(blockIdx.x, P.nb0);
+  const int64_t r = (blk * kBlock + threadIdx.x) / (J.A.G * row_lanes<T, K>());
+  if (r >= J.A.nrows) return;
+  const int32_t b = MODE == kCsrUpper ? J.A.upper[r] : J.A.ptr[r], e = J.A.ptr[r + 1];
+  keep(b, e);
+  if (stop) return;
   switch (J.A.G) {
-    case 2: csr_block<T, K, 2, MODE>(J, blk); break;
-    case 4: csr_block<T, K, 4, MODE>(J, blk); break;
-    case 8: csr_block<T, K, 8, MODE>(J, blk); break;
-    default: csr_block<T, K, 16, MODE>(J, blk); break;
+    case 2: csr_row<T, K, 2, MODE>(J.A, r, b, e, J.x, J.y); break;
+    case 4: csr_row<T, K, 4, MODE>(J.A, r, b, e, J.x, J.y); break;
+    case 8: csr_row<T, K, 8, MODE>(J.A, r, b, e, J.x, J.y); break;
+    default: csr_row<T, K, 16, MODE>(J.A, r, b, e, J.x, J.y); break;
   }
 }
 
@@ -779,7 +908,7 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch_gs(Jobs<PatchJob<T>>
   __shared__ Row<T, K> hs[kPatchLdsRows];
   __shared__ T half[kPatchLdsRows][K];
   __shared__ unsigned ticket;
-  if (done && *done) return;
+  if (*(done ? done : &kNeverDone)) return;  // before a ticket is taken
   // the blocks of two jobs alternate while both last
   const int64_t b = blockIdx.x, both = 2 * (P.nb0 < P.nb1 ? P.nb0 : P.nb1);
   const bool second = b < both ? (b & 1) : P.nb1 > P.nb0;
@@ -1548,21 +1677,21 @@ void launch_slot_copy(hipStream_t stm, unsigned mask, const double *z, double *p
 
 template <class T>
 void launch_spmv(hipStream_t stm, int K, const Sell &A, int mode, int64_t r0, int64_t r1, const T *x, T *y,
-                 double *partial, const int *done, const int32_t *order) {
+                 double *partial, const int *done, const SliceRef *order) {
   int64_t nb = sell_blocks(r0, r1);
   if (!nb) return;
-  int64_t sf = r0 / kWave, ns = (r1 + kWave - 1) / kWave - sf;
+  const int64_t ns = (r1 + kWave - 1) / kWave - r0 / kWave;
   VEMG_K_SWITCH(K, {
     const dim3 blk(kBlock * row_lanes<T, KK>());
     if (mode == 0) {
       if (partial)
-        hipLaunchKernelGGL((k_spmv<T, KK, 0, true>), grid(nb), blk, 0, stm, A, r0, r1, sf, ns, nb, order, x, y,
+        hipLaunchKernelGGL((k_spmv<T, KK, 0, true>), grid(nb), blk, 0, stm, A, r0, r1, ns, nb, order, x, y,
                            partial, done);
       else
-        hipLaunchKernelGGL((k_spmv<T, KK, 0, false>), grid(nb), blk, 0, stm, A, r0, r1, sf, ns, nb, order, x, y,
+        hipLaunchKernelGGL((k_spmv<T, KK, 0, false>), grid(nb), blk, 0, stm, A, r0, r1, ns, nb, order, x, y,
                            partial, done);
     } else {
-      hipLaunchKernelGGL((k_spmv<T, KK, 1, false>), grid(nb), blk, 0, stm, A, r0, r1, sf, ns, nb, order, x, y,
+      hipLaunchKernelGGL((k_spmv<T, KK, 1, false>), grid(nb), blk, 0, stm, A, r0, r1, ns, nb, order, x, y,
                          partial, done);
     }
   })
@@ -1621,7 +1750,7 @@ void launch_gs_merged(hipStream_t stm, int K, const Sell &A, const MergedRows &M
 
 template <class T>
 void launch_res_merged(hipStream_t stm, int K, const Sell &A, const MergedRows &M, const T *x, T *y, const int *done,
-                       const int32_t *order) {
+                       const SliceRef *order) {
   const int64_t nb = sell_blocks(0, M.n), nbx = vec_blocks(M.nr);
   if (!nb) return;
   VEMG_K_SWITCH(K, hipLaunchKernelGGL((k_res_merged<T, KK>), grid(nb + nbx), dim3(kBlock * row_lanes<T, KK>()), 0,
@@ -1813,13 +1942,13 @@ void launch_pcg_resume(hipStream_t stm, int, Scal *s, unsigned keep) {
 
 #define VEMG_INSTANTIATE(T)                                                                                          \
   template void launch_spmv<T>(hipStream_t, int, const Sell &, int, int64_t, int64_t, const T *, T *, double *,       \
-                               const int *, const int32_t *);                                                        \
+                               const int *, const SliceRef *);                                                       \
   template void launch_gs<T>(hipStream_t, int, const Sell &, int64_t, int64_t, int64_t, int64_t, const T *, T *,       \
                              const int *, bool);                                                                     \
   template void launch_gs_merged<T>(hipStream_t, int, const Sell &, const MergedRows &, int64_t, int64_t, int64_t,     \
                                     int64_t, int64_t, int64_t, const T *, T *, const int *, bool);                   \
   template void launch_res_merged<T>(hipStream_t, int, const Sell &, const MergedRows &, const T *, T *, const int *,  \
-                                     const int32_t *);                                                               \
+                                     const SliceRef *);                                                              \
   template void launch_prolong_merged<T>(hipStream_t, int, const MergedRows &, const T *, const T *, T *,             \
                                          const int *);                                                               \
   template void launch_rect<T>(hipStream_t, int, const Sell &, bool, const T *, T *, const int *);                    \

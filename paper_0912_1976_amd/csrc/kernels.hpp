@@ -44,6 +44,12 @@ struct Sell {
   int64_t nrows = 0;
 };
 
+// A slice in a visit order: its number and where its entries, its U entries
+// and its end are (sptr, smid and the next sptr, in one load)
+struct SliceRef {
+  int64_t slice, begin, mid, end;
+};
+
 // CSR matrix (coarse multigrid operators, restrictions, coarse prolongators):
 // a row's entries are dealt in turn to G groups of lanes (a power of two
 // chosen from the mean row length), each group holding the row's K columns 16
@@ -96,12 +102,11 @@ inline int64_t vec_blocks(int64_t n) { return (n + kBlock - 1) / kBlock; }
 // forward multicolour Gauss-Seidel sweep from zero with relaxation 1 that gave
 // x (mode 1): (L + D) x = g, so g - A x = -U x and g is not read.  With
 // partial, partial[block * K + k] = sum over the block's rows of x_ik y_ik.
-// order (optional): the range's slices in visit order (offsets from slice
-// r0 / 64), so that the blocks of one XCD take one spatial region of every
-// colour.
+// order: the range's slices in visit order, such that the blocks of one XCD
+// take one spatial region of every colour.
 template <class T>
 void launch_spmv(hipStream_t st, int K, const Sell &A, int mode, int64_t r0, int64_t r1, const T *x, T *y,
-                 double *partial, const int *done, const int32_t *order = nullptr);
+                 double *partial, const int *done, const SliceRef *order);
 // One multicolour Gauss-Seidel step on the rows [a0,a1) and [b0,b1) (rows of
 // one colour): x_i += (g_i - (A x)_i) / a_ii.  first: the first sweep from
 // x = 0, in ascending colours, x_i = (g_i - (L x)_i) / a_ii; x needs no fill.
@@ -143,7 +148,7 @@ void launch_gs_merged(hipStream_t st, int K, const Sell &A, const MergedRows &M,
 // y = -U x on every row, and on R's extended rows.
 template <class T>
 void launch_res_merged(hipStream_t st, int K, const Sell &A, const MergedRows &M, const T *x, T *y, const int *done,
-                       const int32_t *order);
+                       const SliceRef *order);
 // Between the sweeps: x = x + E~ ys on the top; below it w = (x + E~ ys) +
 // (u + P0 ya), with u + P0 ya stored on X's extended rows.
 template <class T>
