@@ -377,7 +377,9 @@ struct vemg_solver_s {
   vemg::Work<double> v64;
   vemg::Work<float> v32;
   double *b = nullptr, *diag = nullptr, *scale_in = nullptr, *scale_out = nullptr, *dscal = nullptr;
-  double *part_pq = nullptr, *part_rr = nullptr, *part_rz = nullptr, *part_b = nullptr, *part_t = nullptr;
+  double *part_pq = nullptr, *part_rr = nullptr, *part_rz = nullptr, *part_b = nullptr, *part_t = nullptr, *part_c = nullptr;
+  int64_t dot_rows = 0;  // most rows of partial sums of an iteration's dots
+  bool sweep_dot = false;  // the backward sweeps form r . z
   int64_t *perm = nullptr;
   // slice visit orders (spatial, across colours) of the products over all
   // rows and over the non-top rows
@@ -393,7 +395,7 @@ struct vemg_solver_s {
   // the top block of the additive smoother's x (rows [0, n_top) of v64.w and
   // v32.w) is zero in the layout of every batch width up to w_clean
   int w_clean = vemg::kMaxBatch;
-  vemg::Scal *scal = nullptr;
+  vemg::Scal *scal = nullptr;  // two records: between iterations, and within one (launch_pcg_xr)
   int64_t nnz_A = 0, nnz_E = 0;
   std::map<int, vemg::IterGraph> graphs;  // by kind, K and number of iterations
   // false for server lanes once the scheduler runs: a capture on one thread
@@ -735,8 +737,9 @@ CsrJob<T> surface_down(Handle *h, const T *r) {
 // correction through one V-cycle on the surface operator, backward SOR; with
 // dense, the additive smoother of a single dense level runs beside the surface
 // cycle.
+// part (may be null): receives the partial sums of rr . zz; returns their rows
 template <class T>
-void sor_cycle(Handle *h, int K, const T *rr, T *zz, const int *done, bool dense = false) {
+int64_t sor_cycle(Handle *h, int K, const T *rr, T *zz, double *part, const int *done, bool dense = false) {
   hipStream_t st = h->work;
   const Problem &P = h->P;
   const int nc = fine_colours(P);
@@ -761,25 +764,30 @@ void sor_cycle(Handle *h, int K, const T *rr, T *zz, const int *done, bool dense
   coarse_cycles<T>(st, K, S, B, done);
   h->Ab[0].g<T>() = saved;
   if (P.n_top > 0) launch_rect<T>(st, K, h->E, true, h->S[0].x<T>(), zz, done);
+  int64_t np = 0;
   for (int c = nc - 1; c >= 0; --c) {
     const ColourRows q = colour_rows(P, c);
-    launch_gs<T>(st, K, h->A, q.a0, q.a1, q.b0, q.b1, rr, zz, done, false);
+    np += launch_gs<T>(st, K, h->A, q.a0, q.a1, q.b0, q.b1, rr, zz, done, false, part ? part + np * K : nullptr);
   }
+  return np;
 }
 
 // zz = VL_SOR(rr) + Z Vcyc_Abar(Z^T rr) with one pair of fine sweeps for both
-// cycles (MergedRows); zz has n + nx rows.
+// cycles (MergedRows); zz has n + nx rows.  part as in sor_cycle.
 template <class T>
-void merged_cycle(Handle *h, int K, const T *rr, T *zz, const int *done) {
+int64_t merged_cycle(Handle *h, int K, const T *rr, T *zz, double *part, const int *done) {
   hipStream_t st = h->work;
   const Problem &P = h->P;
   const int nc = fine_colours(P);
   Work<T> &v = work_of<T>(h);
+  int64_t np = 0;
   auto sweep = [&](int c, bool first) {
     const ColourRows q = colour_rows(P, c);
     const bool d = c + 1 < (int)h->dstart.size();
-    launch_gs_merged<T>(st, K, h->A, h->M, q.a0, q.a1, q.b0, q.b1, d ? h->dstart[c] : 0, d ? h->dstart[c + 1] : 0,
-                        rr, zz, done, first);
+    const int64_t nb =
+        launch_gs_merged<T>(st, K, h->A, h->M, q.a0, q.a1, q.b0, q.b1, d ? h->dstart[c] : 0, d ? h->dstart[c + 1] : 0,
+                            rr, zz, done, first, first || !part ? nullptr : part + np * K);
+    if (!first) np += nb;
   };
   for (int c = 0; c < nc; ++c) sweep(c, true);
   launch_res_merged<T>(st, K, h->A, h->M, zz, v.res, done, h->order_all);
@@ -794,6 +802,7 @@ void merged_cycle(Handle *h, int K, const T *rr, T *zz, const int *done) {
   const T *ya = h->Ab[1].x<T>();
   launch_prolong_merged<T>(st, K, h->M, P.n_top > 0 ? h->S[0].x<T>() : ya, ya, zz, done);
   for (int c = nc - 1; c >= 0; --c) sweep(c, false);
+  return np;
 }
 
 // w = Z Vcyc_Abar(Z^T rr) (the additive smoother; rows of the top block of w
@@ -806,8 +815,9 @@ void additive_smoother(Handle *h, int K, const T *rr, Cycle<T> other, const CsrJ
   h->Ab[0].g<T>() = saved;
 }
 
-// z = M^{-1} rr in precision T; partial sums of rr . z go to part (blocks in
-// *np).  zz: the handle's own z vector (the merged cycles extend it).
+// z = M^{-1} rr in precision T; partial sums of rr . z go to part (rows in
+// *np) unless it is null.  zz: the handle's own z vector (the merged cycles
+// extend it).
 template <class T>
 void precond(Handle *h, int K, const T *rr, T *zz, double *part, int64_t *np, const int *done) {
   hipStream_t st = h->work;
@@ -818,26 +828,32 @@ void precond(Handle *h, int K, const T *rr, T *zz, double *part, int64_t *np, co
   switch (h->opt.pc) {
     case VEMG_PC_VL_ADDITIVE:
       if (h->merged) {
-        merged_cycle<T>(h, K, rr, zz, done);
-        break;
+        const int64_t rows = merged_cycle<T>(h, K, rr, zz, h->sweep_dot ? part : nullptr, done);
+        if (!h->sweep_dot) break;
+        *np = rows;
+        return;
       }
-      sor_cycle<T>(h, K, rr, zz, done, true);
-      launch_add_dot<T>(st, K, v.w, rr, zz, P.n_top, n, part, done);
+      sor_cycle<T>(h, K, rr, zz, nullptr, done, true);
+      launch_add_dot<T>(st, K, v.w, rr, zz, P.n_top, n, part ? part : h->part_t, done);
       return;
     case VEMG_PC_VL_ADDITIVE_ONLY:
       if (P.n_top > 0) {
         const CsrJob<T> J = surface_down<T>(h, rr);
         additive_smoother<T>(h, K, rr, cycle<T>(h->S, 0), &J, done);
-        launch_prolong_sum<T>(st, K, h->E, P.n_top, h->S[0].x<T>(), v.w, rr, zz, part, done);
+        launch_prolong_sum<T>(st, K, h->E, P.n_top, h->S[0].x<T>(), v.w, rr, zz, part ? part : h->part_t,
+                              done);
         *np = sell_blocks(0, n);
         return;
       }
       additive_smoother<T>(h, K, rr, Cycle<T>(), nullptr, done);  // empty surface: the smoother alone
       launch_copy<T>(st, v.w, zz, n * K, done);
       break;
-    case VEMG_PC_VL_SOR:
-      sor_cycle<T>(h, K, rr, zz, done);
-      break;
+    case VEMG_PC_VL_SOR: {
+      const int64_t rows = sor_cycle<T>(h, K, rr, zz, h->sweep_dot ? part : nullptr, done);
+      if (!h->sweep_dot) break;
+      *np = rows;
+      return;
+    }
     case VEMG_PC_SA: {
       // one V-cycle of the baseline hierarchy, its fine level on rr -> zz
       DLevel &F = h->SA[0];
@@ -856,7 +872,7 @@ void precond(Handle *h, int K, const T *rr, T *zz, double *part, int64_t *np, co
       launch_copy<T>(st, rr, zz, n * K, done);
       break;
   }
-  launch_dot<T>(st, K, rr, zz, n, part, done);
+  if (part) launch_dot<T>(st, K, rr, zz, n, part, done);
 }
 
 // The additive smoother reads the top columns of its x and takes them as
@@ -873,14 +889,12 @@ void batch_layout(Handle *h, int K) {
   h->w_clean = K;
 }
 
-// FP64 CG with the preconditioner applied in FP32 (columns scaled by scale_in)
+// zz = M^{-1} rr in FP32 for FP64 CG (columns scaled by scale_in, rr already
+// scaled and rounded into v32.tmp), with the partial sums of rr . zz in part_rz
 int64_t precond_mixed(Handle *h, int K, const double *rr, double *zz, const int *done) {
-  hipStream_t st = h->work;
   int64_t n = h->P.n, np = 0;
-  launch_demote(st, K, rr, h->scale_in, h->v32.tmp, n, done);
-  precond<float>(h, K, h->v32.tmp, h->v32.z, h->part_t, &np, done);
-  launch_promote(st, K, h->v32.z, h->scale_out, zz, n, false, done);
-  launch_dot<double>(st, K, rr, zz, n, h->part_rz, done);
+  precond<float>(h, K, h->v32.tmp, h->v32.z, nullptr, &np, done);
+  launch_promote_dot(h->work, K, h->v32.z, h->scale_out, rr, zz, n, h->part_rz, done);
   return vec_blocks(n);
 }
 
@@ -908,21 +922,43 @@ void pcg_iteration(Handle *h, int K, int kind) {
   hipStream_t st = h->work;
   int64_t n = h->P.n;
   Work<T> &v = work_of<T>(h);
-  const int *done = &h->scal->all_done;
-  launch_spmv<T>(st, K, h->A, 0, 0, n, v.p, v.q, h->part_pq, done, h->order_all);
-  launch_pcg_alpha(st, K, h->scal, h->part_pq, sell_blocks(0, n));
-  launch_pcg_xr<T>(st, K, h->scal, v.x, v.r, v.p, v.q, n, h->part_rr);
-  launch_pcg_conv(st, K, h->scal, h->part_rr, vec_blocks(n));
+  launch_spmv<T>(st, K, h->A, 0, 0, n, v.p, v.q, h->part_pq, &h->scal->all_done, h->order_all);
+  const bool mixed = kind == kGraphMixedPC;
+  Scal *in = h->scal, *mid = h->scal + 1;
+  // the partial sums of a scalar step, added in parts first where they are many
+  auto sums = [&](const double *p, int64_t np, const Scal *s) {
+    if (np <= kCompactFrom) return PartialSums{p, np};
+    launch_compact(st, K, p, np, h->part_c, &s->all_done);
+    return PartialSums{h->part_c, kCompact};
+  };
+  const bool fold = pcg_folds(h->dot_rows, K);
+  const int64_t nv = vec_blocks(n);
+  PartialSums pq = sums(h->part_pq, sell_blocks(0, n), in);
+  if (!fold) {
+    launch_pcg_alpha(st, K, in, mid, pq);
+    pq = PartialSums();
+  }
+  launch_pcg_xr<T>(st, K, in, mid, pq, v.x, v.r, v.p, v.q, n, h->part_rr, mixed ? h->v32.tmp : nullptr, h->scale_in);
+  PartialSums rr{h->part_rr, nv};
+  if (!fold || n > kFoldConvMax) {
+    launch_pcg_conv(st, K, mid, sums(h->part_rr, nv, mid));
+    rr = PartialSums();
+  }
+  const int *done = &mid->all_done;
   if constexpr (std::is_same<T, float>::value)
     if (kind == kGraphFP32Reliable) reliable_update(h, K);
   int64_t np = 0;
-  if (kind == kGraphMixedPC) {
+  if (mixed) {
     if constexpr (std::is_same<T, double>::value) np = precond_mixed(h, K, v.r, v.z, done);
   } else {
     precond<T>(h, K, v.r, v.z, h->part_rz, &np, done);
   }
-  launch_pcg_beta(st, K, h->scal, h->part_rz, np);
-  launch_pcg_p<T>(st, K, h->scal, v.p, v.z, n);
+  PartialSums rz{h->part_rz, np};
+  if (!fold) {
+    launch_pcg_beta(st, K, mid, in, sums(h->part_rz, np, mid));
+    rz = PartialSums();
+  }
+  launch_pcg_p<T>(st, K, mid, in, rr, rz, v.p, v.z, n);
 }
 
 void destroy_graphs(Handle *h) {
@@ -1062,9 +1098,10 @@ void solve_cg(Handle *h, int K, double rtol, int max_iter, ColResult *res) {
   }
   while (true) {
     int64_t np = 0;
-    if (mixed)
+    if (mixed) {
+      launch_demote(st, K, v.r, h->scale_in, h->v32.tmp, n, nullptr);
       np = precond_mixed(h, K, v.r, v.z, nullptr);
-    else
+    } else
       precond<double>(h, K, v.r, v.z, h->part_rz, &np, nullptr);
     launch_pcg_set_rho(st, K, h->scal, h->part_rz, np);
     launch_copy<double>(st, v.z, v.p, n * K, nullptr);
@@ -1311,6 +1348,8 @@ int64_t merged_rows(Handle *h) {
   return M.nx;
 }
 
+constexpr int64_t kSweepDotMax = 65536, kSweepDotMin = 1000000;
+
 // Packs the host setup into HBM.  With h->ar.count_only the same sequence
 // of allocations is only counted (no device call), which gives the footprint
 // of a handle before (or without) its upload.
@@ -1379,15 +1418,25 @@ void upload(Handle *h) {
   h->order_all = slice_order(0, n);
   h->order_bar = slice_order(m, n);
   int64_t npmax = (std::max(sell_blocks(0, n), vec_blocks(n)) + 8) * kMaxBatch;
+  // A sweep's dot has a row of partial sums per slice and colour (those a
+  // boundary cuts count twice), a dot of its own one per 256 rows.  The sweep
+  // forms it where its rows are few enough to be added by every block
+  // (launch_pcg_p) or the vectors too long to be read once more (44 us at
+  // 2,179,616 unknowns, K = 8); between, 341,825 unknowns with vl_sor took 17.8
+  // ms so and 17.1 with a dot of its own.  By the mesh alone, so that a batch's columns keep the single
+  // column's sums.
+  h->sweep_dot = n <= kSweepDotMax || n >= kSweepDotMin;
+  h->dot_rows = h->sweep_dot ? n / kWave + 4 * (fine_colours(P) + 1) : vec_blocks(n);
   h->part_pq = h->ar.alloc<double>(npmax);
   h->part_rr = h->ar.alloc<double>(npmax);
-  h->part_rz = h->ar.alloc<double>(npmax);
+  h->part_rz = h->ar.alloc<double>(std::max(npmax, h->dot_rows * kMaxBatch));
+  h->part_c = h->ar.alloc<double>(kCompact * kMaxBatch);
   h->part_b = h->ar.alloc<double>(npmax);
   h->part_t = h->ar.alloc<double>(npmax);
   h->dscal = h->ar.alloc<double>(kMaxBatch);
   h->scale_in = h->ar.alloc<double>(kMaxBatch);
   h->scale_out = h->ar.alloc<double>(kMaxBatch);
-  h->scal = h->ar.alloc<Scal>(1);
+  h->scal = h->ar.alloc<Scal>(2);
   if (!count) {
     // every column starts finished (no right-hand side yet)
     launch_fill<double>(st, h->part_b, kMaxBatch, 0.0, nullptr);
@@ -1912,9 +1961,10 @@ void lane_start(Lane &L, unsigned mask, bool restart) {
   launch_slot_scalars(st, mask, restart, h->scal, h->part_b, vec_blocks(n), lane_stop(L), h->scale_in,
                       h->scale_out);
   int64_t np = 0;
-  if (h->opt.precision != VEMG_FP64)
+  if (h->opt.precision != VEMG_FP64) {
+    launch_demote(st, kMaxBatch, h->v64.r, h->scale_in, h->v32.tmp, n, nullptr);
     np = precond_mixed(h, kMaxBatch, h->v64.r, h->v64.z, nullptr);
-  else
+  } else
     precond<double>(h, kMaxBatch, h->v64.r, h->v64.z, h->part_rz, &np, nullptr);
   launch_slot_rho(st, mask, h->scal, h->part_rz, np);
   launch_slot_copy(st, mask, h->v64.z, h->v64.p, n);

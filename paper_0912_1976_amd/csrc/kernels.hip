@@ -78,6 +78,88 @@ __device__ __forceinline__ void block_sum_store(const double (&v)[K], double *ou
   }
 }
 
+// v + the value of lane (own lane xor D), D a power of two, in a few vector
+// instructions (a shuffle through LDS costs a pass of the LDS per word: at
+// K = 8 the reductions by shuffles took most of the restriction's time)
+template <int D>
+__device__ __forceinline__ int lane_xor(int v) {
+  static_assert(D == 1 || D == 2 || D == 4 || D == 8, "lane_xor");
+  if constexpr (D == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);   // quad_perm [1,0,3,2]
+  if constexpr (D == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);   // quad_perm [2,3,0,1]
+  if constexpr (D == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, true);  // row_ror 8
+  if constexpr (D == 4) {
+    const int t = __builtin_amdgcn_update_dpp(0, v, 0x104, 0xf, 0x5, false);  // row_shl 4 in the even banks
+    return __builtin_amdgcn_update_dpp(t, v, 0x114, 0xf, 0xa, false);         // row_shr 4 in the odd ones
+  }
+}
+// cache policy of loads and stores at agent scope on gfx950 (sc1)
+constexpr int kAgentScope = 16;
+
+template <class T, int N>
+struct Words {
+  int w[N];
+};
+template <int D, class T>
+__device__ __forceinline__ T add_xor(T v) {
+  constexpr int N = sizeof(T) / 4;
+  const auto a = __builtin_bit_cast(Words<T, N>, v);
+  Words<T, N> p, q = a;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if constexpr (D == 16) {
+      const auto r = __builtin_amdgcn_permlane16_swap((unsigned)a.w[i], (unsigned)a.w[i], false, false);
+      q.w[i] = r[0];
+      p.w[i] = r[1];
+    } else if constexpr (D == 32) {
+      const auto r = __builtin_amdgcn_permlane32_swap((unsigned)a.w[i], (unsigned)a.w[i], false, false);
+      q.w[i] = r[0];
+      p.w[i] = r[1];
+    } else {
+      p.w[i] = lane_xor<D>(a.w[i]);
+    }
+  }
+  return __builtin_bit_cast(T, q) + __builtin_bit_cast(T, p);
+}
+
+// Sums v over the 64 rows of a block of 64 LPR threads (LPR lanes a row) into
+// out[0..K): adjacent rows first, then pairs of pairs and so on, the same tree
+// for every LPR.  Every thread of the block must call it.
+template <int D>
+__device__ __forceinline__ double rows_tree(double v) {
+  if constexpr (D < kWave)
+    return rows_tree<2 * D>(add_xor<D>(v));
+  else
+    return v;
+}
+template <int K, int LPR>
+__device__ __forceinline__ void slice_sum_store(const double (&v)[K / LPR], double *out) {
+  constexpr int C = K / LPR;
+  double t[C];
+#pragma unroll
+  for (int k = 0; k < C; ++k) t[k] = rows_tree<LPR>(v[k]);
+  const int lane = threadIdx.x & 63;
+  if constexpr (LPR == 1) {
+    if (lane == 0) {
+#pragma unroll
+      for (int k = 0; k < C; ++k) out[k] = t[k];
+    }
+  } else {
+    __shared__ double red[LPR][K];
+    if (lane < LPR) {
+#pragma unroll
+      for (int k = 0; k < C; ++k) red[threadIdx.x >> 6][lane * C + k] = t[k];
+    }
+    __syncthreads();
+    const int k = threadIdx.x;
+    if (k < K) {
+      if constexpr (LPR == 4)
+        out[k] = (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
+      else
+        out[k] = red[0][k] + red[1][k];
+    }
+  }
+}
+
 template <class T>
 __device__ __forceinline__ const T *sell_vals(const Sell &A);
 template <>
@@ -367,10 +449,12 @@ struct GsDev {
 // (columns [q C, q C + C)) with the right-hand side gs g_gi: x_r +
 // (gs g - (A x)_r) / a_rr, or with FIRST (g - (L x)_r) / a_rr, the first
 // sweep's step from zero, which reads L alone.  [begin, end): the entries of the row's slice (its L entries).
+// prod: g x of the row.
 // (mi: the row's index in A; r and gi: its index in x and in g)
 template <class T, int K, bool FIRST>
 __device__ __forceinline__ void gs_row(const Sell &A, int64_t begin, int64_t end, int64_t mi, int64_t r, int64_t gi,
-                                       T gs, int q, const T *__restrict__ g, T *x) {
+                                       T gs, int q, const T *__restrict__ g, T *x,
+                                       double (&prod)[K / row_lanes<T, K>()]) {
   constexpr int LPR = row_lanes<T, K>(), C = K / LPR;
   const int t = (int)(mi & 63);
   Row<T, C> xr{};
@@ -393,6 +477,7 @@ __device__ __forceinline__ void gs_row(const Sell &A, int64_t begin, int64_t end
       out.v[k] = xr.v[k] + (gs * gr.v[k] - (acc[k] + d * xr.v[k])) * i0;
     else
       out.v[k] = xr.v[k] + (gs * gr.v[k] * i0 - (acc[k] + d * xr.v[k]));
+    prod[k] = (double)gr.v[k] * (double)out.v[k];
   }
   stp<T, K, C>(x, r, q, out);
 }
@@ -400,7 +485,8 @@ __device__ __forceinline__ void gs_row(const Sell &A, int64_t begin, int64_t end
 // The backward step of top row r of the merged cycles: as gs_row, its non-top
 // neighbours' values taken as w - u (MergedRows).
 template <class T, int K>
-__device__ __forceinline__ void gs_top_row(const Sell &A, int64_t r, int q, const T *__restrict__ g, T *x) {
+__device__ __forceinline__ void gs_top_row(const Sell &A, int64_t r, int q, const T *__restrict__ g, T *x,
+                                           double (&prod)[K / row_lanes<T, K>()]) {
   constexpr int LPR = row_lanes<T, K>(), C = K / LPR;
   const int64_t s = r >> 6, base = A.sptr[s];
   const int t = (int)(r & 63), len = (int)((A.sptr[s + 1] - base) >> 6);
@@ -432,6 +518,7 @@ __device__ __forceinline__ void gs_top_row(const Sell &A, int64_t r, int q, cons
       out.v[k] = xr.v[k] + (gr.v[k] - (acc[k] + d * xr.v[k])) * i0;
     else
       out.v[k] = xr.v[k] + (gr.v[k] * i0 - (acc[k] + d * xr.v[k]));
+    prod[k] = (double)gr.v[k] * (double)out.v[k];
   }
   stp<T, K, C>(x, r, q, out);
 }
@@ -453,6 +540,7 @@ __device__ __forceinline__ GsSlice gs_slice(const GsDev<T> &J, int64_t b) {
 // top and the non-top rows of one colour)
 template <class T, int K, bool FIRST>
 __global__ __launch_bounds__((kWave * row_lanes<T, K>())) void k_gs(Sell A, GsDev<T> J, const T *__restrict__ g,
+                                                                   double *__restrict__ dot,
                                                                    const int *__restrict__ done) {
   constexpr int LPR = row_lanes<T, K>();
   const int stop = stop_flag(done);
@@ -461,7 +549,9 @@ __global__ __launch_bounds__((kWave * row_lanes<T, K>())) void k_gs(Sell A, GsDe
   keep(begin, end);
   if (stop) return;
   const int64_t r = S.s * 64 + threadIdx.x / LPR;
-  if (r >= S.r0 && r < S.r1) gs_row<T, K, FIRST>(A, begin, end, r, r, r, T(1), threadIdx.x % LPR, g, J.x);
+  double prod[K / LPR] = {};
+  if (r >= S.r0 && r < S.r1) gs_row<T, K, FIRST>(A, begin, end, r, r, r, T(1), threadIdx.x % LPR, g, J.x, prod);
+  if (!FIRST && dot) slice_sum_store<K, LPR>(prod, dot + (int64_t)blockIdx.x * K);
 }
 
 // The merged cycles' colour: k_gs's blocks, then those of D's rows [d0, d1).
@@ -469,16 +559,18 @@ template <class T, int K, bool FIRST>
 __global__ __launch_bounds__((kWave * row_lanes<T, K>())) void k_gs_merged(Sell A, MergedRows M, GsDev<T> J,
                                                                           int64_t d0, int64_t d1,
                                                                           const T *__restrict__ g,
+                                                                          double *__restrict__ dot,
                                                                           const int *__restrict__ done) {
   constexpr int LPR = row_lanes<T, K>();
   const int stop = stop_flag(done);
   const int t = threadIdx.x / LPR, q = threadIdx.x % LPR;
+  double prod[K / LPR] = {};
   if ((int64_t)blockIdx.x >= J.nbt) {
     const Sell &X = FIRST ? M.fwd : M.bwd;
     const int64_t s = d0 / 64 + blockIdx.x - J.nbt, begin = X.sptr[s], end = X.sptr[s + 1], k = s * 64 + t;
     keep(begin, end);
     if (!stop && k >= d0 && k < d1)
-      gs_row<T, K, FIRST>(X, begin, end, k, M.n + k, M.drow[k], T(1), q, g, J.x);
+      gs_row<T, K, FIRST>(X, begin, end, k, M.n + k, M.drow[k], T(1), q, g, J.x, prod);
     return;
   }
   const GsSlice S = gs_slice(J, blockIdx.x);
@@ -486,15 +578,13 @@ __global__ __launch_bounds__((kWave * row_lanes<T, K>())) void k_gs_merged(Sell 
   keep(begin, end);
   if (stop) return;
   const int64_t r = S.s * 64 + t;
-  if (r < S.r0 || r >= S.r1) return;
-  if constexpr (!FIRST) {
-    if (r < M.n_top)
-      gs_top_row<T, K>(M.top, r, q, g, J.x);
+  if (r >= S.r0 && r < S.r1) {
+    if (!FIRST && r < M.n_top)
+      gs_top_row<T, K>(M.top, r, q, g, J.x, prod);
     else
-      gs_row<T, K, FIRST>(A, begin, end, r, r, r, T(2), q, g, J.x);
-  } else {
-    gs_row<T, K, FIRST>(A, begin, end, r, r, r, T(1), q, g, J.x);
+      gs_row<T, K, FIRST>(A, begin, end, r, r, r, FIRST ? T(1) : T(2), q, g, J.x, prod);
   }
+  if (!FIRST && dot) slice_sum_store<K, LPR>(prod, dot + (int64_t)blockIdx.x * K);
 }
 
 // The merged cycles' residual: blocks [0, nb) as k_spmv's over all rows, the
@@ -672,49 +762,6 @@ struct Jobs {
   J j[2];
   int64_t nb0, nb1;
 };
-
-// v + the value of lane (own lane xor D), D a power of two, in a few vector
-// instructions (a shuffle through LDS costs a pass of the LDS per word: at
-// K = 8 the reductions by shuffles took most of the restriction's time)
-template <int D>
-__device__ __forceinline__ int lane_xor(int v) {
-  static_assert(D == 1 || D == 2 || D == 4 || D == 8, "lane_xor");
-  if constexpr (D == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);   // quad_perm [1,0,3,2]
-  if constexpr (D == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);   // quad_perm [2,3,0,1]
-  if constexpr (D == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, true);  // row_ror 8
-  if constexpr (D == 4) {
-    const int t = __builtin_amdgcn_update_dpp(0, v, 0x104, 0xf, 0x5, false);  // row_shl 4 in the even banks
-    return __builtin_amdgcn_update_dpp(t, v, 0x114, 0xf, 0xa, false);         // row_shr 4 in the odd ones
-  }
-}
-// cache policy of loads and stores at agent scope on gfx950 (sc1)
-constexpr int kAgentScope = 16;
-
-template <class T, int N>
-struct Words {
-  int w[N];
-};
-template <int D, class T>
-__device__ __forceinline__ T add_xor(T v) {
-  constexpr int N = sizeof(T) / 4;
-  const auto a = __builtin_bit_cast(Words<T, N>, v);
-  Words<T, N> p, q = a;
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    if constexpr (D == 16) {
-      const auto r = __builtin_amdgcn_permlane16_swap((unsigned)a.w[i], (unsigned)a.w[i], false, false);
-      q.w[i] = r[0];
-      p.w[i] = r[1];
-    } else if constexpr (D == 32) {
-      const auto r = __builtin_amdgcn_permlane32_swap((unsigned)a.w[i], (unsigned)a.w[i], false, false);
-      q.w[i] = r[0];
-      p.w[i] = r[1];
-    } else {
-      p.w[i] = lane_xor<D>(a.w[i]);
-    }
-  }
-  return __builtin_bit_cast(T, q) + __builtin_bit_cast(T, p);
-}
 
 // Sums over the G groups of LPR lanes each (lane = group * LPR + q): the
 // same tree over the groups whatever LPR is.
@@ -1443,47 +1490,176 @@ __device__ __forceinline__ void store_all_done(Scal *s, int K, int mine) {
   }
 }
 
+// sum_partials for a K known at compile time, by a block of kBlock threads
 template <int K>
-__global__ __launch_bounds__(wide_block<K>()) void k_pcg_alpha(Scal *s, const double *p, int64_t np) {
-  if (s->all_done) return;
+__device__ __forceinline__ void sum_rows(const double *__restrict__ p, int64_t np, double (&res)[K]) {
+  double t[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) t[k] = 0.0;
+  constexpr int U = K >= 4 ? 2 : 8;
+  for (int64_t j = threadIdx.x; j < np; j += U * kBlock) {
+    Row<double, K> w[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (j + u * kBlock < np) w[u] = ld<double, K>(p, j + u * kBlock);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (j + u * kBlock < np) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) t[k] += w[u].v[k];
+      }
+  }
+  __shared__ double buf[K][kSlicesPerBlock];
+#pragma unroll
+  for (int k = 0; k < K; ++k) t[k] = wave_sum(t[k]);
+  __syncthreads();
+  if ((threadIdx.x & (kWave - 1)) == 0) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) buf[k][threadIdx.x / kWave] = t[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    double r = 0.0;
+#pragma unroll
+    for (int w = 0; w < kSlicesPerBlock; ++w) r += buf[k][w];
+    res[k] = r;
+  }
+}
+
+template <int K>
+__global__ __launch_bounds__(kBlock) void k_compact(const double *__restrict__ p, int64_t np,
+                                                    double *__restrict__ out, const int *__restrict__ done) {
+  const int stop = stop_flag(done);
+  if (stop) return;
+  const int64_t chunk = (np + kCompact - 1) / kCompact, r0 = blockIdx.x * chunk;
+  double s[K];
+  sum_rows<K>(p + r0 * K, r0 >= np ? 0 : np - r0 < chunk ? np - r0 : chunk, s);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) out[(int64_t)blockIdx.x * K + k] = s[k];
+  }
+}
+
+// The scalar steps of one column, from the record `s` and the column's sum.
+struct Alpha {
+  double alpha;
+  int done, status;
+};
+__device__ __forceinline__ Alpha alpha_step(const Scal *s, int k, double pq) {
+  Alpha a{s->alpha[k], s->done[k], s->status[k]};
+  if (a.done) return a;
+  const double rho = s->rho[k];
+  if (!(pq > 0.0) || !isfinite(pq) || !isfinite(rho)) return Alpha{0.0, 1, -6};
+  a.alpha = rho / pq;
+  return a;
+}
+struct Conv {
+  int iters, done, status;
+};
+__device__ __forceinline__ Conv conv_step(const Scal *s, int k, double rr) {
+  Conv c{s->iters[k], s->done[k], s->status[k]};
+  if (c.done) return c;
+  ++c.iters;
+  c.status = !isfinite(rr) ? -6 : rr <= s->tol2[k] * s->bnorm2[k] ? 1 : c.iters >= s->maxit[k] ? 2 : 0;
+  c.done = c.status != 0;
+  return c;
+}
+// thread k copies column k's record (the columns beyond K too)
+__device__ __forceinline__ void copy_record(const Scal *in, Scal *out) {
+  const int k = threadIdx.x;
+  if (k < kMaxBatch) {
+    out->rho[k] = in->rho[k];
+    out->alpha[k] = in->alpha[k];
+    out->beta[k] = in->beta[k];
+    out->bnorm2[k] = in->bnorm2[k];
+    out->rr[k] = in->rr[k];
+    out->pq[k] = in->pq[k];
+    out->tol2[k] = in->tol2[k];
+    out->done[k] = in->done[k];
+    out->iters[k] = in->iters[k];
+    out->status[k] = in->status[k];
+    out->maxit[k] = in->maxit[k];
+  }
+  if (k == 0) {
+    out->all_done = in->all_done;
+    out->K = in->K;
+  }
+}
+
+template <int K>
+__global__ __launch_bounds__(wide_block<K>()) void k_pcg_alpha(const Scal *in, Scal *out, const double *p,
+                                                               int64_t np) {
+  copy_record(in, out);
+  if (in->all_done) return;
   double sums[kMaxBatch];
   sum_partials_wide<K>(p, np, sums);
   const int k = threadIdx.x;
   int done = 1;
   if (k < K) {
-    done = s->done[k];
-    if (!done) {
-      const double pq = column_of(sums, k), rho = s->rho[k];
-      s->pq[k] = pq;
-      if (!(pq > 0.0) || !isfinite(pq) || !isfinite(rho)) {
-        done = 1;
-        s->done[k] = 1;
-        s->status[k] = -6;
-        s->alpha[k] = 0.0;
-      } else {
-        s->alpha[k] = rho / pq;
-      }
-    }
+    const double pq = column_of(sums, k);
+    const Alpha a = alpha_step(in, k, pq);
+    if (!in->done[k]) out->pq[k] = pq;
+    out->alpha[k] = a.alpha;
+    out->status[k] = a.status;
+    out->done[k] = done = a.done;
   }
-  store_all_done(s, K, done);
+  store_all_done(out, K, done);
 }
 
-template <class T, int K>
-__global__ __launch_bounds__(kBlock) void k_pcg_xr(const Scal *s, T *__restrict__ x, T *__restrict__ r,
-                                                   const T *__restrict__ p, const T *__restrict__ q, int64_t n,
-                                                   double *__restrict__ partial) {
-  if (s->all_done) return;
-  int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+// FOLD: the block forms alpha itself (in -> out written by the first block);
+// else `in` holds it.
+template <class T, int K, bool FOLD, bool DEMOTE>
+__global__ __launch_bounds__(kBlock) void k_pcg_xr(const Scal *__restrict__ in, Scal *__restrict__ out,
+                                                   const double *__restrict__ pq, int64_t np, T *__restrict__ x,
+                                                   T *__restrict__ r, const T *__restrict__ p,
+                                                   const T *__restrict__ q, int64_t n, double *__restrict__ partial,
+                                                   float *__restrict__ r32, const double *__restrict__ scale) {
+  if (FOLD && blockIdx.x == 0) copy_record(in, out);
+  if (in->all_done) return;
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  Row<T, K> xi{}, ri{}, pi{}, qi{};
+  if (i < n) {
+    xi = ld<T, K>(x, i);
+    ri = ld<T, K>(r, i);
+    pi = ld<T, K>(p, i);
+    qi = ld<T, K>(q, i);
+  }
+  double al[K];
+  int dn[K];
+  if constexpr (FOLD) {
+    double sums[K];
+    sum_rows<K>(pq, np, sums);
+    int all = 1;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const Alpha a = alpha_step(in, k, sums[k]);
+      al[k] = a.alpha;
+      dn[k] = a.done;
+      all &= a.done;
+      if (blockIdx.x == 0 && threadIdx.x == k) {
+        if (!in->done[k]) out->pq[k] = sums[k];
+        out->alpha[k] = a.alpha;
+        out->status[k] = a.status;
+        out->done[k] = a.done;
+      }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) out->all_done = all;
+  } else {
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      al[k] = in->alpha[k];
+      dn[k] = in->done[k];
+    }
+  }
   double t[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) t[k] = 0.0;
   if (i < n) {
-    Row<T, K> xi = ld<T, K>(x, i), ri = ld<T, K>(r, i);
-    const Row<T, K> pi = ld<T, K>(p, i), qi = ld<T, K>(q, i);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      if (!s->done[k]) {
-        const T a = (T)s->alpha[k];
+      if (!dn[k]) {
+        const T a = (T)al[k];
         xi.v[k] += a * pi.v[k];
         ri.v[k] -= a * qi.v[k];
       }
@@ -1491,6 +1667,12 @@ __global__ __launch_bounds__(kBlock) void k_pcg_xr(const Scal *s, T *__restrict_
     }
     st<T, K>(x, i, xi);
     st<T, K>(r, i, ri);
+    if constexpr (DEMOTE) {
+      Row<float, K> d;
+#pragma unroll
+      for (int k = 0; k < K; ++k) d.v[k] = (float)((double)ri.v[k] * scale[k]);
+      st<float, K>(r32, i, d);
+    }
   }
   block_sum_store<K>(t, partial + (int64_t)blockIdx.x * K);
 }
@@ -1503,53 +1685,112 @@ __global__ __launch_bounds__(wide_block<K>()) void k_pcg_conv(Scal *s, const dou
   const int k = threadIdx.x;
   int done = 1;
   if (k < K) {
-    done = s->done[k];
-    if (!done) {
-      const double rr = column_of(sums, k);
-      const int it = s->iters[k] + 1;
-      s->iters[k] = it;
-      s->rr[k] = rr;
-      int status = 0;
-      if (!isfinite(rr))
-        status = -6;
-      else if (rr <= s->tol2[k] * s->bnorm2[k])
-        status = 1;
-      else if (it >= s->maxit[k])
-        status = 2;
-      if (status != 0) {
-        done = 1;
-        s->done[k] = 1;
-        s->status[k] = status;
-      }
-    }
+    const Conv c = conv_step(s, k, column_of(sums, k));
+    if (!s->done[k]) s->rr[k] = column_of(sums, k);
+    s->iters[k] = c.iters;
+    s->status[k] = c.status;
+    s->done[k] = done = c.done;
   }
   store_all_done(s, K, done);
 }
 
 template <int K>
-__global__ __launch_bounds__(wide_block<K>()) void k_pcg_beta(Scal *s, const double *p, int64_t np) {
-  if (s->all_done) return;
+__global__ __launch_bounds__(wide_block<K>()) void k_pcg_beta(const Scal *in, Scal *out, const double *p,
+                                                              int64_t np) {
+  copy_record(in, out);
+  if (in->all_done) return;
   double sums[kMaxBatch];
   sum_partials_wide<K>(p, np, sums);
   const int k = threadIdx.x;
-  if (k < K && !s->done[k]) {
+  if (k < K && !in->done[k]) {
     const double rz = column_of(sums, k);
-    s->beta[k] = rz / s->rho[k];
-    s->rho[k] = rz;
+    out->beta[k] = rz / in->rho[k];
+    out->rho[k] = rz;
   }
 }
 
-template <class T, int K>
-__global__ void k_pcg_p(const Scal *s, T *__restrict__ p, const T *__restrict__ z, int64_t n) {
-  if (s->all_done) return;
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// FOLD: the block forms beta itself (in -> out written by the first block), and
+// with CONV applies the convergence test; else `in` holds them.
+template <class T, int K, bool FOLD, bool CONV>
+__global__ __launch_bounds__(kBlock) void k_pcg_p(const Scal *__restrict__ in, Scal *__restrict__ out,
+                                                  const double *__restrict__ rr, int64_t nrr,
+                                                  const double *__restrict__ rz, int64_t nrz, T *__restrict__ p,
+                                                  const T *__restrict__ z, int64_t n) {
+  if (FOLD && blockIdx.x == 0) copy_record(in, out);
+  if (in->all_done) return;
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  Row<T, K> pi{}, zi{};
+  if (i < n) {
+    pi = ld<T, K>(p, i);
+    zi = ld<T, K>(z, i);
+  }
+  double be[K];
+  int dn[K];
+  if constexpr (FOLD) {
+    double s[K], sz[K];
+    if constexpr (CONV) sum_rows<K>(rr, nrr, s);
+    sum_rows<K>(rz, nrz, sz);
+    int all = 1;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      dn[k] = in->done[k];
+      be[k] = sz[k] / in->rho[k];
+      const bool mine = blockIdx.x == 0 && threadIdx.x == k;
+      if constexpr (CONV) {
+        const Conv c = conv_step(in, k, s[k]);
+        if (mine) {
+          if (!dn[k]) out->rr[k] = s[k];
+          out->iters[k] = c.iters;
+          out->status[k] = c.status;
+          out->done[k] = c.done;
+        }
+        dn[k] = c.done;
+      }
+      all &= dn[k];
+      if (mine && !dn[k]) {
+        out->beta[k] = be[k];
+        out->rho[k] = sz[k];
+      }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) out->all_done = all;
+  } else {
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      be[k] = in->beta[k];
+      dn[k] = in->done[k];
+    }
+  }
   if (i >= n) return;
-  Row<T, K> pi = ld<T, K>(p, i);
-  const Row<T, K> zi = ld<T, K>(z, i);
 #pragma unroll
   for (int k = 0; k < K; ++k)
-    if (!s->done[k]) pi.v[k] = zi.v[k] + (T)s->beta[k] * pi.v[k];
+    if (!dn[k]) pi.v[k] = zi.v[k] + (T)be[k] * pi.v[k];
   st<T, K>(p, i, pi);
+}
+
+template <int K>
+__global__ __launch_bounds__(kBlock) void k_promote_dot(const float *__restrict__ z32,
+                                                        const double *__restrict__ scale,
+                                                        const double *__restrict__ r, double *__restrict__ z64,
+                                                        int64_t n, double *__restrict__ partial,
+                                                        const int *__restrict__ done) {
+  const int stop = stop_flag(done);
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  double t[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) t[k] = 0.0;
+  if (stop) return;
+  if (i < n) {
+    const Row<float, K> zi = ld<float, K>(z32, i);
+    const Row<double, K> ri = ld<double, K>(r, i);
+    Row<double, K> out;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      out.v[k] = scale[k] * (double)zi.v[k];
+      t[k] = ri.v[k] * out.v[k];
+    }
+    st<double, K>(z64, i, out);
+  }
+  block_sum_store<K>(t, partial + (int64_t)blockIdx.x * K);
 }
 
 __global__ void k_pcg_resume(Scal *s, unsigned keep) {
@@ -1720,32 +1961,35 @@ static GsDev<T> gs_ranges(int64_t a0, int64_t a1, int64_t b0, int64_t b1, T *x) 
 }
 
 template <class T>
-void launch_gs(hipStream_t stm, int K, const Sell &A, int64_t a0, int64_t a1, int64_t b0, int64_t b1, const T *g,
-               T *x, const int *done, bool first) {
+int64_t launch_gs(hipStream_t stm, int K, const Sell &A, int64_t a0, int64_t a1, int64_t b0, int64_t b1, const T *g,
+                  T *x, const int *done, bool first, double *dot) {
   const GsDev<T> J = gs_ranges(a0, a1, b0, b1, x);
-  if (!J.nbt) return;
+  if (!J.nbt) return 0;
   VEMG_K_SWITCH(K, {
     const dim3 blk(kWave * row_lanes<T, KK>());
     if (first)
-      hipLaunchKernelGGL((k_gs<T, KK, true>), grid(J.nbt), blk, 0, stm, A, J, g, done);
+      hipLaunchKernelGGL((k_gs<T, KK, true>), grid(J.nbt), blk, 0, stm, A, J, g, dot, done);
     else
-      hipLaunchKernelGGL((k_gs<T, KK, false>), grid(J.nbt), blk, 0, stm, A, J, g, done);
+      hipLaunchKernelGGL((k_gs<T, KK, false>), grid(J.nbt), blk, 0, stm, A, J, g, dot, done);
   })
+  return J.nbt;
 }
 
 template <class T>
-void launch_gs_merged(hipStream_t stm, int K, const Sell &A, const MergedRows &M, int64_t a0, int64_t a1, int64_t b0,
-                      int64_t b1, int64_t d0, int64_t d1, const T *g, T *x, const int *done, bool first) {
+int64_t launch_gs_merged(hipStream_t stm, int K, const Sell &A, const MergedRows &M, int64_t a0, int64_t a1,
+                         int64_t b0, int64_t b1, int64_t d0, int64_t d1, const T *g, T *x, const int *done,
+                         bool first, double *dot) {
   const GsDev<T> J = gs_ranges(a0, a1, b0, b1, x);
   const int64_t nb = J.nbt + slices(d0, d1);
-  if (!nb) return;
+  if (!nb) return 0;
   VEMG_K_SWITCH(K, {
     const dim3 blk(kWave * row_lanes<T, KK>());
     if (first)
-      hipLaunchKernelGGL((k_gs_merged<T, KK, true>), grid(nb), blk, 0, stm, A, M, J, d0, d1, g, done);
+      hipLaunchKernelGGL((k_gs_merged<T, KK, true>), grid(nb), blk, 0, stm, A, M, J, d0, d1, g, dot, done);
     else
-      hipLaunchKernelGGL((k_gs_merged<T, KK, false>), grid(nb), blk, 0, stm, A, M, J, d0, d1, g, done);
+      hipLaunchKernelGGL((k_gs_merged<T, KK, false>), grid(nb), blk, 0, stm, A, M, J, d0, d1, g, dot, done);
   })
+  return J.nbt;
 }
 
 template <class T>
@@ -1915,23 +2159,51 @@ void launch_pcg_set_rho(hipStream_t stm, int, Scal *s, const double *p, int64_t 
   hipLaunchKernelGGL(k_pcg_set_rho, dim3(1), dim3(kBlock), 0, stm, s, p, np);
 }
 // the per-iteration scalar kernels take K (= s->K) at compile time
-void launch_pcg_alpha(hipStream_t stm, int K, Scal *s, const double *p, int64_t np) {
-  VEMG_K_SWITCH(K, hipLaunchKernelGGL((k_pcg_alpha<KK>), dim3(1), dim3(wide_block<KK>()), 0, stm, s, p, np))
+void launch_compact(hipStream_t stm, int K, const double *p, int64_t np, double *out, const int *done) {
+  VEMG_K_SWITCH(K, hipLaunchKernelGGL((k_compact<KK>), dim3(kCompact), dim3(kBlock), 0, stm, p, np, out, done))
+}
+void launch_pcg_alpha(hipStream_t stm, int K, const Scal *in, Scal *mid, PartialSums pq) {
+  VEMG_K_SWITCH(K, hipLaunchKernelGGL((k_pcg_alpha<KK>), dim3(1), dim3(wide_block<KK>()), 0, stm, in, mid, pq.p,
+                                      pq.n))
 }
 template <class T>
-void launch_pcg_xr(hipStream_t stm, int K, Scal *s, T *x, T *r, const T *p, const T *q, int64_t n, double *partial) {
-  VEMG_K_SWITCH(K, hipLaunchKernelGGL((k_pcg_xr<T, KK>), grid(vec_blocks(n)), dim3(kBlock), 0, stm, s, x, r, p, q, n,
-                                      partial))
+void launch_pcg_xr(hipStream_t stm, int K, const Scal *in, Scal *mid, PartialSums pq, T *x, T *r, const T *p,
+                   const T *q, int64_t n, double *partial, float *r32, const double *scale) {
+  auto run = [&](auto kernel, const Scal *s) {
+    hipLaunchKernelGGL(kernel, grid(vec_blocks(n)), dim3(kBlock), 0, stm, s, mid, pq.p, pq.n, x, r, p, q, n, partial,
+                       r32, scale);
+  };
+  VEMG_K_SWITCH(K, {
+    if (pq.p)
+      r32 ? run(k_pcg_xr<T, KK, true, true>, in) : run(k_pcg_xr<T, KK, true, false>, in);
+    else
+      r32 ? run(k_pcg_xr<T, KK, false, true>, mid) : run(k_pcg_xr<T, KK, false, false>, mid);
+  })
 }
-void launch_pcg_conv(hipStream_t stm, int K, Scal *s, const double *p, int64_t np) {
-  VEMG_K_SWITCH(K, hipLaunchKernelGGL((k_pcg_conv<KK>), dim3(1), dim3(wide_block<KK>()), 0, stm, s, p, np))
+void launch_pcg_conv(hipStream_t stm, int K, Scal *mid, PartialSums rr) {
+  VEMG_K_SWITCH(K, hipLaunchKernelGGL((k_pcg_conv<KK>), dim3(1), dim3(wide_block<KK>()), 0, stm, mid, rr.p, rr.n))
 }
-void launch_pcg_beta(hipStream_t stm, int K, Scal *s, const double *p, int64_t np) {
-  VEMG_K_SWITCH(K, hipLaunchKernelGGL((k_pcg_beta<KK>), dim3(1), dim3(wide_block<KK>()), 0, stm, s, p, np))
+void launch_pcg_beta(hipStream_t stm, int K, const Scal *mid, Scal *in, PartialSums rz) {
+  VEMG_K_SWITCH(K, hipLaunchKernelGGL((k_pcg_beta<KK>), dim3(1), dim3(wide_block<KK>()), 0, stm, mid, in, rz.p,
+                                      rz.n))
 }
 template <class T>
-void launch_pcg_p(hipStream_t stm, int K, Scal *s, T *pvec, const T *z, int64_t n) {
-  VEMG_K_SWITCH(K, hipLaunchKernelGGL((k_pcg_p<T, KK>), grid(vec_blocks(n)), dim3(kBlock), 0, stm, s, pvec, z, n))
+void launch_pcg_p(hipStream_t stm, int K, const Scal *mid, Scal *in, PartialSums rr, PartialSums rz, T *pvec,
+                  const T *z, int64_t n) {
+  auto run = [&](auto kernel, const Scal *s) {
+    hipLaunchKernelGGL(kernel, grid(vec_blocks(n)), dim3(kBlock), 0, stm, s, in, rr.p, rr.n, rz.p, rz.n, pvec, z, n);
+  };
+  VEMG_K_SWITCH(K, {
+    if (!rz.p)
+      run(k_pcg_p<T, KK, false, false>, (const Scal *)in);
+    else
+      rr.p ? run(k_pcg_p<T, KK, true, true>, mid) : run(k_pcg_p<T, KK, true, false>, mid);
+  })
+}
+void launch_promote_dot(hipStream_t stm, int K, const float *z32, const double *scale, const double *r, double *z64,
+                        int64_t n, double *partial, const int *done) {
+  VEMG_K_SWITCH(K, hipLaunchKernelGGL((k_promote_dot<KK>), grid(vec_blocks(n)), dim3(kBlock), 0, stm, z32, scale, r,
+                                      z64, n, partial, done))
 }
 void launch_reduce(hipStream_t stm, int K, const double *p, int64_t np, double *out) {
   hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, stm, p, np, K, out);
@@ -1943,10 +2215,10 @@ void launch_pcg_resume(hipStream_t stm, int, Scal *s, unsigned keep) {
 #define VEMG_INSTANTIATE(T)                                                                                          \
   template void launch_spmv<T>(hipStream_t, int, const Sell &, int, int64_t, int64_t, const T *, T *, double *,       \
                                const int *, const SliceRef *);                                                       \
-  template void launch_gs<T>(hipStream_t, int, const Sell &, int64_t, int64_t, int64_t, int64_t, const T *, T *,       \
-                             const int *, bool);                                                                     \
-  template void launch_gs_merged<T>(hipStream_t, int, const Sell &, const MergedRows &, int64_t, int64_t, int64_t,     \
-                                    int64_t, int64_t, int64_t, const T *, T *, const int *, bool);                   \
+  template int64_t launch_gs<T>(hipStream_t, int, const Sell &, int64_t, int64_t, int64_t, int64_t, const T *, T *,    \
+                                const int *, bool, double *);                                                        \
+  template int64_t launch_gs_merged<T>(hipStream_t, int, const Sell &, const MergedRows &, int64_t, int64_t, int64_t,  \
+                                       int64_t, int64_t, int64_t, const T *, T *, const int *, bool, double *);      \
   template void launch_res_merged<T>(hipStream_t, int, const Sell &, const MergedRows &, const T *, T *, const int *,  \
                                      const SliceRef *);                                                              \
   template void launch_prolong_merged<T>(hipStream_t, int, const MergedRows &, const T *, const T *, T *,             \
@@ -1963,8 +2235,10 @@ void launch_pcg_resume(hipStream_t stm, int, Scal *s, unsigned keep) {
   template void launch_add_dot<T>(hipStream_t, int, const T *, const T *, T *, int64_t, int64_t, double *,             \
                                   const int *);                                                                      \
   template void launch_jacobi<T>(hipStream_t, int, const T *, const double *, T *, int64_t, const int *);             \
-  template void launch_pcg_xr<T>(hipStream_t, int, Scal *, T *, T *, const T *, const T *, int64_t, double *);        \
-  template void launch_pcg_p<T>(hipStream_t, int, Scal *, T *, const T *, int64_t);
+  template void launch_pcg_xr<T>(hipStream_t, int, const Scal *, Scal *, PartialSums, T *, T *, const T *, const T *,   \
+                                 int64_t, double *, float *, const double *);                                        \
+  template void launch_pcg_p<T>(hipStream_t, int, const Scal *, Scal *, PartialSums, PartialSums, T *, const T *,     \
+                                int64_t);
 
 VEMG_INSTANTIATE(double)
 VEMG_INSTANTIATE(float)

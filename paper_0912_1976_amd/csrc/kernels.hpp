@@ -110,9 +110,12 @@ void launch_spmv(hipStream_t st, int K, const Sell &A, int mode, int64_t r0, int
 // One multicolour Gauss-Seidel step on the rows [a0,a1) and [b0,b1) (rows of
 // one colour): x_i += (g_i - (A x)_i) / a_ii.  first: the first sweep from
 // x = 0, in ascending colours, x_i = (g_i - (L x)_i) / a_ii; x needs no fill.
+// With dot: dot[block * K + k] = sum over the block's rows of g_ik x_ik (the
+// updated x; a backward sweep updates every row once, so its colours together
+// give g . x).  Returns the number of blocks.
 template <class T>
-void launch_gs(hipStream_t st, int K, const Sell &A, int64_t a0, int64_t a1, int64_t b0, int64_t b1, const T *g,
-               T *x, const int *done, bool first);
+int64_t launch_gs(hipStream_t st, int K, const Sell &A, int64_t a0, int64_t a1, int64_t b0, int64_t b1, const T *g,
+                  T *x, const int *done, bool first, double *dot = nullptr);
 
 // VL + additive smoother in one pair of fine sweeps.  The preconditioner is
 // the sum of the SOR cycle (x) and the smoother's cycle on the non-top rows
@@ -141,10 +144,12 @@ struct MergedRows {
   Sell prol;  // [E~ | P0]: columns < n_top of the surface vector, then those of A_bar's first coarse level
 };
 // One colour of the two cycles' forward (first) or backward sweep: the rows
-// [a0,a1) (top), [b0,b1) (non-top) and D's [d0,d1).
+// [a0,a1) (top), [b0,b1) (non-top) and D's [d0,d1); dot as in launch_gs, over
+// the matrix's rows.
 template <class T>
-void launch_gs_merged(hipStream_t st, int K, const Sell &A, const MergedRows &M, int64_t a0, int64_t a1, int64_t b0,
-                      int64_t b1, int64_t d0, int64_t d1, const T *g, T *x, const int *done, bool first);
+int64_t launch_gs_merged(hipStream_t st, int K, const Sell &A, const MergedRows &M, int64_t a0, int64_t a1, int64_t b0,
+                         int64_t b1, int64_t d0, int64_t d1, const T *g, T *x, const int *done, bool first,
+                         double *dot = nullptr);
 // y = -U x on every row, and on R's extended rows.
 template <class T>
 void launch_res_merged(hipStream_t st, int K, const Sell &A, const MergedRows &M, const T *x, T *y, const int *done,
@@ -281,16 +286,50 @@ void launch_demote(hipStream_t st, int K, const double *r64, const double *scale
 void launch_promote(hipStream_t st, int K, const float *d32, const double *scale, double *x64, int64_t n,
                     bool accumulate, const int *done);
 
-// ---- PCG scalars (single-block kernels sum partials in index order) ------
+// z64 = scale[k] z32; partial[block * K + k] = sum r_ik z_ik
+void launch_promote_dot(hipStream_t st, int K, const float *z32, const double *scale, const double *r, double *z64,
+                        int64_t n, double *partial, const int *done);
+
+// ---- PCG scalars (partials are summed in index order) --------------------
+// From kCompactFrom rows of partials on, launch_compact first adds them in
+// kCompact consecutive parts, one block each (a single block takes 14 us for
+// 8514 rows of 8 columns).
+constexpr int64_t kCompactFrom = 4096;
+constexpr int kCompact = 64;
+void launch_compact(hipStream_t st, int K, const double *p, int64_t np, double *out, const int *done);
 void launch_pcg_init(hipStream_t st, int K, Scal *s, const double *pb, int64_t npb, double tol, int maxit);
 void launch_pcg_set_rho(hipStream_t st, int K, Scal *s, const double *p, int64_t np);
-void launch_pcg_alpha(hipStream_t st, int K, Scal *s, const double *p, int64_t np);
+// The scalars alternate between two records: `in` as the iteration finds them,
+// `mid` after alpha (and the convergence test).
+// Folded: launch_pcg_xr takes the partials of p.q and forms alpha,
+// launch_pcg_p those of r.z and forms beta, and with those of r.r applies the
+// convergence test too; every block adds the partials, the first one writes
+// the record.  A launch of one block took 4 to 5 us in their place.  The test
+// folded into launch_pcg_p comes after the preconditioner, whose application
+// in the iteration that converges is then for nothing: only where that costs
+// less than the launches it saves (kFoldConvMax unknowns: at 549,152 the solve
+// took 28.3 ms with it, 28.0 without).
+// Otherwise launch_pcg_alpha (in -> mid), launch_pcg_conv (mid) and
+// launch_pcg_beta (mid -> in) do so in single blocks.
+struct PartialSums {
+  const double *p = nullptr;  // [n][K]; null: not folded
+  int64_t n = 0;
+};
+// whether an iteration on n rows with K columns folds (np: rows of partials of
+// its longest sum)
+inline bool pcg_folds(int64_t np, int K) { return np <= kCompactFrom && np * K <= 8192; }
+constexpr int64_t kFoldConvMax = 250000;
+void launch_pcg_alpha(hipStream_t st, int K, const Scal *in, Scal *mid, PartialSums pq);
+// x += alpha p, r -= alpha q, partial sums of r.r; with r32: r32 = scale r
 template <class T>
-void launch_pcg_xr(hipStream_t st, int K, Scal *s, T *x, T *r, const T *p, const T *q, int64_t n, double *partial);
-void launch_pcg_conv(hipStream_t st, int K, Scal *s, const double *p, int64_t np);
-void launch_pcg_beta(hipStream_t st, int K, Scal *s, const double *p, int64_t np);
+void launch_pcg_xr(hipStream_t st, int K, const Scal *in, Scal *mid, PartialSums pq, T *x, T *r, const T *p,
+                   const T *q, int64_t n, double *partial, float *r32, const double *scale);
+void launch_pcg_conv(hipStream_t st, int K, Scal *mid, PartialSums rr);
+void launch_pcg_beta(hipStream_t st, int K, const Scal *mid, Scal *in, PartialSums rz);
+// p = z + beta p
 template <class T>
-void launch_pcg_p(hipStream_t st, int K, Scal *s, T *pvec, const T *z, int64_t n);
+void launch_pcg_p(hipStream_t st, int K, const Scal *mid, Scal *in, PartialSums rr, PartialSums rz, T *pvec,
+                  const T *z, int64_t n);
 // out[k] = sum of the partials of column k
 void launch_reduce(hipStream_t st, int K, const double *p, int64_t np, double *out);
 // before a restart: clears done/status of the columns whose bit in keep is 0
