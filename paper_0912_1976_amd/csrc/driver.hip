@@ -317,7 +317,8 @@ struct DLevel {
   CsrG Ac;                      // coarse levels: standard form, G lanes per row
   PatchSweep ps;                // coarse levels: the patches of the sweeps
   int64_t np = 0;               // number of patches
-  PatchCount *count = nullptr;
+  unsigned long long *begun = nullptr;  // progress of the sweeps (PatchJob)
+  unsigned *ended = nullptr;
   bool fine = false;
   int64_t n = 0, row0 = 0;
   int64_t n_top = 0;            // fine levels: rows of the top block in the fine matrix
@@ -428,19 +429,15 @@ void pack_patches(Arena &ar, hipStream_t st, const Level &L, DLevel &dl) {
   std::vector<PatchRow> rows(np * S, PatchRow{0, 0, 0, 0});
   std::vector<int32_t> halo, lcol;
   int64_t tiles = 0;
-  for (size_t c = 0; c + 1 < L.pc_start.size(); ++c)  // each colour waits for the one before alone
-    if (L.pc_start[c + 1] <= L.pc_start[c]) throw DeviceError(VEMG_ERR_DEVICE, "empty patch colour");
+  std::vector<int32_t> patch_of(n), nbr;  // stored patch of each row
+  for (int64_t p = 0; p < np; ++p)
+    std::fill(patch_of.begin() + L.patch_row[p], patch_of.begin() + L.patch_row[p + 1], (int32_t)p);
   for (int64_t p = 0; p < np; ++p) {
     const int64_t m = L.patch_row[p + 1] - L.patch_row[p], nt = (m + W - 1) / W;
     if (n * kMaxBatch * 8 > INT32_MAX) throw DeviceError(VEMG_ERR_DEVICE, "coarse level above the sweep kernel's 32-bit offsets");
     if (m > kPatchLdsRows) throw DeviceError(VEMG_ERR_DEVICE, "a patch exceeds the sweep kernel's rows");
-    int c = 0;
-    while (L.pc_start[c + 1] <= p) ++c;
-    auto size = [&](int k) {
-      return k < 0 || k + 1 >= (int)L.pc_start.size() ? 0 : (int32_t)(L.pc_start[k + 1] - L.pc_start[k]);
-    };
-    desc[p] = PatchDesc{(int32_t)L.patch_row[p], (int32_t)m, tiles * W * W, (int32_t)halo.size(), 0, 0, c,
-                        size(c - 1), size(c), size(c + 1)};
+    desc[p] = PatchDesc{(int32_t)L.patch_row[p], (int32_t)m, tiles * W * W, (int32_t)halo.size(), 0, 0,
+                        (int32_t)nbr.size(), 0, 0};
     // the halo: the listed part of the other patches' rows, ascending
     const int64_t ps = L.patch_row[p], pe = ps + m;
     std::vector<int32_t> out;
@@ -448,6 +445,12 @@ void pack_patches(Arena &ar, hipStream_t st, const Level &L, DLevel &dl) {
       if (L.A.idx[k] < ps || L.A.idx[k] >= pe) out.push_back(L.A.idx[k]);
     std::sort(out.begin(), out.end());
     out.erase(std::unique(out.begin(), out.end()), out.end());
+    for (int32_t j : out)  // ascending rows, so ascending patches
+      if ((int32_t)nbr.size() == desc[p].nbr || nbr.back() != patch_of[j]) {
+        nbr.push_back(patch_of[j]);
+        ++desc[p].nbr_all;
+        desc[p].nbr_early += j < ps;
+      }
     if ((int64_t)out.size() > kPatchHalo) out.resize(kPatchHalo);
     desc[p].nhalo = (int32_t)out.size();
     for (int32_t j : out) desc[p].nearly += j < ps;
@@ -522,12 +525,14 @@ void pack_patches(Arena &ar, hipStream_t st, const Level &L, DLevel &dl) {
   dl.ps.tb32 = ar.upload(tb32, st);
   dl.ps.halo = ar.upload(halo, st);
   dl.ps.lcol = ar.upload(lcol, st);
-  dl.ps.ncolours = (int)L.pc_start.size() - 1;
+  dl.ps.nbr = ar.upload(nbr, st);
   dl.np = np;
-  const size_t nc = L.pc_start.size();
-  dl.count = ar.alloc<PatchCount>(nc);
-  if (!ar.count_only)
-    launch_fill<float>(st, (float *)dl.count, (int64_t)(nc * sizeof(PatchCount) / sizeof(float)), 0.0f, nullptr);
+  dl.begun = ar.alloc<unsigned long long>(1);
+  dl.ended = ar.alloc<unsigned>(np);
+  if (!ar.count_only) {
+    launch_fill<float>(st, (float *)dl.begun, 2, 0.0f, nullptr);
+    launch_fill<float>(st, (float *)dl.ended, np, 0.0f, nullptr);
+  }
 }
 
 enum LevelsOf { kLevelsS = 0, kLevelsAbar = 1, kLevelsSA = 2 };
@@ -623,7 +628,8 @@ void coarse_cycles(hipStream_t st, int K, Cycle<T> a, Cycle<T> b, const int *don
   }
   PatchJob<T> gs[2];
   for (int i = 0; i < nl; ++i)
-    gs[i] = PatchJob<T>{L[i]->Ac, L[i]->ps, L[i]->np, L[i]->template g<T>(), L[i]->template x<T>(), L[i]->count};
+    gs[i] = PatchJob<T>{L[i]->Ac, L[i]->ps, L[i]->np, L[i]->template g<T>(), L[i]->template x<T>(), L[i]->begun,
+                        L[i]->ended};
   launch_patch_gs<T>(st, K, kPatchFirst, gs, nl, done);
   Cycle<T> na = a, nb = b;
   if (ra >= rb) ++na.l;
@@ -1613,7 +1619,7 @@ void time_once(Handle *h, int op, int K) {
   }
   if (op == VEMG_OP_GS_COARSE) {
     DLevel &L = h->Ab[1];
-    const PatchJob<T> J{L.Ac, L.ps, L.np, L.g<T>(), L.x<T>(), L.count};
+    const PatchJob<T> J{L.Ac, L.ps, L.np, L.g<T>(), L.x<T>(), L.begun, L.ended};
     launch_patch_gs<T>(st, K, kPatchForward, &J, 1, nullptr);
     return;
   }

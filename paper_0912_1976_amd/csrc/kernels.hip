@@ -888,21 +888,22 @@ __global__ __launch_bounds__(kBlock) void k_csr(Jobs<CsrJob<T>> P, const int *__
 //
 // The patch colours follow one another inside the launch.  A block takes the
 // next patch in colour order (an atomic ticket), reads everything that does
-// not depend on the sweep, waits until the patches of all colours before its
-// own are done, and reports its own when its values have reached memory.  It
-// waits for patches with smaller tickets only, whose blocks have all begun, so
-// the earliest unfinished one never waits and every wait ends, whatever the
-// order and the number in which blocks are placed.  The unknowns' values pass
-// between blocks with loads and stores at agent scope, beyond the caches of
-// one XCD; so each row of the halo is read once, into LDS.  The block that
-// finishes the last colour clears the counters.
+// not depend on the sweep, waits until the patches of earlier colours that it
+// is coupled to are done, and marks its own when its values have reached
+// memory.  It waits for patches with smaller tickets only, whose blocks have
+// all begun, so the earliest unfinished one never waits and every wait ends,
+// whatever the order and the number in which blocks are placed.  The unknowns'
+// values pass between blocks with loads and stores at agent scope, beyond the
+// caches of one XCD; so each row of the halo is read once, into LDS.  Marks are
+// launch numbers, which the ticket gives, so nothing is cleared in between.
 // A launch per colour took 9.3 us at 129 x 129 x 33 (75 blocks a colour), of
 // which the descriptors, entries and factors, now read ahead, and the launch
 // were the larger part: a sweep of seven colours took 65 us in seven launches,
-// 44 in one with every entry gathered at agent scope, and takes 39 with the
-// halo in LDS (2,179,616 unknowns: 92, 82 and 79 us).  One block a CU: two, with
-// the factor and the entries read after the wait to fit their registers, took
-// 173 us there.
+// 44 in one with every entry gathered at agent scope, 39 with the halo in LDS
+// and a counter per colour, and takes 35 with a mark per patch (on 2,179,616
+// unknowns 92, 82, 79 and 59 us, and at K = 8 113 to 150 and 85 to 102 with the
+// last two).  One block a CU: two, with the factor and the entries read after
+// the wait to fit their registers, took 173 us there instead of 79.
 constexpr int kPatchGroups = 8;
 constexpr int kPatchThreads = 1024;
 
@@ -954,17 +955,19 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch_gs(Jobs<PatchJob<T>>
   __shared__ Row<T, K> xs[kPatchLdsRows + kPatchHalo];  // the patch's own old values, and its halo's
   __shared__ Row<T, K> hs[kPatchLdsRows];
   __shared__ T half[kPatchLdsRows][K];
-  __shared__ unsigned ticket;
+  __shared__ unsigned long long ticket;
   if (*(done ? done : &kNeverDone)) return;  // before a ticket is taken
   // the blocks of two jobs alternate while both last
   const int64_t b = blockIdx.x, both = 2 * (P.nb0 < P.nb1 ? P.nb0 : P.nb1);
   const bool second = b < both ? (b & 1) : P.nb1 > P.nb0;
   const PatchJob<T> &J = second ? P.j[1] : P.j[0];
   if (threadIdx.x == 0)
-    ticket = __hip_atomic_fetch_add(&J.count[0].n, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    ticket = __hip_atomic_fetch_add(J.begun, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  const int64_t tk = __builtin_amdgcn_readfirstlane(ticket);
-  const int64_t p = BWD ? J.np - 1 - tk : tk;
+  const unsigned long long tk = ticket, launch = tk / (unsigned long long)J.np;
+  const unsigned mark = __builtin_amdgcn_readfirstlane((unsigned)launch + 1);
+  const int64_t pf = __builtin_amdgcn_readfirstlane((int)(tk - launch * (unsigned long long)J.np));
+  const int64_t p = BWD ? J.np - 1 - pf : pf;
   const PatchDesc D = J.S.desc[p];
   const CsrG &A = J.A;
   const T *__restrict__ g = J.g, *__restrict__ vals = csr_vals<T>(A);
@@ -1020,12 +1023,13 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch_gs(Jobs<PatchJob<T>>
       if (ge < R[s].n) load_entries<T, U, G>(J.S.lcol, vals, R[s], ge, c[s], v[s]);
     }
   }
-  // the patches of the colour before this one's are done (and so all earlier ones)
-  const unsigned need = (unsigned)(BWD ? D.n_after : D.n_before);
-  if (threadIdx.x == 0 && need) {
-    PatchCount *pc = J.count + 1 + (BWD ? D.colour + 1 : D.colour - 1);
-    while (__hip_atomic_load(&pc->n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need)
-      __builtin_amdgcn_s_sleep(1);
+  // the coupled patches swept before this one are done
+  if (threadIdx.x < kWave) {
+    const int32_t n0 = BWD ? D.nbr_early : 0, n1 = BWD ? D.nbr_all : D.nbr_early;
+    for (int32_t i = n0 + threadIdx.x; i < n1; i += kWave) {
+      const unsigned *e = J.ended + J.S.nbr[D.nbr + i];
+      while (__hip_atomic_load(e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != mark) __builtin_amdgcn_s_sleep(1);
+    }
   }
   __syncthreads();
   const __amdgpu_buffer_rsrc_t x =
@@ -1089,17 +1093,11 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch_gs(Jobs<PatchJob<T>>
       }
     }
   }
-  // every wavefront's values have reached memory before the patch is reported
+  // every wavefront's values have reached memory before the patch is marked
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const unsigned n =
-        1 + __hip_atomic_fetch_add(&J.count[1 + D.colour].n, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // the last patch of the last colour: every block of the job has passed its wait
-    if (n == (unsigned)D.n_own && (BWD ? D.n_before : D.n_after) == 0)
-      for (int i = 0; i <= J.S.ncolours; ++i)
-        __hip_atomic_store(&J.count[i].n, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  if (threadIdx.x == 0)
+    __hip_atomic_store(J.ended + p, mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Dense FP64 coarsest inverse applied to K columns, x = C g.  C is symmetric,

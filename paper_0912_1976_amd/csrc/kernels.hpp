@@ -196,17 +196,13 @@ constexpr int kPatchTile = 16;
 constexpr int kPatchHalo = 1024;
 // stored patch: its first row, its number of rows m, where its factor tiles
 // begin; its halo, the rows of other patches it is coupled to, ascending
-// (those of earlier patches first), at most kPatchHalo of them listed; its
-// colour, and the number of patches of the colours before, of and after it
+// (those of earlier patches first), at most kPatchHalo of them listed; and the
+// patches it is coupled to, likewise
 struct PatchDesc {
   int32_t row0, m;
   int64_t toff;
   int32_t halo, nearly, nhalo;
-  int32_t colour, n_before, n_own, n_after;
-};
-// a cache line of its own for each progress counter
-struct PatchCount {
-  unsigned n, pad[31];
+  int32_t nbr, nbr_early, nbr_all;
 };
 // A row's entries (columns ascending, so in sweep order) by what a sweep of
 // its patch takes: [b, own) earlier patches, [own, late) its own patch before
@@ -221,7 +217,7 @@ struct PatchSweep {
   // column of each entry of the level's CsrG: the row in its own patch, or
   // kPatchLdsRows + its place in the halo, or ~column beyond the halo's list
   const int32_t *lcol = nullptr;
-  int ncolours = 0;
+  const int32_t *nbr = nullptr;
   // FP64: F = (D_p + L_p)^{-1}; FP32 (row-scaled operator): F D_p, rounded;
   // tb: the same of F^T.  Tiles of 16 x 16, zero beyond m, tile row I (of
   // t = ceil(m / 16)) holding its tiles J <= I (tb: J >= I) in order from tile
@@ -243,8 +239,11 @@ struct PatchJob {
   int64_t np = 0;
   const T *g = nullptr;
   T *x = nullptr;
-  // patches begun, then patches done of each colour; zero between launches
-  PatchCount *count = nullptr;
+  // Progress of the level's sweeps: the patches begun in all launches so far
+  // (np of them a launch, so begun / np numbers the launch), and for every
+  // patch the number, from 1, of the last launch that has finished it.
+  unsigned long long *begun = nullptr;
+  unsigned *ended = nullptr;
 };
 template <class T>
 void launch_patch_gs(hipStream_t st, int K, PatchDir dir, const PatchJob<T> *jobs, int nj, const int *done);
