@@ -245,9 +245,11 @@ Sell pack_rows(Arena &ar, hipStream_t st, int64_t n, bool pairs, F &&row, G &&pa
 // the rows one XCD works on gather from one region of the fine vector; each
 // row keeps its entries and their order.
 // colmap (optional): the stored column of column c is (*colmap)[c].
+// zero (optional): the entries of the columns c with (*zero)[c + coloff] != 0
+// are left out (the operator's input is zero there).
 CsrG pack_csrg(Arena &ar, hipStream_t st, const Csr &A, bool square, int64_t *stored = nullptr,
                const std::vector<int64_t> *colkey = nullptr, int64_t coloff = 0,
-               const std::vector<int32_t> *colmap = nullptr) {
+               const std::vector<int32_t> *colmap = nullptr, const std::vector<uint8_t> *zero = nullptr) {
   std::vector<int32_t> ptr(A.nrows + 1, 0), upper(square ? A.nrows : 0), col;
   std::vector<double> val, d(square ? A.nrows : 0, 0.0);
   std::vector<float> val32;
@@ -269,6 +271,7 @@ CsrG pack_csrg(Arena &ar, hipStream_t st, const Csr &A, bool square, int64_t *st
     const int64_t r = rows[i];
     for (int64_t k = A.ptr[r]; k < A.ptr[r + 1]; ++k) {
       if (square && A.idx[k] == r) continue;
+      if (zero && (*zero)[A.idx[k] + coloff]) continue;
       if (square && A.idx[k] < r) upper[i] = (int32_t)col.size() + 1;
       col.push_back(colmap ? (*colmap)[A.idx[k]] : A.idx[k]);
       val.push_back(A.val[k]);
@@ -373,7 +376,10 @@ struct vemg_solver_s {
   vemg::Arena ar;
   vemg::Sell A;                           // fine A_UU, difference form
   vemg::Sell E;
-  vemg::CsrG Et;
+  vemg::CsrG Et, Et_res;                  // Et_res: for residuals after a forward sweep (zero_res left out)
+  // fine rows without a neighbour of a later colour, whose residual after the
+  // forward sweep is zero: a quarter of the entries of the restrictions
+  std::vector<uint8_t> zero_res;
   std::vector<vemg::DLevel> S, Ab, SA;  // SA: baseline hierarchy of the whole A_UU (may be empty)
   vemg::Work<double> v64;
   vemg::Work<float> v32;
@@ -583,7 +589,8 @@ void build_levels(Handle *h, std::vector<Level> &H, std::vector<DLevel> &D, int 
       else
         dl.P = pack_csrg(h->ar, st, L.P, false);
       // the fine level's restriction gathers from fine rows row0 + c
-      dl.Pt = dl.fine ? pack_csrg(h->ar, st, transpose(L.P), false, nullptr, &h->P.loc_rank, dl.row0)
+      dl.Pt = dl.fine ? pack_csrg(h->ar, st, transpose(L.P), false, nullptr, &h->P.loc_rank, dl.row0, nullptr,
+                                  &h->zero_res)
                       : pack_csrg(h->ar, st, transpose(L.P), false);
     } else {
       dl.Cinv = h->ar.upload(L.Cinv, st);
@@ -728,11 +735,12 @@ ColourRows colour_rows(const Problem &P, int c) {
   return r;
 }
 
-// The restriction of the SOR cycle's residual to the surface
+// The restriction of r to the surface; residual: of the residual after a
+// forward sweep
 template <class T>
-CsrJob<T> surface_down(Handle *h, const T *r) {
+CsrJob<T> surface_down(Handle *h, const T *r, bool residual) {
   CsrJob<T> J;
-  J.A = h->Et;
+  J.A = residual ? h->Et_res : h->Et;
   J.x = r;
   J.y = h->S[0].g<T>();
   return J;
@@ -758,7 +766,7 @@ int64_t sor_cycle(Handle *h, int K, const T *rr, T *zz, double *part, const int 
   Cycle<T> S, B;
   if (P.n_top > 0) {
     launch_spmv<T>(st, K, h->A, 1, 0, P.n, zz, v.res, nullptr, done, h->order_all);
-    const CsrJob<T> J = surface_down<T>(h, v.res);
+    const CsrJob<T> J = surface_down<T>(h, v.res, true);
     launch_csr<T>(st, K, kCsrMult, &J, 1, done);
     S = cycle<T>(h->S, 0);
   }
@@ -799,7 +807,7 @@ int64_t merged_cycle(Handle *h, int K, const T *rr, T *zz, double *part, const i
   launch_res_merged<T>(st, K, h->A, h->M, zz, v.res, done, h->order_all);
   CsrJob<T> down[2];
   int nd = 0;
-  if (P.n_top > 0) down[nd++] = surface_down<T>(h, v.res);
+  if (P.n_top > 0) down[nd++] = surface_down<T>(h, v.res, true);
   down[nd].A = h->merged_Pt;
   down[nd].x = v.res;
   down[nd++].y = h->Ab[1].g<T>();
@@ -844,7 +852,7 @@ void precond(Handle *h, int K, const T *rr, T *zz, double *part, int64_t *np, co
       return;
     case VEMG_PC_VL_ADDITIVE_ONLY:
       if (P.n_top > 0) {
-        const CsrJob<T> J = surface_down<T>(h, rr);
+        const CsrJob<T> J = surface_down<T>(h, rr, false);
         additive_smoother<T>(h, K, rr, cycle<T>(h->S, 0), &J, done);
         launch_prolong_sum<T>(st, K, h->E, P.n_top, h->S[0].x<T>(), v.w, rr, zz, part ? part : h->part_t,
                               done);
@@ -1347,7 +1355,7 @@ int64_t merged_rows(Handle *h) {
   std::vector<int32_t> map(n - m);
   for (int64_t i = m; i < n; ++i) map[i - m] = (int32_t)i;
   for (int64_t q = 0; q < M.nr; ++q) map[rrow[q] - m] = (int32_t)(n + rpos[q]);
-  h->merged_Pt = pack_csrg(ar, st, transpose(P0), false, nullptr, &P.loc_rank, m, &map);
+  h->merged_Pt = pack_csrg(ar, st, transpose(P0), false, nullptr, &P.loc_rank, m, &map, &h->zero_res);
   M.drow = ar.upload(drow, st);
   M.rpos = ar.upload(rpos, st);
   M.xpos = ar.upload(xpos, st);
@@ -1367,9 +1375,14 @@ void upload(Handle *h) {
   h->ar.release();
   SellSpans spans;
   h->A = pack_sell(h->ar, st, P.Aoff, true, &P.d, &P.diag, &h->nnz_A, &P.colour, &spans);
+  h->zero_res.assign(n, 1);
+  for (int64_t i = 0; i < n; ++i)
+    for (int64_t k = P.Aoff.ptr[i]; k < P.Aoff.ptr[i + 1] && h->zero_res[i]; ++k)
+      if (P.colour[P.Aoff.idx[k]] > P.colour[i]) h->zero_res[i] = 0;
   if (m > 0) {
     h->E = pack_sell(h->ar, st, P.E, false, nullptr, nullptr, &h->nnz_E);
     h->Et = pack_csrg(h->ar, st, P.Et, false, nullptr, &P.loc_rank, 0);
+    h->Et_res = pack_csrg(h->ar, st, P.Et, false, nullptr, &P.loc_rank, 0, nullptr, &h->zero_res);
   }
   size_t cnt = (size_t)n * kMaxBatch;
   const size_t ext = (size_t)(n + merged_rows(h)) * kMaxBatch;
@@ -1603,7 +1616,7 @@ void time_once(Handle *h, int op, int K) {
     return;
   }
   if (op == VEMG_OP_ET) {
-    const CsrJob<T> J = surface_down<T>(h, v.r);
+    const CsrJob<T> J = surface_down<T>(h, v.r, false);
     launch_csr<T>(st, K, kCsrMult, &J, 1, nullptr);
     return;
   }

@@ -810,10 +810,9 @@ __device__ __forceinline__ void add_entries(const EntryRange &R, int32_t t0, X &
     for (int k = 0; k < C; ++k) acc[k] += v[u] * (in ? xc[u].v[k] : T(0));
   }
 }
-template <class T, int C, int G, class X>
+template <class T, int C, int G, int U, class X>
 __device__ __forceinline__ void group_entries(const int32_t *__restrict__ col, const T *__restrict__ val,
                                               const EntryRange &R, int32_t t0, X &&x, T (&acc)[C]) {
-  constexpr int U = entries_ahead<T, C>();
   for (; t0 < R.n; t0 += G * U) {
     int32_t c[U];
     T v[U];
@@ -840,8 +839,10 @@ __device__ __forceinline__ void csr_row(const CsrG &A, int64_t r, int32_t b, int
   T acc[C];
 #pragma unroll
   for (int k = 0; k < C; ++k) acc[k] = T(0);
-  group_entries<T, C, G>(A.col, csr_vals<T>(A), EntryRange{b, e - b, e - b, 0}, ge,
-                         [&](int32_t c) { return ldp<T, K, C>(x, c, q); }, acc);
+  // the restrictions' rows hold about 72 entries for sixteen groups
+  constexpr int U = entries_ahead<T, C>() + (sizeof(T) * C > 8 ? 1 : 0);
+  group_entries<T, C, G, U>(A.col, csr_vals<T>(A), EntryRange{b, e - b, e - b, 0}, ge,
+                            [&](int32_t c) { return ldp<T, K, C>(x, c, q); }, acc);
   groups_sum<T, C, G, LPR>(acc);
   if (ge != 0) return;
 #pragma unroll
@@ -1055,7 +1056,7 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch_gs(Jobs<PatchJob<T>>
 #pragma unroll
       for (int k = 0; k < C; ++k) acc[k] = T(0);
       if (ge < R[s].n) add_entries<T, C, U, G>(R[s], ge, value, c[s], v[s], acc);
-      group_entries<T, C, G>(J.S.lcol, vals, R[s], ge + G * U, value, acc);
+      group_entries<T, C, G, entries_ahead<T, C>()>(J.S.lcol, vals, R[s], ge + G * U, value, acc);
       groups_sum<T, C, G, LPR>(acc);
 #pragma unroll
       for (int k = 0; k < C; ++k) h.v[k] = gr[s].v[k] * inv[s] - acc[k];
