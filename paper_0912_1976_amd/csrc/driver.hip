@@ -394,6 +394,7 @@ struct vemg_solver_s {
   int64_t dot_rows = 0;  // most rows of partial sums of an iteration's dots
   bool sweep_dot = false;  // the backward sweeps form r . z
   int64_t *perm = nullptr;
+  int32_t *pos = nullptr;  // natural node -> storage row, -1: fixed
   // slice visit orders (spatial, across colours) of the products over all
   // rows and over the non-top rows
   vemg::SliceRef *order_all = nullptr, *order_bar = nullptr;
@@ -1004,7 +1005,11 @@ void chunk_iterations(Handle *h, int K, int kind, int count, bool last) {
     pcg_iteration<T>(h, K, kind == kGraphFP32 && last && k + 1 == count ? kGraphFP32Reliable : kind);
 }
 
-// graph of `count` iterations for (kind, K), captured on first use when allowed
+template <class T>
+void start_phase(Handle *h, int K, int kind);
+
+// graph of `count` iterations for (kind, K) (0: of the start of a phase),
+// captured on first use when allowed
 template <class T>
 const IterGraph *iteration_graph(Handle *h, int K, int kind, int count, bool last) {
   const int key = ((last && kind == kGraphFP32 ? kGraphFP32Reliable : kind) * 16 + K) * 32 + count;
@@ -1013,10 +1018,39 @@ const IterGraph *iteration_graph(Handle *h, int K, int kind, int count, bool las
   if (!h->allow_capture) return nullptr;
   IterGraph ig;
   HIPCHK(hipStreamBeginCapture(h->work, hipStreamCaptureModeThreadLocal));
-  chunk_iterations<T>(h, K, kind, count, last);
+  if (count)
+    chunk_iterations<T>(h, K, kind, count, last);
+  else
+    start_phase<T>(h, K, kind);
   HIPCHK(hipStreamEndCapture(h->work, &ig.graph));
   HIPCHK(hipGraphInstantiate(&ig.exec, ig.graph, nullptr, nullptr, 0));
   return &h->graphs.emplace(key, ig).first->second;
+}
+
+// z = M^{-1} r, rho = r . z and p = z: the start of a phase
+template <class T>
+void start_phase(Handle *h, int K, int kind) {
+  Work<T> &v = work_of<T>(h);
+  int64_t np = 0;
+  if (kind == kGraphMixedPC) {
+    if constexpr (std::is_same<T, double>::value) {
+      launch_demote(h->work, K, v.r, h->scale_in, h->v32.tmp, h->P.n, nullptr);
+      np = precond_mixed(h, K, v.r, v.z, nullptr);
+    }
+  } else {
+    precond<T>(h, K, v.r, v.z, h->part_rz, &np, nullptr);
+  }
+  launch_pcg_set_rho(h->work, K, h->scal, h->part_rz, np);
+  launch_copy<T>(h->work, v.z, v.p, h->P.n * K, nullptr);
+}
+
+template <class T>
+void run_start(Handle *h, int K, int kind) {
+  const IterGraph *ig = h->opt.use_graphs ? iteration_graph<T>(h, K, kind, 0, true) : nullptr;
+  if (ig)
+    HIPCHK(hipGraphLaunch(ig->exec, h->work));
+  else
+    start_phase<T>(h, K, kind);
 }
 
 // poll iterations (by default poll_every, after which the host reads the flags)
@@ -1118,23 +1152,13 @@ void solve_cg(Handle *h, int K, double rtol, int max_iter, ColResult *res) {
   Work<double> &v = h->v64;
   bool mixed = h->opt.precision == VEMG_MIXED_PC;
   int kind = mixed ? kGraphMixedPC : kGraphFP64;
-  double bb[kMaxBatch];
-  rhs_norms(h, K, bb);
-  if (mixed) {
-    double sin[kMaxBatch], sout[kMaxBatch];
-    for (int k = 0; k < K; ++k) {
-      double nb = std::sqrt(bb[k]);
-      sin[k] = (nb > 0.0 && std::isfinite(nb)) ? 1.0 / nb : 0.0;
-      sout[k] = (nb > 0.0 && std::isfinite(nb)) ? nb : 0.0;
-    }
-    upload_scales(h, K, sin, sout);
-  }
   launch_fill<double>(st, v.x, n * K, 0.0, nullptr);
   launch_fill<double>(st, v.xs, n * K, 0.0, nullptr);
   launch_fill<double>(st, v.xl, n * K, 0.0, nullptr);
   launch_copy<double>(st, h->b, v.r, n * K, nullptr);
   launch_dot<double>(st, K, h->b, h->b, n, h->part_b, nullptr);
-  launch_pcg_init(st, K, h->scal, h->part_b, vec_blocks(n), rtol, max_iter);
+  launch_pcg_init(st, K, h->scal, h->part_b, vec_blocks(n), rtol, max_iter, mixed ? h->scale_in : nullptr,
+                  h->scale_out);
   const unsigned all = (1u << K) - 1u;
   double prev[kMaxBatch], need = INFINITY;
   bool final_[kMaxBatch];
@@ -1144,15 +1168,9 @@ void solve_cg(Handle *h, int K, double rtol, int max_iter, ColResult *res) {
     final_[k] = false;
   }
   while (true) {
-    int64_t np = 0;
-    if (mixed) {
-      launch_demote(st, K, v.r, h->scale_in, h->v32.tmp, n, nullptr);
-      np = precond_mixed(h, K, v.r, v.z, nullptr);
-    } else
-      precond<double>(h, K, v.r, v.z, h->part_rz, &np, nullptr);
-    launch_pcg_set_rho(st, K, h->scal, h->part_rz, np);
-    launch_copy<double>(st, v.z, v.p, n * K, nullptr);
+    run_start<double>(h, K, kind);
     Scal hs = iterate<double>(h, K, kind, need);
+    const double *bb = hs.bnorm2;
     // columns already final hold x = 0 and are not updated: folding all is exact for them
     launch_fold(st, K, all, v.xs, v.xl, v.x, n);
     double rr[kMaxBatch];
@@ -1239,10 +1257,7 @@ void solve_ir(Handle *h, int K, double rtol, int max_iter, ColResult *res) {
     res[k] = ColResult();
   }
   while (true) {
-    int64_t np = 0;
-    precond<float>(h, K, v.r, v.z, h->part_rz, &np, nullptr);
-    launch_pcg_set_rho(st, K, h->scal, h->part_rz, np);
-    launch_copy<float>(st, v.z, v.p, n * K, nullptr);
+    run_start<float>(h, K, kGraphFP32);
     Scal hs = iterate<float>(h, K, kGraphFP32);
     // the last iteration folded every correction and left b - A (hi + lo) in v64.res
     launch_dot<double>(st, K, h->v64.res, h->v64.res, n, h->part_t, nullptr);
@@ -1451,6 +1466,7 @@ void upload(Handle *h) {
   h->b = h->ar.alloc<double>(cnt);
   h->diag = h->ar.upload(P.diag, st);
   h->perm = h->ar.upload(P.perm, st);
+  h->pos = h->ar.upload(std::vector<int32_t>(P.pos.begin(), P.pos.end()), st);
   // The products over all rows visit their slices in spatial order across
   // the colours (a slice's key: the spatial rank of its first row in the
   // range), so that the contiguous part of the visit order one XCD takes is
@@ -1525,6 +1541,18 @@ void sync_in(Handle *h) {
   HIPCHK(hipStreamWaitEvent(h->work, h->ev, 0));
 }
 
+// y = A x in natural order; ux, uy: n values each.  On the caller's stream:
+// every call leaves the work stream idle, and an event between two queues
+// costs more than the product of a small mesh.
+void matvec(Handle *h, const double *x, double *y, double *ux, double *uy) {
+  const int64_t n = h->P.n, N = h->P.n_nodes;
+  launch_gather_batch(h->user, 1, x, N, h->perm, ux, n, 1);
+  launch_spmv<double>(h->user, 1, h->A, 0, 0, n, ux, uy, nullptr, nullptr, h->order_all);
+  launch_scatter_batch(h->user, 1, uy, h->pos, y, N, 1);
+  HIPCHK(hipGetLastError());
+  HIPCHK(hipStreamSynchronize(h->user));
+}
+
 int batch_width(int m) {
   if (m >= 8) return 8;
   if (m >= 4) return 4;
@@ -1544,17 +1572,14 @@ int do_solve(Handle *h, int nrhs, const double *b_nat, double *x_nat, double rto
     if (m > 4 && m < 8) K = 8;  // pad small remainders up rather than splitting
     else if (m == 3) K = 4;
     int cols = std::min(K, m);
-    if (cols < K) launch_fill<double>(st, h->b, n * K, 0.0, nullptr);
-    for (int k = 0; k < cols; ++k) launch_gather(st, K, k, b_nat + (int64_t)(first + k) * N, h->perm, h->b, n);
+    launch_gather_batch(st, K, b_nat + (int64_t)first * N, N, h->perm, h->b, n, cols);
     ColResult res[kMaxBatch];
     if (h->opt.precision == VEMG_MIXED_IR)
       solve_ir(h, K, rtol, max_iter, res);
     else
       solve_cg(h, K, rtol, max_iter, res);
+    launch_scatter_batch(st, K, h->v64.x, h->pos, x_nat + (int64_t)first * N, N, cols);
     for (int k = 0; k < cols; ++k) {
-      double *xk = x_nat + (int64_t)(first + k) * N;
-      launch_fill<double>(st, xk, N, 0.0, nullptr);
-      launch_scatter(st, K, k, h->v64.x, h->perm, xk, n);
       if (iters) iters[first + k] = res[k].iters;
       if (relres) relres[first + k] = res[k].rel;
       int s = res[k].status;
@@ -2299,15 +2324,7 @@ vemg_status vemg_matvec(vemg_solver s, const double *x_dev, double *y_dev) {
   if (!s || !x_dev || !y_dev) return VEMG_ERR_INVALID_ARG;
   if (!s->ready || s->device < 0) return VEMG_ERR_STATE;
   return (vemg_status)guarded(s, [&]() -> int {
-    hipStream_t st = s->work;
-    int64_t n = s->P.n;
-    vemg::sync_in(s);
-    vemg::launch_gather(st, 1, 0, x_dev, s->perm, s->v64.tmp, n);
-    vemg::launch_spmv<double>(st, 1, s->A, 0, 0, n, s->v64.tmp, s->v64.res, nullptr, nullptr, s->order_all);
-    vemg::launch_fill<double>(st, y_dev, s->P.n_nodes, 0.0, nullptr);
-    vemg::launch_scatter(st, 1, 0, s->v64.res, s->perm, y_dev, n);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipStreamSynchronize(st));
+    vemg::matvec(s, x_dev, y_dev, s->v64.tmp, s->v64.res);
     return VEMG_OK;
   });
 }
@@ -2322,15 +2339,7 @@ vemg_status vemg_matvec_noalloc(vemg_solver s, const double *x_dev, double *y_de
   }
   return (vemg_status)guarded(s, [&]() -> int {
     double *buf = vemg::scratch_of(s->device);  // [0, n): x in storage order; [n, 2n): A x
-    hipStream_t st = s->work;
-    int64_t n = s->P.n;
-    vemg::sync_in(s);
-    vemg::launch_gather(st, 1, 0, x_dev, s->perm, buf, n);
-    vemg::launch_spmv<double>(st, 1, s->A, 0, 0, n, buf, buf + n, nullptr, nullptr, s->order_all);
-    vemg::launch_fill<double>(st, y_dev, s->P.n_nodes, 0.0, nullptr);
-    vemg::launch_scatter(st, 1, 0, buf + n, s->perm, y_dev, n);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipStreamSynchronize(st));
+    vemg::matvec(s, x_dev, y_dev, buf, buf + s->P.n);
     return VEMG_OK;
   });
 }

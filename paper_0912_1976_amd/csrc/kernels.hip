@@ -1260,6 +1260,34 @@ __global__ void k_scatter(const double *__restrict__ sto, const int64_t *__restr
   if (i < n) nat[perm[i]] = sto[i * K + k];
 }
 
+// all columns of a batch at once, a thread per row: whole rows are written or
+// read (a launch per column touched every line of the batch's vector each time)
+template <int K>
+__global__ void k_gather_batch(const double *__restrict__ nat, int64_t N, const int64_t *__restrict__ perm,
+                               double *__restrict__ sto, int64_t n, int cols) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int64_t p = perm[i];
+  Row<double, K> v{};
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+    if (k < cols) v.v[k] = nat[k * N + p];
+  st<double, K>(sto, i, v);
+}
+
+template <int K>
+__global__ void k_scatter_batch(const double *__restrict__ sto, const int32_t *__restrict__ pos,
+                                double *__restrict__ nat, int64_t N, int cols) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= N) return;
+  const int32_t p = pos[i];
+  Row<double, K> v{};
+  if (p >= 0) v = ld<double, K>(sto, p);
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+    if (k < cols) nat[k * N + i] = v.v[k];
+}
+
 __global__ void k_demote(const double *__restrict__ r64, const double *__restrict__ scale, float *__restrict__ r32,
                          int64_t n, int K, const int *__restrict__ done) {
   if (done && *done) return;
@@ -1425,7 +1453,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce(const double *p, int64_t np, 
 }
 
 __global__ __launch_bounds__(kBlock) void k_pcg_init(Scal *s, const double *pb, int64_t npb, int K, double tol,
-                                                     int maxit) {
+                                                     int maxit, double *scale_in, double *scale_out) {
   double sums[kMaxBatch];
   sum_partials(pb, npb, K, sums);
   for (int k = 0; k < kMaxBatch; ++k) {
@@ -1436,6 +1464,12 @@ __global__ __launch_bounds__(kBlock) void k_pcg_init(Scal *s, const double *pb, 
       s->rho[k] = 0.0;
       s->alpha[k] = 0.0;
       s->beta[k] = 0.0;
+      if (scale_in && k < K) {
+        const double nb = sqrt(t);
+        const bool ok = nb > 0.0 && isfinite(nb);
+        scale_in[k] = ok ? 1.0 / nb : 0.0;
+        scale_out[k] = ok ? nb : 0.0;
+      }
       if (k >= K || t == 0.0) {
         s->done[k] = 1;
         s->status[k] = 1;
@@ -2136,6 +2170,20 @@ void launch_scatter(hipStream_t stm, int K, int k, const double *sto, const int6
   hipLaunchKernelGGL(k_scatter, grid(vec_blocks(n)), dim3(kBlock), 0, stm, sto, perm, nat, n, K, k);
 }
 
+void launch_gather_batch(hipStream_t stm, int K, const double *nat, int64_t N, const int64_t *perm, double *sto,
+                         int64_t n, int cols) {
+  if (n <= 0) return;
+  VEMG_K_SWITCH(K, hipLaunchKernelGGL((k_gather_batch<KK>), grid(vec_blocks(n)), dim3(kBlock), 0, stm, nat, N, perm,
+                                      sto, n, cols))
+}
+
+void launch_scatter_batch(hipStream_t stm, int K, const double *sto, const int32_t *pos, double *nat, int64_t N,
+                          int cols) {
+  if (N <= 0) return;
+  VEMG_K_SWITCH(K, hipLaunchKernelGGL((k_scatter_batch<KK>), grid(vec_blocks(N)), dim3(kBlock), 0, stm, sto, pos, nat,
+                                      N, cols))
+}
+
 void launch_demote(hipStream_t stm, int K, const double *r64, const double *scale, float *r32, int64_t n,
                    const int *done) {
   if (n <= 0) return;
@@ -2151,8 +2199,9 @@ void launch_promote(hipStream_t stm, int K, const float *d32, const double *scal
     hipLaunchKernelGGL((k_promote<false>), grid(vec_blocks(n * K)), dim3(kBlock), 0, stm, d32, scale, x64, n, K, done);
 }
 
-void launch_pcg_init(hipStream_t stm, int K, Scal *s, const double *pb, int64_t npb, double tol, int maxit) {
-  hipLaunchKernelGGL(k_pcg_init, dim3(1), dim3(kBlock), 0, stm, s, pb, npb, K, tol, maxit);
+void launch_pcg_init(hipStream_t stm, int K, Scal *s, const double *pb, int64_t npb, double tol, int maxit,
+                     double *scale_in, double *scale_out) {
+  hipLaunchKernelGGL(k_pcg_init, dim3(1), dim3(kBlock), 0, stm, s, pb, npb, K, tol, maxit, scale_in, scale_out);
 }
 void launch_pcg_set_rho(hipStream_t stm, int, Scal *s, const double *p, int64_t np) {
   hipLaunchKernelGGL(k_pcg_set_rho, dim3(1), dim3(kBlock), 0, stm, s, p, np);

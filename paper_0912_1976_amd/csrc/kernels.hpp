@@ -279,6 +279,12 @@ void launch_jacobi(hipStream_t st, int K, const T *r, const double *diag, T *z, 
 // natural <-> storage order for column k of a batch (stride K)
 void launch_gather(hipStream_t st, int K, int k, const double *nat, const int64_t *perm, double *sto, int64_t n);
 void launch_scatter(hipStream_t st, int K, int k, const double *sto, const int64_t *perm, double *nat, int64_t n);
+// the first cols columns of a batch, natural [cols][N] <-> storage [n][K] (the
+// others 0); pos: storage row of each of the N nodes, -1 (value 0) if fixed
+void launch_gather_batch(hipStream_t st, int K, const double *nat, int64_t N, const int64_t *perm, double *sto,
+                         int64_t n, int cols);
+void launch_scatter_batch(hipStream_t st, int K, const double *sto, const int32_t *pos, double *nat, int64_t N,
+                          int cols);
 // mixed precision: r32 = r64 * scale[k];  x64 (+)= scale[k] * d32
 void launch_demote(hipStream_t st, int K, const double *r64, const double *scale, float *r32, int64_t n,
                    const int *done);
@@ -296,7 +302,9 @@ void launch_promote_dot(hipStream_t st, int K, const float *z32, const double *s
 constexpr int64_t kCompactFrom = 4096;
 constexpr int kCompact = 64;
 void launch_compact(hipStream_t st, int K, const double *p, int64_t np, double *out, const int *done);
-void launch_pcg_init(hipStream_t st, int K, Scal *s, const double *pb, int64_t npb, double tol, int maxit);
+// with scale_in: scale_in[k] = 1 / ||b_k||, scale_out[k] = ||b_k|| (0 unless finite and positive)
+void launch_pcg_init(hipStream_t st, int K, Scal *s, const double *pb, int64_t npb, double tol, int maxit,
+                     double *scale_in = nullptr, double *scale_out = nullptr);
 void launch_pcg_set_rho(hipStream_t st, int K, Scal *s, const double *p, int64_t np);
 // The scalars alternate between two records: `in` as the iteration finds them,
 // `mid` after alpha (and the convergence test).
