@@ -149,19 +149,22 @@ def vcycle_bytes(rows, off, pnnz, K, elt, val, fine_rows=None, fine_nnz=None):
     return total
 
 
-# The library's additive smoother takes the SOR cycle's fine forward sweep and
-# residual on meshes of this many fine unknowns or more (the rows where the
-# two differ, a few per cent, are swept again; their bytes are not counted).
+# A count of the two cycles' fine work one after the other: on meshes of this
+# many fine unknowns or more the additive smoother's fine forward sweep and
+# residual count as taken from the SOR cycle.  The library merges the cycles'
+# fine sweeps at every size (merged_iteration_bytes).
 SHARE_MIN_ROWS = 1000000
 
 
 def iteration_bytes(info, K=1, pc="vl_as", precision="fp64"):
     """Algorithmic bytes of one PCG iteration (preconditioner included) for a
-    batch of K columns, from the built arrays' sizes.  Mixed precision: the
-    preconditioner in FP32 (values and vectors), the Krylov part in FP64, plus
-    the demotion of r and promotion of z.  With the shared forward sweep the
-    additive smoother's fine sweep and residual are replaced by the SOR
-    cycle's stores of x and r into the smoother's vectors."""
+    batch of K columns with the preconditioner's two cycles one after the
+    other, every sweep and residual reading whole rows, from the built arrays'
+    sizes.  Mixed precision: the preconditioner in FP32 (values and vectors),
+    the Krylov part in FP64, plus the demotion of r and promotion of z.  From
+    SHARE_MIN_ROWS on the additive smoother's fine sweep and residual are
+    replaced by the SOR cycle's stores of x and r into the smoother's
+    vectors."""
     n = info["n"]
     pe, pv = (4, 4) if precision != "fp64" else (8, 8)
     krylov = spmv_bytes(info, K) + 6 * n * 8 * K + 3 * n * 8 * K   # q = A p with p.q; x, r update; p = z + beta p
@@ -183,6 +186,29 @@ def iteration_bytes(info, K=1, pc="vl_as", precision="fp64"):
         return (krylov + restrict_bytes(info, K, pe, pv) + s_cycle + a_cycle + prolong_bytes(info, K, pe, pv)
                 + join + mixed)
     return krylov + sor + s_cycle + a_cycle + join + mixed
+
+
+def merged_iteration_bytes(info, K=1, precision="fp64"):
+    """Algorithmic bytes of one PCG iteration with VL + additive smoother as
+    the library runs it: one forward sweep over the lower parts of the rows,
+    one residual over the upper parts, the restrictions of both cycles, their
+    coarse cycles (whose residuals read the upper parts too), one prolongation
+    and one backward sweep that also forms r.z.  The rows carried for the
+    smoother apart (a few per cent) are not counted."""
+    n, m, nnz = info["n"], info["n_top"], info["nnz_offdiag"]
+    e, v = (4, 4) if precision != "fp64" else (8, 8)
+    krylov = spmv_bytes(info, K) + 6 * n * 8 * K + 3 * n * 8 * K
+    half, vec = nnz * (v + 4) / 2, n * e * K
+    fine = (half + n * 8 + 2 * vec) + (half + 2 * vec) + gs_sweep_bytes(info, K, e, v)
+    coarse = vcycle_bytes(info["s_rows"], info["s_nnz"], info["p_nnz_s"], K, e, v)
+    coarse += vcycle_bytes(info["abar_rows"][1:], info["abar_nnz"][1:], info["p_nnz_abar"][1:], K, e, v)
+    for rows, off in ((info["s_rows"], info["s_nnz"]), (info["abar_rows"][1:], info["abar_nnz"][1:])):
+        coarse -= sum(o * (v + 4) / 2 + w * e * K for w, o in list(zip(rows, off))[:-1])
+    restrict = restrict_bytes(info, K, e, v) + transfer_bytes(info["p_nnz_abar"][0], n - m, info["abar_rows"][1], K, e,
+                                                              v)[0]
+    prolong = (info["e_nnz"] + info["p_nnz_abar"][0]) * (v + 4) + (m + info["abar_rows"][1]) * e * K + 2 * vec
+    mixed = (n * 4 * K) + (n * 4 * K + 2 * n * 8 * K) if precision != "fp64" else 0  # r demoted beside r; z promoted, r.z
+    return int(krylov + fine + coarse + restrict + prolong + mixed)
 
 
 def coarsest_bytes(info, K=1, elt=8):
@@ -212,35 +238,30 @@ def kernel_rates(s, info, vemg, K=1, reps=20, precision="fp64"):
     return out
 
 
-# Fine-level sweeps, fine SpMVs and sweeps on A_bar's first coarse level per
-# PCG iteration, by preconditioner (the surface levels are not timed apart):
-#   vl_as:  SOR cycle (2 fine sweeps, 1 residual SpMV) and the A_bar V-cycle
-#           (2 fine sweeps over the non-top rows, 1 residual SpMV, 2 sweeps on
-#           A_bar level 1), plus the CG product
+# Fine sweeps, fine SpMVs (in passes over whole rows: the forward sweep reads
+# the lower parts, the residual the upper ones) and sweeps on A_bar's first
+# coarse level per PCG iteration, by preconditioner (the surface levels are not
+# timed apart):
+#   vl_as:  the merged cycles' forward and backward sweep and residual, 2
+#           sweeps on A_bar level 1, plus the CG product
 #   vl_sor: the SOR cycle alone plus the CG product
 #   vl_add: the A_bar V-cycle plus the CG product
-# (vl_as on meshes of SHARE_MIN_ROWS fine unknowns or more: the A_bar
-# V-cycle's forward sweep and residual come from the SOR cycle, so 3 full
-# sweeps and 2 SpMVs)
-PER_ITERATION = {"vl_as": (4, 3, 2), "vl_sor": (2, 2, 0), "vl_add": (2, 2, 2), "jacobi": (0, 1, 0),
+PER_ITERATION = {"vl_as": (1.5, 1.5, 2), "vl_sor": (1.5, 1.5, 0), "vl_add": (1.5, 1.5, 2), "jacobi": (0, 1, 0),
                  "none": (0, 1, 0)}
-PER_ITERATION_SHARED = {"vl_as": (3, 2, 2)}
 KERNEL_NAMES = {
     "gs": "k_gs<double, {K}, false> (fine multicolour SOR, one colour per launch)",
     "spmv": "k_spmv<double, {K}, 0, true> (fine difference-form SpMV fused with p.q)",
-    "cgs": "k_patch_gs<double, {K}, false, false> (coarse block multicolour SOR, one patch colour per launch)",
-    "et": "k_csr_spmv<double, {K}, 64, 2> (restriction E~^T, CSR, 64 lanes per surface row)",
-    "e": "k_rect<double, {K}, true> (prolongation z += E~ y, SELL, one thread per fine row)",
+    "cgs": "k_patch_gs<double, {K}, false, false> (coarse block multicolour SOR, all patch colours in one launch)",
+    "et": "k_csr<double, {K}, (vemg::CsrMode)1> (restriction E~^T, CSR, 16 groups of lanes per surface row)",
+    "e": "k_rect<double, {K}, true> (prolongation z += E~ y, SELL)",
     "dense": "k_dense_part<double, {K}> (the surface coarsest level's explicit inverse streamed by columns)"}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pmc_traffic.json")
 
 
-def dominant_kernel(rates, pc, K, n):
+def dominant_kernel(rates, pc, K):
     """The hot kernel with the largest share of one iteration's time: its
-    algorithmic bytes and average duration per launch (the roofline entry);
-    n: the fine unknowns (whether the forward sweep is shared)."""
-    n_gs, n_spmv, n_cgs = (PER_ITERATION_SHARED[pc] if pc in PER_ITERATION_SHARED and n >= SHARE_MIN_ROWS
-                           else PER_ITERATION[pc])
+    algorithmic bytes and average duration per launch (the roofline entry)."""
+    n_gs, n_spmv, n_cgs = PER_ITERATION[pc]
     share = {"gs": n_gs * rates["fine_sweep"]["ms"], "spmv": n_spmv * rates["spmv"]["ms"],
              "cgs": n_cgs * rates.get("coarse_sweep", {"ms": 0.0})["ms"]}
     key = max(share, key=share.get)
@@ -308,7 +329,7 @@ def pmc_kernels(K):
     """Kernel-name patterns of the hot kernels with K columns (and of the
     calibration copy) in rocprofv3 output."""
     return {"gs": f"k_gs<double, {K}, false>", "spmv": f"k_spmv<double, {K}, 0, true>",
-            "cgs": f"k_patch_gs<double, {K}, false, false>", "et": f"k_csr_spmv<double, {K}, 64, 2>",
+            "cgs": f"k_patch_gs<double, {K}, false, false>", "et": f"k_csr<double, {K}, (vemg::CsrMode)1>",
             "e": f"k_rect<double, {K}, true>", "dense": f"k_dense_part<double, {K}>", "calibration": "MulFunctor"}
 
 
@@ -614,7 +635,7 @@ def serving(nreq, seed, rtol, dev, calib=64):
         return out, xs
 
     out = {"meshes_nodes": sizes, "setup_s": t_setup, "rtol": rtol, "requests": nreq,
-           "stream_pairs": 2}
+           "streams": 4}
     results = {}
     for prec in ("mixed_pc", "fp64"):
         srv.set_precision(prec)
@@ -875,10 +896,11 @@ def main():
 
     # live per-kernel timing (HIP events on the library's stream) and the roofline
     rates = kernel_rates(s, info, vemg, K, reps=20)
-    dom_key, dom = dominant_kernel(rates, args.pc, K, info["n"])
+    dom_key, dom = dominant_kernel(rates, args.pc, K)
     achieved = dom["bytes_per_launch"] / (dom["ms_per_launch"] * 1e-3) / 1e9
     traffic = measured_traffic(dom_key, args.workload, K)
-    it_bytes = iteration_bytes(info, K, args.pc)
+    merged = args.pc == "vl_as" and info["n_top"] > 0 and len(info["abar_rows"]) > 1
+    it_bytes = merged_iteration_bytes(info, K) if merged else iteration_bytes(info, K, args.pc)
     ms_iter = 1e3 * float(np.median(times)) / max_it
     whole = {"bytes_per_iteration": it_bytes, "ms_per_iteration": ms_iter,
              "GBs": it_bytes / (ms_iter * 1e-3) / 1e9,
@@ -901,7 +923,8 @@ def main():
                    "rel_err_vs_oracle_sampled": [error_vs_oracle(Xm[k], fixture, k) for k in range(K)],
                    "max_rel_err_vs_fp64": max(float(np.linalg.norm(Xm[k] - X64[k]) / np.linalg.norm(X64[k]))
                                               for k in range(K)),
-                   "iteration_bytes": iteration_bytes(info, K, args.pc, prec)}
+                   "iteration_bytes": (merged_iteration_bytes(info, K, prec) if merged
+                                       else iteration_bytes(info, K, args.pc, prec))}
             extras[prec] = rec
             log(f"{prec}: {rec['solves_per_s']:.2f} solves/s, iterations {im[0]}")
         s.set_precision("fp64")

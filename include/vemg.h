@@ -241,9 +241,9 @@ vemg_status vemg_apply(vemg_solver s, int op, const double *in_dev, double *out_
 /* Benchmark support: average device time in milliseconds of one
  * application of VEMG_OP_A (one SpMV launch), VEMG_OP_GS_FWD (one forward
  * multicolour sweep over all rows, one launch per colour),
- * VEMG_OP_GS_COARSE (the same on A_bar's first coarse level, one launch per
- * patch colour), VEMG_OP_COARSEST (the explicit inverse of the surface
- * hierarchy's coarsest level times a vector, one launch), VEMG_OP_ET
+ * VEMG_OP_GS_COARSE (the same on A_bar's first coarse level, one launch),
+ * VEMG_OP_COARSEST (the explicit inverse of the surface hierarchy's coarsest
+ * level times a vector, one launch), VEMG_OP_ET
  * (the restriction E~^T, one launch) or VEMG_OP_E (the prolongation E~
  * added into an n-vector, as the SOR cycle applies it, one launch) to nrhs (1..8)
  * columns, in the handle's inner precision (FP32 for VEMG_MIXED_IR, FP64
@@ -326,8 +326,8 @@ typedef struct {
 
 /* hbm_budget: device bytes the resident meshes may use (0 = no limit); a
  * mesh is admitted when its vemg_footprint (nrhs = 0) fits beside the other
- * resident meshes.  All lanes share two pairs of streams (four hardware
- * queues in all): lane i runs on pair i mod 2. */
+ * resident meshes.  All lanes share four streams, each with its own hardware
+ * queue: lane i runs on stream i mod 4. */
 vemg_status vemg_server_create(int device, size_t hbm_budget, const vemg_options *o, vemg_server *out);
 /* Registers a mesh (host setup now; same arguments as vemg_setup).  Fails
  * with VEMG_ERR_OOM if the mesh alone exceeds the budget. */

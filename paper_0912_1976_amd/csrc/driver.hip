@@ -1,13 +1,12 @@
 // Solver handle: packs the host setup into HBM (SELL-64 fine operator,
-// G-lanes-per-row CSR for coarse operators and transfers, FP64 and FP32
-// copies), runs the preconditioned CG loop on the device for batches of up to
+// CSR for coarse operators and transfers, FP64 and FP32 copies), runs the preconditioned CG loop on the device for batches of up to
 // eight right-hand sides, and exposes the C ABI of vemg.h.
 //
-// One PCG iteration is a fixed sequence of kernels whose scalars (alpha,
-// beta, per-column convergence flags) live in device memory, so it is
-// captured once per (precision, batch width) in a hipGraph and replayed;
-// every kernel returns at once when all columns have converged, so the host
-// only polls the flags every few iterations.
+// One PCG iteration is a fixed sequence of kernels on one stream whose scalars
+// (alpha, beta, per-column convergence flags) live in device memory, so the
+// chunk of iterations between two polls of the flags is captured once per
+// (precision, batch width, length) in a hipGraph and replayed; every kernel
+// returns at once when all columns have converged.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -317,7 +316,7 @@ struct Work {
 
 struct DLevel {
   Sell As;                      // fine A_bar level: rows [row0, row0 + n) of the fine SELL matrix
-  CsrG Ac;                      // coarse levels: standard form, G lanes per row
+  CsrG Ac;                      // coarse levels: standard form
   PatchSweep ps;                // coarse levels: the patches of the sweeps
   int64_t np = 0;               // number of patches
   unsigned long long *begun = nullptr;  // progress of the sweeps (PatchJob)
@@ -930,7 +929,7 @@ int64_t precond_mixed(Handle *h, int K, const double *rr, double *zz, const int 
 void reliable_update(Handle *h, int K) {
   hipStream_t st = h->work;
   const int64_t n = h->P.n;
-  launch_promote(st, K, h->v32.x, h->scale_out, h->v64.x, n, false, nullptr);
+  launch_promote(st, K, h->v32.x, h->scale_out, h->v64.x, n, nullptr);
   launch_fold(st, K, (1u << K) - 1u, h->v64.xs, h->v64.xl, h->v64.x, n);
   launch_fill<float>(st, h->v32.x, n * K, 0.0f, nullptr);
   launch_residual_ext(st, K, h->A, h->b, h->v64.xs, h->v64.xl, h->v64.res);
@@ -991,8 +990,8 @@ void destroy_graphs(Handle *h) {
   h->graphs.clear();
 }
 
-// A chunk is poll_every iterations, after which the host reads the flags; the
-// FP32 form's last one ends in the reliable update.  Up to kGraphIterations
+// A chunk is poll_every iterations or fewer (chunk_for), after which the host
+// reads the flags; the FP32 form's last one ends in the reliable update.  Up to kGraphIterations
 // of them are one graph: in a chain of dependent kernels, those of a graph of
 // 40 nodes (one iteration) took 1.73 us each and of one of 400 nodes 1.55 us,
 // launched one by one 2.4 us and more, bound by the host.  A longer chunk
@@ -1659,7 +1658,7 @@ int do_apply(Handle *h, int op, const double *in, double *out) {
     float *in32 = h->v32.res, *out32 = h->v32.q;
     launch_demote(st, 1, in, h->scale_in, in32, nin, nullptr);
     apply_op<float>(h, op, in32, out32);
-    launch_promote(st, 1, out32, h->scale_out, out, nout, false, nullptr);
+    launch_promote(st, 1, out32, h->scale_out, out, nout, nullptr);
   }
   HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(st));
@@ -1849,11 +1848,19 @@ int fail(Handle *h, int code, const std::string &msg) {
 
 template <class F>
 int guarded(Handle *h, F &&f) {
+  // a call that fails leaves nothing running either
+  struct Drain {
+    Handle *h;
+    ~Drain() {
+      if (h && h->work && std::uncaught_exceptions()) (void)hipStreamSynchronize(h->work);
+    }
+  };
   try {
     if (h && h->device >= 0) {
       hipError_t e = hipSetDevice(h->device);
       if (e != hipSuccess) return fail(h, VEMG_ERR_DEVICE, hipGetErrorString(e));
     }
+    Drain drain{h};
     return f();
   } catch (const SetupError &e) {
     return fail(h, e.code, e.what());

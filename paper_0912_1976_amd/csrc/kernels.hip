@@ -1,14 +1,14 @@
 // HIP kernels of the PCG hot path for gfx950 (CDNA4, wave64).
 //
-// The path is sparse and bandwidth-bound, so there is no MFMA here: every
-// kernel streams its matrix once with coalesced loads (SELL-64 for the fine
-// operator, G-lanes-per-row CSR for coarse operators and transfers), reads
-// each matrix entry once for all K right-hand sides of a batch, gathers the
-// vector rows it needs through L2 / the Infinity Cache, and keeps
-// reductions deterministic (per-block partials summed in index order by a
-// single-block consumer).  Blocks are renumbered so that each of the eight
-// XCDs works on a contiguous range of rows, which keeps the gathered vector
-// lines in that XCD's L2.
+// The path is sparse: every kernel streams its matrix once with coalesced loads
+// (SELL-64 for the fine operator, CSR rows over groups of lanes for coarse
+// operators and transfers), reads each matrix entry once for all K right-hand
+// sides of a batch, gathers the vector rows it needs through L2 / the Infinity
+// Cache, and keeps reductions deterministic (per-block partials, added in an
+// order that does not depend on K).  The matrix cores multiply by the dense
+// triangular factors of the coarse levels' patches.  Blocks are renumbered so
+// that each of the eight XCDs works on a contiguous range of rows, which keeps
+// the gathered vector lines in that XCD's L2.
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -946,12 +946,12 @@ __device__ __forceinline__ Row<T, C> agent_row(__amdgpu_buffer_rsrc_t x, int32_t
     return __builtin_bit_cast(Row<T, C>, __builtin_amdgcn_raw_buffer_load_b128(x, off, 0, kAgentScope));
 }
 
-template <class T, int K, PatchDir DIR>
+// FIRST: from x = 0 (forward only)
+template <class T, int K, bool FIRST, bool BWD>
 __global__ __launch_bounds__(kPatchThreads, 4) void k_patch_gs(Jobs<PatchJob<T>> P, const int *__restrict__ done) {
   constexpr int LPR = row_lanes<T, K>(), C = K / LPR, G = kPatchGroups, W = kPatchTile;
   constexpr int RP = kPatchThreads / (G * LPR);  // unknowns summed at once
   constexpr int NP = kPatchLdsRows / RP, U = NP == 4 ? 2 : entries_ahead<T, C>();
-  constexpr bool BWD = DIR == kPatchBackward;
   using Tile = typename std::conditional<sizeof(T) == 8, Tile64, Tile32>::type;
   __shared__ Row<T, K> xs[kPatchLdsRows + kPatchHalo];  // the patch's own old values, and its halo's
   __shared__ Row<T, K> hs[kPatchLdsRows];
@@ -992,8 +992,8 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch_gs(Jobs<PatchJob<T>>
   if constexpr (kFactorAhead) load_factor();
   // the staged rows: with a start the patch's own, then the halo (from zero its
   // earlier patches)
-  constexpr int own = DIR == kPatchFirst ? 0 : kPatchLdsRows;
-  const int nh = DIR == kPatchFirst ? D.nearly : D.nhalo;
+  constexpr int own = FIRST ? 0 : kPatchLdsRows;
+  const int nh = FIRST ? D.nearly : D.nhalo;
   const int st = threadIdx.x / LPR, sq = threadIdx.x % LPR;
   constexpr int SP = kPatchThreads / LPR;  // rows staged at once
   auto staged = [&](int i) {  // global row of staged row i, -1: none
@@ -1018,7 +1018,7 @@ __global__ __launch_bounds__(kPatchThreads, 4) void k_patch_gs(Jobs<PatchJob<T>>
       const int32_t end = pr[1].b;
       // what is taken: earlier patches; those and later ones beside the own patch's old values
       const int32_t cut = BWD ? r.late : r.own, from = BWD ? r.next : r.late;
-      R[s] = EntryRange{r.b, DIR == kPatchFirst ? r.own - r.b : cut - r.b + end - from, cut - r.b, from - cut};
+      R[s] = EntryRange{r.b, FIRST ? r.own - r.b : cut - r.b + end - from, cut - r.b, from - cut};
       gr[s] = ldp<T, K, C>(g, D.row0 + row, q);
       if constexpr (sizeof(T) == 4) inv[s] = 1.0f / A.s32[D.row0 + row];
       if (ge < R[s].n) load_entries<T, U, G>(J.S.lcol, vals, R[s], ge, c[s], v[s]);
@@ -1295,14 +1295,12 @@ __global__ void k_demote(const double *__restrict__ r64, const double *__restric
   if (i < n * K) r32[i] = (float)(r64[i] * scale[i % K]);
 }
 
-template <bool ACC>
 __global__ void k_promote(const float *__restrict__ d32, const double *__restrict__ scale, double *__restrict__ x64,
                           int64_t n, int K, const int *__restrict__ done) {
   if (done && *done) return;
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n * K) return;
-  const double v = scale[i % K] * (double)d32[i];
-  x64[i] = ACC ? x64[i] + v : v;
+  x64[i] = scale[i % K] * (double)d32[i];
 }
 
 // ------------------------------------------------------------- PCG scalars
@@ -2101,11 +2099,11 @@ void launch_patch_gs(hipStream_t stm, int K, PatchDir dir, const PatchJob<T> *jo
   if (!nb) return;
   VEMG_K_SWITCH(K, {
     if (dir == kPatchFirst)
-      hipLaunchKernelGGL((k_patch_gs<T, KK, kPatchFirst>), grid(nb), dim3(kPatchThreads), 0, stm, P, done);
+      hipLaunchKernelGGL((k_patch_gs<T, KK, true, false>), grid(nb), dim3(kPatchThreads), 0, stm, P, done);
     else if (dir == kPatchBackward)
-      hipLaunchKernelGGL((k_patch_gs<T, KK, kPatchBackward>), grid(nb), dim3(kPatchThreads), 0, stm, P, done);
+      hipLaunchKernelGGL((k_patch_gs<T, KK, false, true>), grid(nb), dim3(kPatchThreads), 0, stm, P, done);
     else
-      hipLaunchKernelGGL((k_patch_gs<T, KK, kPatchForward>), grid(nb), dim3(kPatchThreads), 0, stm, P, done);
+      hipLaunchKernelGGL((k_patch_gs<T, KK, false, false>), grid(nb), dim3(kPatchThreads), 0, stm, P, done);
   })
 }
 
@@ -2191,12 +2189,9 @@ void launch_demote(hipStream_t stm, int K, const double *r64, const double *scal
 }
 
 void launch_promote(hipStream_t stm, int K, const float *d32, const double *scale, double *x64, int64_t n,
-                    bool accumulate, const int *done) {
+                    const int *done) {
   if (n <= 0) return;
-  if (accumulate)
-    hipLaunchKernelGGL((k_promote<true>), grid(vec_blocks(n * K)), dim3(kBlock), 0, stm, d32, scale, x64, n, K, done);
-  else
-    hipLaunchKernelGGL((k_promote<false>), grid(vec_blocks(n * K)), dim3(kBlock), 0, stm, d32, scale, x64, n, K, done);
+  hipLaunchKernelGGL(k_promote, grid(vec_blocks(n * K)), dim3(kBlock), 0, stm, d32, scale, x64, n, K, done);
 }
 
 void launch_pcg_init(hipStream_t stm, int K, Scal *s, const double *pb, int64_t npb, double tol, int maxit,

@@ -285,11 +285,11 @@ void launch_gather_batch(hipStream_t st, int K, const double *nat, int64_t N, co
                          int64_t n, int cols);
 void launch_scatter_batch(hipStream_t st, int K, const double *sto, const int32_t *pos, double *nat, int64_t N,
                           int cols);
-// mixed precision: r32 = r64 * scale[k];  x64 (+)= scale[k] * d32
+// mixed precision: r32 = r64 * scale[k];  x64 = scale[k] * d32
 void launch_demote(hipStream_t st, int K, const double *r64, const double *scale, float *r32, int64_t n,
                    const int *done);
 void launch_promote(hipStream_t st, int K, const float *d32, const double *scale, double *x64, int64_t n,
-                    bool accumulate, const int *done);
+                    const int *done);
 
 // z64 = scale[k] z32; partial[block * K + k] = sum r_ik z_ik
 void launch_promote_dot(hipStream_t st, int K, const float *z32, const double *scale, const double *r, double *z64,
