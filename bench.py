@@ -194,7 +194,7 @@ def merged_iteration_bytes(info, K=1, precision="fp64"):
     one residual over the upper parts, the restrictions of both cycles, their
     coarse cycles (whose residuals read the upper parts too), one prolongation
     and one backward sweep that also forms r.z.  The rows carried for the
-    smoother apart (a few per cent) are not counted."""
+    smoother apart (a tenth) are not counted."""
     n, m, nnz = info["n"], info["n_top"], info["nnz_offdiag"]
     e, v = (4, 4) if precision != "fp64" else (8, 8)
     krylov = spmv_bytes(info, K) + 6 * n * 8 * K + 3 * n * 8 * K

@@ -84,6 +84,31 @@ struct SellSpans {
   std::vector<int64_t> sptr, smid;
 };
 
+// fn(s) for every slice, on host threads by ranges of slices
+template <class F>
+void by_slices(int64_t ns, int64_t work, F &&fn) {
+  parallel_threads(work, [&](int t, int nt) {
+    for (int64_t s = ns * t / nt, s1 = ns * (t + 1) / nt; s < s1; ++s) fn(s);
+  });
+}
+
+// the allocations of a Sell of n rows after its slice offsets, counted
+Sell count_sell(Arena &ar, int64_t n, int64_t entries, bool pairs, bool data) {
+  ar.alloc<int32_t>(entries);
+  if (pairs) ar.alloc<int32_t>(entries);
+  ar.alloc<double>(entries);
+  ar.alloc<float>(entries);
+  if (data) {
+    ar.alloc<double>(n);
+    ar.alloc<double>(n);
+    ar.alloc<float>(n);
+    ar.alloc<float>(n);
+  }
+  Sell M;
+  M.nrows = n;
+  return M;
+}
+
 // CSR (host) -> SELL-64 (device).  Square: the diagonal entries are taken
 // out of the stored entries; the FP64 per-row term is `d` if given
 // (difference form: the deficit) else a_ii.  FP32 copy: a_ij / a_ii with
@@ -101,7 +126,7 @@ Sell pack_sell(Arena &ar, hipStream_t st, const Csr &A, bool square, const std::
     return colour && (*colour)[c] > (*colour)[r] ? 1 : 0;
   };
   std::vector<int64_t> sptr(ns + 1, 0), smid(ns, 0);
-  for (int64_t s = 0; s < ns; ++s) {
+  by_slices(ns, A.nnz(), [&](int64_t s) {
     int64_t L[2] = {0, 0};
     for (int64_t r = s * kWave; r < std::min(n, (s + 1) * kWave); ++r) {
       int64_t len[2] = {0, 0};
@@ -111,8 +136,19 @@ Sell pack_sell(Arena &ar, hipStream_t st, const Csr &A, bool square, const std::
       }
       for (int p = 0; p < 2; ++p) L[p] = std::max(L[p], len[p]);
     }
-    smid[s] = sptr[s] + L[0] * kWave;
-    sptr[s + 1] = smid[s] + L[1] * kWave;
+    smid[s] = L[0] * kWave;
+    sptr[s + 1] = L[1] * kWave;
+  });
+  for (int64_t s = 0; s < ns; ++s) {
+    smid[s] += sptr[s];
+    sptr[s + 1] += smid[s];
+  }
+  if (stored) *stored = sptr[ns];
+  if (spans) *spans = SellSpans{sptr, smid};
+  if (ar.count_only) {
+    ar.alloc<int64_t>(ns + 1);
+    if (colour) ar.alloc<int64_t>(ns);
+    return count_sell(ar, n, sptr[ns], false, square);
   }
   std::vector<int32_t> col(sptr[ns]);
   std::vector<double> val(sptr[ns], 0.0);
@@ -124,7 +160,7 @@ Sell pack_sell(Arena &ar, hipStream_t st, const Csr &A, bool square, const std::
       if (A.idx[e] == r) ad[r] = A.val[e];
     dv[r] = d ? (*d)[r] : ad[r];
   }
-  for (int64_t s = 0; s < ns; ++s) {
+  by_slices(ns, A.nnz(), [&](int64_t s) {
     for (int t = 0; t < kWave; ++t) {
       const int64_t r = s * kWave + t;
       int64_t pos[2] = {sptr[s] + t, smid[s] + t};
@@ -140,9 +176,7 @@ Sell pack_sell(Arena &ar, hipStream_t st, const Csr &A, bool square, const std::
       for (int p = 0; p < 2; ++p)
         for (; pos[p] < end[p]; pos[p] += kWave) col[pos[p]] = (square && r < n) ? (int32_t)r : 0;
     }
-  }
-  if (stored) *stored = sptr[ns];
-  if (spans) *spans = SellSpans{sptr, smid};
+  });
   Sell M;
   M.nrows = n;
   M.sptr = ar.upload(sptr, st);
@@ -184,32 +218,40 @@ struct RowData {
 template <class F, class G>
 Sell pack_rows(Arena &ar, hipStream_t st, int64_t n, bool pairs, F &&row, G &&pad, const RowData &data = RowData()) {
   const int64_t ns = (n + kWave - 1) / kWave;
-  std::vector<int64_t> sptr(ns + 1, 0), ptr(n + 1, 0);
-  std::vector<RowEntry> all;
-  for (int64_t i = 0; i < n; ++i) {
-    row(i, all);
-    ptr[i + 1] = (int64_t)all.size();
-  }
-  for (int64_t s = 0; s < ns; ++s) {
-    int64_t L = 0;
-    for (int64_t i = s * kWave; i < std::min(n, (s + 1) * kWave); ++i) L = std::max(L, ptr[i + 1] - ptr[i]);
-    sptr[s + 1] = sptr[s] + L * kWave;
+  std::vector<int64_t> sptr(ns + 1, 0);
+  by_slices(ns, 8 * n, [&](int64_t s) {
+    std::vector<RowEntry> out;
+    for (int64_t i = s * kWave; i < std::min(n, (s + 1) * kWave); ++i) {
+      out.clear();
+      row(i, out);
+      sptr[s + 1] = std::max(sptr[s + 1], (int64_t)out.size() * kWave);
+    }
+  });
+  for (int64_t s = 0; s < ns; ++s) sptr[s + 1] += sptr[s];
+  if (ar.count_only) {
+    ar.alloc<int64_t>(ns + 1);
+    return count_sell(ar, n, sptr[ns], pairs, !data.diag.empty());
   }
   std::vector<int32_t> col(sptr[ns], 0), col2(pairs ? sptr[ns] : 0, -1);
   std::vector<double> val(sptr[ns], 0.0);
   std::vector<float> val32(sptr[ns], 0.0f);
-  for (int64_t s = 0; s < ns; ++s)
+  by_slices(ns, 8 * n, [&](int64_t s) {
+    std::vector<RowEntry> out;
     for (int t = 0; t < kWave && s * kWave + t < n; ++t) {
       const int64_t i = s * kWave + t;
+      out.clear();
+      row(i, out);
       int64_t pos = sptr[s] + t;
-      for (int64_t e = ptr[i]; e < ptr[i + 1]; ++e, pos += kWave) {
-        col[pos] = all[e].col;
-        if (pairs) col2[pos] = all[e].col2;
-        val[pos] = all[e].v;
-        val32[pos] = all[e].v32;
+      for (const RowEntry &e : out) {
+        col[pos] = e.col;
+        if (pairs) col2[pos] = e.col2;
+        val[pos] = e.v;
+        val32[pos] = e.v32;
+        pos += kWave;
       }
       for (; pos < sptr[s + 1]; pos += kWave) col[pos] = pad(i);
     }
+  });
   Sell M;
   M.nrows = n;
   M.sptr = ar.upload(sptr, st);
@@ -249,6 +291,26 @@ Sell pack_rows(Arena &ar, hipStream_t st, int64_t n, bool pairs, F &&row, G &&pa
 CsrG pack_csrg(Arena &ar, hipStream_t st, const Csr &A, bool square, int64_t *stored = nullptr,
                const std::vector<int64_t> *colkey = nullptr, int64_t coloff = 0,
                const std::vector<int32_t> *colmap = nullptr, const std::vector<uint8_t> *zero = nullptr) {
+  if (ar.count_only) {
+    int64_t nnz = 0;
+    for (int64_t r = 0; r < A.nrows; ++r)
+      for (int64_t k = A.ptr[r]; k < A.ptr[r + 1]; ++k)
+        nnz += !(square && A.idx[k] == r) && !(zero && (*zero)[A.idx[k] + coloff]);
+    if (stored) *stored = nnz;
+    ar.alloc<int32_t>(A.nrows + 1);
+    ar.alloc<int32_t>(nnz);
+    ar.alloc<double>(nnz);
+    ar.alloc<float>(nnz);
+    if (colkey && !square) ar.alloc<int32_t>(A.nrows);
+    if (square) {
+      ar.alloc<double>(A.nrows);
+      ar.alloc<float>(A.nrows);
+      ar.alloc<int32_t>(A.nrows);
+    }
+    CsrG M;
+    M.nrows = A.nrows;
+    return M;
+  }
   std::vector<int32_t> ptr(A.nrows + 1, 0), upper(square ? A.nrows : 0), col;
   std::vector<double> val, d(square ? A.nrows : 0, 0.0);
   std::vector<float> val32;
@@ -447,7 +509,7 @@ void pack_patches(Arena &ar, hipStream_t st, const Level &L, DLevel &dl) {
     std::fill(patch_of.begin() + L.patch_row[p], patch_of.begin() + L.patch_row[p + 1], (int32_t)p);
   for (int64_t p = 0; p < np; ++p) {
     const int64_t m = L.patch_row[p + 1] - L.patch_row[p], nt = (m + W - 1) / W;
-    if (n * kMaxBatch * 8 > INT32_MAX) throw DeviceError(VEMG_ERR_DEVICE, "coarse level above the sweep kernel's 32-bit offsets");
+    if (n * kMaxBatch * 8 > UINT32_MAX) throw DeviceError(VEMG_ERR_DEVICE, "coarse level above the sweep kernel's 32-bit offsets");
     if (m > kPatchLdsRows) throw DeviceError(VEMG_ERR_DEVICE, "a patch exceeds the sweep kernel's rows");
     desc[p] = PatchDesc{(int32_t)L.patch_row[p], (int32_t)m, tiles * W * W, (int32_t)halo.size(), 0, 0,
                         (int32_t)nbr.size(), 0, 0};
@@ -478,9 +540,13 @@ void pack_patches(Arena &ar, hipStream_t st, const Level &L, DLevel &dl) {
     halo.insert(halo.end(), out.begin(), out.end());
     tiles += nt * (nt + 1) / 2;
   }
-  std::vector<double> tf(tiles * W * W, 0.0), tb(tiles * W * W, 0.0);
-  std::vector<float> tf32(tiles * W * W, 0.0f), tb32(tiles * W * W, 0.0f);
+  std::vector<double> tf, tb;
+  std::vector<float> tf32, tb32;
   if (!ar.count_only) {
+    tf.assign(tiles * W * W, 0.0);
+    tb.assign(tiles * W * W, 0.0);
+    tf32.assign(tiles * W * W, 0.0f);
+    tb32.assign(tiles * W * W, 0.0f);
     std::vector<double> M, F;
     int64_t diag = 0;  // diagonal entries passed so far: not stored in the CsrG
     for (int64_t p = 0; p < np; ++p) {
@@ -532,10 +598,15 @@ void pack_patches(Arena &ar, hipStream_t st, const Level &L, DLevel &dl) {
   }
   dl.ps.desc = ar.upload(desc, st);
   dl.ps.rows = ar.upload(rows, st);
-  dl.ps.tf64 = ar.upload(tf, st);
-  dl.ps.tb64 = ar.upload(tb, st);
-  dl.ps.tf32 = ar.upload(tf32, st);
-  dl.ps.tb32 = ar.upload(tb32, st);
+  if (ar.count_only) {
+    for (int k = 0; k < 2; ++k) ar.alloc<double>(tiles * W * W);
+    for (int k = 0; k < 2; ++k) ar.alloc<float>(tiles * W * W);
+  } else {
+    dl.ps.tf64 = ar.upload(tf, st);
+    dl.ps.tb64 = ar.upload(tb, st);
+    dl.ps.tf32 = ar.upload(tf32, st);
+    dl.ps.tb32 = ar.upload(tb32, st);
+  }
   dl.ps.halo = ar.upload(halo, st);
   dl.ps.lcol = ar.upload(lcol, st);
   dl.ps.nbr = ar.upload(nbr, st);
@@ -550,7 +621,8 @@ void pack_patches(Arena &ar, hipStream_t st, const Level &L, DLevel &dl) {
 
 enum LevelsOf { kLevelsS = 0, kLevelsAbar = 1, kLevelsSA = 2 };
 
-void build_levels(Handle *h, std::vector<Level> &H, std::vector<DLevel> &D, int of) {
+// fine_Pt: the finest level's restriction where the caller has it
+void build_levels(Handle *h, std::vector<Level> &H, std::vector<DLevel> &D, int of, const Csr *fine_Pt = nullptr) {
   hipStream_t st = h->work;
   D.clear();
   for (size_t l = 0; l < H.size(); ++l) {
@@ -596,8 +668,8 @@ void build_levels(Handle *h, std::vector<Level> &H, std::vector<DLevel> &D, int 
       else
         dl.P = pack_csrg(h->ar, st, L.P, false);
       // the fine level's restriction gathers from fine rows row0 + c
-      dl.Pt = dl.fine ? pack_csrg(h->ar, st, transpose(L.P), false, nullptr, &h->P.loc_rank, dl.row0, nullptr,
-                                  &h->zero_res)
+      dl.Pt = dl.fine ? pack_csrg(h->ar, st, fine_Pt ? *fine_Pt : transpose(L.P), false, nullptr, &h->P.loc_rank,
+                                  dl.row0, nullptr, &h->zero_res)
                       : pack_csrg(h->ar, st, transpose(L.P), false);
     } else {
       dl.Cinv = h->ar.upload(L.Cinv, st);
@@ -1301,8 +1373,8 @@ void solve_ir(Handle *h, int K, double rtol, int max_iter, ColResult *res) {
 }
 
 // The rows of MergedRows (its comment defines D and R) and their packed forms;
-// returns the number of extended rows.
-int64_t merged_rows(Handle *h) {
+// P0t: A_bar's finest restriction.  Returns the number of extended rows.
+int64_t merged_rows(Handle *h, const Csr &P0t) {
   const Problem &P = h->P;
   const Csr &O = P.Aoff;
   const int64_t n = P.n, m = P.n_top;
@@ -1317,11 +1389,15 @@ int64_t merged_rows(Handle *h) {
   const int ncb = (int)P.bar_colour_start.size() - 1;
   h->dstart.assign(1, 0);
   for (int c = 0; c < ncb; ++c) {
-    for (int64_t i = P.bar_colour_start[c]; i < P.bar_colour_start[c + 1]; ++i) {
-      for (int64_t k = O.ptr[i]; k < O.ptr[i + 1] && !dirty[i]; ++k) {
-        const int64_t j = O.idx[k];
-        if (P.colour[j] < c && (j < m || dirty[j])) dirty[i] = 1;
-      }
+    const int64_t i0 = P.bar_colour_start[c], i1 = P.bar_colour_start[c + 1];
+    by_slices((i1 - i0 + kWave - 1) / kWave, 8 * (i1 - i0), [&](int64_t s) {
+      for (int64_t i = i0 + s * kWave; i < std::min(i1, i0 + (s + 1) * kWave); ++i)
+        for (int64_t k = O.ptr[i]; k < O.ptr[i + 1] && !dirty[i]; ++k) {
+          const int64_t j = O.idx[k];
+          if (P.colour[j] < c && (j < m || dirty[j])) dirty[i] = 1;
+        }
+    });
+    for (int64_t i = i0; i < i1; ++i) {
       if (dirty[i]) {
         xpos[i] = (int32_t)drow.size();
         drow.push_back((int32_t)i);
@@ -1332,13 +1408,16 @@ int64_t merged_rows(Handle *h) {
   M.n = n;
   M.n_top = m;
   M.nd = M.nx = (int64_t)drow.size();
+  std::vector<uint8_t> differs(n, 0);
+  by_slices((n + kWave - 1) / kWave, 8 * n, [&](int64_t s) {
+    for (int64_t i = std::max(m, s * kWave); i < std::min(n, (s + 1) * kWave); ++i)
+      for (int64_t k = O.ptr[i]; k < O.ptr[i + 1] && !differs[i]; ++k) {
+        const int64_t j = O.idx[k];
+        differs[i] = P.colour[j] > P.colour[i] && (j < m || dirty[j]);
+      }
+  });
   for (int64_t i = m; i < n; ++i) {
-    bool r = false;
-    for (int64_t k = O.ptr[i]; k < O.ptr[i + 1] && !r; ++k) {
-      const int64_t j = O.idx[k];
-      r = P.colour[j] > P.colour[i] && (j < m || dirty[j]);
-    }
-    if (!r) continue;
+    if (!differs[i]) continue;
     if (xpos[i] < 0) xpos[i] = (int32_t)M.nx++;
     rrow.push_back((int32_t)i);
     rpos.push_back(xpos[i]);
@@ -1405,7 +1484,7 @@ int64_t merged_rows(Handle *h) {
   std::vector<int32_t> map(n - m);
   for (int64_t i = m; i < n; ++i) map[i - m] = (int32_t)i;
   for (int64_t q = 0; q < M.nr; ++q) map[rrow[q] - m] = (int32_t)(n + rpos[q]);
-  h->merged_Pt = pack_csrg(ar, st, transpose(P0), false, nullptr, &P.loc_rank, m, &map, &h->zero_res);
+  h->merged_Pt = pack_csrg(ar, st, P0t, false, nullptr, &P.loc_rank, m, &map, &h->zero_res);
   M.drow = ar.upload(drow, st);
   M.rpos = ar.upload(rpos, st);
   M.xpos = ar.upload(xpos, st);
@@ -1426,16 +1505,20 @@ void upload(Handle *h) {
   SellSpans spans;
   h->A = pack_sell(h->ar, st, P.Aoff, true, &P.d, &P.diag, &h->nnz_A, &P.colour, &spans);
   h->zero_res.assign(n, 1);
-  for (int64_t i = 0; i < n; ++i)
-    for (int64_t k = P.Aoff.ptr[i]; k < P.Aoff.ptr[i + 1] && h->zero_res[i]; ++k)
-      if (P.colour[P.Aoff.idx[k]] > P.colour[i]) h->zero_res[i] = 0;
+  by_slices((n + kWave - 1) / kWave, P.Aoff.nnz(), [&](int64_t s) {
+    for (int64_t i = s * kWave; i < std::min(n, (s + 1) * kWave); ++i)
+      for (int64_t k = P.Aoff.ptr[i]; k < P.Aoff.ptr[i + 1] && h->zero_res[i]; ++k)
+        if (P.colour[P.Aoff.idx[k]] > P.colour[i]) h->zero_res[i] = 0;
+  });
   if (m > 0) {
     h->E = pack_sell(h->ar, st, P.E, false, nullptr, nullptr, &h->nnz_E);
     h->Et = pack_csrg(h->ar, st, P.Et, false, nullptr, &P.loc_rank, 0);
     h->Et_res = pack_csrg(h->ar, st, P.Et, false, nullptr, &P.loc_rank, 0, nullptr, &h->zero_res);
   }
   size_t cnt = (size_t)n * kMaxBatch;
-  const size_t ext = (size_t)(n + merged_rows(h)) * kMaxBatch;
+  Csr P0t;
+  if (P.Abar.size() > 1) P0t = transpose(P.Abar[0].P);
+  const size_t ext = (size_t)(n + merged_rows(h, P0t)) * kMaxBatch;
   auto mk64 = [&](Work<double> &v) {
     v.x = h->ar.alloc<double>(cnt);
     v.r = h->ar.alloc<double>(cnt);
@@ -1516,7 +1599,7 @@ void upload(Handle *h) {
     launch_fill<float>(st, h->v32.w, (int64_t)cnt, 0.0f, nullptr);
   }
   if (m > 0) build_levels(h, P.S, h->S, kLevelsS);
-  build_levels(h, P.Abar, h->Ab, kLevelsAbar);
+  build_levels(h, P.Abar, h->Ab, kLevelsAbar, &P0t);
   h->SA.clear();
   if (!P.SA.empty()) build_levels(h, P.SA, h->SA, kLevelsSA);
   if (!count) HIPCHK(hipStreamSynchronize(st));
