@@ -909,8 +909,10 @@ void additive_smoother(Handle *h, int K, const T *rr, Cycle<T> other, const CsrJ
 }
 
 // z = M^{-1} rr in precision T; partial sums of rr . z go to part (rows in
-// *np) unless it is null.  zz: the handle's own z vector (the merged cycles
-// extend it).
+// *np) unless it is null.  part holds dot_rows rows, as part_rz alone does: the
+// backward sweeps write one per slice and colour, which for few unknowns of
+// many colours is more than the other buffers have.  zz: the handle's own z
+// vector (the merged cycles extend it).
 template <class T>
 void precond(Handle *h, int K, const T *rr, T *zz, double *part, int64_t *np, const int *done) {
   hipStream_t st = h->work;
@@ -1691,7 +1693,7 @@ void apply_op(Handle *h, int op, const T *in, T *out) {
     case VEMG_OP_PRECOND: {
       launch_copy<T>(st, in, v.tmp, n, nullptr);
       int64_t np = 0;
-      precond<T>(h, 1, v.tmp, v.z, h->part_t, &np, nullptr);
+      precond<T>(h, 1, v.tmp, v.z, nullptr, &np, nullptr);  // z alone: no partial sums of r . z
       launch_copy<T>(st, v.z, out, n, nullptr);
       break;
     }
