@@ -131,7 +131,9 @@ typedef struct {
                           FP64 inverse), 8192 (at most 8192) */
   int poll_every;      /* most PCG iterations per host poll of the convergence flag, 8 */
   int max_restarts;    /* restarts from the true residual, 5 */
-  int use_graphs;      /* capture one PCG iteration in a hipGraph, 1 */
+  int use_graphs;      /* replay the start of a solve and the iterations between two polls as hipGraphs,
+                          all captured by the first solve of a preconditioner, precision and batch
+                          width (1, 2, 4 or 8 columns): no later solve captures any, 1 */
   int precision;       /* vemg_precision, VEMG_FP64 */
   double inner_rtol;   /* in (0, 1); not used by the solver (kept for the layout), 1e-4 */
   int max_outer;       /* >= 1; not used by the solver (kept for the layout), 30 */
@@ -283,7 +285,8 @@ vemg_status vemg_set_precision(vemg_solver s, int precision);
 /* Copies a setup array to host memory for inspection (bit-exact tests).
  * name: "perm" (int64 [n], storage -> natural), "colour" (int32 [n]),
  * "Aoff.ptr" (int64), "Aoff.idx" (int32), "Aoff.val", "d", "diag" (double),
- * "E.ptr", "E.idx", "E.val", "S_perm" (int64),
+ * "E.ptr", "E.idx", "E.val", "S_perm" (int64), "graphs" (int64, the number
+ * of hipGraphs captured so far),
  * "<h>.<level>.<what>" with h in {S, Abar, SA} and what in {A.ptr, A.idx, A.val,
  * P.ptr, P.idx, P.val, colour, node, agg, Cinv, rank (int64)}; levels in the
  * block multicolour order of the coarse SOR sweeps (all but the fine levels

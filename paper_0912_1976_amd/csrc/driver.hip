@@ -1126,11 +1126,14 @@ void run_start(Handle *h, int K, int kind) {
     start_phase<T>(h, K, kind);
 }
 
+// iterations of the graph that a chunk of poll iterations repeats
+int chunk_unit(int poll) { return poll <= kGraphIterations ? poll : 1; }
+
 // poll iterations (by default poll_every, after which the host reads the flags)
 template <class T>
 void run_chunk(Handle *h, int K, int kind, int poll = 0) {
   if (!poll) poll = std::max(1, h->opt.poll_every);
-  const int unit = poll <= kGraphIterations ? poll : 1;
+  const int unit = chunk_unit(poll);
   for (int done = 0; done < poll; done += unit) {
     const bool last = done + unit == poll;
     const IterGraph *ig = h->opt.use_graphs ? iteration_graph<T>(h, K, kind, unit, last) : nullptr;
@@ -1154,6 +1157,17 @@ int chunk_for(const Handle *h, double need) {
   return c;
 }
 
+// Captures what later chunks and later solves of (kind, K) may replay, so that
+// they capture nothing: which lengths a solve takes depends on its residuals.
+// Called while the device works on the first chunk, which hides most of it.
+template <class T>
+void capture_chunks(Handle *h, int K, int kind) {
+  if (!h->opt.use_graphs || kind == kGraphFP32) return;  // that form runs whole chunks alone
+  const int poll = std::max(1, h->opt.poll_every);
+  for (const int c : {chunk_for(h, poll / 4), chunk_for(h, poll / 2)})
+    iteration_graph<T>(h, K, kind, chunk_unit(c), true);
+}
+
 // Iterates until every column is done.  need: an estimate of the iterations
 // to come; later chunks take theirs from each column's residual reduction over
 // the chunk before.  Iterations after the last column is done cost an empty
@@ -1165,6 +1179,7 @@ Scal iterate(Handle *h, int K, int kind, double need = INFINITY) {
   bool have = false;
   while (true) {
     run_chunk<T>(h, K, kind, kind == kGraphFP32 ? 0 : chunk_for(h, need));
+    capture_chunks<T>(h, K, kind);
     const Scal hs = read_scal(h);
     if (hs.all_done) return hs;
     need = 0.0;
@@ -1894,6 +1909,7 @@ int do_export(Handle *h, const std::string &name, void *buf, size_t *bytes) {
   if (name == "d") return export_vec(P.d, buf, bytes);
   if (name == "diag") return export_vec(P.diag, buf, bytes);
   if (name == "S_perm") return export_vec(P.S_perm, buf, bytes);
+  if (name == "graphs") return export_vec(std::vector<int64_t>{(int64_t)h->graphs.size()}, buf, bytes);
   auto dot = name.find('.');
   if (dot == std::string::npos) return VEMG_ERR_INVALID_ARG;
   std::string head = name.substr(0, dot), rest = name.substr(dot + 1);
@@ -2626,7 +2642,7 @@ vemg_status vemg_server_add_mesh(vemg_server sv, int64_t n_nodes, const double *
       throw vemg::DeviceError(VEMG_ERR_DEVICE, "device allocations differ from the counted footprint");
     // capture both precisions' graphs now, while no other thread uses the device
     if (h->opt.use_graphs) {
-      const int poll = h->opt.poll_every, unit = poll <= vemg::kGraphIterations ? poll : 1;
+      const int unit = vemg::chunk_unit(h->opt.poll_every);
       vemg::iteration_graph<double>(h, vemg::kMaxBatch, vemg::kGraphFP64, unit, true);
       vemg::iteration_graph<double>(h, vemg::kMaxBatch, vemg::kGraphMixedPC, unit, true);
       HIPCHK(hipStreamSynchronize(h->work));

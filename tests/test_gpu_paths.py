@@ -168,3 +168,20 @@ def test_a_column_of_nan_or_infinity_stays_alone(precision):
     assert st == -6
     for k in (0, 3):
         assert its[k] == single[k][1][0] and torch.equal(x[k], single[k][0]), k
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed_pc", "mixed_ir"])
+@pytest.mark.parametrize("poll", [8, 5, 40])
+def test_only_the_first_solve_captures(precision, poll):
+    # the lengths of the chunks follow the residuals, so each tolerance takes others
+    m = box_mesh(21, 13, 6, 1e-2, jitter=0.3, seed=2, bathymetry=True)
+    s = _solver(m, "N", poll_every=poll, precision=precision, coarse_max=64)
+    b = s.rhs(fourier_field(m.xyz, 1e-2, 970))
+    s.solve(b, rtol=0.5)
+    first = s.export("graphs", np.int64)[0]
+    assert first > 0
+    for rtol in 10.0 ** -np.arange(1, 11):
+        s.solve(b, rtol=rtol)
+        assert s.export("graphs", np.int64)[0] == first, rtol
+    s.solve(np.stack([b, b]), rtol=1e-6)
+    assert s.export("graphs", np.int64)[0] > first  # another width
