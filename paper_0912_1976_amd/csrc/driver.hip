@@ -277,7 +277,7 @@ Sell pack_rows(Arena &ar, hipStream_t st, int64_t n, bool pairs, F &&row, G &&pa
 }
 
 // CSR (host) -> CsrG (device).  Square matrices keep only off-diagonals
-// (FP64 values with d64 = a_ii; FP32 values a_ij / a_ii with s32 = a_ii).
+// (FP64 values; FP32 values a_ij / a_ii with s32 = a_ii).
 // G = smallest power of two >= a sixth of the mean row length, clamped to
 // [2, 16]: a group of lanes keeps four to eight entries in flight.
 // With colkey (rectangular operators gathering from the fine level: the
@@ -288,27 +288,30 @@ Sell pack_rows(Arena &ar, hipStream_t st, int64_t n, bool pairs, F &&row, G &&pa
 // colmap (optional): the stored column of column c is (*colmap)[c].
 // zero (optional): the entries of the columns c with (*zero)[c + coloff] != 0
 // are left out (the operator's input is zero there).
+// like (optional): the same operator packed before with another colmap, whose
+// other arrays serve this one too.
 CsrG pack_csrg(Arena &ar, hipStream_t st, const Csr &A, bool square, int64_t *stored = nullptr,
                const std::vector<int64_t> *colkey = nullptr, int64_t coloff = 0,
-               const std::vector<int32_t> *colmap = nullptr, const std::vector<uint8_t> *zero = nullptr) {
+               const std::vector<int32_t> *colmap = nullptr, const std::vector<uint8_t> *zero = nullptr,
+               const CsrG *like = nullptr) {
   if (ar.count_only) {
     int64_t nnz = 0;
     for (int64_t r = 0; r < A.nrows; ++r)
       for (int64_t k = A.ptr[r]; k < A.ptr[r + 1]; ++k)
         nnz += !(square && A.idx[k] == r) && !(zero && (*zero)[A.idx[k] + coloff]);
     if (stored) *stored = nnz;
-    ar.alloc<int32_t>(A.nrows + 1);
     ar.alloc<int32_t>(nnz);
+    CsrG M;
+    M.nrows = A.nrows;
+    if (like) return M;
+    ar.alloc<int32_t>(A.nrows + 1);
     ar.alloc<double>(nnz);
     ar.alloc<float>(nnz);
     if (colkey && !square) ar.alloc<int32_t>(A.nrows);
     if (square) {
-      ar.alloc<double>(A.nrows);
       ar.alloc<float>(A.nrows);
       ar.alloc<int32_t>(A.nrows);
     }
-    CsrG M;
-    M.nrows = A.nrows;
     return M;
   }
   std::vector<int32_t> ptr(A.nrows + 1, 0), upper(square ? A.nrows : 0), col;
@@ -346,10 +349,15 @@ CsrG pack_csrg(Arena &ar, hipStream_t st, const Csr &A, bool square, int64_t *st
   while (G < 16 && G < mean / 6.0) G *= 2;
   if (stored) *stored = (int64_t)col.size();
   CsrG M;
+  if (like) {
+    M = *like;
+    M.col = ar.upload(col, st);
+    return M;
+  }
   M.nrows = A.nrows;
   M.G = G;
-  M.ptr = ar.upload(ptr, st);
   M.col = ar.upload(col, st);
+  M.ptr = ar.upload(ptr, st);
   M.val64 = ar.upload(val, st);
   M.val32 = ar.upload(val32, st);
   if (permute) {
@@ -359,7 +367,6 @@ CsrG pack_csrg(Arena &ar, hipStream_t st, const Csr &A, bool square, int64_t *st
   if (square) {
     std::vector<float> s32(A.nrows);
     for (int64_t r = 0; r < A.nrows; ++r) s32[r] = (float)d[r];
-    M.d64 = ar.upload(d, st);
     M.s32 = ar.upload(s32, st);
     M.upper = ar.upload(upper, st);
   }
@@ -467,9 +474,9 @@ struct vemg_solver_s {
   vemg::MergedRows M;
   std::vector<int64_t> dstart;
   vemg::CsrG merged_Pt;
-  // the top block of the additive smoother's x (rows [0, n_top) of v64.w and
-  // v32.w) is zero in the layout of every batch width up to w_clean
-  int w_clean = vemg::kMaxBatch;
+  // the top block of the additive smoother's x (rows [0, n_top) of w) is zero
+  // for rows of up to w_clean bytes
+  int w_clean = vemg::kMaxBatch * (int)sizeof(double);
   vemg::HostBox *host = nullptr;
   vemg::Scal *scal = nullptr;  // two records: between iterations, and within one (launch_pcg_xr)
   int64_t nnz_A = 0, nnz_E = 0;
@@ -652,15 +659,17 @@ void build_levels(Handle *h, std::vector<Level> &H, std::vector<DLevel> &D, int 
       dl.g32 = h->v32.r;
       dl.r32 = h->v32.resA;
     } else {
-      dl.Ac = pack_csrg(h->ar, st, L.A, true);
-      pack_patches(h->ar, st, L, dl);
       size_t cnt = (size_t)dl.n * kMaxBatch;
       dl.x64 = h->ar.alloc<double>(cnt);
       dl.g64 = h->ar.alloc<double>(cnt);
-      dl.r64 = h->ar.alloc<double>(cnt);
       dl.x32 = h->ar.alloc<float>(cnt);
       dl.g32 = h->ar.alloc<float>(cnt);
-      dl.r32 = h->ar.alloc<float>(cnt);
+      if (!dl.coarsest) {  // the coarsest is solved by its inverse alone
+        dl.Ac = pack_csrg(h->ar, st, L.A, true);
+        pack_patches(h->ar, st, L, dl);
+        dl.r64 = h->ar.alloc<double>(cnt);
+        dl.r32 = h->ar.alloc<float>(cnt);
+      }
     }
     if (!dl.coarsest) {
       if (dl.fine)
@@ -669,7 +678,8 @@ void build_levels(Handle *h, std::vector<Level> &H, std::vector<DLevel> &D, int 
         dl.P = pack_csrg(h->ar, st, L.P, false);
       // the fine level's restriction gathers from fine rows row0 + c
       dl.Pt = dl.fine ? pack_csrg(h->ar, st, fine_Pt ? *fine_Pt : transpose(L.P), false, nullptr, &h->P.loc_rank,
-                                  dl.row0, nullptr, &h->zero_res)
+                                  dl.row0, nullptr, &h->zero_res,
+                                  of == kLevelsAbar && h->merged ? &h->merged_Pt : nullptr)
                       : pack_csrg(h->ar, st, transpose(L.P), false);
     } else {
       dl.Cinv = h->ar.upload(L.Cinv, st);
@@ -971,17 +981,15 @@ void precond(Handle *h, int K, const T *rr, T *zz, double *part, int64_t *np, co
 }
 
 // The additive smoother reads the top columns of its x and takes them as
-// zero, so the top block of v64.w and v32.w must be zero.  Vectors are laid
-// out [n][K]: a call with K columns writes the non-top rows at [n_top K,
-// n K), which a later call with more columns reads as part of its top block
-// [0, n_top K).  Every call with K columns calls this first.
+// zero, so the top block of w must be zero.  Vectors are laid out [n][K], and
+// both precisions' w is one array: a call with K columns writes the non-top
+// rows from n_top K words on, which a later call with wider rows reads as part
+// of its top block.  Every call with K columns calls this first.
 void batch_layout(Handle *h, int K) {
   const int64_t m = h->P.n_top;
-  if (K > h->w_clean && m > 0) {
-    launch_fill<double>(h->work, h->v64.w, m * K, 0.0, nullptr);
-    launch_fill<float>(h->work, h->v32.w, m * K, 0.0f, nullptr);
-  }
-  h->w_clean = K;
+  const int width = K * (int)(h->opt.precision == VEMG_FP64 ? sizeof(double) : sizeof(float));
+  if (width > h->w_clean && m > 0) launch_fill<float>(h->work, h->v32.w, m * width / 4, 0.0f, nullptr);
+  h->w_clean = width;
 }
 
 // zz = M^{-1} rr in FP32 for FP64 CG (columns scaled by scale_in, rr already
@@ -1452,7 +1460,7 @@ int64_t merged_rows(Handle *h, const Csr &P0t) {
   auto entry = [&](int64_t i, int64_t k, int32_t col, int32_t col2) {
     return RowEntry{col, col2, O.val[k], (float)(O.val[k] / P.diag[i])};
   };
-  RowData dd, dt;
+  RowData dd;
   dd.d.resize(M.nd);
   dd.diag.resize(M.nd);
   for (int64_t q = 0; q < M.nd; ++q) {
@@ -1464,30 +1472,37 @@ int64_t merged_rows(Handle *h, const Csr &P0t) {
     dd.diag[q] = P.diag[i];
   }
   auto dpad = [&](int64_t q) { return (int32_t)(n + q); };
+  // row data that another matrix holds
+  auto row_data = [](Sell &to, const Sell &from) {
+    to.d64 = from.d64;
+    to.i64 = from.i64;
+    to.s32 = from.s32;
+    to.dh32 = from.dh32;
+  };
   M.fwd = pack_rows(ar, st, M.nd, false, [&](int64_t q, std::vector<RowEntry> &out) {
     const int64_t i = drow[q];
     for (int64_t k = O.ptr[i]; k < O.ptr[i + 1]; ++k)
       if (on(i, O.idx[k]) < 0) out.push_back(entry(i, k, fwd_col(O.idx[k]), -1));
-  }, dpad, dd);
+  }, dpad);
   M.bwd = pack_rows(ar, st, M.nd, false, [&](int64_t q, std::vector<RowEntry> &out) {
     const int64_t i = drow[q];
     for (int64_t k = O.ptr[i]; k < O.ptr[i + 1]; ++k)
       if (on(i, O.idx[k]) != 0) out.push_back(entry(i, k, ext_col(O.idx[k]), -1));
   }, dpad, dd);
-  RowData dr;
-  dr.d.assign(M.nr, 0.0);
-  for (int64_t q = 0; q < M.nr; ++q) dr.diag.push_back(P.diag[rrow[q]]);
+  row_data(M.fwd, M.bwd);
   M.res = pack_rows(ar, st, M.nr, false, [&](int64_t q, std::vector<RowEntry> &out) {
     const int64_t i = rrow[q];
     for (int64_t k = O.ptr[i]; k < O.ptr[i + 1]; ++k)
       if (on(i, O.idx[k]) > 0) out.push_back(entry(i, k, fwd_col(O.idx[k]), -1));
-  }, [&](int64_t q) { return rrow[q]; }, dr);
-  dt.d.assign(P.d.begin(), P.d.begin() + m);
-  dt.diag.assign(P.diag.begin(), P.diag.begin() + m);
+  }, [&](int64_t q) { return rrow[q]; });
+  std::vector<float> res_scale(M.nr);
+  for (int64_t q = 0; q < M.nr; ++q) res_scale[q] = (float)P.diag[rrow[q]];
+  M.res.s32 = ar.upload(res_scale, st);
   M.top = pack_rows(ar, st, m, true, [&](int64_t i, std::vector<RowEntry> &out) {
     for (int64_t k = O.ptr[i]; k < O.ptr[i + 1]; ++k)
       out.push_back(entry(i, k, O.idx[k], O.idx[k] < m ? -1 : ext_col(O.idx[k])));
-  }, [&](int64_t i) { return (int32_t)i; }, dt);
+  }, [&](int64_t i) { return (int32_t)i; });
+  row_data(M.top, h->A);  // its first rows
   const Csr &P0 = P.Abar[0].P;
   M.prol = pack_rows(ar, st, n, false, [&](int64_t i, std::vector<RowEntry> &out) {
     if (m > 0)
@@ -1536,32 +1551,28 @@ void upload(Handle *h) {
   Csr P0t;
   if (P.Abar.size() > 1) P0t = transpose(P.Abar[0].P);
   const size_t ext = (size_t)(n + merged_rows(h, P0t)) * kMaxBatch;
-  auto mk64 = [&](Work<double> &v) {
-    v.x = h->ar.alloc<double>(cnt);
-    v.r = h->ar.alloc<double>(cnt);
-    v.z = h->ar.alloc<double>(ext);
-    v.p = h->ar.alloc<double>(cnt);
-    v.q = h->ar.alloc<double>(cnt);
-    v.w = h->ar.alloc<double>(cnt);
-    v.res = h->ar.alloc<double>(ext);
-    v.resA = h->ar.alloc<double>(cnt);
-    v.tmp = h->ar.alloc<double>(cnt);
-    v.xs = h->ar.alloc<double>(cnt);
-    v.xl = h->ar.alloc<double>(cnt);
-  };
-  auto mk32 = [&](Work<float> &v) {
-    v.x = h->ar.alloc<float>(cnt);
-    v.r = h->ar.alloc<float>(cnt);
-    v.z = h->ar.alloc<float>(ext);
-    v.p = h->ar.alloc<float>(cnt);
-    v.q = h->ar.alloc<float>(cnt);
-    v.w = h->ar.alloc<float>(cnt);
-    v.res = h->ar.alloc<float>(ext);
-    v.resA = h->ar.alloc<float>(cnt);
-    v.tmp = h->ar.alloc<float>(cnt);
-  };
-  mk64(h->v64);
-  mk32(h->v32);
+  // Vectors that are never live together share memory (416 bytes a row).
+  Work<double> &v = h->v64;
+  Work<float> &f = h->v32;
+  for (double **p : {&v.x, &v.r, &v.p, &v.q, &v.w, &v.xs, &v.xl}) *p = h->ar.alloc<double>(cnt);
+  for (double **p : {&v.z, &v.res}) *p = h->ar.alloc<double>(ext);
+  f.r = h->ar.alloc<float>(cnt);
+  f.z = h->ar.alloc<float>(ext);
+  f.w = (float *)v.w;  // one precision's smoother at a time (batch_layout)
+  // q lives from an iteration's product to its x and r.  Beside it: a single
+  // operator's input, a served column's solution, and the FP32
+  // preconditioner's residual (as long as q: the extended rows are at most n).
+  v.tmp = v.q;
+  f.res = (float *)v.q;
+  // the smoother's cycle alone and the baseline's need no residual of the SOR cycle
+  v.resA = v.res;
+  f.resA = f.res;
+  // the FP32 preconditioner's input in FP64 CG, which has no FP32 r
+  f.tmp = f.r;
+  // FP32 PCG keeps in FP64 the solution and the true residual alone
+  f.x = (float *)v.p;
+  f.p = (float *)v.r;
+  f.q = (float *)v.z;
   h->b = h->ar.alloc<double>(cnt);
   h->diag = h->ar.upload(P.diag, st);
   h->perm = h->ar.upload(P.perm, st);
@@ -1611,9 +1622,8 @@ void upload(Handle *h) {
     // every column starts finished (no right-hand side yet)
     launch_fill<double>(st, h->part_b, kMaxBatch, 0.0, nullptr);
     launch_pcg_init(st, kMaxBatch, h->scal, h->part_b, 1, 1.0, 1);
-    // the top block of the smoother vectors stays zero
+    // the top block of the smoother's vector stays zero
     launch_fill<double>(st, h->v64.w, (int64_t)cnt, 0.0, nullptr);
-    launch_fill<float>(st, h->v32.w, (int64_t)cnt, 0.0f, nullptr);
   }
   if (m > 0) build_levels(h, P.S, h->S, kLevelsS);
   build_levels(h, P.Abar, h->Ab, kLevelsAbar, &P0t);

@@ -54,16 +54,15 @@ struct SliceRef {
 // a row's entries are dealt in turn to G groups of lanes (a power of two
 // chosen from the mean row length), each group holding the row's K columns 16
 // bytes a lane, and the groups' sums are added across lanes.  Square
-// operators store off-diagonals only: FP64 values with d64 = a_ii; FP32
-// values a_ij / a_ii with s32 = a_ii; row i's entries with columns > i (later
-// in the sweep order) begin at upper[i].
+// operators store off-diagonals only: FP64 values; FP32 values a_ij / a_ii
+// with s32 = a_ii; row i's entries with columns > i (later in the sweep order)
+// begin at upper[i].
 struct CsrG {
   const int32_t *ptr = nullptr;  // nrows + 1
   const int32_t *upper = nullptr;
   const int32_t *col = nullptr;
   const double *val64 = nullptr;
   const float *val32 = nullptr;
-  const double *d64 = nullptr;
   const float *s32 = nullptr;
   // rectangular operators only: stored row i is output row orow[i] (the rows
   // are stored in the spatial order of the columns they gather); null: i

@@ -185,3 +185,37 @@ def test_only_the_first_solve_captures(precision, poll):
         assert s.export("graphs", np.int64)[0] == first, rtol
     s.solve(np.stack([b, b]), rtol=1e-6)
     assert s.export("graphs", np.int64)[0] > first  # another width
+
+
+@pytest.mark.parametrize("pc", ["vl_as", "vl_add", "sa"])
+@pytest.mark.parametrize("coarse_max", [64, 8192])  # 8192: A_bar is one dense level
+def test_calls_of_every_precision_share_vectors_and_keep_apart(pc, coarse_max):
+    # the precisions' vectors overlap in memory; whatever ran before, in any
+    # precision, width or operator, a call gives what a fresh handle does
+    m = box_mesh(21, 13, 6, 1e-2, jitter=0.3, seed=2, bathymetry=True)
+    kw = dict(coarse_max=coarse_max, pc=pc)
+    s = _solver(m, "N", **kw)
+    n, nt = s.info()["n"], s.info()["n_top"]
+    B = np.stack([s.rhs(fourier_field(m.xyz, 1e-2, 990 + k)) for k in range(8)])
+    r = np.random.default_rng(6).standard_normal(n)
+    xn = np.random.default_rng(7).standard_normal(m.n)
+
+    def calls(h):
+        return {"solve 1": lambda: h.solve(B[0], rtol=1e-9)[0], "solve 8": lambda: h.solve(B, rtol=1e-9)[0],
+                "solve 2": lambda: h.solve(B[:2], rtol=1e-9)[0], "matvec": lambda: h.matvec(xn),
+                "precond": lambda: h.apply(lib.OP_PRECOND, r, n),
+                "vcycle": lambda: h.apply(lib.OP_VCYCLE_ABAR, r[nt:], n - nt),
+                "time": lambda: torch.tensor(h.time_op(lib.OP_A, nrhs=8, reps=1)[1])}
+
+    want = {}
+    for precision in ("fp64", "mixed_pc", "mixed_ir"):
+        for name in calls(s):
+            f = _solver(m, "N", precision=precision, **kw)
+            want[precision, name] = calls(f)[name]()
+            f.close()
+    order = [(p, c) for p in ("fp64", "mixed_pc", "mixed_ir") for c in calls(s)]
+    for k in range(3):
+        for i in np.random.default_rng(20 + k).permutation(len(order)):
+            precision, name = order[i]
+            s.set_precision(precision)
+            assert torch.equal(calls(s)[name](), want[precision, name]), (precision, name)
