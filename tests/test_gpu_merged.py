@@ -54,3 +54,27 @@ def test_merged_cycles_do_not_depend_on_the_batch_width(precision):
         assert st == 0
         for k in range(K):
             assert its[k] == single[k][1][0] and torch.equal(x[k], single[k][0]), (K, k)
+
+
+@pytest.mark.parametrize("nx,ny,nz,mode", [(9, 7, 2, "N"), (21, 5, 3, "R"), (19, 14, 8, "N"), (17, 13, 7, "D")])
+@pytest.mark.parametrize("precision", ["fp64", "mixed_pc"])
+def test_the_merged_cycles_are_the_sum_of_the_separate_ones(nx, ny, nz, mode, precision):
+    # the SOR cycle and the smoother's each with fine sweeps of its own, as the
+    # other preconditioners run them
+    m, s, o = _build(nx, ny, nz, mode, precision)
+    r = np.random.default_rng(5).standard_normal(o.n)
+    z = s.apply(lib.OP_PRECOND, r, o.n).cpu().numpy()
+    s.set_preconditioner("vl_sor")
+    ref = s.apply(lib.OP_PRECOND, r, o.n).cpu().numpy()
+    ref[o.n_top:] += s.apply(lib.OP_VCYCLE_ABAR, r[o.n_top:], o.n - o.n_top).cpu().numpy()
+    # the same terms summed in another order: some 15 a row, through the colours of two sweeps
+    eps = np.finfo(np.float64 if precision == "fp64" else np.float32).eps
+    colours = len(np.unique(s.export("colour", np.int32)))
+    err, tol = np.linalg.norm(z - ref) / np.linalg.norm(ref), 2 * 15 * colours * eps
+    print("separate", err, "tol", tol, flush=True)
+    assert err < tol
+    if precision != "fp64":  # FP32 operators against the oracle's
+        want = precond.make(o, "vl_as")(r)
+        err = np.linalg.norm(z - want) / np.linalg.norm(want)
+        print("oracle", err, flush=True)
+        assert err < 1e-4

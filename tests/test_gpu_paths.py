@@ -219,3 +219,9 @@ def test_calls_of_every_precision_share_vectors_and_keep_apart(pc, coarse_max):
             precision, name = order[i]
             s.set_precision(precision)
             assert torch.equal(calls(s)[name](), want[precision, name]), (precision, name)
+
+
+# where the sweeps form r.z again
+@pytest.mark.parametrize("nx,ny,nz", [(101, 99, 100), (100, 100, 100)])
+def test_sums_of_a_million_rows_do_not_depend_on_the_batch_width(nx, ny, nz):
+    test_scalar_steps_do_not_depend_on_the_batch_width(nx, ny, nz)
