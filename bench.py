@@ -188,27 +188,35 @@ def iteration_bytes(info, K=1, pc="vl_as", precision="fp64"):
     return krylov + sor + s_cycle + a_cycle + join + mixed
 
 
+def merged_fine_bytes(info, K=1, elt=8, val=8):
+    """The fine steps of VL + additive smoother, by the keys of KERNEL_NAMES:
+    the forward sweep over the lower parts of the rows, the residual over the
+    upper parts, the prolongation of both coarse corrections, the backward
+    sweep.  The rows carried for the smoother apart (a tenth) are not counted."""
+    n, half, vec = info["n"], info["nnz_offdiag"] * (val + 4) / 2, info["n"] * elt * K
+    prolong = (info["e_nnz"] + info["p_nnz_abar"][0]) * (val + 4) + (info["n_top"] + info["abar_rows"][1]) * elt * K
+    return {"merged_fwd": half + n * 8 + 2 * vec, "merged_res": half + 2 * vec, "merged_prolong": prolong + 2 * vec,
+            "merged_bwd": gs_sweep_bytes(info, K, elt, val)}
+
+
 def merged_iteration_bytes(info, K=1, precision="fp64"):
     """Algorithmic bytes of one PCG iteration with VL + additive smoother as
     the library runs it: one forward sweep over the lower parts of the rows,
     one residual over the upper parts, the restrictions of both cycles, their
     coarse cycles (whose residuals read the upper parts too), one prolongation
-    and one backward sweep that also forms r.z.  The rows carried for the
-    smoother apart (a tenth) are not counted."""
-    n, m, nnz = info["n"], info["n_top"], info["nnz_offdiag"]
+    and one backward sweep that also forms r.z."""
+    n, m = info["n"], info["n_top"]
     e, v = (4, 4) if precision != "fp64" else (8, 8)
     krylov = spmv_bytes(info, K) + 6 * n * 8 * K + 3 * n * 8 * K
-    half, vec = nnz * (v + 4) / 2, n * e * K
-    fine = (half + n * 8 + 2 * vec) + (half + 2 * vec) + gs_sweep_bytes(info, K, e, v)
+    fine = sum(merged_fine_bytes(info, K, e, v).values())
     coarse = vcycle_bytes(info["s_rows"], info["s_nnz"], info["p_nnz_s"], K, e, v)
     coarse += vcycle_bytes(info["abar_rows"][1:], info["abar_nnz"][1:], info["p_nnz_abar"][1:], K, e, v)
     for rows, off in ((info["s_rows"], info["s_nnz"]), (info["abar_rows"][1:], info["abar_nnz"][1:])):
         coarse -= sum(o * (v + 4) / 2 + w * e * K for w, o in list(zip(rows, off))[:-1])
     restrict = restrict_bytes(info, K, e, v) + transfer_bytes(info["p_nnz_abar"][0], n - m, info["abar_rows"][1], K, e,
                                                               v)[0]
-    prolong = (info["e_nnz"] + info["p_nnz_abar"][0]) * (v + 4) + (m + info["abar_rows"][1]) * e * K + 2 * vec
     mixed = (n * 4 * K) + (n * 4 * K + 2 * n * 8 * K) if precision != "fp64" else 0  # r demoted beside r; z promoted, r.z
-    return int(krylov + fine + coarse + restrict + prolong + mixed)
+    return int(krylov + fine + coarse + restrict + mixed)
 
 
 def coarsest_bytes(info, K=1, elt=8):
@@ -220,10 +228,15 @@ def coarsest_bytes(info, K=1, elt=8):
 
 def kernel_rates(s, info, vemg, K=1, reps=20, precision="fp64"):
     """Live per-application times of the hot operators of one iteration
-    (HIP events on the library's stream) and their algorithmic rates."""
+    (HIP events on the library's stream) and their algorithmic rates.  The fine
+    steps of the merged cycles where the handle has them; fine_sweep,
+    coarse_sweep and prolong_E are the general forms, with a start and on their
+    own, as the other preconditioners take them."""
     pe, pv = (4, 4) if precision == "mixed_ir" else (8, 8)
     out = {}
-    for name, op, nbytes in (("spmv", vemg.OP_A, spmv_bytes(info, K, pe, pv)),
+    merged = merged_fine_bytes(info, K, pe, pv) if len(info["abar_rows"]) > 1 else {}
+    steps = [(key, getattr(vemg, "OP_" + key.upper()), nbytes) for key, nbytes in merged.items()]
+    for name, op, nbytes in (*steps, ("spmv", vemg.OP_A, spmv_bytes(info, K, pe, pv)),
                              ("fine_sweep", vemg.OP_GS_FWD, gs_sweep_bytes(info, K, pe, pv)),
                              ("coarse_sweep", vemg.OP_GS_COARSE, coarse_gs_bytes(info, 1, K, pe, pv)),
                              ("coarsest_dense", vemg.OP_COARSEST, coarsest_bytes(info, K, pe)),
@@ -249,6 +262,10 @@ def kernel_rates(s, info, vemg, K=1, reps=20, precision="fp64"):
 PER_ITERATION = {"vl_as": (1.5, 1.5, 2), "vl_sor": (1.5, 1.5, 0), "vl_add": (1.5, 1.5, 2), "jacobi": (0, 1, 0),
                  "none": (0, 1, 0)}
 KERNEL_NAMES = {
+    "merged_fwd": "k_gs_merged<double, {K}, true> (both cycles' forward SOR from zero, one colour per launch)",
+    "merged_res": "k_res_merged<double, {K}> (both cycles' residual after it)",
+    "merged_prolong": "k_prolong_merged<double, {K}> (both coarse corrections prolonged and the cycles added)",
+    "merged_bwd": "k_gs_merged<double, {K}, false> (both cycles' backward SOR, one colour per launch)",
     "gs": "k_gs<double, {K}, false> (fine multicolour SOR, one colour per launch)",
     "spmv": "k_spmv<double, {K}, 0, true> (fine difference-form SpMV fused with p.q)",
     "cgs": "k_patch_gs<double, {K}, false, false> (coarse block multicolour SOR, all patch colours in one launch)",
@@ -264,8 +281,11 @@ def dominant_kernel(rates, pc, K):
     n_gs, n_spmv, n_cgs = PER_ITERATION[pc]
     share = {"gs": n_gs * rates["fine_sweep"]["ms"], "spmv": n_spmv * rates["spmv"]["ms"],
              "cgs": n_cgs * rates.get("coarse_sweep", {"ms": 0.0})["ms"]}
+    if pc == "vl_as" and "merged_bwd" in rates:  # the merged steps and the CG product
+        share = {"spmv": rates["spmv"]["ms"], "cgs": share["cgs"],
+                 **{key: rates[key]["ms"] for key in rates if key.startswith("merged_")}}
     key = max(share, key=share.get)
-    r = rates[{"gs": "fine_sweep", "spmv": "spmv", "cgs": "coarse_sweep"}[key]]
+    r = rates[{"gs": "fine_sweep", "cgs": "coarse_sweep"}.get(key, key)]
     return key, {"kernel": KERNEL_NAMES[key].format(K=K), "bytes_per_launch": r["bytes"] / r["launches"],
                  "ms_per_launch": r["ms"] / r["launches"], "launches_per_application": r["launches"],
                  "ms_per_iteration_estimate": share}
@@ -308,7 +328,9 @@ def profile_kernels(workload, K=1):
     mesh = build_mesh(WORKLOADS[workload])
     s = vemg.Solver(mesh.xyz, mesh.tets, mesh.top, top_bc="pinned", pc="vl_as", device=0)
     info = s.info()
-    for name, op in (("fine sweep", vemg.OP_GS_FWD), ("fine spmv", vemg.OP_A), ("coarse sweep", vemg.OP_GS_COARSE),
+    for name, op in (("merged forward sweep", vemg.OP_MERGED_FWD), ("merged residual", vemg.OP_MERGED_RES),
+                     ("merged prolongation", vemg.OP_MERGED_PROLONG), ("merged backward sweep", vemg.OP_MERGED_BWD),
+                     ("fine sweep", vemg.OP_GS_FWD), ("fine spmv", vemg.OP_A), ("coarse sweep", vemg.OP_GS_COARSE),
                      ("coarsest dense product", vemg.OP_COARSEST), ("restriction E~^T", vemg.OP_ET),
                      ("prolongation E~", vemg.OP_E)):
         ms, nl = s.time_op(op, reps=10, nrhs=K)
@@ -328,7 +350,9 @@ CALIBRATION_BYTES = 512 << 20
 def pmc_kernels(K):
     """Kernel-name patterns of the hot kernels with K columns (and of the
     calibration copy) in rocprofv3 output."""
-    return {"gs": f"k_gs<double, {K}, false>", "spmv": f"k_spmv<double, {K}, 0, true>",
+    return {"merged_fwd": f"k_gs_merged<double, {K}, true>", "merged_res": f"k_res_merged<double, {K}>",
+            "merged_prolong": f"k_prolong_merged<double, {K}>", "merged_bwd": f"k_gs_merged<double, {K}, false>",
+            "gs": f"k_gs<double, {K}, false>", "spmv": f"k_spmv<double, {K}, 0, true>",
             "cgs": f"k_patch_gs<double, {K}, false, false>", "et": f"k_csr<double, {K}, (vemg::CsrMode)1>",
             "e": f"k_rect<double, {K}, true>", "dense": f"k_dense_part<double, {K}>", "calibration": "MulFunctor"}
 
@@ -369,7 +393,7 @@ def pmc_traffic(fetch_dir, write_dir, workload, K):
                         f"python3 bench.py --pmc-traffic {fetch_dir} {write_dir} --workload {workload} "
                         f"--profile-batch {K}"],
            "kernels": {}}
-    for key in ("gs", "spmv", "cgs", "et", "e", "dense"):
+    for key in KERNEL_NAMES:
         if key in fetch and key in write:
             rec["kernels"][key] = {"kernel": KERNEL_NAMES[key].format(K=K), "fetch_kib": fetch[key],
                                    "write_kib": write[key],
@@ -393,7 +417,7 @@ def trace_timed(path, K):
     rows.sort()
     out = {}
     pats = pmc_kernels(K)
-    for key in ("spmv", "gs", "cgs"):
+    for key in ("merged_fwd", "merged_res", "merged_prolong", "merged_bwd", "spmv", "gs", "cgs"):
         pat = pats[key]
         run, last = [], []
         for t0, t1, name in rows:

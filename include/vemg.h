@@ -236,7 +236,12 @@ typedef enum {
   VEMG_OP_VCYCLE_ABAR = 5,
   VEMG_OP_GS_FWD = 6,
   VEMG_OP_GS_COARSE = 7, /* vemg_time_op only: one forward sweep on the first coarse level of A_bar */
-  VEMG_OP_COARSEST = 8   /* vemg_time_op only: the coarsest surface level's dense inverse times a vector */
+  VEMG_OP_COARSEST = 8,  /* vemg_time_op only: the coarsest surface level's dense inverse times a vector */
+  /* vemg_time_op only, the fine steps of VEMG_PC_VL_ADDITIVE, whose two cycles share them: */
+  VEMG_OP_MERGED_FWD = 9,      /* the forward sweep from zero */
+  VEMG_OP_MERGED_RES = 10,     /* the residual after it */
+  VEMG_OP_MERGED_PROLONG = 11, /* the prolongation of both coarse corrections */
+  VEMG_OP_MERGED_BWD = 12      /* the backward sweep, with its part of r . z where the solve forms it so */
 } vemg_op;
 vemg_status vemg_apply(vemg_solver s, int op, const double *in_dev, double *out_dev);
 
@@ -246,9 +251,11 @@ vemg_status vemg_apply(vemg_solver s, int op, const double *in_dev, double *out_
  * VEMG_OP_GS_COARSE (the same on A_bar's first coarse level, one launch),
  * VEMG_OP_COARSEST (the explicit inverse of the surface hierarchy's coarsest
  * level times a vector, one launch), VEMG_OP_ET
- * (the restriction E~^T, one launch) or VEMG_OP_E (the prolongation E~
- * added into an n-vector, as the SOR cycle applies it, one launch) to nrhs (1..8)
- * columns, in the handle's inner precision (FP32 for VEMG_MIXED_IR, FP64
+ * (the restriction E~^T, one launch), VEMG_OP_E (the prolongation E~
+ * added into an n-vector, as the SOR cycle applies it, one launch) or a
+ * VEMG_OP_MERGED_* step (the sweeps one launch per colour, the others one;
+ * VEMG_ERR_STATE where A_bar is a single dense level, whose cycles are not
+ * merged) to nrhs (1, 2, 4 or 8) columns, in the handle's inner precision (FP32 for VEMG_MIXED_IR, FP64
  * otherwise), measured with HIP events on the handle's own stream around
  * `reps` back-to-back applications on internal buffers, after one untimed
  * application.  *launches receives the kernel launches per application. */

@@ -7,5 +7,6 @@ that passes PyTorch device tensors as raw pointers.
 """
 from ._lib import (  # noqa: F401
     Solver, Server, VemgError, load_library, library_path, OP_A, OP_PRECOND, OP_ET, OP_E,
-    OP_VCYCLE_S, OP_VCYCLE_ABAR, OP_GS_FWD, OP_GS_COARSE, OP_COARSEST, STATUS,
+    OP_VCYCLE_S, OP_VCYCLE_ABAR, OP_GS_FWD, OP_GS_COARSE, OP_COARSEST, OP_MERGED_FWD, OP_MERGED_RES,
+    OP_MERGED_PROLONG, OP_MERGED_BWD, STATUS,
 )

@@ -882,24 +882,41 @@ int64_t sor_cycle(Handle *h, int K, const T *rr, T *zz, double *part, const int 
   return np;
 }
 
+// The fine parts of the two cycles in one (MergedRows): the forward sweep of
+// rr from zero, the backward sweep (part as in sor_cycle) and, between them,
+// the prolongation of both coarse corrections; zz has n + nx rows.
+template <class T>
+int64_t merged_colour(Handle *h, int K, int c, bool first, const T *rr, T *zz, double *part, const int *done) {
+  const ColourRows q = colour_rows(h->P, c);
+  const bool d = c + 1 < (int)h->dstart.size();
+  return launch_gs_merged<T>(h->work, K, h->A, h->M, q.a0, q.a1, q.b0, q.b1, d ? h->dstart[c] : 0,
+                             d ? h->dstart[c + 1] : 0, rr, zz, done, first, part);
+}
+template <class T>
+void merged_forward(Handle *h, int K, const T *rr, T *zz, const int *done) {
+  for (int c = 0; c < fine_colours(h->P); ++c) merged_colour<T>(h, K, c, true, rr, zz, nullptr, done);
+}
+template <class T>
+int64_t merged_backward(Handle *h, int K, const T *rr, T *zz, double *part, const int *done) {
+  int64_t np = 0;
+  for (int c = fine_colours(h->P) - 1; c >= 0; --c)
+    np += merged_colour<T>(h, K, c, false, rr, zz, part ? part + np * K : nullptr, done);
+  return np;
+}
+template <class T>
+void merged_prolong(Handle *h, int K, T *zz, const int *done) {
+  const T *ya = h->Ab[1].x<T>();
+  launch_prolong_merged<T>(h->work, K, h->M, h->P.n_top > 0 ? h->S[0].x<T>() : ya, ya, zz, done);
+}
+
 // zz = VL_SOR(rr) + Z Vcyc_Abar(Z^T rr) with one pair of fine sweeps for both
-// cycles (MergedRows); zz has n + nx rows.  part as in sor_cycle.
+// cycles.  part as in sor_cycle.
 template <class T>
 int64_t merged_cycle(Handle *h, int K, const T *rr, T *zz, double *part, const int *done) {
   hipStream_t st = h->work;
   const Problem &P = h->P;
-  const int nc = fine_colours(P);
   Work<T> &v = work_of<T>(h);
-  int64_t np = 0;
-  auto sweep = [&](int c, bool first) {
-    const ColourRows q = colour_rows(P, c);
-    const bool d = c + 1 < (int)h->dstart.size();
-    const int64_t nb =
-        launch_gs_merged<T>(st, K, h->A, h->M, q.a0, q.a1, q.b0, q.b1, d ? h->dstart[c] : 0, d ? h->dstart[c + 1] : 0,
-                            rr, zz, done, first, first || !part ? nullptr : part + np * K);
-    if (!first) np += nb;
-  };
-  for (int c = 0; c < nc; ++c) sweep(c, true);
+  merged_forward<T>(h, K, rr, zz, done);
   launch_res_merged<T>(st, K, h->A, h->M, zz, v.res, done, h->order_all);
   CsrJob<T> down[2];
   int nd = 0;
@@ -909,10 +926,8 @@ int64_t merged_cycle(Handle *h, int K, const T *rr, T *zz, double *part, const i
   down[nd++].y = h->Ab[1].g<T>();
   launch_csr<T>(st, K, kCsrMult, down, nd, done);
   coarse_cycles<T>(st, K, P.n_top > 0 ? cycle<T>(h->S, 0) : Cycle<T>(), cycle<T>(h->Ab, 1), done);
-  const T *ya = h->Ab[1].x<T>();
-  launch_prolong_merged<T>(st, K, h->M, P.n_top > 0 ? h->S[0].x<T>() : ya, ya, zz, done);
-  for (int c = nc - 1; c >= 0; --c) sweep(c, false);
-  return np;
+  merged_prolong<T>(h, K, zz, done);
+  return merged_backward<T>(h, K, rr, zz, part, done);
 }
 
 // w = Z Vcyc_Abar(Z^T rr) (the additive smoother; rows of the top block of w
@@ -1826,6 +1841,12 @@ void time_once(Handle *h, int op, int K) {
     launch_patch_gs<T>(st, K, kPatchForward, &J, 1, nullptr);
     return;
   }
+  switch (op) {
+    case VEMG_OP_MERGED_FWD: merged_forward<T>(h, K, v.r, v.z, nullptr); return;
+    case VEMG_OP_MERGED_RES: launch_res_merged<T>(st, K, h->A, h->M, v.z, v.res, nullptr, h->order_all); return;
+    case VEMG_OP_MERGED_PROLONG: merged_prolong<T>(h, K, v.z, nullptr); return;
+    case VEMG_OP_MERGED_BWD: merged_backward<T>(h, K, v.r, v.z, h->sweep_dot ? h->part_rz : nullptr, nullptr); return;
+  }
   for (int c = 0; c < fine_colours(P); ++c) {
     const ColourRows q = colour_rows(P, c);
     launch_gs<T>(st, K, h->A, q.a0, q.a1, q.b0, q.b1, v.r, v.z, nullptr, false);
@@ -1836,9 +1857,11 @@ int do_time(Handle *h, int op, int K, int reps, double *avg_ms, int *launches) {
   hipStream_t st = h->work;
   const Problem &P = h->P;
   int64_t n = P.n;
+  const bool merged = op >= VEMG_OP_MERGED_FWD && op <= VEMG_OP_MERGED_BWD;
   if (op != VEMG_OP_A && op != VEMG_OP_GS_FWD && op != VEMG_OP_GS_COARSE && op != VEMG_OP_ET && op != VEMG_OP_E &&
-      op != VEMG_OP_COARSEST)
+      op != VEMG_OP_COARSEST && !merged)
     return VEMG_ERR_INVALID_ARG;
+  if (merged && !h->merged) return VEMG_ERR_STATE;
   if (op == VEMG_OP_COARSEST && (P.n_top == 0 || h->S.empty())) return VEMG_ERR_STATE;
   if (op == VEMG_OP_GS_COARSE && (h->Ab.size() < 2 || h->Ab[1].coarsest)) return VEMG_ERR_STATE;
   if ((op == VEMG_OP_ET || op == VEMG_OP_E) && (P.n_top == 0 || h->S.empty())) return VEMG_ERR_STATE;
@@ -1866,12 +1889,17 @@ int do_time(Handle *h, int op, int K, int reps, double *avg_ms, int *launches) {
   if (f32) {
     launch_fill<float>(st, h->v32.p, n * K, 1.0f, nullptr);
     launch_fill<float>(st, h->v32.r, n * K, 1.0f, nullptr);
-    launch_fill<float>(st, h->v32.z, n * K, 0.0f, nullptr);
+    launch_fill<float>(st, h->v32.z, (n + h->M.nx) * K, 0.0f, nullptr);
   } else {
     launch_fill<double>(st, h->v64.p, n * K, 1.0, nullptr);
     launch_fill<double>(st, h->v64.r, n * K, 1.0, nullptr);
-    launch_fill<double>(st, h->v64.z, n * K, 0.0, nullptr);
+    launch_fill<double>(st, h->v64.z, (n + h->M.nx) * K, 0.0, nullptr);
   }
+  if (op == VEMG_OP_MERGED_PROLONG)
+    for (DLevel *L : {P.n_top > 0 ? &h->S[0] : &h->Ab[1], &h->Ab[1]}) {
+      launch_fill<float>(st, L->x32, L->n * K, 1.0f, nullptr);
+      launch_fill<double>(st, L->x64, L->n * K, 1.0, nullptr);
+    }
   auto once = [&]() {
     if (f32) time_once<float>(h, op, K); else time_once<double>(h, op, K);
   };
@@ -1896,7 +1924,10 @@ int do_time(Handle *h, int op, int K, int reps, double *avg_ms, int *launches) {
       launch_fill<double>(st, L.g64, L.n * K, 1.0, nullptr);
     HIPCHK(hipStreamSynchronize(st));
   }
-  if (launches) *launches = (op == VEMG_OP_A || op == VEMG_OP_ET || op == VEMG_OP_E || op == VEMG_OP_COARSEST) ? 1 : nc;
+  if (launches) {
+    const bool sweep = op == VEMG_OP_GS_FWD || op == VEMG_OP_GS_COARSE || op == VEMG_OP_MERGED_FWD || op == VEMG_OP_MERGED_BWD;
+    *launches = sweep ? nc : 1;
+  }
   return VEMG_OK;
 }
 

@@ -174,3 +174,24 @@ def test_cpu_baseline_child_reports_each_config():
     assert r["value"] > 0.0
     assert "whole solve" in r["sample"]
     assert not h[0].is_alive()
+
+
+def test_the_roofline_names_a_kernel_that_the_solve_runs():
+    # the general sweep with a start belongs to the other preconditioners, whatever it takes
+    r = {k: {"ms": 1.0, "launches": 1, "bytes": 10}
+         for k in ("spmv", "coarse_sweep", "merged_fwd", "merged_res", "merged_prolong", "merged_bwd")}
+    r["fine_sweep"] = {"ms": 9.0, "launches": 4, "bytes": 10}
+    r["merged_bwd"] = {"ms": 3.0, "launches": 4, "bytes": 120}
+    key, d = bench.dominant_kernel(r, "vl_as", 8)
+    assert key == "merged_bwd" and d["kernel"].startswith("k_gs_merged<double, 8, false>")
+    assert d["bytes_per_launch"] == 30 and d["ms_per_launch"] == 0.75
+    assert bench.dominant_kernel(r, "vl_sor", 8)[0] == "gs"
+    assert all(k in bench.pmc_kernels(8) for k in bench.KERNEL_NAMES)
+
+
+def test_merged_fine_bytes_read_every_entry_twice():
+    info = _info()
+    b = bench.merged_fine_bytes(info, 2)
+    entries = 1300 * 12 * 2 + (280 + 300) * 12  # L, U, the whole rows; both prolongations
+    vectors = 100 * 16 * (2 + 2 + 2 + 3) + (10 + 20) * 16
+    assert sum(b.values()) == entries + vectors + 2 * 100 * 8

@@ -78,3 +78,23 @@ def test_the_merged_cycles_are_the_sum_of_the_separate_ones(nx, ny, nz, mode, pr
         err = np.linalg.norm(z - want) / np.linalg.norm(want)
         print("oracle", err, flush=True)
         assert err < 1e-4
+
+
+@pytest.mark.parametrize("mode", ["N", "D"])
+@pytest.mark.parametrize("precision", ["fp64", "mixed_ir"])
+def test_the_merged_steps_are_timed(mode, precision):
+    m, s, o = _build(17, 13, 7, mode, precision)
+    colours = max(s.info()["fine_colours_top"], s.info()["fine_colours_bar"])
+    b = s.rhs(fourier_field(m.xyz, 1e-2, 650))
+    x = s.solve(b, rtol=1e-8)[0]
+    for K in (1, 8):
+        for op, launches in ((lib.OP_MERGED_FWD, colours), (lib.OP_MERGED_RES, 1), (lib.OP_MERGED_PROLONG, 1),
+                             (lib.OP_MERGED_BWD, colours)):
+            ms, nl = s.time_op(op, reps=3, nrhs=K)
+            assert ms > 0 and nl == launches
+    assert torch.equal(s.solve(b, rtol=1e-8)[0], x)
+    f = lib.Solver(m.xyz, m.tets, m.top, top_bc=mode, device=0)  # A_bar is one dense level
+    assert f.info()["abar_levels"] == 1
+    with pytest.raises(lib.VemgError) as e:
+        f.time_op(lib.OP_MERGED_BWD)
+    assert e.value.status == -7
