@@ -1,6 +1,7 @@
 // Solver handle: packs the host setup into HBM (SELL-64 fine operator,
-// CSR for coarse operators and transfers, FP64 and FP32 copies), runs the preconditioned CG loop on the device for batches of up to
-// eight right-hand sides, and exposes the C ABI of vemg.h.
+// CSR for coarse operators and transfers, FP64 and FP32 copies), runs the
+// preconditioned CG loop on the device for batches of up to eight right-hand
+// sides, and exposes the C ABI of vemg.h.
 //
 // One PCG iteration is a fixed sequence of kernels on one stream whose scalars
 // (alpha, beta, per-column convergence flags) live in device memory, so the
@@ -49,9 +50,9 @@ struct DeviceError : std::runtime_error {
 // device memory owned by a handle; with count_only set nothing is allocated or
 // copied, only the bytes are added up (the footprint query).  All of it is one
 // allocation: what an iteration reads of a mesh whose inverses nearly fill the
-// Infinity Cache (71,824 unknowns with inverses of 210 MB) is kept there only
-// if it lies together, and with an allocation per array its solve took 6.2 to
-// 7.0 ms by what the process had allocated before, in one 6.4.
+// Infinity Cache (71,824 unknowns, inverses of 210 MB) is kept there only if it
+// lies together.  With an allocation per array its solve took 6.1 to 7.1 ms by
+// what the process had allocated before, in one 6.0 to 6.6.
 struct Arena {
   static constexpr size_t kAlign = 256;
   char *base = nullptr;
@@ -1095,8 +1096,8 @@ void destroy_graphs(Handle *h) {
 }
 
 // A chunk is poll_every iterations or fewer (chunk_for), after which the host
-// reads the flags; the FP32 form's last one ends in the reliable update.  Up to kGraphIterations
-// of them are one graph: in a chain of dependent kernels, those of a graph of
+// reads the flags; the FP32 form's last one ends in the reliable update.  Up to
+// kGraphIterations of them are one graph: in a chain of dependent kernels, those of a graph of
 // 40 nodes (one iteration) took 1.73 us each and of one of 400 nodes 1.55 us,
 // launched one by one 2.4 us and more, bound by the host.  A longer chunk
 // repeats the graph of one iteration.
@@ -1623,12 +1624,16 @@ void upload(Handle *h) {
   h->order_bar = slice_order(m, n);
   int64_t npmax = (std::max(sell_blocks(0, n), vec_blocks(n)) + 8) * kMaxBatch;
   // A sweep's dot has a row of partial sums per slice and colour (those a
-  // boundary cuts count twice), a dot of its own one per 256 rows.  The sweep
-  // forms it where its rows are few enough to be added by every block
-  // (launch_pcg_p) or the vectors too long to be read once more (44 us at
-  // 2,179,616 unknowns, K = 8); between, 341,825 unknowns with vl_sor took 17.8
-  // ms so and 17.1 with a dot of its own.  By the mesh alone, so that a batch's columns keep the single
-  // column's sums.
+  // boundary cuts count twice), a dot of its own one per 256 rows and a pass
+  // over z and r.  The sweep forms it where its rows are few enough to be added
+  // by every block for eight columns (launch_pcg_p: n / 64 rows, up to 65,536
+  // unknowns), and again where those of a dot of its own are too many even for
+  // one (n / 256, from a million), so that no width loses.  Time of an FP64
+  // solve with the sweep's against one of its own, on one handle: 2600 to
+  // 61,730 unknowns 0.96 to 1.00; 70,698 and 100,819 one column 0.98 to 0.99,
+  // eight 1.00 to 1.02; 198,743 and 255,024 0.96 to 0.99; 330,749 to 752,432 one
+  // column 1.00 to 1.04, eight 0.97 to 0.98; 1,033,856 0.97 to 0.99.  By the mesh
+  // alone, so that a batch's columns keep the single column's sums.
   h->sweep_dot = n <= kSweepDotMax || n >= kSweepDotMin;
   h->dot_rows = h->sweep_dot ? n / kWave + 4 * (fine_colours(P) + 1) : vec_blocks(n);
   h->part_pq = h->ar.alloc<double>(npmax);

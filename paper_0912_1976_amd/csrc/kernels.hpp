@@ -31,7 +31,7 @@ constexpr int kMaxBatch = 8;
 // (the lower part L of its multicolour order), then those to later ones (U);
 // in slice s the L entries end at smid[s], each part padded to the slice's
 // longest.  The forward sweep from zero reads L alone and the residual after
-// it U alone (sell_row).
+// it U alone (sell_span).
 struct Sell {
   const int64_t *sptr = nullptr;  // nslices + 1 entry offsets
   const int64_t *smid = nullptr;  // fine A: where slice s's U entries begin
@@ -312,9 +312,13 @@ void launch_pcg_set_rho(hipStream_t st, int K, Scal *s, const double *p, int64_t
 // convergence test too; every block adds the partials, the first one writes
 // the record.  A launch of one block took 4 to 5 us in their place.  The test
 // folded into launch_pcg_p comes after the preconditioner, whose application
-// in the iteration that converges is then for nothing: only where that costs
-// less than the launches it saves (kFoldConvMax unknowns: at 549,152 the solve
-// took 28.3 ms with it, 28.0 without).
+// in the iteration that converges is then for nothing, and every block adds
+// the partials of r.r too.  Time of a solve with the test folded against a
+// launch of its own, on one handle at 2600 to 255,024 unknowns: one column
+// 0.995 to 1.013, eight 1.002 to 1.034; 113 x 105 x 21 with two columns 0.99,
+// 25 x 25 x 17 mixed with four 0.99.  Above, one column at 330,749 to 515,624
+// 0.991 to 1.003 and at 752,432 1.006 to 1.012 (eight do not fold).  The line
+// (kFoldConvMax unknowns) bounds what the wasted application costs.
 // Otherwise launch_pcg_alpha (in -> mid), launch_pcg_conv (mid) and
 // launch_pcg_beta (mid -> in) do so in single blocks.
 struct PartialSums {
